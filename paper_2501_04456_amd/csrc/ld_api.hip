@@ -174,6 +174,10 @@ using namespace ld::host;
 
 void build_tables(ld_ctx* c) { make_tables(c->p, c->R, c->tab, c->ext); }
 
+// The symmetric pair kernel takes over from n = kSymMinN: below it its blocks
+// are too few workgroups for the chip.
+constexpr int64_t kSymMinN = 24576;
+
 void default_tuning(ld_ctx* c) {
     ld_tuning& t = c->tune;
     std::memset(&t, 0, sizeof t);
@@ -219,6 +223,20 @@ ld_status ensure_split_capacity(ld_ctx* c, int split) {
 }
 
 
+// Whether the direct forces come from the symmetric pair kernel: the
+// context has a plan, the slots are in the order it wants and kept so by
+// re-sorts, and the tuning asks for culled tiles (without culling every pair
+// takes the exact near loop).
+bool use_sym(const ld_ctx* c) {
+    return c->sym.slots > 0 && c->charged_first && c->spatial && c->tune.cull == 1 &&
+           c->tune.sort_every > 0 && c->sym.slots <= c->j_split_cap;
+}
+
+// Force partials the update and the gather add up, and the slots that have
+// more than the first.
+int pair_parts(const ld_ctx* c) { return use_sym(c) ? c->sym.slots : c->tune.j_split; }
+int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; }
+
 ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
     ld::PairLaunch L{};
     L.pos = c->pos;
@@ -233,8 +251,7 @@ ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
     L.Fpart = c->Fpart;
     L.S = diag ? c->S_slot : nullptr;
     L.U = diag ? c->U_slot : nullptr;
-    L.nearbits = c->nearbits;
-    L.nb_words = c->nb_words;
+    L.sym = !diag && use_sym(c) ? &c->sym : nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         if (!ld::timing_events(c, ld::kTimedCoulomb, &e0, &e1))
@@ -256,6 +273,7 @@ ld_status run_sort(ld_ctx* c, hipStream_t s) {
     HIP_TRY(ld::launch_sort(c->pos, c->lo, c->typ, c->oid, (int)c->n, c->sb, s, clip));
     HIP_TRY(ld::launch_boxes(c->pos, (int)c->n, c->box, s));
     c->steps_since_sort = 0;
+    c->charged_first = c->spatial = true;
     return LD_OK;
 }
 
@@ -268,7 +286,8 @@ ld::StepLaunch step_launch(ld_ctx* c, double dt) {
     L.typ = c->typ;
     L.oid = c->oid;
     L.Fpart = c->Fpart;
-    L.j_split = c->tune.j_split;
+    L.j_split = pair_parts(c);
+    L.n_full = pair_full(c);
     L.n = (int)c->n;
     L.dt = dt;
     L.seed = c->seed;
@@ -290,6 +309,7 @@ ld_status enqueue_step(ld_ctx* c, double dt, hipStream_t s, bool timed) {
         if (st != LD_OK) return st;
         ld::StepLaunch L = step_launch(c, dt);
         L.j_split = js;
+        L.n_full = (int)c->n;
         HIP_TRY(ld::launch_update(L, c->ext, s));
         ++c->steps_since_sort;
         return LD_OK;
@@ -364,7 +384,7 @@ void free_all(ld_ctx* c) {
     void* bufs[] = {c->pos,     c->lo,     c->typ,         c->oid,       c->box,  c->aux,
                     c->Fpart,   c->S_slot, c->U_slot,      c->work,      c->st,  c->ref,
                     c->sb.keys, c->sb.tmp4, c->sb.tmp_i,   c->sb.bounds, c->sb.bounds_part,
-                    c->sb.hist, c->pos2,  c->lo2,   c->typ2,       c->oid2, c->nearbits};
+                    c->sb.hist, c->pos2,  c->lo2,   c->typ2,       c->oid2};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
@@ -537,11 +557,17 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
               hipMalloc(&c->sb.bounds_part, sizeof(float) * 6 * 64) == hipSuccess &&
               hipMalloc(&c->sb.hist, sizeof(unsigned) * 256 * (ld::radix_tiles((int)n) + 1)) ==
                   hipSuccess;
-    if (ok && n <= ld::kNearBitsMaxN) {
-        c->nb_words = (ngroups + 31) / 32;
-        const size_t bytes = sizeof(unsigned) * (size_t)ngroups * c->nb_words;
-        ok = hipMalloc(&c->nearbits, bytes) == hipSuccess &&
-             hipMemsetAsync(c->nearbits, 0, bytes, s) == hipSuccess;
+    const double q1 = std::sqrt(p->kT * p->bjerrum);
+    for (int64_t i = 0; i < n; ++i) c->n_charged += (float)(q[i] * q1) != 0.f;
+    if (ok && n >= kSymMinN) {
+        // the symmetric kernel, if its partials can be had
+        if (!ld::sym_plan(n, c->n_charged, &c->sym)) {
+            c->sym.slots = 0;
+        } else if (ensure_split_capacity(c, c->sym.slots) != LD_OK) {
+            c->sym.slots = 0;
+            g_err.clear();
+            (void)hipGetLastError();
+        }
     }
     if (!ok || ensure_split_capacity(c, c->tune.j_split) != LD_OK) {
         free_all(c);
@@ -615,7 +641,8 @@ ld_status ld_forces(ld_ctx* c, double* F_pair, double* F_ext, double* S, double*
     double* dS = c->work + 6 * N;            // [N]
     double* dU = c->work + 7 * N;            // [2]
     HIP_TRY(ld::launch_gather(c->pos, c->lo, c->typ, c->oid, c->Fpart,
-                              diag ? 1 : c->tune.j_split, c->S_slot, (int)N, c->st, c->ext,
+                              diag ? 1 : pair_parts(c), diag ? (int)N : pair_full(c), c->S_slot,
+                              (int)N, c->st, c->ext,
                               F_pair ? dF : nullptr, F_ext ? dE : nullptr, S ? dS : nullptr,
                               c->stream));
     if (U) HIP_TRY(ld::launch_rowsum(c->U_slot, 2, (int)N, dU, c->stream));
@@ -685,6 +712,7 @@ ld_status step_loop(ld_ctx* c, double dt, int64_t n_steps) {
                 if (st != LD_OK) return st;
             }
             HIP_TRY(hipGraphLaunch(c->graph, c->stream));
+            if (c->tune.sort_every > 0) c->charged_first = c->spatial = true;
             c->steps_since_sort = c->tune.sort_every > 0 ? len : 0;
             left -= len;
             continue;
@@ -759,6 +787,7 @@ ld_status ld_set_positions(ld_ctx* c, const float* pos, const float* pos_lo) {
     HIP_TRY(ld::launch_boxes(c->pos, (int)N, c->box, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->tune.sort_every > 0) c->steps_since_sort = c->tune.sort_every;
+    c->spatial = false;
     return LD_OK;
 }
 
@@ -1214,6 +1243,11 @@ ld_status ld_checkpoint_load(ld_ctx** out, const char* path, void* stream) {
         return st;
     }
     c->steps_since_sort = sss;
+    // the saved slot order decides, as it did for the saved context
+    bool first = true;
+    for (size_t s = 1; s < N; ++s) first = first && (h[s - 1].w != 0.f || h[s].w == 0.f);
+    c->charged_first = first;
+    c->spatial = !(tune.sort_every > 0 && sss >= tune.sort_every);
     *out = c;
     return LD_OK;
 }

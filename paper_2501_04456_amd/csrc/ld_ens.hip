@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair(
     const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ typ,
     const int* __restrict__ off, const int2* __restrict__ items, int W, unsigned* counter, const PairTable* __restrict__ tabs,
     const Box* __restrict__ box, const int* __restrict__ tbase, double* __restrict__ F,
-    int total, unsigned* __restrict__ nearbits, int nb_words) {
+    int total) {
     __shared__ float4 sp[kWaves][kGroup];
     __shared__ float4 sl[kWaves][kGroup];          // low words (stretched tiles only)
     const int w = threadIdx.x / kGroup;
@@ -129,15 +129,10 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair(
             sp[w][lane] = pj;
             wave_sync();
             if (near) {
-                const bool lj =
-                    rel ? pair::group_near_rel<COMP, false>(sp[w], jt, i, pr, cull2, a)
-                        : pair::group_near<COMP, false>(sp[w], sl[w], jt, i, pi, li, cull2, a);
-                // tile pairs with a Lennard-Jones candidate, for k_ens_lj
-                if (__ballot(lj && live) && lane == 0) {
-                    const int gj = jt / kGroup;
-                    atomicOr(&nearbits[(size_t)(t0 + it.y / kGroup) * nb_words + (gj >> 5)],
-                             1u << (gj & 31));
-                }
+                if (rel)
+                    pair::group_near_rel<COMP, false>(sp[w], jt, i, pr, a);
+                else
+                    pair::group_near<COMP, false>(sp[w], sl[w], jt, i, pi, li, a);
             } else
                 pair::group_far<COMP, UNROLL>(sp[w], pi, a);
         }
@@ -168,8 +163,7 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair_b(
     const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ off,
     const int2* __restrict__ items, int W, unsigned* counter,
     const PairTable* __restrict__ tabs, const Box* __restrict__ box,
-    const int* __restrict__ tbase, double* __restrict__ F, int total,
-    unsigned* __restrict__ nearbits, int nb_words) {
+    const int* __restrict__ tbase, double* __restrict__ F, int total) {
     __shared__ float4 sp[kEnsBlock];                 // shared j tile (high words)
     __shared__ float4 sl[kEnsBlock];                 // and its low words
     __shared__ float4 sr[kWaves][kGroup];            // a wavefront's near group, relative
@@ -232,7 +226,6 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair_b(
                     if (!near && !coulomb) continue;
                 }
                 if (near) {
-                    bool lj;
                     if (rel) {
                         const int j = jg + lane;
                         float4 pj = sp[g * kGroup + lane];
@@ -244,15 +237,10 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair_b(
                         wave_sync();
                         sr[w][lane] = pj;
                         wave_sync();
-                        lj = pair::group_near_rel<COMP, false>(sr[w], jg, i, pr, cull2, a);
+                        pair::group_near_rel<COMP, false>(sr[w], jg, i, pr, a);
                     } else {
-                        lj = pair::group_near<COMP, false>(sp + g * kGroup, sl + g * kGroup, jg,
-                                                           i, pi, li, cull2, a);
-                    }
-                    if (__ballot(lj && live) && lane == 0) {
-                        const int gj = jg / kGroup;
-                        atomicOr(&nearbits[(size_t)(t0 + i0 / kGroup) * nb_words + (gj >> 5)],
-                                 1u << (gj & 31));
+                        pair::group_near<COMP, false>(sp + g * kGroup, sl + g * kGroup, jg, i, pi,
+                                                      li, a);
                     }
                 } else {
                     pair::group_far<COMP, UNROLL>(sp + g * kGroup, pi, a);
@@ -275,85 +263,26 @@ __global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair_b(
 }
 
 // Lennard-Jones forces of every tile of every droplet, in FP64, added into F
-// after k_ens_pair.  One workgroup per 64-slot tile: its four wavefronts
-// share round-robin the j tiles in which k_ens_pair found a pair within the
-// largest LJ range (a bitmap row per tile, cleared here); each stages its j
-// tiles in its own LDS slice, and the partial sums are added in wavefront
-// order.
+// after k_ens_pair.  One workgroup per 64-slot tile (pair::lj_group).
 __global__ __launch_bounds__(kEnsBlock) void k_ens_lj(
     const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ typ,
-    const int* __restrict__ off, const int2* __restrict__ tiles, int ntiles,
+    const int* __restrict__ off, const int2* __restrict__ tiles,
     const PairTable* __restrict__ tabs, const Box* __restrict__ box,
-    const int* __restrict__ tbase, double* __restrict__ F, int total,
-    unsigned* __restrict__ nearbits, int nb_words) {
-    __shared__ float4 sh[kWaves][kGroup];
-    __shared__ float4 sl[kWaves][kGroup];
-    __shared__ int st[kWaves][kGroup];
-    __shared__ double red[kWaves][3][kGroup];
-    const int w = threadIdx.x / kGroup;
-    const int lane = threadIdx.x % kGroup;
-    const int t = blockIdx.x;
-    const int2 tl = tiles[t];
+    const int* __restrict__ tbase, double* __restrict__ F, int total) {
+    __shared__ pair::LjShared<kWaves, 3> sh;
+    const int2 tl = tiles[blockIdx.x];
     const int d = tl.x;
     const int o = off[d];
-    const int nd = off[d + 1] - o;
-    const int i = tl.y - o + lane;
-    const bool live = i < nd;
-    const PairTable* tb = tabs + d;
-    const double* t64 = tb->sig2d;           // sig2d, e24d, e4d, rc2d follow each other
-    const int T = tb->T;
-    const float4 pi = live ? pos[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 li = live ? lo[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int ti = live ? typ[o + i] : 0;
-    Box bi;
-    if (box) bi = box[t];
-    const float cull2 = tb->rc2max * 1.0001f;
-    const int ng = (nd + kGroup - 1) / kGroup;
-    const int t0 = tbase[d];
-    double L[3] = {0.0, 0.0, 0.0};
-    double S = 0.0, U = 0.0;
-    int rank = 0;
-    unsigned* row = nearbits + (size_t)t * nb_words;   // tiles k_ens_pair found an LJ candidate in
-    for (int c0 = 0; c0 < ng; c0 += kGroup) {
-        const int gj = c0 + lane;
-        const bool nb = gj < ng && ((row[gj >> 5] >> (gj & 31)) & 1u);
-        unsigned long long m = __ballot(nb);
-        while (m) {
-            const int g = c0 + __builtin_ctzll(m);
-            m &= m - 1ull;
-            if ((rank++ & (kWaves - 1)) != w) continue;
-            const int j = g * kGroup + lane;
-            wave_sync();
-            sh[w][lane] = j < nd ? pos[o + j] : make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-            sl[w][lane] = j < nd ? lo[o + j] : make_float4(0.f, 0.f, 0.f, 0.f);
-            st[w][lane] = j < nd ? typ[o + j] : 0;
-            wave_sync();
-#pragma unroll 2
-            for (int k = 0; k < kGroup; ++k) {
-                const float4 pj = sh[w][k];
-                const float4 lj = sl[w][k];
-                const float dx = (pj.x - pi.x) + (lj.x - li.x);
-                const float dy = (pj.y - pi.y) + (lj.y - li.y);
-                const float dz = (pj.z - pi.z) + (lj.z - li.z);
-                const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                if (r2 < cull2 && live && g * kGroup + k != i)
-                    pair::lj_pair64<false>(pj, lj, pi, li, t64, ti * T + st[w][k], L, S, U);
-            }
-        }
-    }
-    red[w][0][lane] = L[0];
-    red[w][1][lane] = L[1];
-    red[w][2][lane] = L[2];
-    __syncthreads();
-    for (int k = threadIdx.x; k < nb_words; k += kEnsBlock) row[k] = 0u;   // all zero at rest
-    if (w != 0 || !live) return;
-    double Ls[3] = {0.0, 0.0, 0.0};
-    for (int v = 0; v < kWaves; ++v)
-        for (int c = 0; c < 3; ++c) Ls[c] += red[v][c][lane];
-    const size_t s = (size_t)(o + i);
-    F[s] -= Ls[0];
-    F[(size_t)total + s] -= Ls[1];
-    F[2 * (size_t)total + s] -= Ls[2];
+    const PairTable* tb = tabs + d;          // sig2d, e24d, e4d, rc2d follow each other
+    double sums[3];
+    if (!pair::lj_group<false, false, kWaves>(pos + o, lo + o, typ + o, box + tbase[d],
+                                              off[d + 1] - o, (tl.y - o) / kGroup, tb->T,
+                                              tb->rc2max, tb->sig2d, sh, sums))
+        return;
+    const size_t s = (size_t)tl.y + threadIdx.x;
+    F[s] -= sums[0];
+    F[(size_t)total + s] -= sums[1];
+    F[2 * (size_t)total + s] -= sums[2];
 }
 
 __global__ __launch_bounds__(256) void k_ens_update(float4* pos, float4* lo,
@@ -516,8 +445,6 @@ struct ld_ens {
     int comp = 0;
     int graph_steps = 0;
     int unroll = 16;                     // Coulomb pairs in flight per lane (8, 16 or 32)
-    unsigned* nearbits = nullptr;        // [ntiles][nb_words] tile pairs with an LJ candidate
-    int nb_words = 0;
     hipGraphExec_t graph = nullptr;
     double graph_dt = 0.0;
     int graph_len = 0;
@@ -541,7 +468,7 @@ void ens_free(ld_ens* e) {
     void* bufs[] = {e->pos,   e->lo,   e->typ,   e->did,     e->lid,   e->off,
                     e->items, e->counter, e->tabs, e->ext,   e->seeds, e->F, e->items_b,
                     e->work,  e->st,   e->box,   e->tbase,   e->tiles, e->dbounds,
-                    e->sb.keys, e->sb.tmp4, e->sb.tmp_i, e->nearbits};
+                    e->sb.keys, e->sb.tmp4, e->sb.tmp_i};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     if (e->graph) (void)hipGraphExecDestroy(e->graph);
@@ -577,24 +504,21 @@ void launch_ens_pair_u(ld_ens* e, hipStream_t s) {
         if (e->cull)
             hipLaunchKernelGGL((k_ens_pair_b<COMP, true, UNROLL>), dim3(e->workgroups),
                                dim3(kEnsBlock), 0, s, e->pos, e->lo, e->off, e->items_b, e->W_b,
-                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total,
-                               e->nearbits, e->nb_words);
+                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
         else
             hipLaunchKernelGGL((k_ens_pair_b<COMP, false, UNROLL>), dim3(e->workgroups),
                                dim3(kEnsBlock), 0, s, e->pos, e->lo, e->off, e->items_b, e->W_b,
-                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total,
-                               e->nearbits, e->nb_words);
+                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
         return;
     }
     if (e->cull)
         hipLaunchKernelGGL((k_ens_pair<COMP, true, UNROLL>), dim3(e->workgroups), dim3(kEnsBlock),
                            0, s, e->pos, e->lo, e->typ, e->off, e->items, e->W, e->counter,
-                           e->tabs, e->box, e->tbase, e->F, e->total, e->nearbits, e->nb_words);
+                           e->tabs, e->box, e->tbase, e->F, e->total);
     else
         hipLaunchKernelGGL((k_ens_pair<COMP, false, UNROLL>), dim3(e->workgroups),
                            dim3(kEnsBlock), 0, s, e->pos, e->lo, e->typ, e->off, e->items, e->W,
-                           e->counter, e->tabs, e->box, e->tbase, e->F, e->total, e->nearbits,
-                           e->nb_words);
+                           e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
 }
 
 template <int COMP>
@@ -611,9 +535,8 @@ void launch_ens_pair(ld_ens* e, hipStream_t s) {
 // t0 / t1 (or null) are recorded around the Coulomb kernel.
 ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
                        hipEvent_t t1 = nullptr) {
-    if (e->cull)
-        hipLaunchKernelGGL(k_ens_boxes, dim3((e->ntiles + 3) / 4), dim3(256), 0, s, e->pos,
-                           e->off, e->tiles, e->ntiles, e->box);
+    hipLaunchKernelGGL(k_ens_boxes, dim3((e->ntiles + 3) / 4), dim3(256), 0, s, e->pos, e->off,
+                       e->tiles, e->ntiles, e->box);
     hipLaunchKernelGGL(k_ens_reset, dim3(1), dim3(1), 0, s, e->counter);
     if (t0) HIP_TRY(hipEventRecord(t0, s));
     if (e->comp == 0)
@@ -623,9 +546,8 @@ ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
     HIP_TRY(hipGetLastError());
     if (t1) HIP_TRY(hipEventRecord(t1, s));
     hipLaunchKernelGGL(k_ens_lj, dim3(e->ntiles), dim3(kEnsBlock), 0, s,
-                       e->pos, e->lo, e->typ, e->off, e->tiles, e->ntiles, e->tabs,
-                       e->cull ? e->box : nullptr, e->tbase, e->F, e->total, e->nearbits,
-                       e->nb_words);
+                       e->pos, e->lo, e->typ, e->off, e->tiles, e->tabs, e->box, e->tbase, e->F,
+                       e->total);
     HIP_TRY(hipGetLastError());
     return LD_OK;
 }
@@ -792,21 +714,12 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     // spatial ordering needs the droplet index in 13 bits
     e->cull = n_drop <= (1 << 13);
     e->ntiles = (int)tiles.size();
-    {
-        int max_ng = 1;
-        for (int d = 0; d < n_drop; ++d)
-            max_ng = std::max(max_ng, (int)((offs[d + 1] - offs[d] + kGroup - 1) / kGroup));
-        e->nb_words = (max_ng + 31) / 32;
-        const size_t bytes = sizeof(unsigned) * tiles.size() * (size_t)e->nb_words;
-        ok = ok && hipMalloc(&e->nearbits, bytes) == hipSuccess &&
-             hipMemsetAsync(e->nearbits, 0, bytes, s) == hipSuccess;
-    }
     int n_pow2 = 2048;                                   // the bitonic sort's smallest size
     while (n_pow2 < (int)total) n_pow2 <<= 1;
     e->sb.n_pow2 = n_pow2;
+    ok = ok && hipMalloc(&e->box, sizeof(Box) * tiles.size()) == hipSuccess;
     if (ok && e->cull)
-        ok = hipMalloc(&e->box, sizeof(Box) * tiles.size()) == hipSuccess &&
-             hipMalloc(&e->dbounds, sizeof(float) * 6 * n_drop) == hipSuccess &&
+        ok = hipMalloc(&e->dbounds, sizeof(float) * 6 * n_drop) == hipSuccess &&
              hipMalloc(&e->sb.keys, sizeof(unsigned long long) * n_pow2) == hipSuccess &&
              hipMalloc(&e->sb.tmp4, sizeof(float4) * N) == hipSuccess &&
              hipMalloc(&e->sb.tmp_i, sizeof(int) * N) == hipSuccess;

@@ -1822,6 +1822,7 @@ ld_status ff_near(ld_ctx* c, hipStream_t s) {
         }
         HIP_TRY(ld::permute_slots_into(c->sb.keys, n, c->pos, c->lo, c->typ, c->oid, c->pos2,
                                        c->lo2, c->typ2, c->oid2, s));
+        c->charged_first = c->n_charged == c->n;   // cell order mixes the two kinds
         std::swap(c->pos, c->pos2);
         std::swap(c->lo, c->lo2);
         std::swap(c->typ, c->typ2);
@@ -1959,7 +1960,6 @@ ld_status ff_direct_total(ld_ctx* c, hipStream_t s, double* dst) {
     L.pos = c->pos; L.lo = c->lo; L.typ = c->typ; L.box = c->box; L.n = (int)c->n;
     L.block = c->tune.block; L.j_split = c->tune.j_split; L.comp = c->tune.comp;
     L.cull = c->tune.cull; L.Fpart = c->Fpart;
-    L.nearbits = c->nearbits; L.nb_words = c->nb_words;
     HIP_TRY(ld::launch_pair(L, c->tab, s));
     KLAUNCH(k_sum_parts, dim3((3 * (int)c->n + kB - 1) / kB), dim3(kB), s, c->Fpart,
             c->tune.j_split, (int)c->n, dst);

@@ -14,8 +14,6 @@ namespace ld {
 
 constexpr int kMaxTypes = LD_MAX_TYPES;
 constexpr int kGroup = 64;            // one wavefront: the unit of tile culling
-// Largest n with a near-group bitmap (ceil(n/64)^2 bits: 32 MiB at 2^20)
-constexpr int64_t kNearBitsMaxN = 1 << 20;
 
 // Far-away, uncharged filler for the padded tail of a j tile: its Coulomb
 // weight is exactly zero and it never enters the LJ range.
@@ -96,6 +94,24 @@ __host__ __device__ inline double radius_at(const ld_radius& R, double t) {
 
 // ---- launchers (each returns hipSuccess or the first HIP error) --------
 
+// Launch plan of the symmetric pair kernel (ld_pair_sym.hip).
+constexpr int kSymWaves = 4;             // wavefronts per workgroup
+constexpr int kSymMaxChunks = 96;
+constexpr int64_t kSymSmallN = 81920;    // blocks of 4 groups below, 8 from here on
+struct SymPlan {
+    int jb;                              // 64-slot groups per block
+    int nbc;                             // blocks that hold charged slots (the first ones)
+    int mA, nA;                          // blocks per row super-block; super-blocks
+    int nds, nchunk;                     // column super-blocks per row super-block; runs of them
+    int slots;                           // force partials: Lennard-Jones, columns, rows
+    int n_full;                          // slots below it have every partial, the rest only 0
+    short start[kSymMaxChunks + 1];      // first column super-block of each run
+};
+// The plan for n slots with the charged ones first; false if its partials
+// would take more than kSymMaxBytes.
+constexpr size_t kSymAimBytes = (size_t)1 << 30, kSymMaxBytes = (size_t)6 << 30;
+bool sym_plan(int64_t n, int64_t charged, SymPlan* p);
+
 struct PairLaunch {
     const float4* pos;
     const float4* lo;                    // low words of the positions
@@ -109,12 +125,11 @@ struct PairLaunch {
     double* Fpart;                       // [j_split][3][n]
     double* S;                           // [n] or nullptr (diagnostic mode)
     double* U;                           // [2][n] or nullptr (diagnostic mode)
-    // Near-group bitmap [ceil(n/64)][nb_words] (or nullptr): the Coulomb
-    // kernel sets bit (gi, gj) for every group pair it takes as near, the
-    // Lennard-Jones kernel reads and clears row gi (all zero between launches).
-    unsigned* nearbits;
-    int nb_words;
+    // Symmetric kernel instead of k_pair (or nullptr): charged slots first,
+    // culling on, Fpart [sym->slots][3][n].
+    const SymPlan* sym;
 };
+hipError_t launch_coulomb_sym(const PairLaunch& L, const PairTable& tab, hipStream_t s);
 // The Coulomb kernel (k_pair) and then the FP64 Lennard-Jones kernel (k_lj);
 // after_coulomb, if given, is recorded between the two.
 hipError_t launch_pair(const PairLaunch& L, const PairTable& tab, hipStream_t s,
@@ -132,7 +147,8 @@ struct StepLaunch {
     const int* typ;
     const int* oid;
     const double* Fpart;
-    int j_split;
+    int j_split;                         // force partials
+    int n_full;                          // slots from here on have partial 0 only
     int n;
     double dt;
     unsigned long long seed;
@@ -148,8 +164,8 @@ hipError_t launch_boxes(const float4* pos, int n, Box* box, hipStream_t s);
 // Gather into original order: pair force totals, external forces at R(t),
 // and optional S.  Any output may be null.
 hipError_t launch_gather(const float4* pos, const float4* lo, const int* typ, const int* oid,
-                         const double* Fpart, int j_split, const double* S_slot, int n,
-                         const DevState* st, const ExtParams& P, double* F_pair,
+                         const double* Fpart, int j_split, int n_full, const double* S_slot,
+                         int n, const DevState* st, const ExtParams& P, double* F_pair,
                          double* F_ext, double* S, hipStream_t s);
 
 // Deterministic FP64 sum of m rows of length n: out[r] = sum_s in[r*n + s].
@@ -358,10 +374,16 @@ struct ld_ctx {
     int* typ2 = nullptr;
     int* oid2 = nullptr;
     ld::Box* box = nullptr;              // [ceil(n/64)] group boxes
-    unsigned* nearbits = nullptr;        // near-group bitmap (n <= kNearBitsMaxN), zero at rest
-    int nb_words = 0;
     double* Fpart = nullptr;             // [j_split_cap][3][n]
     int j_split_cap = 0;
+    // symmetric pair kernel: its plan (slots = 0: not used for this context),
+    // whether the slots hold the charged particles first (a Hilbert sort does
+    // that, a cell sort only where all are charged), and whether they are in
+    // spatial order (not between ld_set_positions and the next sort)
+    ld::SymPlan sym{};
+    int64_t n_charged = 0;
+    bool charged_first = false;
+    bool spatial = false;
     double* S_slot = nullptr;            // [n]
     double* U_slot = nullptr;            // [2][n]
     double* work = nullptr;              // [16][n] FP64 scratch (outputs, reductions)

@@ -14,16 +14,13 @@
 // FP32 high words; a nearer group takes the loop on positions relative to
 // the centre c of the workgroup's box, (hi - c) + lo, staged beside the high
 // words (same instruction count, and the rounding of |x - c| instead of
-// |x|), which also leaves out the self pair and flags LJ candidates; a far
+// |x|), which also leaves out the self pair; a far
 // pair of groups one of which is uncharged is skipped (no force at all).
 //
-// k_lj: the Lennard-Jones sum, which is short-ranged (lj_cut sigma_ij): one
-// workgroup per 64-slot i group visits the j groups that k_pair found to
-// hold a pair within the largest LJ range (a bitmap k_pair fills and k_lj
-// clears; without it, the groups whose boxes come that close), stages each
-// in LDS and evaluates the pairs inside the cutoff in FP64.  It adds its
-// result into the first force partial of each slot after k_pair has
-// written it (same stream, one writer per slot).
+// k_lj: the Lennard-Jones sum, which is short-ranged (lj_cut sigma_ij), in
+// FP64: the groups whose boxes come within the largest LJ range, screened
+// slot by slot.  It adds its result into the first force partial of each
+// slot after k_pair has written it (same stream, one writer per slot).
 //
 // Precision.  The Coulomb pair terms are FP32.  Each lane sums KB = 32 of
 // them in an FP32 block accumulator and then moves the block into FP64
@@ -67,8 +64,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 64 ? 1 : LD_PAIR_MIN_WAVES) void k_
                                                 int j_per_split, float rc2max,
                                                 double* __restrict__ Fpart,
                                                 double* __restrict__ S_out,
-                                                double* __restrict__ U_out,
-                                                unsigned* __restrict__ nearbits, int nb_words) {
+                                                double* __restrict__ U_out) {
     __shared__ float4 sp[BLOCK];             // j tile, high words
     __shared__ float4 sr[BLOCK];             // near loop: positions relative to c, or low words
 
@@ -186,18 +182,10 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 64 ? 1 : LD_PAIR_MIN_WAVES) void k_
             }
             if constexpr (DIAG) near = true;
             if (__builtin_amdgcn_readfirstlane((int)near)) {
-                bool lj;
                 if constexpr (REL)
-                    lj = group_near_rel<COMP, DIAG>(sr + g * kGroup, jg, i, pr, cull2, a);
+                    group_near_rel<COMP, DIAG>(sr + g * kGroup, jg, i, pr, a);
                 else
-                    lj = group_near<COMP, DIAG>(sp + g * kGroup, sr + g * kGroup, jg, i, pi, li,
-                                                cull2, a);
-                // record the pair of groups if it holds a Lennard-Jones
-                // candidate, for the Lennard-Jones kernel
-                if (nearbits && __ballot(lj && live) && (tid & (kGroup - 1)) == 0) {
-                    const int gi = (tx * BLOCK + tid) / kGroup, gj = jg / kGroup;
-                    atomicOr(&nearbits[(size_t)gi * nb_words + (gj >> 5)], 1u << (gj & 31));
-                }
+                    group_near<COMP, DIAG>(sp + g * kGroup, sr + g * kGroup, jg, i, pi, li, a);
             } else {
                 group_far<COMP>(sp + g * kGroup, pi, a);
             }
@@ -229,118 +217,57 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 64 ? 1 : LD_PAIR_MIN_WAVES) void k_
     }
 }
 
-constexpr int kLjBlock = 256;
-constexpr int kLjWaves = kLjBlock / kGroup;
-
-// Lennard-Jones forces of every slot, added into partial 0 (and, with DIAG,
-// into S and the LJ energy row of U).  One workgroup per 64-slot i group:
-// its four wavefronts test the same 64 boxes at a time and share the j
-// groups that come within the largest LJ range round-robin (the r-th near
-// group goes to wavefront r mod 4); each wavefront stages its j groups in
-// its own LDS slice, and the four partial sums are added in wavefront order
-// at the end.  Without boxes every group is visited.
-template <bool DIAG>
-__global__ __launch_bounds__(kLjBlock) void k_lj(const float4* __restrict__ pos,
-                                                  const float4* __restrict__ lo,
-                                                  const int* __restrict__ typ,
-                                                  const Box* __restrict__ box, int n,
-                                                  double* __restrict__ F,
-                                                  double* __restrict__ S_out,
-                                                  double* __restrict__ U_out, PairTable tab,
-                                                  unsigned* __restrict__ nearbits,
-                                                  int nb_words) {
-    __shared__ float4 sh[kLjWaves][kGroup];
-    __shared__ float4 sl[kLjWaves][kGroup];
-    __shared__ int st[kLjWaves][kGroup];
+// Lennard-Jones forces of every slot (and, with DIAG, S and the LJ energy row
+// of U): added into partial 0 after k_pair, or, SYM, stored there after the
+// symmetric kernel, whose partial 0 is this kernel's alone.  One workgroup
+// per 64-slot i group (lj_group).
+template <bool DIAG, bool SYM, int WAVES>
+__global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict__ pos,
+                                                        const float4* __restrict__ lo,
+                                                        const int* __restrict__ typ,
+                                                        const Box* __restrict__ box, int n,
+                                                        double* __restrict__ F,
+                                                        double* __restrict__ S_out,
+                                                        double* __restrict__ U_out,
+                                                        PairTable tab) {
     __shared__ double t64[4 * kMaxTypes * kMaxTypes];
-    __shared__ double red[kLjWaves][5][kGroup];
-    for (int k = threadIdx.x; k < kMaxTypes * kMaxTypes; k += kLjBlock) {
+    __shared__ LjShared<WAVES, DIAG ? 5 : 3> sh;
+    for (int k = threadIdx.x; k < kMaxTypes * kMaxTypes; k += WAVES * kGroup) {
         t64[k] = tab.sig2d[k];
         t64[kMaxTypes * kMaxTypes + k] = tab.e24d[k];
         t64[2 * kMaxTypes * kMaxTypes + k] = tab.e4d[k];
         t64[3 * kMaxTypes * kMaxTypes + k] = tab.rc2d[k];
     }
     __syncthreads();
-    const int w = threadIdx.x / kGroup;
-    const int lane = threadIdx.x % kGroup;
-    const int ngroups = (n + kGroup - 1) / kGroup;
-    const int gi = blockIdx.x;
-    const int i = gi * kGroup + lane;
-    const bool live = i < n;
-    const float4 pi = live ? pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 li = live ? lo[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int ti = live ? typ[i] : 0;
-    const int T = tab.T;
-    Box bi;
-    if (box) bi = box[gi];
-    // box test and FP32 screen (the (hi, lo) difference: relative error
-    // ~1e-7 in r^2) with a margin; the cutoff itself is decided in FP64
-    const float cull2 = tab.rc2max * 1.0001f;
-    double L[3] = {0.0, 0.0, 0.0};
-    double S = 0.0, U = 0.0;
-    int rank = 0;                                // near groups seen so far (all wavefronts)
-    const unsigned* row = nearbits ? nearbits + (size_t)gi * nb_words : nullptr;
-    for (int c0 = 0; c0 < ngroups; c0 += kGroup) {
-        const int gj = c0 + lane;
-        bool nb = gj < ngroups;
-        if (row)                                 // the pairs the Coulomb kernel found near
-            nb = nb && ((row[gj >> 5] >> (gj & 31)) & 1u);
-        else if (nb && box)
-            nb = box_dist2(bi, box[gj]) < cull2;
-        unsigned long long m = __ballot(nb);
-        while (m) {
-            const int g = c0 + __builtin_ctzll(m);
-            m &= m - 1ull;
-            if ((rank++ & (kLjWaves - 1)) != w) continue;
-            const int j = g * kGroup + lane;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            sh[w][lane] = j < n ? pos[j] : make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-            sl[w][lane] = j < n ? lo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-            st[w][lane] = j < n ? typ[j] : 0;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 2
-            for (int k = 0; k < kGroup; ++k) {
-                const float4 pj = sh[w][k];
-                const float4 lj = sl[w][k];
-                const float dx = (pj.x - pi.x) + (lj.x - li.x);
-                const float dy = (pj.y - pi.y) + (lj.y - li.y);
-                const float dz = (pj.z - pi.z) + (lj.z - li.z);
-                const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                if (r2 < cull2 && live && g * kGroup + k != i)
-                    lj_pair64<DIAG>(pj, lj, pi, li, t64, ti * T + st[w][k], L, S, U);
-            }
-        }
+    double sums[DIAG ? 5 : 3];
+    const int i = blockIdx.x * kGroup + threadIdx.x;
+    if (!lj_group<DIAG, SYM, WAVES>(pos, lo, typ, box, n, blockIdx.x, tab.T, tab.rc2max, t64, sh,
+                                    sums))
+        return;
+    for (int c = 0; c < 3; ++c) {
+        double* Fi = F + (size_t)c * (size_t)n + i;
+        if constexpr (SYM)
+            *Fi = -sums[c];
+        else
+            *Fi -= sums[c];
     }
-    red[w][0][lane] = L[0];
-    red[w][1][lane] = L[1];
-    red[w][2][lane] = L[2];
     if constexpr (DIAG) {
-        red[w][3][lane] = S;
-        red[w][4][lane] = U;
+        S_out[i] += sums[3];
+        U_out[i] += sums[4];
     }
-    __syncthreads();
-    if (row)                                     // leave the bitmap all zero
-        for (int k = threadIdx.x; k < nb_words; k += kLjBlock) nearbits[(size_t)gi * nb_words + k] = 0u;
-    if (w != 0 || !live) return;
-    double Ls[3] = {0.0, 0.0, 0.0}, Ss = 0.0, Us = 0.0;
-    for (int v = 0; v < kLjWaves; ++v) {
-        for (int c = 0; c < 3; ++c) Ls[c] += red[v][c][lane];
-        if constexpr (DIAG) {
-            Ss += red[v][3][lane];
-            Us += red[v][4][lane];
-        }
-    }
-    // F_i += -sum_j g_ij (x_j - x_i)
-    F[i] -= Ls[0];
-    F[(size_t)n + i] -= Ls[1];
-    F[2 * (size_t)n + i] -= Ls[2];
-    if constexpr (DIAG) {
-        S_out[i] += Ss;
-        U_out[i] += Us;
-    }
+}
+
+// Wavefronts per i group: 16 while the groups are too few to fill the chip
+// with four each.
+template <bool DIAG, bool SYM>
+void launch_lj(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
+    const dim3 grid((L.n + kGroup - 1) / kGroup);
+    if (grid.x < 1024)
+        hipLaunchKernelGGL((k_lj<DIAG, SYM, 16>), grid, dim3(16 * kGroup), 0, s, L.pos, L.lo, L.typ,
+                           L.box, L.n, L.Fpart, L.S, L.U, tab);
+    else
+        hipLaunchKernelGGL((k_lj<DIAG, SYM, 4>), grid, dim3(4 * kGroup), 0, s, L.pos, L.lo, L.typ,
+                           L.box, L.n, L.Fpart, L.S, L.U, tab);
 }
 
 template <int BLOCK, int COMP, bool DIAG, bool CULL>
@@ -353,12 +280,10 @@ hipError_t launch_t(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
     // instance alone
     if (!(CULL && !DIAG) || LD_PAIR_REL_GUARD)
         hipLaunchKernelGGL((k_pair<BLOCK, COMP, DIAG, CULL, false>), grid, dim3(BLOCK), 0, s,
-                           L.pos, L.lo, L.box, L.n, per * BLOCK, tab.rc2max, L.Fpart, L.S, L.U,
-                           L.nearbits, L.nb_words);
+                           L.pos, L.lo, L.box, L.n, per * BLOCK, tab.rc2max, L.Fpart, L.S, L.U);
     if constexpr (CULL && !DIAG)
         hipLaunchKernelGGL((k_pair<BLOCK, COMP, DIAG, CULL, true>), grid, dim3(BLOCK), 0, s,
-                           L.pos, L.lo, L.box, L.n, per * BLOCK, tab.rc2max, L.Fpart, L.S, L.U,
-                           L.nearbits, L.nb_words);
+                           L.pos, L.lo, L.box, L.n, per * BLOCK, tab.rc2max, L.Fpart, L.S, L.U);
     return hipGetLastError();
 }
 
@@ -388,18 +313,15 @@ hipError_t launch_coulomb(const PairLaunch& L, const PairTable& tab, hipStream_t
 
 hipError_t launch_pair(const PairLaunch& L, const PairTable& tab, hipStream_t s,
                        hipEvent_t after_coulomb) {
-    hipError_t e = launch_coulomb(L, tab, s);
+    hipError_t e = L.sym ? launch_coulomb_sym(L, tab, s) : launch_coulomb(L, tab, s);
     if (e != hipSuccess) return e;
     if (after_coulomb && (e = hipEventRecord(after_coulomb, s)) != hipSuccess) return e;
-    const int ngroups = (L.n + kGroup - 1) / kGroup;
-    const dim3 grid(ngroups);
-    const Box* box = L.box;          // boxes are kept current by sort and update
-    if (L.S)
-        hipLaunchKernelGGL(k_lj<true>, grid, dim3(kLjBlock), 0, s, L.pos, L.lo, L.typ, box, L.n,
-                           L.Fpart, L.S, L.U, tab, L.nearbits, L.nb_words);
+    if (L.sym)
+        launch_lj<false, true>(L, tab, s);
+    else if (L.S)
+        launch_lj<true, false>(L, tab, s);
     else
-        hipLaunchKernelGGL(k_lj<false>, grid, dim3(kLjBlock), 0, s, L.pos, L.lo, L.typ, box,
-                           L.n, L.Fpart, L.S, L.U, tab, L.nearbits, L.nb_words);
+        launch_lj<false, false>(L, tab, s);
     return hipGetLastError();
 }
 

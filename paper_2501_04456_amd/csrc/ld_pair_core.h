@@ -78,14 +78,11 @@ __device__ __forceinline__ void group_far(const float4* __restrict__ sp, const f
 // high words of two nearby particles is exact, and adding the difference of
 // their low words gives r_ij to FP32 rounding of r_ij itself.  Used where
 // the relative positions below would lose too much (a workgroup whose box
-// is stretched by NPs thrown far out).  Returns whether any j of the group
-// lies within sqrt(lj2) of i (i itself counts, so the group holding i is
-// always flagged; the Lennard-Jones kernels skip j = i).
+// is stretched by NPs thrown far out).
 template <int COMP, bool DIAG>
-__device__ __forceinline__ bool group_near(const float4* __restrict__ sp,
+__device__ __forceinline__ void group_near(const float4* __restrict__ sp,
                                            const float4* __restrict__ sl, int jbase, int i,
-                                           const float4 pi, const float4 li, float lj2, Acc& a) {
-    bool lj_any = false;
+                                           const float4 pi, const float4 li, Acc& a) {
 #pragma unroll
     for (int kb = 0; kb < kGroup; kb += KB) {
         float bx = 0.f, by = 0.f, bz = 0.f;   // Coulomb, FP32 block
@@ -101,7 +98,6 @@ __device__ __forceinline__ bool group_near(const float4* __restrict__ sp,
             // its weight finite, so its term is 0 without a test
             const float ri = fminf(__builtin_amdgcn_rsqf(r2), kInvRCap);
             const float w = (pj.w * ri) * (ri * ri);
-            lj_any |= r2 < lj2;                 // the self pair flags the diagonal group
             if constexpr (DIAG) {
                 if (jbase + kb + k != i) {
                     const float qq = pi.w * pj.w;
@@ -115,7 +111,6 @@ __device__ __forceinline__ bool group_near(const float4* __restrict__ sp,
         }
         flush<COMP>(a, bx, by, bz);
     }
-    return lj_any;
 }
 
 // 64 j particles near i's group (within the largest LJ range of its box) or
@@ -129,14 +124,10 @@ __device__ __forceinline__ bool group_near(const float4* __restrict__ sp,
 // term by ~1e-4 of itself; at |x - c| = 64 sigma it is 8e-6 sigma.  One LDS
 // read and three subtractions per pair, as in the far loop.  The
 // Lennard-Jones terms of these groups are added by a kernel of their own
-// (k_lj), in FP64 from the exact (hi, lo) differences.  Returns whether any
-// j of the group lies within sqrt(lj2) of i (i itself counts, so the group
-// holding i is always flagged): the Lennard-Jones kernel visits only such
-// group pairs and skips j = i.
+// (k_lj), in FP64 from the exact (hi, lo) differences.
 template <int COMP, bool DIAG>
-__device__ __forceinline__ bool group_near_rel(const float4* __restrict__ sr, int jbase, int i,
-                                               const float4 ri4, float lj2, Acc& a) {
-    bool lj_any = false;
+__device__ __forceinline__ void group_near_rel(const float4* __restrict__ sr, int jbase, int i,
+                                               const float4 ri4, Acc& a) {
 #pragma unroll
     for (int kb = 0; kb < kGroup; kb += KB) {
         float bx = 0.f, by = 0.f, bz = 0.f;   // Coulomb, FP32 block
@@ -149,7 +140,6 @@ __device__ __forceinline__ bool group_near_rel(const float4* __restrict__ sr, in
             // its weight finite, so its term is 0 without a test
             const float ri = fminf(__builtin_amdgcn_rsqf(r2), kInvRCap);
             const float w = (pj.w * ri) * (ri * ri);
-            lj_any |= r2 < lj2;                 // the self pair flags the diagonal group
             if constexpr (DIAG) {
                 if (jbase + kb + k != i) {
                     const float qq = ri4.w * pj.w;
@@ -163,7 +153,6 @@ __device__ __forceinline__ bool group_near_rel(const float4* __restrict__ sr, in
         }
         flush<COMP>(a, bx, by, bz);
     }
-    return lj_any;
 }
 
 // One Lennard-Jones pair (section 2.1: truncated at lj_cut sigma_ij, not
@@ -202,12 +191,228 @@ __device__ __forceinline__ float box_dist2(const Box& a, const Box& b) {
     return gx * gx + gy * gy + gz * gz;
 }
 
+// A box whose half-extent is below 255 sigma: positions relative to its
+// centre carry at most two FP32 roundings of 2^-17 sigma.  False for NaN or
+// infinite boxes.
+constexpr float kCompactExtent = 510.f;
+__device__ __forceinline__ bool box_compact(const Box& b) {
+    return fmaxf(fmaxf(b.hi.x - b.lo.x, b.hi.y - b.lo.y), b.hi.z - b.lo.z) < kCompactExtent;
+}
+
+// Coulomb pairs that the symmetric kernel leaves to k_lj: both groups
+// charged, near, one of the boxes stretched.  (Whether any particle of the
+// one comes near the other's box is tested by both kernels alike.)
+__device__ __forceinline__ bool sym_leaves_out(const Box& a, const Box& b) {
+    return (!box_compact(a) || !box_compact(b)) && a.lo.w != 0.f && b.lo.w != 0.f;
+}
+
 // Squared distance from point p to box b (0 inside; NaN coordinates give 0).
 __device__ __forceinline__ float point_box_dist2(const float4& p, const Box& b) {
     const float gx = fmaxf(0.f, fmaxf(b.lo.x - p.x, p.x - b.hi.x));
     const float gy = fmaxf(0.f, fmaxf(b.lo.y - p.y, p.y - b.hi.y));
     const float gz = fmaxf(0.f, fmaxf(b.lo.z - p.z, p.z - b.hi.z));
     return gx * gx + gy * gy + gz * gz;
+}
+
+// Lennard-Jones sums of one 64-slot i group, by a workgroup of WAVES
+// wavefronts, which share the tests of the boxes and then the near groups.
+// Bound by latency and by the FP64
+// pair arithmetic: a near group pair has a few hundred pairs in sight and a
+// handful in range, so
+//   - of a near group's slots only those within range of the i group's box
+//     are paired with the 64 i (about an eighth in a dispersed droplet);
+//   - those pairs are only screened, in FP32 with a margin; a lane notes its
+//     partners in a short list (LDS) and the FP64 terms are evaluated for the
+//     lists at once, so the FP64 code runs as often as the longest list is
+//     long, not for every slot that some lane has in range.
+// Measured against a loop over every slot of the near groups with the FP64
+// terms inline: 5000 slots 27.5 -> 14.3 us a launch, 32768 slots 30.8 -> 27.9
+// us; at 250 000 slots 126 -> 140 us, where the pair loops no longer flag the
+// group pairs that hold a pair in range (one operation in fourteen of their
+// near loops).
+// Partners come in the same order whatever the timing, and the wavefronts'
+// sums are added in order.
+//
+// SYM: group pairs that the symmetric Coulomb kernel leaves out, near ones
+// with a stretched box, get their Coulomb terms here, in FP64 from the exact
+// (hi, lo) differences.
+//
+// pos .. box point at the droplet's first slot and group; t64 as for
+// lj_pair64.  Returns true for the work-items that hold a slot's sums (the
+// first wavefront's, lane = slot): sum_j g_ij (x_j - x_i) and, with DIAG, S
+// and the energy.
+constexpr int kLjList = 8;               // partners a lane holds between evaluations
+
+constexpr int kLjScan = 4;               // boxes / 64 a wavefront tests per round
+
+template <int WAVES, int SUMS>
+struct LjShared {
+    union {
+        struct {
+            float4 hi[WAVES][kGroup], lo[WAVES][kGroup];
+            int list[WAVES][kLjList][kGroup];
+        };
+        double red[WAVES][SUMS][kGroup];         // after the last round
+    };
+    int near[WAVES][kLjScan * kGroup];
+    int found[WAVES];
+};
+
+template <bool DIAG, bool SYM, int WAVES>
+__device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
+                                         const float4* __restrict__ lo,
+                                         const int* __restrict__ typ, const Box* __restrict__ box,
+                                         int n, int gi, int T, float rc2max,
+                                         const double* __restrict__ t64,
+                                         LjShared<WAVES, DIAG ? 5 : 3>& sh,
+                                         double (&sums)[DIAG ? 5 : 3]) {
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
+    const int lane = threadIdx.x % kGroup;
+    const int ngroups = (n + kGroup - 1) / kGroup;
+    const int i = gi * kGroup + lane;
+    const bool live = i < n;
+    const float4 pi = live ? pos[i] : make_float4(kFarAway, kFarAway, kFarAway, 0.f);
+    const float4 li = live ? lo[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const int ti = live ? typ[i] : 0;
+    const Box bi = box[gi];
+    // box tests and FP32 screen (the (hi, lo) difference: relative error
+    // ~1e-7 in r^2) with a margin; the cutoff itself is decided in FP64
+    const float cull2 = rc2max * 1.0001f;
+    double L[3] = {0.0, 0.0, 0.0};
+    double S = 0.0, U = 0.0;
+    int cnt = 0;                                 // partners in this lane's list
+    auto evaluate = [&]() {
+        for (int t = 0; __any(t < cnt); ++t) {
+            if (t < cnt) {
+                const int j = sh.list[w][t][lane];
+                lj_pair64<DIAG>(pos[j], lo[j], pi, li, t64, ti * T + typ[j], L, S, U);
+            }
+        }
+        cnt = 0;
+    };
+    // one near group g: its slots (hj, lj of lane), its box
+    auto visit = [&](int g, const float4 hj, float4 lj, const Box& bj) {
+        if (!__any(live && point_box_dist2(pi, bj) < cull2)) return;
+        const int j = g * kGroup + lane;
+        const unsigned long long jclose = __ballot(j < n && point_box_dist2(hj, bi) < cull2);
+        if (jclose == 0ull) return;
+        // the close slots, packed; lo.w carries the slot; padded to a
+        // multiple of four with filler out of everyone's range
+        const int at = __popcll(jclose & ((1ull << lane) - 1ull));
+        const int m4 = (__popcll(jclose) + 3) & ~3;
+        lj.w = __int_as_float(j);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if ((jclose >> lane) & 1ull) {
+            sh.hi[w][at] = hj;
+            sh.lo[w][at] = lj;
+        }
+        if (lane >= __popcll(jclose) && lane < m4) {
+            sh.hi[w][lane] = make_float4(kFarAway, kFarAway, kFarAway, 0.f);
+            sh.lo[w][lane] = make_float4(0.f, 0.f, 0.f, __int_as_float(i));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int k0 = 0; k0 < m4; k0 += 4) {
+            // four slots in flight: the loop is bound by LDS latency
+            float r2[4];
+            int jj[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 pj = sh.hi[w][k0 + k];
+                const float4 qj = sh.lo[w][k0 + k];
+                const float dx = (pj.x - pi.x) + (qj.x - li.x);
+                const float dy = (pj.y - pi.y) + (qj.y - li.y);
+                const float dz = (pj.z - pi.z) + (qj.z - li.z);
+                r2[k] = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                jj[k] = __float_as_int(qj.w);
+            }
+            bool in[4], any = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                in[k] = live && !(r2[k] >= cull2) && jj[k] != i;
+                any = any || in[k];
+            }
+            if (!__any(any)) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (in[k]) sh.list[w][cnt++][lane] = jj[k];
+            if (__any(cnt > kLjList - 4)) evaluate();
+        }
+        if (SYM && sym_leaves_out(bi, bj)) {
+            for (int k = 0; k < min(kGroup, n - g * kGroup); ++k) {
+                const float4 pj = pos[g * kGroup + k];
+                const float4 qj = lo[g * kGroup + k];
+                const double ex = ((double)pj.x - (double)pi.x) + ((double)qj.x - (double)li.x);
+                const double ey = ((double)pj.y - (double)pi.y) + ((double)qj.y - (double)li.y);
+                const double ez = ((double)pj.z - (double)pi.z) + ((double)qj.z - (double)li.z);
+                const double q2 = ex * ex + ey * ey + ez * ez;
+                if (live && q2 > 0.0) {
+                    const double f = (double)pi.w * (double)pj.w / (q2 * sqrt(q2));
+                    L[0] += f * ex;
+                    L[1] += f * ey;
+                    L[2] += f * ez;
+                }
+            }
+        }
+    };
+    // Rounds of kLjScan x 64 boxes per wavefront: each notes the near groups,
+    // then all share the notes round-robin.
+    for (int r0 = 0; r0 < ngroups; r0 += WAVES * kLjScan * kGroup) {
+        int found = 0;
+        for (int k = 0; k < kLjScan; ++k) {
+            const int gc = r0 + (k * WAVES + w) * kGroup + lane;
+            const bool near = gc < ngroups && box_dist2(bi, box[min(gc, ngroups - 1)]) < cull2;
+            const unsigned long long m = __ballot(near);
+            if (near) sh.near[w][found + __popcll(m & ((1ull << lane) - 1ull))] = gc;
+            found += __popcll(m);
+        }
+        if (lane == 0) sh.found[w] = found;
+        __syncthreads();
+        int skip = w;                            // next of the notes that is this wavefront's
+        for (int v = 0; v < WAVES; ++v) {
+            const int cntv = __builtin_amdgcn_readfirstlane(sh.found[v]);
+            int q = skip;
+            if (q < cntv) {
+                // a group's slots are loaded while the one before is screened
+                int g = __builtin_amdgcn_readfirstlane(sh.near[v][q]);
+                float4 h = pos[min(g * kGroup + lane, n - 1)], l = lo[min(g * kGroup + lane, n - 1)];
+                Box b = box[g];
+                while (q < cntv) {
+                    const int gc = g;
+                    const float4 hc = h, lc = l;
+                    const Box bc = b;
+                    q += WAVES;
+                    if (q < cntv) {
+                        g = __builtin_amdgcn_readfirstlane(sh.near[v][q]);
+                        h = pos[min(g * kGroup + lane, n - 1)];
+                        l = lo[min(g * kGroup + lane, n - 1)];
+                        b = box[g];
+                    }
+                    visit(gc, hc, lc, bc);
+                }
+            }
+            skip = q - cntv;
+        }
+        __syncthreads();
+    }
+    evaluate();
+    __syncthreads();
+    sh.red[w][0][lane] = L[0];
+    sh.red[w][1][lane] = L[1];
+    sh.red[w][2][lane] = L[2];
+    if constexpr (DIAG) {
+        sh.red[w][3][lane] = S;
+        sh.red[w][4][lane] = U;
+    }
+    __syncthreads();
+    if (w != 0 || !live) return false;
+    for (int c = 0; c < (DIAG ? 5 : 3); ++c) {
+        sums[c] = 0.0;
+        for (int v = 0; v < WAVES; ++v) sums[c] += sh.red[v][c][lane];
+    }
+    return true;
 }
 
 }  // namespace pair

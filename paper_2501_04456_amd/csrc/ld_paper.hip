@@ -339,6 +339,7 @@ ld_status pm_forces(ld_ctx* c, hipStream_t s) {
     HIP_TRY(permute_slots_into(keys, n, c->pos, c->lo, c->typ, c->oid, c->pos2, c->lo2,
                                c->typ2, c->oid2, s));
     PM_LAUNCH(k_pm_permute_v, dim3((n + kB - 1) / kB), dim3(kB), s, keys, n, m->v, m->v2);
+    c->charged_first = c->n_charged == c->n;   // cell order mixes the two kinds
     std::swap(c->pos, c->pos2);
     std::swap(c->lo, c->lo2);
     std::swap(c->typ, c->typ2);

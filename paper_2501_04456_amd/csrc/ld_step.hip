@@ -10,6 +10,20 @@ using namespace upd;
 
 constexpr int kBlock = 256;
 
+// Force partials of slot s summed in order, four in flight.
+__device__ __forceinline__ void sum_parts(const double* __restrict__ Fpart, int parts, int n,
+                                          int s, double F[3]) {
+    F[0] = F[1] = F[2] = 0.0;
+    const double* Fp = Fpart + s;
+    const size_t N = (size_t)n;
+#pragma unroll 4
+    for (int k = 0; k < parts; ++k, Fp += 3 * N) {
+        F[0] += Fp[0];
+        F[1] += Fp[N];
+        F[2] += Fp[2 * N];
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_update(StepLaunch L, ExtParams P) {
     const long long step = L.st->step;
     const double t = L.st->t;
@@ -22,13 +36,8 @@ __global__ __launch_bounds__(kBlock) void k_update(StepLaunch L, ExtParams P) {
         h = L.pos[s];
         const float4 l = L.lo[s];
         const int ty = L.typ[s];
-        double F[3] = {0.0, 0.0, 0.0};
-        for (int k = 0; k < L.j_split; ++k) {
-            const double* Fp = L.Fpart + (size_t)k * 3 * (size_t)L.n;
-            F[0] += Fp[s];
-            F[1] += Fp[(size_t)L.n + s];
-            F[2] += Fp[2 * (size_t)L.n + s];
-        }
+        double F[3];
+        sum_parts(L.Fpart, s < L.n_full ? L.j_split : 1, L.n, s, F);
         float4 nl = l;
         if (!advance(h, nl, F, ty, R, L.dt, P, (uint32_t)L.oid[s], (unsigned long long)step,
                      L.seed))
@@ -57,20 +66,15 @@ __global__ __launch_bounds__(kBlock) void k_boxes(const float4* __restrict__ pos
 
 __global__ __launch_bounds__(kBlock) void k_gather(
     const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ typ,
-    const int* __restrict__ oid, const double* __restrict__ Fpart, int j_split,
+    const int* __restrict__ oid, const double* __restrict__ Fpart, int j_split, int n_full,
     const double* __restrict__ S_slot, int n, const DevState* st, ExtParams P, double* F_pair,
     double* F_ext, double* S) {
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= n) return;
     const int o = oid[s];
     if (F_pair) {
-        double F[3] = {0.0, 0.0, 0.0};
-        for (int k = 0; k < j_split; ++k) {
-            const double* Fp = Fpart + (size_t)k * 3 * (size_t)n;
-            F[0] += Fp[s];
-            F[1] += Fp[(size_t)n + s];
-            F[2] += Fp[2 * (size_t)n + s];
-        }
+        double F[3];
+        sum_parts(Fpart, s < n_full ? j_split : 1, n, s, F);
         F_pair[3 * (size_t)o] = F[0];
         F_pair[3 * (size_t)o + 1] = F[1];
         F_pair[3 * (size_t)o + 2] = F[2];
@@ -233,12 +237,12 @@ hipError_t launch_boxes(const float4* pos, int n, Box* box, hipStream_t s) {
 }
 
 hipError_t launch_gather(const float4* pos, const float4* lo, const int* typ, const int* oid,
-                         const double* Fpart, int j_split, const double* S_slot, int n,
-                         const DevState* st, const ExtParams& P, double* F_pair,
+                         const double* Fpart, int j_split, int n_full, const double* S_slot,
+                         int n, const DevState* st, const ExtParams& P, double* F_pair,
                          double* F_ext, double* S, hipStream_t s) {
     const int blocks = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_gather, dim3(blocks), dim3(kBlock), 0, s, pos, lo, typ, oid, Fpart,
-                       j_split, S_slot, n, st, P, F_pair, F_ext, S);
+                       j_split, n_full, S_slot, n, st, P, F_pair, F_ext, S);
     return hipGetLastError();
 }
 
