@@ -182,20 +182,27 @@ void default_tuning(ld_ctx* c) {
     ld_tuning& t = c->tune;
     std::memset(&t, 0, sizeof t);
     const int64_t n = c->n;
-    // Enough workgroups to fill 256 CUs (7 resident per CU) many times over
-    // (a short tail), but at least 256 j per split so each workgroup streams
-    // whole LDS tiles.
-    // (block 64 with culling keeps a whole j tile in registers: one
-    // wavefront per SIMD; 128 keeps eight)
-    t.block = n >= 16384 ? 256 : 128;
-    const int64_t tiles = (n + t.block - 1) / t.block;
-    int64_t split = (32768 + tiles - 1) / tiles;
-    int64_t cap = n / 256;
-    if (cap < 1) cap = 1;
-    if (split > cap) split = cap;
-    if (split > 32) split = 32;
-    if (split < 1) split = 1;
-    t.j_split = (int)split;
+    t.block = 256;
+    if (n < kSymMinN) {
+        // One-launch kernel.  Up to 8192 slots eight wavefronts to a workgroup
+        // and two groups each (the Lennard-Jones workgroups are the longest
+        // chains: 5000 slots 28 us a step against 30 with four wavefronts);
+        // above, four, and as many as make eight per SIMD (8192).
+        const int64_t groups = (n + ld::kGroup - 1) / ld::kGroup;
+        if (n <= 8192) t.block = 512;
+        int64_t split = n <= 8192 ? (groups + 15) / 16 : (2048 + groups - 1) / groups;
+        t.j_split = (int)split;
+    } else {
+        // k_pair, where it still runs: enough workgroups to fill 256 CUs (7
+        // resident per CU) many times over (a short tail), but at least 256 j
+        // per split so each workgroup streams whole LDS tiles
+        const int64_t tiles = (n + t.block - 1) / t.block;
+        int64_t split = (32768 + tiles - 1) / tiles;
+        const int64_t cap = n / 256;
+        if (split > cap) split = cap;
+        if (split > 32) split = 32;
+        t.j_split = (int)split;
+    }
     t.comp = 1;            // blocked Kahan over the FP32 blocks (costs ~1 %)
     t.sort_every = 50;
     t.cull = 1;
@@ -210,6 +217,7 @@ void invalidate_graph(ld_ctx* c) {
     }
 }
 
+// Room for `split` force partials.
 ld_status ensure_split_capacity(ld_ctx* c, int split) {
     if (split <= c->j_split_cap) return LD_OK;
     invalidate_graph(c);
@@ -232,9 +240,17 @@ bool use_sym(const ld_ctx* c) {
            c->tune.sort_every > 0 && c->sym.slots <= c->j_split_cap;
 }
 
+// Whether they come from the one-launch kernel of small droplets (with
+// culling; block and j_split shape it).
+bool use_direct(const ld_ctx* c) {
+    return !use_sym(c) && c->n < kSymMinN && c->tune.cull == 1 && c->tune.j_split < c->j_split_cap;
+}
+
 // Force partials the update and the gather add up, and the slots that have
 // more than the first.
-int pair_parts(const ld_ctx* c) { return use_sym(c) ? c->sym.slots : c->tune.j_split; }
+int pair_parts(const ld_ctx* c) {
+    return use_sym(c) ? c->sym.slots : use_direct(c) ? 1 + c->tune.j_split : c->tune.j_split;
+}
 int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; }
 
 ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
@@ -252,14 +268,17 @@ ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
     L.S = diag ? c->S_slot : nullptr;
     L.U = diag ? c->U_slot : nullptr;
     L.sym = !diag && use_sym(c) ? &c->sym : nullptr;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (timed) {
-        if (!ld::timing_events(c, ld::kTimedCoulomb, &e0, &e1))
-            return fail(LD_EHIP, "cannot create timing events");
-        HIP_TRY(hipEventRecord(e0, s));
+    L.direct = !diag && use_direct(c) ? 1 : 0;
+    L.st = c->st;
+    if (L.sym || L.direct) {
+        L.adv_dt = c->pend_dt;             // the last step's clock advance
+        c->pend_dt = 0.0;
     }
-    // timed: the Coulomb kernel alone (the Lennard-Jones kernel follows it)
-    HIP_TRY(ld::launch_pair(L, c->tab, s, timed ? e1 : nullptr));
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (timed && !ld::timing_events(c, ld::kTimedCoulomb, &e0, &e1))
+        return fail(LD_EHIP, "cannot create timing events");
+    // timed: the Coulomb kernel alone, without the Lennard-Jones part
+    HIP_TRY(ld::launch_pair(L, c->tab, s, e0, e1));
     return LD_OK;
 }
 
@@ -296,7 +315,17 @@ ld::StepLaunch step_launch(ld_ctx* c, double dt) {
     return L;
 }
 
-// One step (re-sorting first when due) on stream s.
+// The clock advance of the last update, if it is still due.
+ld_status flush_advance(ld_ctx* c, hipStream_t s) {
+    if (c->pend_dt > 0.0) {
+        HIP_TRY(ld::launch_advance(c->st, c->pend_dt, s));
+        c->pend_dt = 0.0;
+    }
+    return LD_OK;
+}
+
+// One step (re-sorting first when due) on stream s.  The clock advance is
+// left due (flush_advance) for the next step's force launch to take along.
 ld_status enqueue_step(ld_ctx* c, double dt, hipStream_t s, bool timed) {
     if (c->pm) return ld::pm_step(c, dt, s);   // the paper's scheme sorts by cell itself
     if (c->tune.sort_every > 0 && c->steps_since_sort >= c->tune.sort_every) {
@@ -311,12 +340,14 @@ ld_status enqueue_step(ld_ctx* c, double dt, hipStream_t s, bool timed) {
         L.j_split = js;
         L.n_full = (int)c->n;
         HIP_TRY(ld::launch_update(L, c->ext, s));
+        HIP_TRY(ld::launch_advance(c->st, dt, s));
         ++c->steps_since_sort;
         return LD_OK;
     }
     ld_status st = run_pair(c, false, s, timed);
-    if (st != LD_OK) return st;
+    if (st != LD_OK || (st = flush_advance(c, s)) != LD_OK) return st;   // k_pair takes none along
     HIP_TRY(ld::launch_update(step_launch(c, dt), c->ext, s));
+    c->pend_dt = dt;
     ++c->steps_since_sort;
     return LD_OK;
 }
@@ -333,6 +364,8 @@ ld_status capture_chunk(ld_ctx* c, double dt, int len) {
     ld_status st = LD_OK;
     if (c->tune.sort_every > 0) c->steps_since_sort = c->tune.sort_every;
     for (int k = 0; k < len && st == LD_OK; ++k) st = enqueue_step(c, dt, c->cap_stream, false);
+    if (st == LD_OK) st = flush_advance(c, c->cap_stream);
+    c->pend_dt = 0.0;
     hipGraph_t g = nullptr;
     hipError_t err = hipStreamEndCapture(c->cap_stream, &g);
     c->steps_since_sort = saved;
@@ -569,7 +602,7 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
             (void)hipGetLastError();
         }
     }
-    if (!ok || ensure_split_capacity(c, c->tune.j_split) != LD_OK) {
+    if (!ok || ensure_split_capacity(c, c->tune.j_split + 1) != LD_OK) {
         free_all(c);
         delete c;
         return fail(LD_ENOMEM, "device allocation failed for n=%lld", (long long)n);
@@ -706,6 +739,8 @@ ld_status step_loop(ld_ctx* c, double dt, int64_t n_steps) {
         // used once the current sort interval is used up.
         const bool at_chunk = c->tune.sort_every <= 0 || c->steps_since_sort >= c->tune.sort_every;
         if (use_graph && at_chunk && left >= len) {
+            ld_status ast = flush_advance(c, c->stream);
+            if (ast != LD_OK) return ast;
             if (!c->graph || c->graph_dt != dt || c->graph_len != len ||
                 !same_tuning(c->graph_key, c->tune)) {
                 ld_status st = capture_chunk(c, dt, len);
@@ -718,11 +753,12 @@ ld_status step_loop(ld_ctx* c, double dt, int64_t n_steps) {
             continue;
         }
         ld_status st = enqueue_step(c, dt, c->stream, c->timing);
+        if (st == LD_OK && c->rec) st = flush_advance(c, c->stream);   // a frame holds the clock
         if (st != LD_OK) return st;
         if (c->rec && (st = ld::rec_after_step(c, dt, c->stream)) != LD_OK) return st;
         --left;
     }
-    return LD_OK;
+    return flush_advance(c, c->stream);
 }
 
 // Wait for the steps, then the state and FP64 diagnostics at R(t) into *d;
@@ -1120,7 +1156,7 @@ ld_status ld_set_tuning(ld_ctx* c, const ld_tuning* t) {
         return fail(LD_EINVAL, "graph_steps must be in [0, 4096]");
     if (u.sort_every > 4096) return fail(LD_EINVAL, "sort_every must be <= 4096");
     HIP_TRY(hipStreamSynchronize(c->stream));
-    ld_status st = ensure_split_capacity(c, u.j_split);
+    ld_status st = ensure_split_capacity(c, u.j_split + 1);
     if (st != LD_OK) return st;
     c->tune = u;
     invalidate_graph(c);
@@ -1304,7 +1340,7 @@ ld_status ld_autotune(ld_ctx* c, const char* cache_path, int32_t force, ld_tunin
     for (int b : blocks) {
         for (int js : splits) {
             if (js > cap || (c->n + b - 1) / b * (int64_t)js > 65535 * 8) continue;
-            if (ensure_split_capacity(c, js) != LD_OK) continue;
+            if (ensure_split_capacity(c, js + 1) != LD_OK) continue;
             c->tune.block = b;
             c->tune.j_split = js;
             double ms_min = INFINITY;

@@ -128,12 +128,22 @@ struct PairLaunch {
     // Symmetric kernel instead of k_pair (or nullptr): charged slots first,
     // culling on, Fpart [sym->slots][3][n].
     const SymPlan* sym;
+    // One launch for a small droplet (ld_direct.hip) instead of k_pair:
+    // culling on, Fpart [1 + j_split][3][n].
+    int direct;
+    // With sym or direct: the step clock to advance by adv_dt > 0 before
+    // anything reads it (the advance of the step before).
+    DevState* st;
+    double adv_dt;
 };
-hipError_t launch_coulomb_sym(const PairLaunch& L, const PairTable& tab, hipStream_t s);
-// The Coulomb kernel (k_pair) and then the FP64 Lennard-Jones kernel (k_lj);
-// after_coulomb, if given, is recorded between the two.
+hipError_t launch_pair_sym(const PairLaunch& L, const PairTable& tab, hipStream_t s,
+                           hipEvent_t before_coulomb, hipEvent_t after_coulomb);
+hipError_t launch_direct(const PairLaunch& L, const PairTable& tab, hipStream_t s,
+                         hipEvent_t before_coulomb, hipEvent_t after_coulomb);
+// Pair forces into L.Fpart.  The two events, if given, are recorded around
+// the Coulomb part, which then has a launch of its own.
 hipError_t launch_pair(const PairLaunch& L, const PairTable& tab, hipStream_t s,
-                       hipEvent_t after_coulomb = nullptr);
+                       hipEvent_t before_coulomb = nullptr, hipEvent_t after_coulomb = nullptr);
 // Mean square displacement against FP64 reference positions [3][n] in
 // original order: store the reference, or reduce the mean into out[0].
 hipError_t launch_msd_ref(const float4* pos, const float4* lo, const int* oid, int n,
@@ -156,7 +166,8 @@ struct StepLaunch {
     Box* box;                            // refreshed for the new positions
 };
 hipError_t launch_update(const StepLaunch& L, const ExtParams& P, hipStream_t s);
-// Step counter + 1 and t + dt (enqueued after an update).
+// Step counter + 1 and t + dt (enqueued after an update, unless the next
+// step's force launch does it).
 hipError_t launch_advance(DevState* st, double dt, hipStream_t s);
 
 hipError_t launch_boxes(const float4* pos, int n, Box* box, hipStream_t s);
@@ -392,6 +403,7 @@ struct ld_ctx {
     ld::DevState* st = nullptr;
     ld::SortBuffers sb{};
     int64_t steps_since_sort = 0;
+    double pend_dt = 0.0;                // > 0: the last update's clock advance is still due
 
     bool timing = false;
     std::vector<hipEvent_t> ev_pool;

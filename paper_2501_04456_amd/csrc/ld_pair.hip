@@ -218,10 +218,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 64 ? 1 : LD_PAIR_MIN_WAVES) void k_
 }
 
 // Lennard-Jones forces of every slot (and, with DIAG, S and the LJ energy row
-// of U): added into partial 0 after k_pair, or, SYM, stored there after the
-// symmetric kernel, whose partial 0 is this kernel's alone.  One workgroup
-// per 64-slot i group (lj_group).
-template <bool DIAG, bool SYM, int WAVES>
+// of U), added into partial 0 after k_pair.  One workgroup per 64-slot i
+// group (lj_group).
+template <bool DIAG, int WAVES>
 __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict__ pos,
                                                         const float4* __restrict__ lo,
                                                         const int* __restrict__ typ,
@@ -230,27 +229,11 @@ __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict_
                                                         double* __restrict__ S_out,
                                                         double* __restrict__ U_out,
                                                         PairTable tab) {
-    __shared__ double t64[4 * kMaxTypes * kMaxTypes];
-    __shared__ LjShared<WAVES, DIAG ? 5 : 3> sh;
-    for (int k = threadIdx.x; k < kMaxTypes * kMaxTypes; k += WAVES * kGroup) {
-        t64[k] = tab.sig2d[k];
-        t64[kMaxTypes * kMaxTypes + k] = tab.e24d[k];
-        t64[2 * kMaxTypes * kMaxTypes + k] = tab.e4d[k];
-        t64[3 * kMaxTypes * kMaxTypes + k] = tab.rc2d[k];
-    }
-    __syncthreads();
+    __shared__ LjBlock<WAVES, DIAG ? 5 : 3> sh;
     double sums[DIAG ? 5 : 3];
     const int i = blockIdx.x * kGroup + threadIdx.x;
-    if (!lj_group<DIAG, SYM, WAVES>(pos, lo, typ, box, n, blockIdx.x, tab.T, tab.rc2max, t64, sh,
-                                    sums))
-        return;
-    for (int c = 0; c < 3; ++c) {
-        double* Fi = F + (size_t)c * (size_t)n + i;
-        if constexpr (SYM)
-            *Fi = -sums[c];
-        else
-            *Fi -= sums[c];
-    }
+    if (!lj_block<DIAG, false, WAVES>(pos, lo, typ, box, n, blockIdx.x, tab, sh, sums)) return;
+    for (int c = 0; c < 3; ++c) F[(size_t)c * (size_t)n + i] -= sums[c];
     if constexpr (DIAG) {
         S_out[i] += sums[3];
         U_out[i] += sums[4];
@@ -259,14 +242,14 @@ __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict_
 
 // Wavefronts per i group: 16 while the groups are too few to fill the chip
 // with four each.
-template <bool DIAG, bool SYM>
+template <bool DIAG>
 void launch_lj(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
     const dim3 grid((L.n + kGroup - 1) / kGroup);
     if (grid.x < 1024)
-        hipLaunchKernelGGL((k_lj<DIAG, SYM, 16>), grid, dim3(16 * kGroup), 0, s, L.pos, L.lo, L.typ,
+        hipLaunchKernelGGL((k_lj<DIAG, 16>), grid, dim3(16 * kGroup), 0, s, L.pos, L.lo, L.typ,
                            L.box, L.n, L.Fpart, L.S, L.U, tab);
     else
-        hipLaunchKernelGGL((k_lj<DIAG, SYM, 4>), grid, dim3(4 * kGroup), 0, s, L.pos, L.lo, L.typ,
+        hipLaunchKernelGGL((k_lj<DIAG, 4>), grid, dim3(4 * kGroup), 0, s, L.pos, L.lo, L.typ,
                            L.box, L.n, L.Fpart, L.S, L.U, tab);
 }
 
@@ -312,16 +295,17 @@ hipError_t launch_coulomb(const PairLaunch& L, const PairTable& tab, hipStream_t
 }  // namespace
 
 hipError_t launch_pair(const PairLaunch& L, const PairTable& tab, hipStream_t s,
-                       hipEvent_t after_coulomb) {
-    hipError_t e = L.sym ? launch_coulomb_sym(L, tab, s) : launch_coulomb(L, tab, s);
-    if (e != hipSuccess) return e;
+                       hipEvent_t before_coulomb, hipEvent_t after_coulomb) {
+    if (L.sym) return launch_pair_sym(L, tab, s, before_coulomb, after_coulomb);
+    if (L.direct) return launch_direct(L, tab, s, before_coulomb, after_coulomb);
+    hipError_t e;
+    if (before_coulomb && (e = hipEventRecord(before_coulomb, s)) != hipSuccess) return e;
+    if ((e = launch_coulomb(L, tab, s)) != hipSuccess) return e;
     if (after_coulomb && (e = hipEventRecord(after_coulomb, s)) != hipSuccess) return e;
-    if (L.sym)
-        launch_lj<false, true>(L, tab, s);
-    else if (L.S)
-        launch_lj<true, false>(L, tab, s);
+    if (L.S)
+        launch_lj<true>(L, tab, s);
     else
-        launch_lj<false, false>(L, tab, s);
+        launch_lj<false>(L, tab, s);
     return hipGetLastError();
 }
 

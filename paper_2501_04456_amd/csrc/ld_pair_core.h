@@ -72,6 +72,33 @@ __device__ __forceinline__ void group_far(const float4* __restrict__ sp, const f
     }
 }
 
+// 64 j particles at any distance, i itself among them or not, positions
+// relative to one origin near i's group: the far loop, with kTiny added to
+// r^2 so that the self pair's weight stays finite (its differences are 0; the
+// r^2 of any two particles is far above it).
+constexpr float kTiny = 1e-20f;
+template <int COMP>
+__device__ __forceinline__ void group_rel(const float4* __restrict__ sp, const float4 pi, Acc& a) {
+#pragma unroll
+    for (int kb = 0; kb < kGroup; kb += KB) {
+        float bx = 0.f, by = 0.f, bz = 0.f;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            const float4 pj = sp[kb + k];
+            const float dx = pj.x - pi.x;
+            const float dy = pj.y - pi.y;
+            const float dz = pj.z - pi.z;
+            const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, kTiny)));
+            const float ri = __builtin_amdgcn_rsqf(r2);
+            const float w = (pj.w * ri) * (ri * ri);
+            bx = fmaf(w, dx, bx);
+            by = fmaf(w, dy, by);
+            bz = fmaf(w, dz, bz);
+        }
+        flush<COMP>(a, bx, by, bz);
+    }
+}
+
 // 64 j particles near i's group (within the largest LJ range of its box) or
 // holding i itself: the Coulomb terms with the low words of the positions
 // in the differences, the self pair left out.  The difference of the FP32
@@ -413,6 +440,31 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
         for (int v = 0; v < WAVES; ++v) sums[c] += sh.red[v][c][lane];
     }
     return true;
+}
+
+// lj_group with the type constants staged in LDS first (a whole workgroup).
+template <int WAVES, int SUMS>
+struct LjBlock {
+    double t64[4 * kMaxTypes * kMaxTypes];
+    LjShared<WAVES, SUMS> g;
+};
+
+template <bool DIAG, bool SYM, int WAVES>
+__device__ __forceinline__ bool lj_block(const float4* __restrict__ pos,
+                                         const float4* __restrict__ lo,
+                                         const int* __restrict__ typ, const Box* __restrict__ box,
+                                         int n, int gi, const PairTable& tab,
+                                         LjBlock<WAVES, DIAG ? 5 : 3>& sh,
+                                         double (&sums)[DIAG ? 5 : 3]) {
+    for (int k = threadIdx.x; k < kMaxTypes * kMaxTypes; k += WAVES * kGroup) {
+        sh.t64[k] = tab.sig2d[k];
+        sh.t64[kMaxTypes * kMaxTypes + k] = tab.e24d[k];
+        sh.t64[2 * kMaxTypes * kMaxTypes + k] = tab.e4d[k];
+        sh.t64[3 * kMaxTypes * kMaxTypes + k] = tab.rc2d[k];
+    }
+    __syncthreads();
+    return lj_group<DIAG, SYM, WAVES>(pos, lo, typ, box, n, gi, tab.T, tab.rc2max, sh.t64, sh.g,
+                                      sums);
 }
 
 }  // namespace pair

@@ -1,281 +1,62 @@
-// The all-pairs Coulomb sum with every unordered pair evaluated once
-// (Newton's third law), for droplets large enough to fill the chip with it.
-//
-// What bounds it: FP32 VALU issue.  A pair costs 3 differences, 3 for r^2,
-// v_rsq_f32, 2 for r^-3, 2 for the two charge weights and 6 for the two
-// sums -- 16 operations and a root for two forces, where the one-sided loop
-// (k_pair) takes 12 and a root for each.
-//
-// Layout.  A wavefront holds the 64 rows of one slot group I, 16 rows in
-// the registers of each of its four 16-lane groups (position relative to
-// the centre of I's box, and charge: 64 VGPRs, with 48 for their sums), and
-// streams column groups J past them, 16 columns at a time, one column per
-// lane: a lane meets 16 rows per column, so each of the 64 x 16 pairs of a
-// column tile is met by one lane.  Row sums stay in the lane until the end;
-// a column's sum over the 64 rows is finished per column tile by adding the
-// four lane groups (v_permlane32_swap, v_permlane16_swap: 6 operations per
-// 16 pairs).  Rotating columns through the lanes by DPP instead costs a
-// half-rate operation per value and measured no faster than k_pair.
-// Measured, this kernel against k_pair (same box): 250 000 slots, 200 000 of
-// them charged, 10.85 -> 8.05 ms a launch; 32768 charged slots, 331 -> 250 us.
-// The loop alone runs at 29 clocks (2.4 GHz) per 64 ordered pairs per SIMD,
-// k_pair's at 43, and no faster with two or four wavefronts per SIMD than
-// with the three its 160 VGPRs leave.
-//
-// Blocks.  jb consecutive groups (4 or 8) make a block; a workgroup of
-// kSymWaves wavefronts takes the rows of mA blocks against a run of column
-// blocks.  In a column block its wavefronts start at different groups and
-// go round, a barrier per group, so the FP64 column sums in LDS have one
-// writer at a time and a fixed order.  Block pairs are shared out
-// cyclically (a takes b = a + 1 .. a + nbc/2 mod nbc), so every row block
-// has the same work and each unordered pair of blocks one owner.
-//
-// Sums.  Row sums are FP32 over at most 32 columns per lane, added across
-// the 16 lanes and then in FP64; column sums are FP32 over 16 rows per
-// lane and four lane groups, then FP64.  The partial sums a workgroup
-// stores are FP64: one per column block and row super-block, one per row
-// and chunk of column blocks; the update adds them in slot order, so the
-// forces do not depend on timing.
-//
-// Near pairs take the same loop: positions relative to the centre of I's box
-// carry the rounding of tens of sigma.  Where a box is stretched (half-extent
-// of 255 sigma or more: NPs thrown out by a blown-up step), they would lose
-// too much: pairs with a stretched I then use the high words, and pairs of
-// groups near each other of which one is stretched are left to k_lj, which
-// takes their Coulomb terms from the exact (hi, lo) differences in FP64.
-// Groups without charge have no Coulomb terms and are not visited.
-#include "ld_pair_core.h"
+// Forces of a large droplet: the symmetric Coulomb tasks (ld_sym_core.h) and,
+// in the same launch, the Lennard-Jones groups, whose latency they hide.
+#include "ld_sym_core.h"
 
 namespace ld {
 namespace {
 
-using namespace pair;
-
-constexpr int kW = kSymWaves;
-constexpr int kRows = 16;                  // rows per lane
-
 struct SymArgs {
     const float4* pos;
     const float4* lo;
+    const int* typ;
     const Box* box;
     int n, ngroups;
-    float rc2max;
     double* F;                             // [slots][3][n]
+    DevState* st;                          // step clock to advance by adv_dt first (or null)
+    double adv_dt;
+    int lj_blocks, lj_every;               // workgroups that take Lennard-Jones groups
+    PairTable tab;
     SymPlan p;
 };
 
-__device__ __forceinline__ void sync_wave() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ bool stretched(const Box& b) { return !box_compact(b); }
-
-// Slot s relative to o, (hi - o) + lo, or its high words (words); filler past
-// the last slot.
-__device__ __forceinline__ float4 rel_slot(const SymArgs& A, int s, bool words, float3 o) {
-    if (s >= A.n) return make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-    const float4 h = A.pos[s];
-    if (words) return h;
-    const float4 lw = A.lo[s];
-    return make_float4((h.x - o.x) + lw.x, (h.y - o.y) + lw.y, (h.z - o.z) + lw.z, h.w);
-}
-
-// a.lo + a.hi in lanes 0..31, b.lo + b.hi in lanes 32..63.
-__device__ __forceinline__ float fold32(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-// The same between the odd and even 16-lane rows.
-__device__ __forceinline__ float fold16(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-
-// Sums over the 16 lanes of a row of 16 values each: lane c returns the sum
-// of v[c].  A step keeps the half of the values that the lane's bit names and
-// adds the partner's copy of it; the partners (c^15, c^7, c^2, c^1) differ
-// in the step's bit and agree in the bits already used.
-__device__ __forceinline__ float fold_rows(const float (&v)[kRows], int c) {
-    const bool b3 = c & 8, b2 = c & 4, b1 = c & 2, b0 = c & 1;
-    float p[8], q[4], r[2];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        p[k] = (b3 ? v[k + 8] : v[k]) + dpp<0x140>(b3 ? v[k] : v[k + 8]);   // row_mirror
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        q[k] = (b2 ? p[k + 4] : p[k]) + dpp<0x141>(b2 ? p[k] : p[k + 4]);   // row_half_mirror
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-        r[k] = (b1 ? q[k + 2] : q[k]) + dpp<0x4e>(b1 ? q[k] : q[k + 2]);    // lanes 2 3 0 1
-    return (b0 ? r[1] : r[0]) + dpp<0xb1>(b0 ? r[0] : r[1]);                // lanes 1 0 3 2
-}
-
-// One 64 x 64 tile: rows in P (registers), columns in sx (LDS, lane order).
-// Row sums go on in S; the column sums, 64 x {x, y, z}, into sj.  kTiny keeps
-// the self pair's weight finite (its differences are 0) and is far below the
-// r^2 of any two particles; one loop serves near and far tiles alike, as two
-// would each want their own registers for the 48 row sums.
-constexpr float kTiny = 1e-20f;
-__device__ __forceinline__ void tile(const float4* __restrict__ sx, float* __restrict__ sj,
-                                     const float4 (&P)[kRows], float (&Sx)[kRows],
-                                     float (&Sy)[kRows], float (&Sz)[kRows], int g, int c) {
-#pragma unroll 1
-    for (int ct = 0; ct < 4; ++ct) {
-        const float4 v = sx[16 * ct + c];
-        float jx = 0.f, jy = 0.f, jz = 0.f;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const float dx = v.x - P[r].x, dy = v.y - P[r].y, dz = v.z - P[r].z;
-            const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, kTiny)));
-            const float ri = __builtin_amdgcn_rsqf(r2);
-            const float w = ri * (ri * ri);
-            const float wi = w * v.w, wj = w * P[r].w;
-            Sx[r] = fmaf(wi, dx, Sx[r]);
-            Sy[r] = fmaf(wi, dy, Sy[r]);
-            Sz[r] = fmaf(wi, dz, Sz[r]);
-            jx = fmaf(wj, dx, jx);
-            jy = fmaf(wj, dy, jy);
-            jz = fmaf(wj, dz, jz);
-        }
-        // lane group 0: x, 1: y, 2: z of the 16 columns (3: nothing of use)
-        sj[g * kGroup + 16 * ct + c] = fold16(fold32(jx, jz), fold32(jy, 0.f));
-    }
-}
-
-// Does block pair (a, b), taken from row block a, belong to a?  (a != b)
-__device__ __forceinline__ bool owns(int a, int b, int nbc) {
-    int d = b - a;
-    if (d < 0) d += nbc;
-    return 2 * d < nbc || (2 * d == nbc && a < b);
-}
-
 template <int kJB>
-__global__ __launch_bounds__(64 * kW, 3) void k_pair_sym(SymArgs A) {
-    __shared__ float4 sx[kW][kGroup];
-    __shared__ float sj[kW][4 * kGroup];
-    __shared__ double acc[kJB][3][kGroup];      // column sums of the current block
-    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
-    const int l = threadIdx.x % kGroup, g = l >> 4, c = l & 15;
-    const size_t n = (size_t)A.n;
-    const float cull2 = A.rc2max * 1.0001f;
-    // Row super-block and the run of column super-blocks.
-    const int chunk = (int)blockIdx.x / A.p.nA, sa = (int)blockIdx.x % A.p.nA;
-    const int a0 = sa * A.p.mA, a1 = min(a0 + A.p.mA, A.p.nbc);
-    const int s0 = A.p.start[chunk], s1 = A.p.start[chunk + 1];
-    double* Fr = A.F + (size_t)(1 + A.p.nds + chunk) * 3 * n;    // the rows' partials
-    for (int i = a0 * kJB * kGroup + (int)threadIdx.x; i < min(a1 * kJB * kGroup, A.n);
-         i += 64 * kW)
-        for (int k = 0; k < 3; ++k) Fr[k * n + i] = 0.0;
-    for (int ds = s0; ds < s1; ++ds) {
-        const int sb = (sa + ds) % A.p.nA;
-        const int b0 = sb * A.p.mA, b1 = min(b0 + A.p.mA, A.p.nbc);
-        for (int b = b0; b < b1; ++b) {
-            __syncthreads();                     // the last block's sums are read
-            for (int k = threadIdx.x; k < kJB * 3 * kGroup; k += 64 * kW) (&acc[0][0][0])[k] = 0.0;
-            __syncthreads();
-            for (int a = a0; a < a1; ++a) {
-                if (a != b && !owns(a, b, A.p.nbc)) continue;
-#pragma unroll 1
-                for (int ii = 0; ii < kJB / kW; ++ii) {
-                    const int gl = ii * kW + w;           // group within the block
-                    const int gi = a * kJB + gl;
-                    const bool ilive = gi < A.ngroups;
-                    Box bi;
-                    bool ist = false;
-                    float4 P[kRows];
-                    float3 o = make_float3(0.f, 0.f, 0.f);
-                    if (ilive) {
-                        bi = A.box[gi];
-                        ist = stretched(bi);
-                        if (!ist)
-                            o = make_float3(0.5f * (bi.lo.x + bi.hi.x), 0.5f * (bi.lo.y + bi.hi.y),
-                                            0.5f * (bi.lo.z + bi.hi.z));
-                    }
-                    // rows through LDS: a lane's 16 rows are 16-lane broadcasts
-                    sync_wave();
-                    sx[w][l] = rel_slot(A, gi * kGroup + l, ist, o);
-                    sync_wave();
-                    float Sx[kRows], Sy[kRows], Sz[kRows];
-#pragma unroll
-                    for (int r = 0; r < kRows; ++r) {
-                        P[r] = sx[w][g * kRows + r];
-                        Sx[r] = Sy[r] = Sz[r] = 0.f;
-                    }
-#pragma unroll 1
-                    for (int k = 0; k < kJB; ++k) {
-                        const int jl = (k + w * (kJB / kW)) % kJB;
-                        const int gj = b * kJB + jl;
-                        bool take = ilive && gj < A.ngroups;
-                        if (a == b) {                     // within a block, cyclic too
-                            const int d = (jl - gl + kJB) % kJB;
-                            take = take && (2 * d < kJB || (2 * d == kJB && gl < jl));
-                        }
-                        Box bj;
-                        if (take) {
-                            bj = A.box[gj];
-                            take = bi.lo.w != 0.f && bj.lo.w != 0.f;   // both charged
-                        }
-                        if (__builtin_amdgcn_readfirstlane((int)take)) {
-                            const int j = gj * kGroup + l;
-                            const float4 q = rel_slot(A, j, ist, o);
-                            // near pairs with a stretched box are left to k_lj, which
-                            // decides by the same tests (such a box is near almost
-                            // everything, so the particles are tested one by one)
-                            bool exact = false;
-                            if (sym_leaves_out(bi, bj) && box_dist2(bi, bj) < cull2) {
-                                const int i = gi * kGroup + l;
-                                exact = __any(i < A.n && point_box_dist2(A.pos[min(i, A.n - 1)],
-                                                                         bj) < cull2) &&
-                                        __any(j < A.n && point_box_dist2(A.pos[min(j, A.n - 1)],
-                                                                         bi) < cull2);
-                            }
-                            if (!exact) {
-                                sync_wave();
-                                sx[w][l] = q;
-                                sync_wave();
-                                tile(sx[w], sj[w], P, Sx, Sy, Sz, g, c);
-                                sync_wave();
-                                if (gi != gj) {
-                                    for (int d = 0; d < 3; ++d)
-                                        acc[jl][d][l] += (double)sj[w][d * kGroup + l];
-                                }
-                            }
-                        }
-                        // the wavefronts are kJB / kW groups apart
-                        if (k % (kJB / kW) == kJB / kW - 1) __syncthreads();
-                    }
-                    // rows: F_i -= q_i sum_j q_j r^-3 (x_j - x_i)
-                    const float fx = fold_rows(Sx, c), fy = fold_rows(Sy, c),
-                                fz = fold_rows(Sz, c);
-                    const int i = gi * kGroup + l;         // lane (g, c) holds row 16 g + c
-                    if (i < A.n) {
-                        const double qi = (double)A.pos[i].w;
-                        Fr[i] -= qi * (double)fx;
-                        Fr[n + i] -= qi * (double)fy;
-                        Fr[2 * n + i] -= qi * (double)fz;
-                    }
-                }
-            }
-            // columns: F_j += q_j sum_i q_i r^-3 (x_j - x_i)
-            double* Fc = A.F + (size_t)(1 + ds) * 3 * n;
-            for (int jl = w; jl < kJB; jl += kW) {
-                const int j = (b * kJB + jl) * kGroup + l;
-                if (j < A.n) {
-                    const double qj = (double)A.pos[j].w;
-                    for (int d = 0; d < 3; ++d) Fc[d * n + j] = qj * acc[jl][d][l];
-                }
-            }
-        }
+__global__ __launch_bounds__(64 * sym::kW, 3) void k_pair_sym(SymArgs A) {
+    __shared__ union U {
+        sym::Shared<kJB> c;
+        pair::LjBlock<sym::kW, 3> lj;
+        __device__ U() {}
+    } sh;
+    if (A.adv_dt > 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
+        A.st->t = A.st->t + A.adv_dt;
+        A.st->step = A.st->step + 1;
     }
+    // every lj_every-th workgroup takes a Lennard-Jones group while there are any
+    const int turn = (int)blockIdx.x / A.lj_every;
+    if ((int)blockIdx.x % A.lj_every == 0 && turn < A.lj_blocks) {
+        double sums[3];
+        if (!pair::lj_block<false, true, sym::kW>(A.pos, A.lo, A.typ, A.box, A.n, turn, A.tab,
+                                                  sh.lj, sums))
+            return;
+        const size_t i = (size_t)turn * kGroup + threadIdx.x;
+        for (int c = 0; c < 3; ++c) A.F[c * (size_t)A.n + i] = -sums[c];
+        return;
+    }
+    const int t = (int)blockIdx.x - min(A.lj_blocks, turn + 1);
+    const int chunk = t / A.p.nA, sa = t % A.p.nA;
+    sym::View V;
+    V.pos = A.pos;
+    V.lo = A.lo;
+    V.box = A.box;
+    V.n = A.n;
+    V.ngroups = A.ngroups;
+    V.cull2 = A.tab.rc2max * 1.0001f;
+    V.F = A.F;
+    V.stride = (size_t)A.n;
+    V.nbc = A.p.nbc;
+    V.mA = A.p.mA;
+    V.nA = A.p.nA;
+    V.nds = A.p.nds;
+    sym::task<kJB>(V, sa, chunk, A.p.start[chunk], A.p.start[chunk + 1], sh.c);
 }
 
 }  // namespace
@@ -323,23 +104,42 @@ bool sym_plan(int64_t n, int64_t charged, SymPlan* p) {
     return false;
 }
 
-hipError_t launch_coulomb_sym(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
+hipError_t launch_pair_sym(const PairLaunch& L, const PairTable& tab, hipStream_t s,
+                           hipEvent_t before_coulomb, hipEvent_t after_coulomb) {
     SymArgs A{};
     A.pos = L.pos;
     A.lo = L.lo;
+    A.typ = L.typ;
     A.box = L.box;
     A.n = L.n;
     A.ngroups = (L.n + kGroup - 1) / kGroup;
-    A.rc2max = tab.rc2max;
     A.F = L.Fpart;
+    A.st = L.st;
+    A.adv_dt = L.adv_dt;
+    A.tab = tab;
     A.p = *L.sym;
-    const dim3 grid(A.p.nA * A.p.nchunk);
-    if (grid.x == 0) return hipSuccess;                      // nothing charged
-    if (A.p.jb == 4)
-        hipLaunchKernelGGL(k_pair_sym<4>, grid, dim3(64 * kW), 0, s, A);
-    else
-        hipLaunchKernelGGL(k_pair_sym<8>, grid, dim3(64 * kW), 0, s, A);
-    return hipGetLastError();
+    const int tasks = A.p.nA * A.p.nchunk;                   // 0: nothing charged
+    auto launch = [&](int lj, int coulomb) {
+        A.lj_blocks = lj;
+        if (lj + coulomb == 0) return;
+        A.lj_every = lj > 0 ? (lj + coulomb) / lj : 1;
+        if (A.p.jb == 4)
+            hipLaunchKernelGGL(k_pair_sym<4>, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
+        else
+            hipLaunchKernelGGL(k_pair_sym<8>, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
+        A.adv_dt = 0.0;
+    };
+    if (!after_coulomb) {
+        launch(A.ngroups, tasks);
+        return hipGetLastError();
+    }
+    // timed: the Coulomb tasks by themselves
+    launch(A.ngroups, 0);
+    hipError_t e = hipEventRecord(before_coulomb, s);
+    if (e != hipSuccess) return e;
+    launch(0, tasks);
+    e = hipEventRecord(after_coulomb, s);
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace ld

@@ -48,9 +48,10 @@ __global__ __launch_bounds__(kBlock) void k_update(StepLaunch L, ExtParams P) {
     if (L.box) write_box(h, live, s, L.box);
 }
 
-// Step counter and time advance after the update (a launch of its own: a
-// per-workgroup completion count would serialise one device-scope atomic
-// and fence per workgroup).  t_{n+1} = t_n + dt as the update computed it.
+// Step counter and time advance after the update (every workgroup of which
+// reads them; a per-workgroup completion count would serialise one
+// device-scope atomic and fence per workgroup).  A launch of its own after
+// the last step of a run; between steps the next force launch does it.  t_{n+1} = t_n + dt as the update computed it.
 __global__ void k_advance(DevState* st, double dt) {
     st->t = st->t + dt;
     st->step = st->step + 1;
@@ -221,7 +222,6 @@ hipError_t launch_msd(const float4* pos, const float4* lo, const int* oid, int n
 hipError_t launch_update(const StepLaunch& L, const ExtParams& P, hipStream_t s) {
     const int blocks = (L.n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_update, dim3(blocks), dim3(kBlock), 0, s, L, P);
-    hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, L.st, L.dt);
     return hipGetLastError();
 }
 
