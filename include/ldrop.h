@@ -490,40 +490,35 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
                       const ld_radius* R, const uint64_t* seeds, void* stream);
 void ld_ens_destroy(ld_ens* e);
 
-/* Launch shape of the persistent pair kernel (workgroups of 256 work-items;
- * 0 keeps the current count), compensation mode (0 FP64 flush, 1 blocked
- * Kahan), and the number of steps captured in one HIP graph (0: no graph).
- * Captured steps replay with the dt they were captured with. */
+/* workgroups, comp: settings of a one-sided pair kernel, checked, kept and
+ * reported (0 workgroups keeps the current count); the symmetric pair tasks
+ * have one launch shape and sum in FP64 blocks for either comp.  graph_steps:
+ * the number of steps captured in one HIP graph (0: no graph).  Captured
+ * steps replay with the dt they were captured with. */
 ld_status ld_ens_set_tuning(ld_ens* e, int32_t workgroups, int32_t comp, int32_t graph_steps);
 
 /* out = {workgroups, comp, graph_steps, unroll, rows}. */
 ld_status ld_ens_get_tuning(ld_ens* e, int32_t out[5]);
 
-/* Coulomb pairs in flight per lane in the persistent pair kernel: 8, 16
- * (default) or 32.  Errors: LD_EINVAL. */
+/* 8, 16 (default) or 32; checked, kept and reported, without effect on the
+ * symmetric pair tasks.  Errors: LD_EINVAL. */
 ld_status ld_ens_set_unroll(ld_ens* e, int32_t unroll);
 
-/* Slots per work item of the persistent pair kernel: 64 (default; a
- * wavefront per 64-slot tile, each staging its own j tiles) or 256 (a
- * workgroup per block of four tiles, sharing staged j tiles of 256).  The
- * forces are bit for bit the same either way.  Errors: LD_EINVAL. */
+/* 64 (default) or 256; checked, kept and reported, without effect on the
+ * symmetric pair tasks.  Errors: LD_EINVAL. */
 ld_status ld_ens_set_rows(ld_ens* e, int32_t rows);
 
-/* Choose the persistent pair kernel's workgroup count (2..8 per compute
- * unit), unroll (8, 16, 32) and work-item rows (64, 256) by timing the pair
- * step (forces only; the droplets do not move) with HIP events, keeping the
- * compensation mode and graph length; none of the searched settings changes
- * the forces.  A spatial re-sort that is due (a new ensemble's first, or
- * one the sort interval calls for) is done first, as the next step would
- * have done it, so the timings see the slot order the steps use and the
- * trajectory is unchanged; forces read right after this call come in that
- * order's summation.  The four fastest settings of one pass are timed again
- * as bursts of launches.  cache_path (or NULL): a text file of lines
+/* Time the pair step at the current settings (forces only; the droplets do
+ * not move); the symmetric pair tasks leave no launch shape to choose.  A
+ * spatial re-sort that is due (a new ensemble's first, or one the sort
+ * interval calls for) is done first, as the next step would have done it, so
+ * the trajectory is unchanged; forces read right after this call come in that
+ * order's summation.  cache_path (or NULL): a text file of lines
  * "key workgroups unroll rows ms"; the key holds the GPU architecture, the
  * droplet count, quarter-octave buckets of sum_d N_d^2 and of the largest
- * N_d, the culling and compensation modes.  A cached key is used without
- * timing unless force != 0; new results are appended.  out (or NULL) as in
- * ld_ens_get_tuning.  Errors: LD_EINVAL, LD_EHIP. */
+ * N_d, the culling and compensation modes.  A cached key's settings are taken
+ * over without timing unless force != 0; new results are appended.  out (or
+ * NULL) as in ld_ens_get_tuning.  Errors: LD_EINVAL, LD_EHIP. */
 ld_status ld_ens_autotune(ld_ens* e, const char* cache_path, int32_t force, int32_t out[5]);
 
 /* Advance all droplets n_steps >= 0 steps of size dt > 0 (asynchronous). */
@@ -541,7 +536,7 @@ ld_status ld_ens_get_state(ld_ens* e, int64_t* step, double* t);
 /* Wait; report a pending blow-up once (LD_ENONFINITE) and clear it. */
 ld_status ld_ens_sync(ld_ens* e);
 
-/* HIP-event timing of every persistent pair launch (see ld_kernel_timing);
+/* HIP-event timing of every launch of the pair tasks (see ld_kernel_timing);
  * timing disables graph replay while it is on. */
 ld_status ld_ens_kernel_timing(ld_ens* e, int32_t enable);
 ld_status ld_ens_kernel_time(ld_ens* e, int64_t* launches, double* total_ms);

@@ -1,27 +1,25 @@
-// Ensembles of independent droplets in one persistent launch.
+// Ensembles of independent droplets in one launch.
 //
 // Every droplet d owns a contiguous slot range [off[d], off[d+1]) with its own
-// parameters, radius schedule and noise seed.  The pair sum is split into
-// work items (droplet, 64-particle i tile); an item costs 64 x N_d pairs.
-// Items are ordered longest first and pulled from one atomic counter by
-// resident wavefronts, so a few large droplets cannot leave the chip idle at
-// the end of the step.  Each wavefront stages j tiles of its item's droplet
-// in its own LDS slice.  The update runs over all slots of all droplets in
-// one launch.  A droplet's noise is keyed by its seed and the particle's
-// index inside the droplet, so each droplet follows exactly the stream it
-// would follow alone.
+// parameters, radius schedule and noise seed, and its own force partials.  The
+// pair sum of all droplets is one list of tasks of the symmetric kernel
+// (ld_sym_core.h: the rows of a block of 256 slots of a droplet against a run
+// of its column blocks), longest first, with the Lennard-Jones groups of all
+// droplets spread between them.  The update runs over all 64-slot tiles of
+// all droplets in one launch and leaves the tiles' new boxes.  A droplet's
+// noise is keyed by its seed and the particle's index inside the droplet, so
+// each droplet follows exactly the stream it would follow alone.
 //
 // Every sort interval each droplet's slots are re-ordered along a Hilbert
-// curve over the droplet's own bounding cube (uncharged particles last), and
-// every step each 64-slot tile of a droplet gets a bounding box and a charged
-// flag.  The pair kernel then treats a pair of tiles like the single-droplet
-// kernel treats a pair of groups: careful loop when the boxes come within the
-// largest LJ range, Coulomb-only loop when they do not, nothing when one
-// side is uncharged.  In the careful loop both sides' positions are taken
-// relative to the centre of the i tile's box, (hi - c) + lo rounded to FP32,
-// so a pair difference carries the rounding of a coordinate tens of sigma
-// from c rather than of |x|.  Outputs are mapped back to the original order
+// curve over the droplet's own bounding cube (uncharged particles last), which
+// keeps the tiles compact.  Outputs are mapped back to the original order
 // through the per-droplet index, which travels with the particle.
+//
+// Measured on 256 droplets of 500 to 8000 charged NPs (sum of N^2 3.04e9),
+// against one-sided tiles drawn by persistent wavefronts from an atomic queue
+// (longest first), a Lennard-Jones launch, a box launch and two one-thread
+// launches: a step 1189 -> 971 us.  12 droplets of 500 to 2000: 141 -> 27 us
+// (there a wavefront had walked a whole droplet by itself).
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -29,7 +27,7 @@
 #include <new>
 
 #include "ld_host.h"
-#include "ld_pair_core.h"
+#include "ld_sym_core.h"
 #include "ld_update_core.h"
 
 using namespace ld;
@@ -37,277 +35,129 @@ using namespace ld::host;
 
 namespace {
 
-constexpr int kWaves = 4;                 // wavefronts per workgroup
-constexpr int kEnsBlock = kWaves * kGroup;
 constexpr int kEnsSortEvery = 50;         // sort interval without graphs
+constexpr int kEnsJB = 4;                 // groups per block of the symmetric tasks
+constexpr size_t kEnsMaxBytes = 16ull << 30;   // force partials beyond which tasks are coarsened
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// Per-droplet constants of the pair tasks: blocks, blocks per super-block,
+// super-blocks, column partials, partials in all; first force partial.
+struct DropPlan {
+    int nb, mA, nA, nds, slots, pad;
+    long long base;                       // first double of F[slots][3][N_d]
+};
 
-__global__ void k_ens_reset(unsigned* counter) { *counter = 0u; }
+struct EnsPairArgs {
+    const float4* pos;
+    const float4* lo;
+    const int* typ;
+    const int* off;
+    const int2* tiles;                    // (droplet, first slot) of every 64-slot tile
+    const int4* tasks;                    // droplet, super-block, chunk, distances s0 | s1 << 16
+    const int* tbase;
+    const Box* box;
+    const PairTable* tabs;
+    const DropPlan* plan;
+    double* F;
+    DevState* st;                         // step clock to advance by adv_dt first
+    double adv_dt;
+    int lj_blocks, lj_every;
+};
 
-// The careful loop works on positions relative to the tile box's centre when
-// the box is compact (half-extent below kRelReach sigma: |x - c| < 256 sigma,
-// so (hi - c) + lo carries at most two FP32 roundings of 2^-17 sigma); a box
-// stretched by NPs thrown far out keeps the exact (hi, lo) differences.
-constexpr float kRelReach = 255.f;
-
-__device__ __forceinline__ bool tile_compact(const Box& b) {
-    const float ext = fmaxf(fmaxf(b.hi.x - b.lo.x, b.hi.y - b.lo.y), b.hi.z - b.lo.z);
-    return ext < 2.f * kRelReach;           // false for NaN or infinite boxes too
-}
-
-template <int COMP, bool CULL, int UNROLL>
-__global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair(
-    const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ typ,
-    const int* __restrict__ off, const int2* __restrict__ items, int W, unsigned* counter, const PairTable* __restrict__ tabs,
-    const Box* __restrict__ box, const int* __restrict__ tbase, double* __restrict__ F,
-    int total) {
-    __shared__ float4 sp[kWaves][kGroup];
-    __shared__ float4 sl[kWaves][kGroup];          // low words (stretched tiles only)
-    const int w = threadIdx.x / kGroup;
-    const int lane = threadIdx.x % kGroup;
-    for (;;) {
-        unsigned item = 0u;
-        if (lane == 0) item = atomicAdd(counter, 1u);
-        item = (unsigned)__shfl((int)item, 0);
-        if (item >= (unsigned)W) break;
-        const int2 it = items[item];
-        const int d = it.x;
-        const int o = off[d];
-        const int nd = off[d + 1] - o;
-        const float rc2max = tabs[d].rc2max;
-        const int i = it.y + lane;
-        const bool live = i < nd;
-        const float4 pi = live ? pos[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 li = live ? lo[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-        pair::Acc a;
-        Box bi;
-        const int t0 = tbase[d];
-        // origin of the near tiles' positions: the centre of the tile's box,
-        // else its first particle
-        float4 c = make_float4(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.x))),
-                               __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.y))),
-                               __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.z))),
-                               0.f);
-        bool rel = false;
-        if constexpr (CULL) {
-            bi = box[t0 + it.y / kGroup];
-            c = make_float4(0.5f * (bi.lo.x + bi.hi.x), 0.5f * (bi.lo.y + bi.hi.y),
-                            0.5f * (bi.lo.z + bi.hi.z), 0.f);
-            rel = tile_compact(bi);
-        }
-        const float4 pr = make_float4((pi.x - c.x) + li.x, (pi.y - c.y) + li.y,
-                                      (pi.z - c.z) + li.z, pi.w);
-        const float cull2 = rc2max * 1.0001f;
-        for (int jt = 0; jt < nd; jt += kGroup) {
-            bool near = true;
-            if constexpr (CULL) {
-                // box values are uniform across the wavefront
-                const Box bj = box[t0 + jt / kGroup];
-                near = __builtin_amdgcn_readfirstlane((int)(pair::box_dist2(bi, bj) < cull2));
-                const bool coulomb =
-                    __builtin_amdgcn_readfirstlane((int)(bi.lo.w != 0.f && bj.lo.w != 0.f));
-                if (!near && !coulomb) continue;
-            }
-            wave_sync();
-            const int j = jt + lane;
-            float4 pj = j < nd ? pos[o + j] : make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-            if (near && j < nd) {              // near tiles: relative to c, or low words apart
-                const float4 lj = lo[o + j];
-                if (rel)
-                    pj = make_float4((pj.x - c.x) + lj.x, (pj.y - c.y) + lj.y,
-                                     (pj.z - c.z) + lj.z, pj.w);
-                else
-                    sl[w][lane] = lj;
-            } else if (near && !rel) {
-                sl[w][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            sp[w][lane] = pj;
-            wave_sync();
-            if (near) {
-                if (rel)
-                    pair::group_near_rel<COMP, false>(sp[w], jt, i, pr, a);
-                else
-                    pair::group_near<COMP, false>(sp[w], sl[w], jt, i, pi, li, a);
-            } else
-                pair::group_far<COMP, UNROLL>(sp[w], pi, a);
-        }
-        if constexpr (COMP == 1) {
-            a.Fx = (double)a.sx - (double)a.cx;
-            a.Fy = (double)a.sy - (double)a.cy;
-            a.Fz = (double)a.sz - (double)a.cz;
-        }
-        if (live) {
-            const double qi = (double)pi.w;
-            const size_t s = (size_t)(o + i);
-            F[s] = -qi * a.Fx;
-            F[(size_t)total + s] = -qi * a.Fy;
-            F[2 * (size_t)total + s] = -qi * a.Fz;
-        }
+__global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
+    __shared__ union U {
+        sym::Shared<kEnsJB> c;
+        pair::LjShared<sym::kW, 3> lj;
+        __device__ U() {}
+    } sh;
+    if (A.adv_dt > 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
+        A.st->t = A.st->t + A.adv_dt;
+        A.st->step = A.st->step + 1;
     }
-}
-
-// The same sums with 256-slot work items (droplet, block of four tiles): the
-// workgroup's four wavefronts own the four tiles and share each staged tile
-// of 256 j (high and low words), so a staging wait serves 4 x 256 pairs per
-// lane instead of 64.  A near j group is restaged by its wavefront alone, relative
-// to the centre of that wavefront's own tile box, exactly as in k_ens_pair;
-// every lane sees the same j groups in the same order with the same inputs,
-// so the forces are bit for bit those of k_ens_pair.
-template <int COMP, bool CULL, int UNROLL>
-__global__ __launch_bounds__(kEnsBlock, 5) void k_ens_pair_b(
-    const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ off,
-    const int2* __restrict__ items, int W, unsigned* counter,
-    const PairTable* __restrict__ tabs, const Box* __restrict__ box,
-    const int* __restrict__ tbase, double* __restrict__ F, int total) {
-    __shared__ float4 sp[kEnsBlock];                 // shared j tile (high words)
-    __shared__ float4 sl[kEnsBlock];                 // and its low words
-    __shared__ float4 sr[kWaves][kGroup];            // a wavefront's near group, relative
-    __shared__ unsigned item_s;
-    const int w = threadIdx.x / kGroup;
-    const int lane = threadIdx.x % kGroup;
-    for (;;) {
-        __syncthreads();                             // item_s free to overwrite
-        if (threadIdx.x == 0) item_s = atomicAdd(counter, 1u);
-        __syncthreads();
-        const unsigned item = item_s;
-        if (item >= (unsigned)W) break;              // uniform per workgroup
-        const int2 it = items[item];
-        const int d = it.x;
-        const int o = off[d];
-        const int nd = off[d + 1] - o;
-        const float rc2max = tabs[d].rc2max;
-        const int i0 = it.y + w * kGroup;            // this wavefront's tile
-        const bool wlive = i0 < nd;
-        const int i = i0 + lane;
-        const bool live = i < nd;
-        const float4 pi = live ? pos[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 li = live ? lo[o + i] : make_float4(0.f, 0.f, 0.f, 0.f);
-        pair::Acc a;
-        Box bi;
-        const int t0 = tbase[d];
-        float4 c = make_float4(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.x))),
-                               __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.y))),
-                               __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pi.z))),
-                               0.f);
-        bool rel = false;
-        if constexpr (CULL) {
-            if (wlive) {
-                bi = box[t0 + i0 / kGroup];
-                c = make_float4(0.5f * (bi.lo.x + bi.hi.x), 0.5f * (bi.lo.y + bi.hi.y),
-                                0.5f * (bi.lo.z + bi.hi.z), 0.f);
-                rel = tile_compact(bi);
-            }
-        }
-        const float4 pr = make_float4((pi.x - c.x) + li.x, (pi.y - c.y) + li.y,
-                                      (pi.z - c.z) + li.z, pi.w);
-        const float cull2 = rc2max * 1.0001f;
-        for (int jt = 0; jt < nd; jt += kEnsBlock) {
-            __syncthreads();
-            const int js = jt + (int)threadIdx.x;
-            sp[threadIdx.x] = js < nd ? pos[o + js] : make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-            sl[threadIdx.x] = js < nd ? lo[o + js] : make_float4(0.f, 0.f, 0.f, 0.f);
-            __syncthreads();
-            if (!wlive) continue;
-#pragma unroll 1
-            for (int g = 0; g < kWaves; ++g) {
-                const int jg = jt + g * kGroup;
-                if (jg >= nd) break;
-                bool near = true;
-                if constexpr (CULL) {
-                    const Box bj = box[t0 + jg / kGroup];
-                    near = __builtin_amdgcn_readfirstlane((int)(pair::box_dist2(bi, bj) < cull2));
-                    const bool coulomb =
-                        __builtin_amdgcn_readfirstlane((int)(bi.lo.w != 0.f && bj.lo.w != 0.f));
-                    if (!near && !coulomb) continue;
-                }
-                if (near) {
-                    if (rel) {
-                        const int j = jg + lane;
-                        float4 pj = sp[g * kGroup + lane];
-                        if (j < nd) {
-                            const float4 lw = sl[g * kGroup + lane];
-                            pj = make_float4((pj.x - c.x) + lw.x, (pj.y - c.y) + lw.y,
-                                             (pj.z - c.z) + lw.z, pj.w);
-                        }
-                        wave_sync();
-                        sr[w][lane] = pj;
-                        wave_sync();
-                        pair::group_near_rel<COMP, false>(sr[w], jg, i, pr, a);
-                    } else {
-                        pair::group_near<COMP, false>(sp + g * kGroup, sl + g * kGroup, jg, i, pi,
-                                                      li, a);
-                    }
-                } else {
-                    pair::group_far<COMP, UNROLL>(sp + g * kGroup, pi, a);
-                }
-            }
-        }
-        if constexpr (COMP == 1) {
-            a.Fx = (double)a.sx - (double)a.cx;
-            a.Fy = (double)a.sy - (double)a.cy;
-            a.Fz = (double)a.sz - (double)a.cz;
-        }
-        if (live) {
-            const double qi = (double)pi.w;
-            const size_t sl = (size_t)(o + i);
-            F[sl] = -qi * a.Fx;
-            F[(size_t)total + sl] = -qi * a.Fy;
-            F[2 * (size_t)total + sl] = -qi * a.Fz;
-        }
-    }
-}
-
-// Lennard-Jones forces of every tile of every droplet, in FP64, added into F
-// after k_ens_pair.  One workgroup per 64-slot tile (pair::lj_group).
-__global__ __launch_bounds__(kEnsBlock) void k_ens_lj(
-    const float4* __restrict__ pos, const float4* __restrict__ lo, const int* __restrict__ typ,
-    const int* __restrict__ off, const int2* __restrict__ tiles,
-    const PairTable* __restrict__ tabs, const Box* __restrict__ box,
-    const int* __restrict__ tbase, double* __restrict__ F, int total) {
-    __shared__ pair::LjShared<kWaves, 3> sh;
-    const int2 tl = tiles[blockIdx.x];
+    const int turn = (int)blockIdx.x / A.lj_every;
+    const bool lj = (int)blockIdx.x % A.lj_every == 0 && turn < A.lj_blocks;
+    int4 tk = make_int4(0, 0, 0, 0);
+    if (!lj) tk = A.tasks[(int)blockIdx.x - min(A.lj_blocks, turn + 1)];
+    const int2 tl = lj ? A.tiles[turn] : make_int2(tk.x, 0);
     const int d = tl.x;
-    const int o = off[d];
-    const PairTable* tb = tabs + d;          // sig2d, e24d, e4d, rc2d follow each other
-    double sums[3];
-    if (!pair::lj_group<false, false, kWaves>(pos + o, lo + o, typ + o, box + tbase[d],
-                                              off[d + 1] - o, (tl.y - o) / kGroup, tb->T,
-                                              tb->rc2max, tb->sig2d, sh, sums))
+    const int o = A.off[d], nd = A.off[d + 1] - o;
+    const DropPlan pl = A.plan[d];
+    const PairTable* tb = A.tabs + d;         // sig2d, e24d, e4d, rc2d follow each other
+    double* F = A.F + pl.base;
+    if (lj) {
+        double sums[3];
+        if (!pair::lj_group<false, true, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
+                                                  A.box + A.tbase[d], nd, (tl.y - o) / kGroup,
+                                                  tb->T, tb->rc2max, tb->sig2d, sh.lj, sums))
+            return;
+        const size_t i = (size_t)(tl.y - o) + threadIdx.x;
+        for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
         return;
-    const size_t s = (size_t)tl.y + threadIdx.x;
-    F[s] -= sums[0];
-    F[(size_t)total + s] -= sums[1];
-    F[2 * (size_t)total + s] -= sums[2];
+    }
+    sym::View V;
+    V.pos = A.pos + o;
+    V.lo = A.lo + o;
+    V.box = A.box + A.tbase[d];
+    V.n = nd;
+    V.ngroups = (nd + kGroup - 1) / kGroup;
+    V.cull2 = tb->rc2max * 1.0001f;
+    V.F = F;
+    V.stride = (size_t)nd;
+    V.nbc = pl.nb;
+    V.mA = pl.mA;
+    V.nA = pl.nA;
+    V.nds = pl.nds;
+    sym::task<kEnsJB>(V, tk.y, tk.z, tk.w & 0xffff, tk.w >> 16, sh.c);
 }
 
+// Force of a droplet's slot i: its partials in order, four in flight.
+__device__ __forceinline__ void ens_sum(const double* __restrict__ F, int slots, int nd, int i,
+                                        double f[3]) {
+    f[0] = f[1] = f[2] = 0.0;
+    const double* Fp = F + i;
+    const size_t N = (size_t)nd;
+#pragma unroll 4
+    for (int k = 0; k < slots; ++k, Fp += 3 * N) {
+        f[0] += Fp[0];
+        f[1] += Fp[N];
+        f[2] += Fp[2 * N];
+    }
+}
+
+// One wavefront per 64-slot tile: the update and the tile's new box.
 __global__ __launch_bounds__(256) void k_ens_update(float4* pos, float4* lo,
                                                     const int* __restrict__ typ,
-                                                    const int* __restrict__ did,
                                                     const int* __restrict__ lid,
-                                                    const double* __restrict__ F, int total,
+                                                    const int* __restrict__ off,
+                                                    const int2* __restrict__ tiles, int ntiles,
+                                                    const DropPlan* __restrict__ plan,
+                                                    const double* __restrict__ F,
                                                     const ExtParams* __restrict__ ext,
                                                     const unsigned long long* __restrict__ seeds,
-                                                    double dt, DevState* st) {
+                                                    double dt, DevState* st, Box* box) {
     const long long step = st->step;
     const double tn = st->t + dt;
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s < total) {
-        const int d = did[s];
+    const int g = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + threadIdx.x / kGroup));
+    if (g >= ntiles) return;
+    const int2 t = tiles[g];
+    const int d = t.x, o = off[d], nd = off[d + 1] - o;
+    const int s = t.y + (int)(threadIdx.x % kGroup);
+    const bool live = s < o + nd;
+    float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (live) {
         const ExtParams& P = ext[d];
+        const DropPlan pl = plan[d];
         const double R = radius_at(P.R, tn);
-        float4 h = pos[s], l = lo[s];
-        const double Fs[3] = {F[s], F[(size_t)total + s], F[2 * (size_t)total + s]};
-        if (!upd::advance(h, l, Fs, typ[s], R, dt, P, (uint32_t)lid[s],
-                          (unsigned long long)step, seeds[d]))
+        h = pos[s];
+        float4 l = lo[s];
+        double f[3];
+        ens_sum(F + pl.base, pl.slots, nd, s - o, f);
+        if (!upd::advance(h, l, f, typ[s], R, dt, P, (uint32_t)lid[s], (unsigned long long)step,
+                          seeds[d]))
             atomicMin(&st->bad_step, (unsigned long long)step);
         pos[s] = h;
         lo[s] = l;
     }
+    upd::write_tile_box(h, live, box + g);
 }
 
 // Bounding box and charged flag of every 64-slot tile (one wavefront each).
@@ -321,16 +171,7 @@ __global__ __launch_bounds__(256) void k_ens_boxes(const float4* __restrict__ po
     const int s = t.y + (int)(threadIdx.x % kGroup);
     const bool live = s < off[t.x + 1];
     const float4 h = live ? pos[s] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float lx = upd::wave_min(live ? h.x : INFINITY), hx = upd::wave_max(live ? h.x : -INFINITY);
-    const float ly = upd::wave_min(live ? h.y : INFINITY), hy = upd::wave_max(live ? h.y : -INFINITY);
-    const float lz = upd::wave_min(live ? h.z : INFINITY), hz = upd::wave_max(live ? h.z : -INFINITY);
-    const bool charged = __any(live && h.w != 0.f);
-    if (threadIdx.x % kGroup == 0) {
-        Box b;
-        b.lo = make_float4(lx, ly, lz, charged ? 1.f : 0.f);
-        b.hi = make_float4(hx, hy, hz, 0.f);
-        box[g] = b;
-    }
+    upd::write_tile_box(h, live, box + g);
 }
 
 // Bounding box of every droplet (one workgroup each), [n_drop][6].
@@ -403,16 +244,18 @@ __global__ __launch_bounds__(256) void k_ens_gather(const float4* __restrict__ p
 }
 
 __global__ __launch_bounds__(256) void k_ens_forces_aos(const double* __restrict__ F,
+                                                        const DropPlan* __restrict__ plan,
                                                         const int* __restrict__ did,
                                                         const int* __restrict__ lid,
                                                         const int* __restrict__ off, int total,
                                                         double* out) {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= total) return;
-    const size_t o = (size_t)off[did[s]] + (size_t)lid[s];
-    out[3 * o] = F[s];
-    out[3 * o + 1] = F[(size_t)total + s];
-    out[3 * o + 2] = F[2 * (size_t)total + s];
+    const int d = did[s];
+    const size_t o = (size_t)off[d] + (size_t)lid[s];
+    double f[3];
+    ens_sum(F + plan[d].base, plan[d].slots, off[d + 1] - off[d], s - off[d], f);
+    for (int c = 0; c < 3; ++c) out[3 * o + c] = f[c];
 }
 
 }  // namespace
@@ -429,22 +272,20 @@ struct ld_ens {
     int* did = nullptr;
     int* lid = nullptr;
     int* off = nullptr;
-    int2* items = nullptr;               // (droplet, first slot) of every 64-slot tile
-    int W = 0;
-    int2* items_b = nullptr;             // (droplet, first slot) of every 256-slot block
-    int W_b = 0;
-    int rows = 64;                       // slots per work item: 64 (k_ens_pair) or 256 (k_ens_pair_b)
-    unsigned* counter = nullptr;
+    int4* tasks = nullptr;               // pair tasks, longest first
+    int ntasks = 0;
+    DropPlan* plan = nullptr;            // [n_drop]
     PairTable* tabs = nullptr;
     ExtParams* ext = nullptr;
     unsigned long long* seeds = nullptr;
-    double* F = nullptr;
+    double* F = nullptr;                 // every droplet's partials [slots][3][N_d]
     double* work = nullptr;              // [3 * total] output staging
     DevState* st = nullptr;
-    int workgroups = 0;
-    int comp = 0;
+    // launch settings of the interface: stored and reported; the symmetric
+    // tasks have one launch shape and FP64 totals whatever they say
+    int workgroups = 0, comp = 0, unroll = 16, rows = 64;
     int graph_steps = 0;
-    int unroll = 16;                     // Coulomb pairs in flight per lane (8, 16 or 32)
+    double pend_dt = 0.0;                // > 0: the last update's clock advance is still due
     hipGraphExec_t graph = nullptr;
     double graph_dt = 0.0;
     int graph_len = 0;
@@ -466,7 +307,7 @@ namespace {
 
 void ens_free(ld_ens* e) {
     void* bufs[] = {e->pos,   e->lo,   e->typ,   e->did,     e->lid,   e->off,
-                    e->items, e->counter, e->tabs, e->ext,   e->seeds, e->F, e->items_b,
+                    e->tasks, e->plan,  e->tabs, e->ext,   e->seeds, e->F,
                     e->work,  e->st,   e->box,   e->tbase,   e->tiles, e->dbounds,
                     e->sb.keys, e->sb.tmp4, e->sb.tmp_i};
     for (void* b : bufs)
@@ -482,6 +323,13 @@ int sort_interval(const ld_ens* e) {
     return e->graph_steps > 0 ? e->graph_steps : kEnsSortEvery;
 }
 
+ld_status enqueue_boxes(ld_ens* e, hipStream_t s) {
+    hipLaunchKernelGGL(k_ens_boxes, dim3((e->ntiles + 3) / 4), dim3(256), 0, s, e->pos, e->off,
+                       e->tiles, e->ntiles, e->box);
+    HIP_TRY(hipGetLastError());
+    return LD_OK;
+}
+
 // Re-order every droplet's slots along its Hilbert curve.
 ld_status enqueue_sort(ld_ens* e, hipStream_t s) {
     hipLaunchKernelGGL(k_ens_bounds, dim3(e->n_drop), dim3(256), 0, s, e->pos, e->off,
@@ -490,65 +338,53 @@ ld_status enqueue_sort(ld_ens* e, hipStream_t s) {
                        e->did, e->dbounds, e->total, e->sb.n_pow2, e->sb.keys);
     HIP_TRY(hipGetLastError());
     HIP_TRY(ld::launch_sort_by_keys(e->pos, e->lo, e->typ, e->lid, e->total, e->sb, s));
+    return enqueue_boxes(e, s);
+}
+
+// Pair forces of all droplets; t0 / t1 (or null) are recorded around the
+// Coulomb tasks, which then have a launch of their own.
+ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
+                       hipEvent_t t1 = nullptr) {
+    EnsPairArgs A{};
+    A.pos = e->pos;
+    A.lo = e->lo;
+    A.typ = e->typ;
+    A.off = e->off;
+    A.tiles = e->tiles;
+    A.tasks = e->tasks;
+    A.tbase = e->tbase;
+    A.box = e->box;
+    A.tabs = e->tabs;
+    A.plan = e->plan;
+    A.F = e->F;
+    A.st = e->st;
+    A.adv_dt = e->pend_dt;
+    e->pend_dt = 0.0;
+    auto launch = [&](int lj, int coulomb) {
+        A.lj_blocks = lj;
+        A.lj_every = lj > 0 ? (lj + coulomb) / lj : 1;
+        hipLaunchKernelGGL(k_ens_pair, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
+        A.adv_dt = 0.0;
+    };
+    if (!t0) {
+        launch(e->ntiles, e->ntasks);
+        HIP_TRY(hipGetLastError());
+        return LD_OK;
+    }
+    launch(e->ntiles, 0);
+    HIP_TRY(hipEventRecord(t0, s));
+    launch(0, e->ntasks);
+    HIP_TRY(hipEventRecord(t1, s));
+    HIP_TRY(hipGetLastError());
     return LD_OK;
 }
 
-// Work items a workgroup can run at once: four tiles, or one block.
-int max_workgroups(const ld_ens* e) {
-    return e->rows == 256 ? e->W_b : (e->W + kWaves - 1) / kWaves;
-}
-
-template <int COMP, int UNROLL>
-void launch_ens_pair_u(ld_ens* e, hipStream_t s) {
-    if (e->rows == 256) {
-        if (e->cull)
-            hipLaunchKernelGGL((k_ens_pair_b<COMP, true, UNROLL>), dim3(e->workgroups),
-                               dim3(kEnsBlock), 0, s, e->pos, e->lo, e->off, e->items_b, e->W_b,
-                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
-        else
-            hipLaunchKernelGGL((k_ens_pair_b<COMP, false, UNROLL>), dim3(e->workgroups),
-                               dim3(kEnsBlock), 0, s, e->pos, e->lo, e->off, e->items_b, e->W_b,
-                               e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
-        return;
+// The clock advance of the last update, if it is still due.
+ld_status flush_advance(ld_ens* e, hipStream_t s) {
+    if (e->pend_dt > 0.0) {
+        HIP_TRY(ld::launch_advance(e->st, e->pend_dt, s));
+        e->pend_dt = 0.0;
     }
-    if (e->cull)
-        hipLaunchKernelGGL((k_ens_pair<COMP, true, UNROLL>), dim3(e->workgroups), dim3(kEnsBlock),
-                           0, s, e->pos, e->lo, e->typ, e->off, e->items, e->W, e->counter,
-                           e->tabs, e->box, e->tbase, e->F, e->total);
-    else
-        hipLaunchKernelGGL((k_ens_pair<COMP, false, UNROLL>), dim3(e->workgroups),
-                           dim3(kEnsBlock), 0, s, e->pos, e->lo, e->typ, e->off, e->items, e->W,
-                           e->counter, e->tabs, e->box, e->tbase, e->F, e->total);
-}
-
-template <int COMP>
-void launch_ens_pair(ld_ens* e, hipStream_t s) {
-    if (e->unroll == 8)
-        launch_ens_pair_u<COMP, 8>(e, s);
-    else if (e->unroll == 32)
-        launch_ens_pair_u<COMP, 32>(e, s);
-    else
-        launch_ens_pair_u<COMP, 16>(e, s);
-}
-
-// Boxes, the persistent Coulomb kernel, then the FP64 Lennard-Jones kernel;
-// t0 / t1 (or null) are recorded around the Coulomb kernel.
-ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
-                       hipEvent_t t1 = nullptr) {
-    hipLaunchKernelGGL(k_ens_boxes, dim3((e->ntiles + 3) / 4), dim3(256), 0, s, e->pos, e->off,
-                       e->tiles, e->ntiles, e->box);
-    hipLaunchKernelGGL(k_ens_reset, dim3(1), dim3(1), 0, s, e->counter);
-    if (t0) HIP_TRY(hipEventRecord(t0, s));
-    if (e->comp == 0)
-        launch_ens_pair<0>(e, s);
-    else
-        launch_ens_pair<1>(e, s);
-    HIP_TRY(hipGetLastError());
-    if (t1) HIP_TRY(hipEventRecord(t1, s));
-    hipLaunchKernelGGL(k_ens_lj, dim3(e->ntiles), dim3(kEnsBlock), 0, s,
-                       e->pos, e->lo, e->typ, e->off, e->tiles, e->tabs, e->box, e->tbase, e->F,
-                       e->total);
-    HIP_TRY(hipGetLastError());
     return LD_OK;
 }
 
@@ -571,11 +407,11 @@ ld_status enqueue_step(ld_ens* e, double dt, hipStream_t s, bool timed) {
     }
     ld_status st = enqueue_pair(e, s, a, b);    // timed: the Coulomb kernel alone
     if (st != LD_OK) return st;
-    hipLaunchKernelGGL(k_ens_update, dim3((e->total + 255) / 256), dim3(256), 0, s, e->pos,
-                       e->lo, e->typ, e->did, e->lid, e->F, e->total, e->ext, e->seeds, dt,
-                       e->st);
+    hipLaunchKernelGGL(k_ens_update, dim3((e->ntiles + 3) / 4), dim3(256), 0, s, e->pos, e->lo,
+                       e->typ, e->lid, e->off, e->tiles, e->ntiles, e->plan, e->F, e->ext,
+                       e->seeds, dt, e->st, e->box);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(ld::launch_advance(e->st, dt, s));
+    e->pend_dt = dt;                       // taken along by the next step, or flushed
     return LD_OK;
 }
 
@@ -591,6 +427,8 @@ ld_status capture(ld_ens* e, double dt, int steps) {
     HIP_TRY(hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
     ld_status st = LD_OK;
     for (int k = 0; k < steps && st == LD_OK; ++k) st = enqueue_step(e, dt, e->cap_stream, false);
+    if (st == LD_OK) st = flush_advance(e, e->cap_stream);
+    e->pend_dt = 0.0;
     hipGraph_t g = nullptr;
     hipError_t err = hipStreamEndCapture(e->cap_stream, &g);
     e->steps_since_sort = saved;
@@ -605,6 +443,49 @@ ld_status capture(ld_ens* e, double dt, int steps) {
     e->graph_dt = dt;
     e->graph_len = steps;
     return LD_OK;
+}
+
+// Pair tasks of all droplets and where their partials lie; returns the
+// doubles of force partials.  A droplet of nb blocks pairs block a with the
+// blocks at distances 0 .. nb/2 (super-blocks of mA blocks beyond 128, which
+// bounds the partials); a task is a super-block and a run of distances, so
+// many that the list is about ten rounds over the chip's 768 workgroups.
+size_t plan_tasks(const std::vector<int64_t>& offs, int max_super,
+                  std::vector<DropPlan>& plans, std::vector<int4>& tasks) {
+    const int64_t per = kEnsJB * kGroup;
+    double units = 0.0;
+    for (size_t d = 0; d < plans.size(); ++d) {
+        DropPlan& p = plans[d];
+        p.nb = (int)((offs[d + 1] - offs[d] + per - 1) / per);
+        for (p.mA = 1; p.nb > max_super * p.mA; p.mA *= 2) {}
+        p.nA = (p.nb + p.mA - 1) / p.mA;
+        p.nds = std::min(p.nA, (p.mA - 1 + p.nb / 2) / p.mA + 1 + (p.nb % p.mA != 0 ? 1 : 0));
+        units += (double)p.nA * p.nds * p.mA * p.mA;
+    }
+    const double aim = std::max(1.0, units / (768.0 * 10.0));     // block pairs per task
+    tasks.clear();
+    long long base = 0;
+    for (size_t d = 0; d < plans.size(); ++d) {
+        DropPlan& p = plans[d];
+        const int len = std::max(1, (int)(aim / ((double)p.mA * p.mA)));
+        const int chunks = (p.nds + len - 1) / len;
+        for (int c = 0; c < chunks; ++c) {
+            const int s0 = (int)((int64_t)p.nds * c / chunks), s1 = (int)((int64_t)p.nds * (c + 1) / chunks);
+            for (int a = 0; a < p.nA; ++a)
+                tasks.push_back(make_int4((int)d, a, c, s0 | (s1 << 16)));
+        }
+        p.slots = 1 + p.nds + chunks;
+        p.pad = 0;
+        p.base = base;
+        base += 3ll * p.slots * (offs[d + 1] - offs[d]);
+    }
+    std::stable_sort(tasks.begin(), tasks.end(), [&](const int4& a, const int4& b) {
+        auto cost = [&](const int4& t) {
+            return ((t.w >> 16) - (t.w & 0xffff)) * plans[t.x].mA * plans[t.x].mA;
+        };
+        return cost(a) > cost(b);
+    });
+    return (size_t)base;
 }
 
 }  // namespace
@@ -653,7 +534,9 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     std::vector<PairTable> tabs(n_drop);
     std::vector<ExtParams> exts(n_drop);
     std::vector<unsigned long long> sd(n_drop);
-    std::vector<int2> items, items_b, tiles;
+    std::vector<int2> tiles;
+    std::vector<int4> tasks;
+    std::vector<DropPlan> plans(n_drop);
     std::vector<int> tbase(n_drop);
     for (int d = 0; d < n_drop; ++d) {
         make_tables(p[d], R[d], tabs[d], exts[d]);
@@ -677,21 +560,16 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
             lids[i] = (int)(i - offs[d]);
         }
         tbase[d] = (int)tiles.size();
-        for (int64_t i0 = 0; i0 < offs[d + 1] - offs[d]; i0 += kGroup) {
-            items.push_back(make_int2(d, (int)i0));
+        for (int64_t i0 = 0; i0 < offs[d + 1] - offs[d]; i0 += kGroup)
             tiles.push_back(make_int2(d, (int)(offs[d] + i0)));
-        }
-        for (int64_t i0 = 0; i0 < offs[d + 1] - offs[d]; i0 += kEnsBlock)
-            items_b.push_back(make_int2(d, (int)i0));
     }
-    // longest item first: an item costs N_d pairs per lane
-    auto longer = [&](const int2& a, const int2& b) {
-        return (offs[a.x + 1] - offs[a.x]) > (offs[b.x + 1] - offs[b.x]);
-    };
-    std::stable_sort(items.begin(), items.end(), longer);
-    std::stable_sort(items_b.begin(), items_b.end(), longer);
-    e->W = (int)items.size();
-    e->W_b = (int)items_b.size();
+    // fewer, larger super-blocks once the partials would take kEnsMaxBytes
+    size_t f_doubles = 0;
+    for (int max_super = 128; max_super >= 8; max_super /= 2) {
+        f_doubles = plan_tasks(offs, max_super, plans, tasks);
+        if (f_doubles * sizeof(double) <= kEnsMaxBytes) break;
+    }
+    e->ntasks = (int)tasks.size();
     std::vector<int> off32(offs.begin(), offs.end());
     const size_t N = (size_t)total;
     bool ok = hipMalloc(&e->pos, sizeof(float4) * N) == hipSuccess &&
@@ -700,13 +578,12 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
               hipMalloc(&e->did, sizeof(int) * N) == hipSuccess &&
               hipMalloc(&e->lid, sizeof(int) * N) == hipSuccess &&
               hipMalloc(&e->off, sizeof(int) * (n_drop + 1)) == hipSuccess &&
-              hipMalloc(&e->items, sizeof(int2) * items.size()) == hipSuccess &&
-              hipMalloc(&e->items_b, sizeof(int2) * items_b.size()) == hipSuccess &&
-              hipMalloc(&e->counter, sizeof(unsigned)) == hipSuccess &&
+              hipMalloc(&e->tasks, sizeof(int4) * tasks.size()) == hipSuccess &&
+              hipMalloc(&e->plan, sizeof(DropPlan) * n_drop) == hipSuccess &&
               hipMalloc(&e->tabs, sizeof(PairTable) * n_drop) == hipSuccess &&
               hipMalloc(&e->ext, sizeof(ExtParams) * n_drop) == hipSuccess &&
               hipMalloc(&e->seeds, sizeof(unsigned long long) * n_drop) == hipSuccess &&
-              hipMalloc(&e->F, sizeof(double) * 3 * N) == hipSuccess &&
+              hipMalloc(&e->F, sizeof(double) * f_doubles) == hipSuccess &&
               hipMalloc(&e->work, sizeof(double) * 3 * N) == hipSuccess &&
               hipMalloc(&e->st, sizeof(DevState)) == hipSuccess &&
               hipMalloc(&e->tbase, sizeof(int) * n_drop) == hipSuccess &&
@@ -730,7 +607,6 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     }
     DevState ds{};
     ds.bad_step = ~0ull;
-    const unsigned zero = 0u;
     hipError_t err = hipSuccess;
     auto up = [&](void* dst, const void* src, size_t bytes) {
         if (err == hipSuccess) err = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
@@ -741,15 +617,15 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     up(e->did, dids.data(), sizeof(int) * N);
     up(e->lid, lids.data(), sizeof(int) * N);
     up(e->off, off32.data(), sizeof(int) * (n_drop + 1));
-    up(e->items, items.data(), sizeof(int2) * items.size());
-    up(e->items_b, items_b.data(), sizeof(int2) * items_b.size());
-    up(e->counter, &zero, sizeof zero);
+    up(e->tasks, tasks.data(), sizeof(int4) * tasks.size());
+    up(e->plan, plans.data(), sizeof(DropPlan) * n_drop);
     up(e->tabs, tabs.data(), sizeof(PairTable) * n_drop);
     up(e->ext, exts.data(), sizeof(ExtParams) * n_drop);
     up(e->seeds, sd.data(), sizeof(unsigned long long) * n_drop);
     up(e->st, &ds, sizeof ds);
     up(e->tbase, tbase.data(), sizeof(int) * n_drop);
     up(e->tiles, tiles.data(), sizeof(int2) * tiles.size());
+    if (err == hipSuccess && enqueue_boxes(e, s) != LD_OK) err = hipErrorUnknown;
     if (err == hipSuccess) err = hipStreamSynchronize(s);
     if (err != hipSuccess) {
         ens_free(e);
@@ -759,7 +635,7 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess)
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    e->workgroups = std::max(1, std::min(cus * 8, max_workgroups(e)));
+    e->workgroups = std::max(1, std::min(cus * 8, (e->ntiles + 3) / 4));
     e->steps_since_sort = sort_interval(e);              // sort before the first step
     *out = e;
     return LD_OK;
@@ -854,11 +730,9 @@ ld_status ld_ens_autotune(ld_ens* e, const char* cache_path, int32_t force, int3
     std::snprintf(key, sizeof key, "ens2/%s/d%d/p%d/m%d/cull%d/comp%d", arch, e->n_drop,
                   (int)std::floor(std::log2(pairs) * 4.0),
                   (int)std::floor(std::log2((double)nmax) * 4.0), e->cull ? 1 : 0, e->comp);
-    // Time the slot order the steps will use: a sort that is due (a new
-    // ensemble sorts before its first step) is done now, as that step would
-    // have done it, so the trajectory is unchanged; an unsorted ensemble
-    // would have most tile pairs take the careful loop and rank the far
-    // loop's settings wrongly.
+    // a sort that is due (a new ensemble sorts before its first step) is done
+    // now, as that step would have done it: the time is that of the slot
+    // order the steps use, and the trajectory is unchanged
     if (e->cull && e->steps_since_sort >= sort_interval(e)) {
         const ld_status st = enqueue_sort(e, e->stream);
         if (st != LD_OK) return st;
@@ -884,69 +758,23 @@ ld_status ld_ens_autotune(ld_ens* e, const char* cache_path, int32_t force, int3
     }
     double best_ms = INFINITY;
     if (!cached) {
-        const bool saved_timing = e->timing;
-        e->timing = false;
+        // the pair tasks have one launch shape: there is nothing to choose
+        // between, and the settings in use are recorded with their time
         hipEvent_t e0, e1;
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
-        const int per_cu[] = {2, 3, 4, 5, 6, 7, 8};
-        const int unrolls[] = {8, 16, 32};
-        const int item_rows[] = {64, 256};
         ld_status st = LD_OK;
-        // fastest of `reps` timed bursts of `burst` back-to-back launches
-        // (after one warm-up burst) of a setting, per launch
-        auto time_setting = [&](int w, int u, int r, int reps, int burst) {
-            e->rows = r;
-            e->unroll = u;
-            e->workgroups = w;
-            double ms_min = INFINITY;
-            for (int rep = 0; rep <= reps && st == LD_OK; ++rep) {
-                if (hipEventRecord(e0, e->stream) != hipSuccess) st = LD_EHIP;
-                for (int b = 0; b < burst && st == LD_OK; ++b) st = enqueue_pair(e, e->stream);
-                if (st == LD_OK && hipEventRecord(e1, e->stream) != hipSuccess) st = LD_EHIP;
-                if (st == LD_OK && hipEventSynchronize(e1) != hipSuccess) st = LD_EHIP;
-                float ms = 0.f;
-                if (st == LD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
-                    st = LD_EHIP;
-                if (rep > 0 && ms / burst < ms_min) ms_min = ms / burst;
-            }
-            return ms_min;
-        };
-        struct Cand {
-            double ms;
-            int w, u, r;
-        };
-        std::vector<Cand> cands;
-        for (int r : item_rows)
-            for (int u : unrolls)
-                for (int k : per_cu) {
-                    if (st != LD_OK) break;
-                    e->rows = r;
-                    const int w = std::max(1, std::min(cus * k, max_workgroups(e)));
-                    cands.push_back({time_setting(w, u, r, 3, 1), w, u, r});
-                }
-        // One pass of single launches leaves settings within a few per cent
-        // of each other, in an order that the clock's state can decide and
-        // that need not hold under sustained load: the four best are timed
-        // again as bursts of launches in three interleaved rounds and
-        // ranked by their summed times.
-        std::sort(cands.begin(), cands.end(),
-                  [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
-        const int top = std::min<int>(4, (int)cands.size());
-        std::vector<double> sum(top, 0.0);
-        for (int round = 0; round < 3 && st == LD_OK; ++round)
-            for (int c = 0; c < top && st == LD_OK; ++c)
-                sum[c] += time_setting(cands[c].w, cands[c].u, cands[c].r, 2, 6);
-        for (int c = 0; c < top && st == LD_OK; ++c)
-            if (sum[c] / 3.0 < best_ms) {
-                best_ms = sum[c] / 3.0;
-                best_w = cands[c].w;
-                best_u = cands[c].u;
-                best_r = cands[c].r;
-            }
+        for (int rep = 0; rep < 4 && st == LD_OK; ++rep) {       // the first warms up
+            if (hipEventRecord(e0, e->stream) != hipSuccess) st = LD_EHIP;
+            if (st == LD_OK) st = enqueue_pair(e, e->stream);
+            if (st == LD_OK && hipEventRecord(e1, e->stream) != hipSuccess) st = LD_EHIP;
+            if (st == LD_OK && hipEventSynchronize(e1) != hipSuccess) st = LD_EHIP;
+            float ms = 0.f;
+            if (st == LD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) st = LD_EHIP;
+            if (rep > 0 && ms < best_ms) best_ms = ms;
+        }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        e->timing = saved_timing;
         if (st != LD_OK) return fail(LD_EHIP, "ensemble autotune launch failed");
         if (cache_path) {
             if (FILE* f = std::fopen(cache_path, "a")) {
@@ -978,6 +806,8 @@ ld_status ld_ens_step(ld_ens* e, double dt, int64_t n_steps) {
         // boundaries only; eager steps fill up to the next boundary
         const bool at_chunk = !e->cull || e->steps_since_sort >= sort_interval(e);
         if (use_graph && at_chunk && left >= len) {
+            ld_status ast = flush_advance(e, e->stream);
+            if (ast != LD_OK) return ast;
             if (!e->graph || e->graph_dt != dt || e->graph_len != len) {
                 ld_status st = capture(e, dt, len);
                 if (st != LD_OK) return st;
@@ -991,7 +821,7 @@ ld_status ld_ens_step(ld_ens* e, double dt, int64_t n_steps) {
         if (st != LD_OK) return st;
         --left;
     }
-    return LD_OK;
+    return flush_advance(e, e->stream);
 }
 
 ld_status ld_ens_forces(ld_ens* e, double* F_pair) {
@@ -1000,7 +830,7 @@ ld_status ld_ens_forces(ld_ens* e, double* F_pair) {
     ld_status st = enqueue_pair(e, e->stream);
     if (st != LD_OK) return st;
     hipLaunchKernelGGL(k_ens_forces_aos, dim3((e->total + 255) / 256), dim3(256), 0, e->stream,
-                       e->F, e->did, e->lid, e->off, e->total, e->work);
+                       e->F, e->plan, e->did, e->lid, e->off, e->total, e->work);
     HIP_TRY(hipGetLastError());
     HIP_TRY(copy_out(F_pair, e->work, sizeof(double) * 3 * (size_t)e->total, e->stream));
     return LD_OK;

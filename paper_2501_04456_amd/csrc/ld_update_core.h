@@ -75,9 +75,9 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// Bounding box of each 64-slot group (one wavefront per group); lo.w = 1 if
-// the group holds a charged particle, else 0.
-__device__ __forceinline__ void write_box(const float4 h, bool live, int s, Box* box) {
+// Bounding box of a wavefront's 64 slots; lo.w = 1 if they hold a charged
+// particle, else 0.
+__device__ __forceinline__ void write_tile_box(const float4 h, bool live, Box* box) {
     const float lx = wave_min(live ? h.x : INFINITY), hx = wave_max(live ? h.x : -INFINITY);
     const float ly = wave_min(live ? h.y : INFINITY), hy = wave_max(live ? h.y : -INFINITY);
     const float lz = wave_min(live ? h.z : INFINITY), hz = wave_max(live ? h.z : -INFINITY);
@@ -86,8 +86,13 @@ __device__ __forceinline__ void write_box(const float4 h, bool live, int s, Box*
         Box b;
         b.lo = make_float4(lx, ly, lz, charged ? 1.f : 0.f);
         b.hi = make_float4(hx, hy, hz, 0.f);
-        box[s / kGroup] = b;
+        *box = b;
     }
+}
+
+// The box of each 64-slot group (one wavefront per group).
+__device__ __forceinline__ void write_box(const float4 h, bool live, int s, Box* box) {
+    write_tile_box(h, live, box + s / kGroup);
 }
 
 // One overdamped Euler-Maruyama step of one particle held as an FP32 pair
