@@ -248,6 +248,9 @@ ld_status ld_sync(ld_ctx* ctx);
  * (either may be NULL).  Waits for the stream. */
 ld_status ld_get_positions(ld_ctx* ctx, float* pos, float* pos_lo);
 
+/* Positions x [n*3] FP64 (hi + lo) in original order.  Waits for the stream. */
+ld_status ld_get_positions64(ld_ctx* ctx, double* x);
+
 /* Replace the positions: pos [n*3] FP32 in original order (host or device),
  * pos_lo [n*3] the low parts of the FP32 pairs or NULL for zeros.  Types,
  * charges, parameters, the step clock and the noise stream are kept (section
@@ -529,6 +532,9 @@ ld_status ld_ens_forces(ld_ens* e, double* F_pair);
 
 /* Positions [total*3] FP32 hi and lo parts (either may be NULL). */
 ld_status ld_ens_get_positions(ld_ens* e, float* pos, float* pos_lo);
+
+/* Positions x [total*3] FP64 (hi + lo). */
+ld_status ld_ens_get_positions64(ld_ens* e, double* x);
 
 /* Shared step counter and time. */
 ld_status ld_ens_get_state(ld_ens* e, int64_t* step, double* t);

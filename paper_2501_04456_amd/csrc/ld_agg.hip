@@ -722,7 +722,7 @@ ld_status ld_aggregates(ld_ctx* c, double contact_factor, int64_t stats[3], int3
     HIP_TRY(hipMemcpyAsync(part.data(), b.part, sizeof(long long) * part.size(),
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&err, b.err, sizeof(int), hipMemcpyDeviceToHost, s));
-    if (labels) HIP_TRY(copy_out(labels, b.labels, sizeof(int32_t) * (size_t)n, s));
+    if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (err) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
     long long comp = 0, agg = 0, big = 0;
@@ -769,7 +769,7 @@ ld_status ld_surface_fractal(ld_ctx* c, double R, double contact_factor, double 
     HIP_TRY(hipMemcpyAsync(part.data(), b.part, sizeof(long long) * part.size(),
                            hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&err, b.err, sizeof(int), hipMemcpyDeviceToHost, s));
-    if (labels) HIP_TRY(copy_out(labels, b.labels, sizeof(int32_t) * (size_t)n, s));
+    if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (err) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
     long long comp = 0, best = -1;

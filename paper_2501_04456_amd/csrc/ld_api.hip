@@ -49,6 +49,106 @@ hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s) {
     return hipStreamSynchronize(s);
 }
 
+void stage_init(HostStage& h, size_t bytes, size_t max_slot) {
+    size_t slot = (bytes / HostStage::kSlots + 4095) / 4096 * 4096;
+    slot = std::min(std::max(slot, HostStage::kMinSlot), max_slot);
+    bool ok = hipHostMalloc((void**)&h.buf, slot * HostStage::kSlots) == hipSuccess;
+    for (hipEvent_t& e : h.ev)
+        ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    h.slot = slot;
+    if (!ok) {
+        stage_free(h);
+        (void)hipGetLastError();
+    }
+}
+
+void stage_free(HostStage& h) {
+    for (hipEvent_t& e : h.ev)
+        if (e) (void)hipEventDestroy(e);
+    if (h.buf) (void)hipHostFree(h.buf);
+    h = HostStage{};
+}
+
+hipError_t stage_take(HostStage& h, char** slot, int* k) {
+    *k = (int)(h.turn++ % HostStage::kSlots);
+    *slot = h.buf + *k * h.slot;
+    return hipEventSynchronize(h.ev[*k]);
+}
+
+hipError_t stage_mark(HostStage& h, int k, hipStream_t s) { return hipEventRecord(h.ev[k], s); }
+
+namespace {
+
+template <class T>
+__global__ __launch_bounds__(256) void k_to_slot(const T* __restrict__ src, T* dst, int count) {
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < count; i += gridDim.x * 256) dst[i] = src[i];
+}
+
+// Device memory to a pinned slot by a kernel's stores: a launch follows the
+// kernel before it in a few us, a DMA engine in 10 to 15.
+template <class T>
+hipError_t to_slot_as(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    const int count = (int)(bytes / sizeof(T));
+    hipLaunchKernelGGL(k_to_slot<T>, dim3(std::min(256, (count + 255) / 256)), dim3(256), 0, s,
+                       (const T*)src, (T*)dst, count);
+    return hipGetLastError();
+}
+
+hipError_t to_slot(void* dst, const void* src, size_t bytes, hipStream_t s) {
+    const size_t low = (size_t)src | bytes;
+    if (low % 16 == 0) return to_slot_as<uint4>(dst, src, bytes, s);
+    if (low % 4 == 0) return to_slot_as<unsigned>(dst, src, bytes, s);
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+}
+
+}  // namespace
+
+hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
+    if (!h.buf || is_device_ptr(dst)) return copy_out(dst, src, bytes, s);
+    struct Piece {
+        char* slot;
+        int k;
+        size_t at, len;
+    } q[HostStage::kSlots];
+    size_t issued = 0, done = 0, at = 0;
+    hipError_t e = hipSuccess;
+    while (e == hipSuccess && (at < bytes || done < issued)) {
+        if (at < bytes && issued - done < HostStage::kSlots) {
+            Piece& p = q[issued % HostStage::kSlots];
+            p.at = at;
+            p.len = std::min(h.slot, bytes - at);
+            e = stage_take(h, &p.slot, &p.k);
+            if (e == hipSuccess)
+                e = to_slot(p.slot, (const char*)src + at, p.len, s);
+            if (e == hipSuccess) e = stage_mark(h, p.k, s);
+            at += p.len;
+            ++issued;
+        } else {
+            const Piece& p = q[done % HostStage::kSlots];
+            e = hipEventSynchronize(h.ev[p.k]);
+            if (e == hipSuccess) std::memcpy((char*)dst + p.at, p.slot, p.len);
+            ++done;
+        }
+    }
+    return e;
+}
+
+hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
+    if (!h.buf || is_device_ptr(src)) return copy_in(dst, src, bytes, s);
+    hipError_t e = hipSuccess;
+    for (size_t at = 0; at < bytes && e == hipSuccess; at += h.slot) {
+        const size_t len = std::min(h.slot, bytes - at);
+        char* p;
+        int k;
+        e = stage_take(h, &p, &k);
+        if (e != hipSuccess) break;
+        std::memcpy(p, (const char*)src + at, len);
+        e = hipMemcpyAsync((char*)dst + at, p, len, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = stage_mark(h, k, s);
+    }
+    return e;
+}
+
 ld_status check_params(const ld_params* p) {
     if (!p) return fail(LD_EINVAL, "params is NULL");
     if (p->n_types < 1 || p->n_types > LD_MAX_TYPES)
@@ -420,6 +520,7 @@ void free_all(ld_ctx* c) {
                     c->sb.hist, c->pos2,  c->lo2,   c->typ2,       c->oid2};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
+    stage_free(c->stage);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->graph) (void)hipGraphExecDestroy(c->graph);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -608,6 +709,7 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
         return fail(LD_ENOMEM, "device allocation failed for n=%lld", (long long)n);
     }
 
+    stage_init(c->stage, 3 * sizeof(double) * N, kReadSlot);
     const double qs = std::sqrt(p->kT * p->bjerrum);
     std::vector<float4> h4(N), l4(N);
     std::vector<int> ids(N);
@@ -679,9 +781,9 @@ ld_status ld_forces(ld_ctx* c, double* F_pair, double* F_ext, double* S, double*
                               F_pair ? dF : nullptr, F_ext ? dE : nullptr, S ? dS : nullptr,
                               c->stream));
     if (U) HIP_TRY(ld::launch_rowsum(c->U_slot, 2, (int)N, dU, c->stream));
-    if (F_pair) HIP_TRY(copy_out(F_pair, dF, sizeof(double) * 3 * N, c->stream));
-    if (F_ext) HIP_TRY(copy_out(F_ext, dE, sizeof(double) * 3 * N, c->stream));
-    if (S) HIP_TRY(copy_out(S, dS, sizeof(double) * N, c->stream));
+    if (F_pair) HIP_TRY(copy_out(c->stage, F_pair, dF, sizeof(double) * 3 * N, c->stream));
+    if (F_ext) HIP_TRY(copy_out(c->stage, F_ext, dE, sizeof(double) * 3 * N, c->stream));
+    if (S) HIP_TRY(copy_out(c->stage, S, dS, sizeof(double) * N, c->stream));
     if (U) HIP_TRY(copy_out(U, dU, sizeof(double) * 2, c->stream));
     return wait_stream(c);
 }
@@ -831,37 +933,35 @@ ld_status ld_get_positions(ld_ctx* c, float* pos, float* pos_lo) {
     g_err.clear();
     if (!c) return fail(LD_EINVAL, "ctx is NULL");
     const size_t N = (size_t)c->n;
-    std::vector<float4> h(N), l(N);
-    std::vector<int> ids(N);
-    HIP_TRY(hipMemcpyAsync(h.data(), c->pos, sizeof(float4) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(l.data(), c->lo, sizeof(float4) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(ids.data(), c->oid, sizeof(int) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    std::vector<float> a(pos ? 3 * N : 0), b(pos_lo ? 3 * N : 0);
-    for (size_t s = 0; s < N; ++s) {
-        const size_t o = (size_t)ids[s];
-        if (pos) { a[3 * o] = h[s].x; a[3 * o + 1] = h[s].y; a[3 * o + 2] = h[s].z; }
-        if (pos_lo) { b[3 * o] = l[s].x; b[3 * o + 1] = l[s].y; b[3 * o + 2] = l[s].z; }
-    }
-    if (pos) {
-        if (is_device_ptr(pos)) {
-            HIP_TRY(hipMemcpyAsync(pos, a.data(), sizeof(float) * 3 * N, hipMemcpyHostToDevice,
-                                   c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-        } else {
-            std::memcpy(pos, a.data(), sizeof(float) * 3 * N);
-        }
-    }
-    if (pos_lo) {
-        if (is_device_ptr(pos_lo)) {
-            HIP_TRY(hipMemcpyAsync(pos_lo, b.data(), sizeof(float) * 3 * N,
-                                   hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-        } else {
-            std::memcpy(pos_lo, b.data(), sizeof(float) * 3 * N);
-        }
-    }
+    float* hi = reinterpret_cast<float*>(c->work);
+    float* lo = hi + 3 * N;
+    HIP_TRY(ld::launch_positions(c->pos, c->lo, c->oid, (int)N, nullptr, pos ? hi : nullptr,
+                                 pos_lo ? lo : nullptr, c->stream));
+    if (pos) HIP_TRY(copy_out(c->stage, pos, hi, sizeof(float) * 3 * N, c->stream));
+    if (pos_lo) HIP_TRY(copy_out(c->stage, pos_lo, lo, sizeof(float) * 3 * N, c->stream));
     return wait_stream(c);
+}
+
+ld_status ld_get_positions64(ld_ctx* c, double* x) {
+    g_err.clear();
+    if (!c || !x) return fail(LD_EINVAL, "ctx and x are required");
+    const size_t N = (size_t)c->n, bytes = sizeof(double) * 3 * N;
+    // a small frame is written to the pinned slot by the kernel itself
+    if (c->stage.buf && bytes <= ld::kDirectOut && !is_device_ptr(x)) {
+        char* p;
+        int k;
+        HIP_TRY(stage_take(c->stage, &p, &k));
+        HIP_TRY(ld::launch_positions(c->pos, c->lo, c->oid, (int)N, (double*)p, nullptr, nullptr,
+                                     c->stream));
+        HIP_TRY(stage_mark(c->stage, k, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        std::memcpy(x, p, bytes);
+        return LD_OK;
+    }
+    HIP_TRY(ld::launch_positions(c->pos, c->lo, c->oid, (int)N, c->work, nullptr, nullptr,
+                                 c->stream));
+    HIP_TRY(copy_out(c->stage, x, c->work, bytes, c->stream));
+    return LD_OK;
 }
 
 ld_status ld_get_state(ld_ctx* c, int64_t* step, double* t, double* R) {

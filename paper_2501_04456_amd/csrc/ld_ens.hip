@@ -230,11 +230,17 @@ __global__ __launch_bounds__(256) void k_ens_gather(const float4* __restrict__ p
                                                     const int* __restrict__ did,
                                                     const int* __restrict__ lid,
                                                     const int* __restrict__ off, int total,
-                                                    float* hi_out, float* lo_out) {
+                                                    double* x, float* hi_out, float* lo_out) {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= total) return;
     const size_t o = (size_t)off[did[s]] + (size_t)lid[s];
     const float4 h = pos[s], l = lo[s];
+    if (x) {
+        x[3 * o] = (double)h.x + (double)l.x;
+        x[3 * o + 1] = (double)h.y + (double)l.y;
+        x[3 * o + 2] = (double)h.z + (double)l.z;
+        return;
+    }
     hi_out[3 * o] = h.x;
     hi_out[3 * o + 1] = h.y;
     hi_out[3 * o + 2] = h.z;
@@ -280,6 +286,7 @@ struct ld_ens {
     unsigned long long* seeds = nullptr;
     double* F = nullptr;                 // every droplet's partials [slots][3][N_d]
     double* work = nullptr;              // [3 * total] output staging
+    HostStage stage;                     // read-back
     DevState* st = nullptr;
     // launch settings of the interface: stored and reported; the symmetric
     // tasks have one launch shape and FP64 totals whatever they say
@@ -312,6 +319,7 @@ void ens_free(ld_ens* e) {
                     e->sb.keys, e->sb.tmp4, e->sb.tmp_i};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
+    stage_free(e->stage);
     if (e->graph) (void)hipGraphExecDestroy(e->graph);
     if (e->cap_stream) (void)hipStreamDestroy(e->cap_stream);
     for (hipEvent_t v : e->ev) (void)hipEventDestroy(v);
@@ -605,6 +613,7 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
         delete e;
         return fail(LD_ENOMEM, "device allocation failed for %lld particles", (long long)total);
     }
+    stage_init(e->stage, 3 * sizeof(double) * N, kReadSlot);
     DevState ds{};
     ds.bad_step = ~0ull;
     hipError_t err = hipSuccess;
@@ -832,7 +841,7 @@ ld_status ld_ens_forces(ld_ens* e, double* F_pair) {
     hipLaunchKernelGGL(k_ens_forces_aos, dim3((e->total + 255) / 256), dim3(256), 0, e->stream,
                        e->F, e->plan, e->did, e->lid, e->off, e->total, e->work);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(copy_out(F_pair, e->work, sizeof(double) * 3 * (size_t)e->total, e->stream));
+    HIP_TRY(copy_out(e->stage, F_pair, e->work, sizeof(double) * 3 * (size_t)e->total, e->stream));
     return LD_OK;
 }
 
@@ -843,11 +852,23 @@ ld_status ld_ens_get_positions(ld_ens* e, float* pos, float* pos_lo) {
     float* hi = reinterpret_cast<float*>(e->work);
     float* lo = hi + 3 * N;
     hipLaunchKernelGGL(k_ens_gather, dim3((e->total + 255) / 256), dim3(256), 0, e->stream,
-                       e->pos, e->lo, e->did, e->lid, e->off, e->total, hi, lo);
+                       e->pos, e->lo, e->did, e->lid, e->off, e->total,
+                       (double*)nullptr, hi, lo);
     HIP_TRY(hipGetLastError());
-    if (pos) HIP_TRY(copy_out(pos, hi, sizeof(float) * 3 * N, e->stream));
-    if (pos_lo) HIP_TRY(copy_out(pos_lo, lo, sizeof(float) * 3 * N, e->stream));
+    if (pos) HIP_TRY(copy_out(e->stage, pos, hi, sizeof(float) * 3 * N, e->stream));
+    if (pos_lo) HIP_TRY(copy_out(e->stage, pos_lo, lo, sizeof(float) * 3 * N, e->stream));
     HIP_TRY(hipStreamSynchronize(e->stream));
+    return LD_OK;
+}
+
+ld_status ld_ens_get_positions64(ld_ens* e, double* x) {
+    g_err.clear();
+    if (!e || !x) return fail(LD_EINVAL, "ensemble and x are required");
+    hipLaunchKernelGGL(k_ens_gather, dim3((e->total + 255) / 256), dim3(256), 0, e->stream,
+                       e->pos, e->lo, e->did, e->lid, e->off, e->total, e->work,
+                       (float*)nullptr, (float*)nullptr);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(copy_out(e->stage, x, e->work, sizeof(double) * 3 * (size_t)e->total, e->stream));
     return LD_OK;
 }
 

@@ -63,6 +63,7 @@ constexpr int kLoc = 19;               // E (3), J (6), H (10) per cell
 
 struct FarField {
     ld_ff_config cfg{};
+    HostStage stage;                   // the training entries' host batches
     double rlj = 0.0;                  // largest LJ range
     int K = 0, Kp = 0, Op = 16, H = 0;
     size_t offW1 = 0, offb1 = 0, offW2 = 0, offb2 = 0, offW3 = 0, offb3 = 0, nW = 0;
@@ -1734,6 +1735,7 @@ void ff_free_bufs(FarField* f) {
                  f->bd1, f->bidx, f->loss_part, f->gws};
     for (void* p : b)
         if (p) (void)hipFree(p);
+    stage_free(f->stage);
     conv_free(&f->conv);
 }
 
@@ -2370,6 +2372,48 @@ ld_status ld_ff_forces(ld_ctx* c, int32_t part, double* out) {
     return LD_OK;
 }
 
+static hipError_t pad_in(ld_ctx* c, const float* X, int m, hipStream_t s) {
+    // the caller's m x K rows (host or device), padded to Kp, into bX; host
+    // rows pass through pinned slots that the padding kernel reads itself
+    FarField* f = c->ff;
+    const size_t row = sizeof(float) * (size_t)f->K;
+    const float* src = X;
+    float* tmp = nullptr;
+    hipError_t e = hipSuccess;
+    if (!is_device_ptr(X)) {
+        if (!f->stage.buf) stage_init(f->stage, HostStage::kSlots * kBatchSlot, kBatchSlot);
+        const int per = f->stage.buf ? (int)(f->stage.slot / row) : 0;
+        if (per > 0) {
+            for (int r = 0; r < m && e == hipSuccess; r += per) {
+                const int k = std::min(per, m - r);
+                char* slot;
+                int i;
+                e = stage_take(f->stage, &slot, &i);
+                if (e != hipSuccess) break;
+                std::memcpy(slot, X + (size_t)r * f->K, k * row);
+                hipLaunchKernelGGL(k_pad_rows, dim3((unsigned)k), dim3(kB), 0, s,
+                                   (const float*)slot, k, f->K, f->Kp, f->bX + (size_t)r * f->Kp);
+                e = hipGetLastError();
+                if (e == hipSuccess) e = stage_mark(f->stage, i, s);
+            }
+            return e;
+        }
+        e = hipMalloc(&tmp, m * row);
+        if (e == hipSuccess) e = copy_in(tmp, X, m * row, s);
+        src = tmp;
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_pad_rows, dim3((unsigned)m), dim3(kB), 0, s, src, m, f->K, f->Kp,
+                           f->bX);
+        e = hipGetLastError();
+    }
+    if (tmp) {
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        (void)hipFree(tmp);
+    }
+    return e;
+}
+
 ld_status ld_ff_mlp(ld_ctx* c, const float* X, int64_t m, float* Y) {
     g_err.clear();
     if (!c || !c->ff) return fail(LD_ESTATE, "ld_ff_enable first");
@@ -2378,17 +2422,7 @@ ld_status ld_ff_mlp(ld_ctx* c, const float* X, int64_t m, float* Y) {
     hipStream_t s = c->stream;
     ld_status st = ensure_batch(f, (int)m);
     if (st != LD_OK) return st;
-    // stage the caller's m x K rows, then pad to Kp
-    float* tmp = nullptr;
-    HIP_TRY(hipMalloc(&tmp, sizeof(float) * (size_t)m * f->K));
-    hipError_t e = copy_in(tmp, X, sizeof(float) * (size_t)m * f->K, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_pad_rows, dim3((unsigned)m), dim3(kB), 0, s, tmp, (int)m, f->K, f->Kp,
-                           f->bX);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(tmp);
+    const hipError_t e = pad_in(c, X, (int)m, s);
     if (e != hipSuccess) return fail(LD_EHIP, "staging features: %s", hipGetErrorString(e));
     const int H = f->H, Op = f->Op;
     st = gemm(s, f->bX, f->Kp, 0, f->W + f->offW1, H, 0, f->bA1, H, (int)m, H, f->Kp,
@@ -2419,21 +2453,12 @@ ld_status ld_ff_grads(ld_ctx* c, const float* X, const float* T, int64_t m, floa
     hipStream_t s = c->stream;
     ld_status st = ensure_batch(f, (int)m);
     if (st != LD_OK) return st;
-    float* tmp = nullptr;
-    HIP_TRY(hipMalloc(&tmp, sizeof(float) * (size_t)m * f->K));
-    hipError_t e = copy_in(tmp, X, sizeof(float) * (size_t)m * f->K, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_pad_rows, dim3((unsigned)m), dim3(kB), 0, s, tmp, (int)m, f->K, f->Kp,
-                           f->bX);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = copy_in(f->bT, T, sizeof(float) * (size_t)m * 3, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(tmp);
+    hipError_t e = pad_in(c, X, (int)m, s);
+    if (e == hipSuccess) e = copy_in(f->stage, f->bT, T, sizeof(float) * (size_t)m * 3, s);
     if (e != hipSuccess) return fail(LD_EHIP, "staging batch: %s", hipGetErrorString(e));
     st = fwd_bwd(f, (int)m, s, loss);
     if (st != LD_OK) return st;
-    HIP_TRY(copy_out(grads, f->grad, sizeof(float) * f->nW, s));
+    HIP_TRY(copy_out(f->stage, grads, f->grad, sizeof(float) * f->nW, s));
     return LD_OK;
 }
 

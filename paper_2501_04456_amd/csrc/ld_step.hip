@@ -168,6 +168,24 @@ __global__ void k_diag_finish(const double* sums, const double* maxes, const dou
     out[9] = maxes[1];
 }
 
+// Positions in original order (x = hi + lo exactly).
+__global__ __launch_bounds__(256) void k_positions(const float4* __restrict__ pos,
+                                                   const float4* __restrict__ lo,
+                                                   const int* __restrict__ oid, int n, double* x,
+                                                   float* hi_out, float* lo_out) {
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s >= n) return;
+    const size_t o = 3 * (size_t)oid[s];
+    const float4 h = pos[s], l = lo[s];
+    if (x) {
+        x[o] = (double)h.x + (double)l.x;
+        x[o + 1] = (double)h.y + (double)l.y;
+        x[o + 2] = (double)h.z + (double)l.z;
+    }
+    if (hi_out) { hi_out[o] = h.x; hi_out[o + 1] = h.y; hi_out[o + 2] = h.z; }
+    if (lo_out) { lo_out[o] = l.x; lo_out[o + 1] = l.y; lo_out[o + 2] = l.z; }
+}
+
 // MSD reference: the FP64 position hi + lo of every NP, in original order
 // ([3][n]).
 __global__ __launch_bounds__(kBlock) void k_msd_ref(const float4* __restrict__ pos,
@@ -202,6 +220,13 @@ __global__ __launch_bounds__(kBlock) void k_msd_terms(const float4* __restrict__
 __global__ void k_mean_finish(double* v, int n) { v[0] = v[0] / (double)n; }
 
 }  // namespace
+
+hipError_t launch_positions(const float4* pos, const float4* lo, const int* oid, int n, double* x,
+                            float* hi_out, float* lo_out, hipStream_t s) {
+    hipLaunchKernelGGL(k_positions, dim3((n + 255) / 256), dim3(256), 0, s, pos, lo, oid, n, x,
+                       hi_out, lo_out);
+    return hipGetLastError();
+}
 
 hipError_t launch_msd_ref(const float4* pos, const float4* lo, const int* oid, int n,
                           double* ref, hipStream_t s) {

@@ -102,7 +102,8 @@ NEAR_RADIAL, NEAR_BLOCK = 0, 1
 
 SYMBOLS = [
     "ld_init", "ld_destroy", "ld_last_error", "ld_forces", "ld_step", "ld_sync",
-    "ld_get_positions", "ld_get_state", "ld_set_params", "ld_diagnostics", "ld_rdf",
+    "ld_get_positions", "ld_get_positions64", "ld_get_state", "ld_set_params", "ld_diagnostics",
+    "ld_rdf",
     "ld_fractal", "ld_get_tuning", "ld_set_tuning", "ld_kernel_timing", "ld_kernel_time",
     "ld_near_kernel_time", "ld_autotune", "ld_checkpoint_save", "ld_checkpoint_load",
     "ld_set_positions",
@@ -110,8 +111,8 @@ SYMBOLS = [
     "ld_ff_grid", "ld_ff_forces", "ld_ff_mlp", "ld_ff_grads", "ld_ff_collect", "ld_ff_train",
     "ld_ff_judge", "ld_ff_stats",
     "ld_ens_init", "ld_ens_destroy", "ld_ens_set_tuning", "ld_ens_step", "ld_ens_forces",
-    "ld_ens_get_positions", "ld_ens_get_state", "ld_ens_sync", "ld_ens_kernel_timing",
-    "ld_ens_kernel_time",
+    "ld_ens_get_positions", "ld_ens_get_positions64", "ld_ens_get_state", "ld_ens_sync",
+    "ld_ens_kernel_timing", "ld_ens_kernel_time",
     "ld_paper_enable", "ld_paper_disable", "ld_paper_forces", "ld_paper_get_velocities",
     "ld_paper_set_velocities", "ld_aggregates", "ld_surface_count", "ld_record_open",
     "ld_record_close", "ld_cbar_type", "ld_surface_fractal", "ld_ff_save", "ld_ff_load",
@@ -143,6 +144,7 @@ def lib():
         L.ld_msd_reset.argtypes = [vp]
         L.ld_sync.argtypes = [vp]
         L.ld_get_positions.argtypes = [vp, fp, fp]
+        L.ld_get_positions64.argtypes = [vp, vp]
         L.ld_set_positions.argtypes = [vp, vp, vp]
         L.ld_get_state.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_double),
                                    C.POINTER(C.c_double)]
@@ -170,6 +172,7 @@ def lib():
         L.ld_ens_autotune.argtypes = [vp, C.c_char_p, C.c_int32, vp]
         L.ld_ens_forces.argtypes = [vp, vp]
         L.ld_ens_get_positions.argtypes = [vp, vp, vp]
+        L.ld_ens_get_positions64.argtypes = [vp, vp]
         L.ld_ens_get_state.argtypes = [vp, C.POINTER(C.c_int64), C.POINTER(C.c_double)]
         L.ld_ens_sync.argtypes = [vp]
         L.ld_ens_kernel_timing.argtypes = [vp, C.c_int32]
@@ -380,15 +383,16 @@ class System:
     # -- state --------------------------------------------------------------
     def positions(self):
         """(hi, lo) FP32 numpy arrays [n,3] in original order."""
-        hi = np.zeros((self.n, 3), np.float32)
-        lo = np.zeros((self.n, 3), np.float32)
+        hi = np.empty((self.n, 3), np.float32)
+        lo = np.empty((self.n, 3), np.float32)
         _check(lib().ld_get_positions(self.h, hi.ctypes.data_as(C.c_void_p),
                                       lo.ctypes.data_as(C.c_void_p)))
         return hi, lo
 
     def positions64(self) -> np.ndarray:
-        hi, lo = self.positions()
-        return hi.astype(np.float64) + lo.astype(np.float64)
+        x = np.empty((self.n, 3))
+        _check(lib().ld_get_positions64(self.h, x.ctypes.data_as(C.c_void_p)))
+        return x
 
     def positions_into(self, hi: np.ndarray, lo: np.ndarray = None):
         """Write the FP32 (hi, lo) positions, original order, into given
@@ -475,12 +479,12 @@ class System:
         _check(lib().ld_paper_disable(self.h))
 
     def paper_forces(self) -> np.ndarray:
-        F = np.zeros((self.n, 3))
+        F = np.empty((self.n, 3))
         _check(lib().ld_paper_forces(self.h, F.ctypes.data_as(C.c_void_p)))
         return F
 
     def velocities(self) -> np.ndarray:
-        v = np.zeros((self.n, 3))
+        v = np.empty((self.n, 3))
         _check(lib().ld_paper_get_velocities(self.h, v.ctypes.data_as(C.c_void_p)))
         return v
 
@@ -728,15 +732,16 @@ class Ensemble:
 
     def positions(self):
         """(hi, lo) FP32 numpy arrays [total,3] in original order."""
-        hi = np.zeros((self.total, 3), np.float32)
-        lo = np.zeros((self.total, 3), np.float32)
+        hi = np.empty((self.total, 3), np.float32)
+        lo = np.empty((self.total, 3), np.float32)
         _check(lib().ld_ens_get_positions(self.h, hi.ctypes.data_as(C.c_void_p),
                                           lo.ctypes.data_as(C.c_void_p)))
         return hi, lo
 
     def positions64(self):
-        hi, lo = self.positions()
-        return hi.astype(np.float64) + lo.astype(np.float64)
+        x = np.empty((self.total, 3))
+        _check(lib().ld_ens_get_positions64(self.h, x.ctypes.data_as(C.c_void_p)))
+        return x
 
     def state(self):
         s, t = C.c_int64(), C.c_double()
