@@ -427,7 +427,6 @@ ld_status flush_advance(ld_ctx* c, hipStream_t s) {
 // One step (re-sorting first when due) on stream s.  The clock advance is
 // left due (flush_advance) for the next step's force launch to take along.
 ld_status enqueue_step(ld_ctx* c, double dt, hipStream_t s, bool timed) {
-    if (c->pm) return ld::pm_step(c, dt, s);   // the paper's scheme sorts by cell itself
     if (c->tune.sort_every > 0 && c->steps_since_sort >= c->tune.sort_every) {
         ld_status st = run_sort(c, s);
         if (st != LD_OK) return st;
@@ -854,7 +853,9 @@ ld_status step_loop(ld_ctx* c, double dt, int64_t n_steps) {
             left -= len;
             continue;
         }
-        ld_status st = enqueue_step(c, dt, c->stream, c->timing);
+        // the paper's scheme sorts by cell itself
+        ld_status st = c->pm ? ld::pm_step(c, dt, c->stream, left == n_steps, left == 1)
+                             : enqueue_step(c, dt, c->stream, c->timing);
         if (st == LD_OK && c->rec) st = flush_advance(c, c->stream);   // a frame holds the clock
         if (st != LD_OK) return st;
         if (c->rec && (st = ld::rec_after_step(c, dt, c->stream)) != LD_OK) return st;

@@ -32,10 +32,9 @@ using host::fail;
 constexpr int kPmMaxCells = 64;         // cells per axis at most
 
 struct PmGrid {
-    double L;                           // half width of the cube holding every particle
+    double L;                           // half width of the cube the cells divide
     double hc;                          // cell side (>= the largest pair range)
     int Gc;                             // cells per axis
-    int pad;
 };
 
 // Pair constants: range^2, sigma^2 and 24 eps per type pair (FP64).
@@ -46,6 +45,7 @@ struct PmTable {
     double e24[kMaxTypes * kMaxTypes];
     double inv_m[kMaxTypes];            // 1 / inertial mass
     double gamma[kMaxTypes];
+    double rtype[kMaxTypes];            // largest pair range of a type
     double rmax;                        // largest pair range
     double kick;
 };
@@ -56,16 +56,76 @@ struct PaperMode {
     double* v = nullptr;                // [3][n] velocities, slot order
     double* v2 = nullptr;               // [3][n] second buffer (re-sort)
     double* F = nullptr;                // [3][n] pair forces, slot order
-    PmGrid* grid = nullptr;             // device
-    int* cfirst = nullptr;              // [64^3 + 1] first slot of every cell
+    unsigned turn = 0;                  // steps since the cells were counted on their own
+    int* cells = nullptr;               // counts, coarse counts, first slots, largest coordinates
 };
 
 namespace {
 
 constexpr int kB = 256;
 constexpr int kNC = kPmMaxCells * kPmMaxCells * kPmMaxCells;
-constexpr int kPmWin = 4;               // candidates loaded together (2 and 8 are slower)
+constexpr int kCoarse = 1024;           // cells of a coarse count (a scan workgroup's share)
+constexpr int kPmWin = 4;               // candidates loaded together
+constexpr int kPmSplitN = 75000;        // particles from which a lane takes one by itself
 
+// The integer workspace of the cell sort.  count and coarse are zero between
+// sorts; mx holds bits of the largest |coordinate| at three consecutive steps.
+struct PmCells {
+    int* count;                         // [kNC]
+    int* coarse;                        // [kNC / kCoarse]
+    int* first;                         // [kNC + 1] first slot of every cell
+    unsigned* mx;                       // [3]
+};
+constexpr size_t kCellInts = (size_t)kNC + kNC / kCoarse + kNC + 1 + 3;
+
+__host__ __device__ inline PmCells pm_cells(int* b) {
+    return PmCells{b, b + kNC, b + kNC + kNC / kCoarse,
+                   reinterpret_cast<unsigned*>(b + kNC + kNC / kCoarse + kNC + 1)};
+}
+
+// The grid of a largest coordinate m.  Coordinates beyond L fall into the edge
+// cells, which keeps any two particles closer than hc in adjacent cells, so
+// the m of an earlier step is as right as the present one.
+__device__ __forceinline__ PmGrid pm_grid(float m, double rmax) {
+    PmGrid g;
+    m = fmaxf(m, 1e-3f);
+    g.L = (double)(m * 1.0009765625f);
+    int G = (int)floor(2.0 * g.L / rmax);
+    G = G < 1 ? 1 : (G > kPmMaxCells ? kPmMaxCells : G);
+    g.Gc = G;
+    g.hc = 2.0 * g.L / G;
+    return g;
+}
+
+__device__ __forceinline__ int pm_cell1(double x, double L, double h, int G) {
+    int c = (int)floor((x + L) / h);
+    return c < 0 ? 0 : (c > G - 1 ? G - 1 : c);
+}
+
+// Count slot s (live lanes of one wavefront) into its cell; the coarse counts
+// take one atomic per distinct coarse cell of the wavefront (neighbours in
+// slot order share them).
+__device__ __forceinline__ void pm_bin(const PmGrid& g, bool live, int s, const double x[3],
+                                       const PmCells& C, int* cell, int* rank) {
+    const int c = live ? (pm_cell1(x[2], g.L, g.hc, g.Gc) * g.Gc +
+                          pm_cell1(x[1], g.L, g.hc, g.Gc)) * g.Gc +
+                             pm_cell1(x[0], g.L, g.hc, g.Gc)
+                       : -1;
+    if (live) {
+        cell[s] = c;
+        rank[s] = atomicAdd(&C.count[c], 1);
+    }
+    unsigned long long left = __ballot(live);
+    while (left) {
+        const int k = __shfl(c, (int)__builtin_ctzll(left)) / kCoarse;
+        const unsigned long long same = __ballot(live && c / kCoarse == k) & left;
+        if ((int)(threadIdx.x % 64) == (int)__builtin_ctzll(left))
+            atomicAdd(&C.coarse[k], __popcll(same));
+        left &= ~same;
+    }
+}
+
+// Largest |coordinate|, 64 partial maxima.
 __global__ __launch_bounds__(kB) void k_pm_absmax(const float4* __restrict__ pos, int n,
                                                   float* part) {
     __shared__ float red[kB];
@@ -83,203 +143,321 @@ __global__ __launch_bounds__(kB) void k_pm_absmax(const float4* __restrict__ pos
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__device__ __forceinline__ int pm_cell1(double x, double L, double h, int G) {
-    int c = (int)floor((x + L) / h);
-    return c < 0 ? 0 : (c > G - 1 ? G - 1 : c);
-}
-
-// Grid from the 64 partial maxima (block 0 stores it), cell keys
-// (cell << 32 | slot) from the FP64 positions, and the first radix pass's
-// digit counts of each radix tile.
-__global__ __launch_bounds__(kB) void k_pm_keys(const float4* __restrict__ pos,
-                                                const float4* __restrict__ lo, int n,
-                                                const float* __restrict__ part, double rmax,
-                                                PmGrid* g, unsigned long long* keys,
-                                                unsigned* hist, int nwg) {
-    __shared__ PmGrid sg;
-    __shared__ unsigned h[256];
-    const int t = threadIdx.x;
-    h[t] = 0u;
-    if (t < 64) {
-        float m = part[t];
+// Cells of all slots at positions no step of the same call has left (the
+// steps bin what they move themselves): mx[0] = mx[1] = the largest coordinate.
+__global__ __launch_bounds__(kB) void k_pm_bin(const float4* __restrict__ pos,
+                                               const float4* __restrict__ lo, int n,
+                                               const float* __restrict__ part, double rmax,
+                                               PmCells C, int* cell, int* rank) {
+    float m = part[threadIdx.x % 64];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-        if (t == 0) {
-            m = fmaxf(m, 1e-3f);
-            const double L = (double)(m * 1.0009765625f);
-            int G = (int)floor(2.0 * L / rmax);
-            G = G < 1 ? 1 : (G > kPmMaxCells ? kPmMaxCells : G);
-            sg.L = L;
-            sg.Gc = G;
-            sg.hc = 2.0 * L / G;
-            sg.pad = 0;
-            if (blockIdx.x == 0) *g = sg;
-        }
-    }
-    __syncthreads();
-    const int G = sg.Gc;
-    for (int r = 0; r < kRadixRounds; ++r) {
-        const int s = blockIdx.x * kRadixTile + r * kB + t;
-        if (s < n) {
-            const float4 hp = pos[s], l = lo[s];
-            const int cx = pm_cell1((double)hp.x + (double)l.x, sg.L, sg.hc, G),
-                      cy = pm_cell1((double)hp.y + (double)l.y, sg.L, sg.hc, G),
-                      cz = pm_cell1((double)hp.z + (double)l.z, sg.L, sg.hc, G);
-            const unsigned c = (unsigned)((cz * G + cy) * G + cx);
-            keys[s] = ((unsigned long long)c << 32) | (unsigned)s;
-            atomicAdd(&h[c & 255u], 1u);
-        }
-    }
-    __syncthreads();
-    hist[(size_t)t * nwg + blockIdx.x] = h[t];
-}
-
-// First slot of every cell of the grid (G^3 cells, G from the device grid).
-__global__ __launch_bounds__(kB) void k_pm_first(const unsigned long long* __restrict__ keys,
-                                                 int n, const PmGrid* __restrict__ g,
-                                                 int* cfirst) {
-    const int G = g->Gc;
-    fill_cell_first(keys, n, G * G * G, blockIdx.x * kB + threadIdx.x, cfirst);
-}
-
-// Velocities follow the slots: v2[.][s] = v[.][src(s)].
-__global__ __launch_bounds__(kB) void k_pm_permute_v(const unsigned long long* __restrict__ keys,
-                                                     int n, const double* __restrict__ v,
-                                                     double* __restrict__ v2) {
+    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (blockIdx.x == 0 && threadIdx.x == 0) C.mx[0] = C.mx[1] = __float_as_uint(m);
+    const PmGrid g = pm_grid(m, rmax);
     const int s = blockIdx.x * kB + threadIdx.x;
-    if (s >= n) return;
-    const int src = (int)(unsigned)keys[s];
-    v2[s] = v[src];
-    v2[(size_t)n + s] = v[(size_t)n + src];
-    v2[2 * (size_t)n + s] = v[2 * (size_t)n + src];
+    double x[3] = {0.0, 0.0, 0.0};
+    if (s < n) {
+        const float4 h = pos[s], l = lo[s];
+        x[0] = (double)h.x + (double)l.x;
+        x[1] = (double)h.y + (double)l.y;
+        x[2] = (double)h.z + (double)l.z;
+    }
+    pm_bin(g, s < n, s, x, C, cell, rank);
 }
 
-// Step (ii): the truncated pair forces on slot i from the 27 cells around
-// its cell, in cell order and slot order within a cell (FP64).  The three
-// cells of an x-row are consecutive in key order, so their slots form one
-// range [cfirst[a], cfirst[b + 1]) and nine ranges cover the 27 cells.  Each
-// candidate is first screened in FP32 from its hi word against the largest
-// range widened by the screen's worst rounding (coordinates within L: hi
-// rounding and the FP32 difference move each component by <= L 2^-22, the
-// squared sum by a few ulp), so every pair the FP64 test keeps passes the
-// screen; only the survivors load lo and the type.
-__global__ __launch_bounds__(kB) void k_pm_forces(const float4* __restrict__ pos,
-                                                  const float4* __restrict__ lo,
-                                                  const int* __restrict__ typ,
-                                                  const unsigned long long* __restrict__ keys,
-                                                  const PmGrid* __restrict__ g,
-                                                  const int* __restrict__ cfirst, int n,
-                                                  PmTable tb, double* F) {
-    const int i = blockIdx.x * kB + threadIdx.x;
-    if (i >= n) return;
-    const PmGrid gr = *g;
-    const double wide = tb.rmax + gr.L * 0x1p-20;
-    const float screen2 = (float)(wide * wide * (1.0 + 0x1p-18));
-    const float4 hi = pos[i], li = lo[i];
-    const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
-                 zi = (double)hi.z + (double)li.z;
-    const int ti = typ[i];
-    const double qi = (double)hi.w;                 // q_hat = q sqrt(kT l_B)
+// First slot of every cell: a workgroup adds the coarse counts before its
+// kCoarse cells, scans those, and leaves their counts zero.  Also takes the
+// last step's clock advance along and clears the maximum of the next step.
+__global__ __launch_bounds__(256) void k_pm_scan(PmCells C, int grid_mx, int next_mx, double rmax,
+                                                 int n, DevState* st, double adv_dt) {
+    static_assert(kCoarse == 4 * 256 && kNC / kCoarse == 256, "one int4 and one count per thread");
+    __shared__ int wsum[2][4];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (adv_dt > 0.0) {
+            st->t = st->t + adv_dt;
+            st->step = st->step + 1;
+        }
+        C.mx[next_mx] = 0u;
+    }
+    const int G = pm_grid(__uint_as_float(C.mx[grid_mx]), rmax).Gc, M = G * G * G;
+    const int b = blockIdx.x, t = threadIdx.x, w = t / 64, lane = t % 64;
+    if (b * kCoarse >= M) return;
+    const int4 v = reinterpret_cast<const int4*>(C.count)[b * 256 + t];
+    int before = t < b ? C.coarse[t] : 0;
+    const int sum = v.x + v.y + v.z + v.w;
+    int x = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        before += __shfl_xor(before, o);
+        const int y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) {
+        wsum[0][w] = before;
+        wsum[1][w] = x;
+    }
+    __syncthreads();
+    int at = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3] + x - sum;
+    for (int k = 0; k < w; ++k) at += wsum[1][k];
+    const int c = b * kCoarse + 4 * t;               // kNC is a multiple of 4
+    C.first[c] = at;
+    C.first[c + 1] = at + v.x;
+    C.first[c + 2] = at + v.x + v.y;
+    C.first[c + 3] = at + v.x + v.y + v.z;
+    if (M - 1 >= c && M - 1 < c + 4) C.first[M] = n;
+    reinterpret_cast<int4*>(C.count)[b * 256 + t] = make_int4(0, 0, 0, 0);
+}
+
+// The slots of every cell, in the order the counting met them.
+__global__ __launch_bounds__(kB) void k_pm_list(const int* __restrict__ cell,
+                                                const int* __restrict__ rank, int n, PmCells C,
+                                                int* list) {
+    const int s = blockIdx.x * kB + threadIdx.x;
+    if (blockIdx.x == 0) C.coarse[threadIdx.x] = 0;
+    if (s < n) list[C.first[cell[s]] + rank[s]] = s;
+}
+
+// The sort itself: slot s goes to its cell's place by the number of smaller
+// slots listed there, so the order does not depend on the atomics'.
+struct PmPlace {
+    const float4 *pos, *lo;
+    const int *typ, *oid, *cell, *list, *first;
+    const double* v;
+    float4 *pos2, *lo2;
+    int *typ2, *oid2, *cell2;
+    double* v2;
+    int n;
+};
+__global__ __launch_bounds__(kB) void k_pm_place(PmPlace A) {
+    const int k = blockIdx.x * kB + threadIdx.x;
+    if (k >= A.n) return;
+    const int s = A.list[k], c = A.cell[s];
+    const int f = A.first[c], e = A.first[c + 1];
+    const size_t n = (size_t)A.n;
+    const float4 h = A.pos[s], l = A.lo[s];
+    const int ty = A.typ[s], id = A.oid[s];
+    const double v0 = A.v[s], v1 = A.v[n + s], v2 = A.v[2 * n + s];
+    int d = f;
+    for (int q = f; q < e; ++q) d += A.list[q] < s;
+    A.pos2[d] = h;
+    A.lo2[d] = l;
+    A.typ2[d] = ty;
+    A.oid2[d] = id;
+    A.cell2[d] = c;
+    A.v2[d] = v0;
+    A.v2[n + d] = v1;
+    A.v2[2 * n + d] = v2;
+}
+
+// Steps (ii)-(vi) of consecutive slots in cell order.
+//
+// Pairs: LANES lanes share a particle and walk the 27 cells around its cell
+// (the three cells of an x-row are consecutive in key order, so nine slot
+// ranges cover them).  A candidate is first screened in FP32 from its hi word
+// against the type's largest range widened by the screen's worst rounding
+// (coordinates within the present largest one, L: hi rounding and the FP32
+// difference move each component by <= L 2^-22, the squared sum by a few
+// ulp), so every pair the FP64 test keeps passes the screen.  What passes is
+// listed per lane and evaluated in FP64 when the walk is over or a list full:
+// about 5 of 70 candidates pass at the headline's density, and evaluated
+// where they were met nearly every candidate cost a wavefront the FP64 body.
+//
+// A step of 250 000: 138 us (a sort of 24-bit keys in three passes, forces a
+// lane per particle and an update, 15 launches) -> 65 us in four launches; of
+// 5000: 110 -> 26 us.
+//
+// With STEP the slots are then moved into the second buffers (other
+// workgroups still read the first), and with bin counted into the next
+// step's cells; without, the forces are stored.
+struct PmStep {
+    const float4 *pos, *lo;
+    const int *typ, *oid, *cell, *first;
+    const double* v;
+    int n, grid_mx, cur_mx, next_mx;
+    double* F;
+    float4 *pos2, *lo2;
+    double* v2;
+    DevState* st;
+    double dt;
+    unsigned long long seed;
+    int bin;
+    int *ncell, *nrank;
+};
+
+template <int LANES>
+constexpr int kPmBlock = LANES == 1 ? 256 : 64 * LANES;   // threads; 64 slots where lanes share
+
+template <bool STEP, int LANES>
+__global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable tb, ExtParams P,
+                                                             PmCells C) {
+    constexpr int kBlock = kPmBlock<LANES>, kPart = kBlock / LANES;
+    constexpr int kList = LANES == 1 ? 16 : 8;
+    __shared__ double tr[kMaxTypes * kMaxTypes], ts[kMaxTypes * kMaxTypes],
+        te[kMaxTypes * kMaxTypes], sF[3][LANES == 1 ? 1 : kPart];
+    __shared__ int list[kList][kBlock];
+    const int t = threadIdx.x, sub = t % LANES;
+    const int i = blockIdx.x * kPart + t / LANES;
+    const bool live = i < A.n;
+    if (t < tb.T * tb.T) {
+        tr[t] = tb.rint2[t];
+        ts[t] = tb.sig2[t];
+        te[t] = tb.e24[t];
+    }
+    const float mcur = __uint_as_float(C.mx[A.cur_mx]);
+    const PmGrid gr = pm_grid(__uint_as_float(C.mx[A.grid_mx]), tb.rmax);
     const int G = gr.Gc;
-    const int c = (int)(keys[i] >> 32);
-    const int cx = c % G, cy = (c / G) % G, cz = c / (G * G);
-    const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < G - 1 ? cx + 1 : G - 1;
-    // the nine row ranges first (independent loads), empty where the row
-    // falls outside the grid
+    float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), li = hi;
+    int ty = 0;
+    float screen2 = 0.f;
     int r0[9], r1[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const int z = cz + k / 3 - 1, y = cy + k % 3 - 1;
-        const bool in = z >= 0 && z < G && y >= 0 && y < G;
-        const int row = (z * G + y) * G;
-        r0[k] = in ? cfirst[row + x0] : 0;
-        r1[k] = in ? cfirst[row + x1 + 1] : 0;
-    }
-    double fx = 0.0, fy = 0.0, fz = 0.0;
+    for (int k = 0; k < 9; ++k) r0[k] = r1[k] = 0;
+    if (live) {
+        hi = A.pos[i];
+        li = A.lo[i];
+        ty = A.typ[i];
+        const int c = A.cell[i];
+        const double wide = tb.rtype[ty] + (double)(fmaxf(mcur, 1e-3f) * 1.0009765625f) * 0x1p-20;
+        screen2 = (float)(wide * wide * (1.0 + 0x1p-18));
+        const int cx = c % G, cy = (c / G) % G, cz = c / (G * G);
+        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < G - 1 ? cx + 1 : G - 1;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const int j1 = r1[k];
-        for (int jb = r0[k]; jb < j1; jb += kPmWin) {
-            // kPmWin candidates' hi words in flight, then screened in order
-            float4 hq[kPmWin];
-#pragma unroll
-            for (int u = 0; u < kPmWin; ++u) hq[u] = pos[min(jb + u, j1 - 1)];
-#pragma unroll
-            for (int u = 0; u < kPmWin; ++u) {
-                const int j = jb + u;
-                const float4 hj = hq[u];
-                const float sx = hj.x - hi.x, sy = hj.y - hi.y, sz = hj.z - hi.z;
-                if (j >= j1 || !(fmaf(sz, sz, fmaf(sy, sy, sx * sx)) < screen2) || j == i)
-                    continue;
-                const float4 lj = lo[j];
-                const double ddx = xi - ((double)hj.x + (double)lj.x);
-                const double ddy = yi - ((double)hj.y + (double)lj.y);
-                const double ddz = zi - ((double)hj.z + (double)lj.z);
-                const double r2 = ddx * ddx + ddy * ddy + ddz * ddz;
-                const int p = ti * tb.T + typ[j];
-                if (!(r2 < tb.rint2[p])) continue;
-                const double ir2 = 1.0 / r2;
-                const double s2 = tb.sig2[p] * ir2, s6 = s2 * s2 * s2;
-                const double glj = tb.e24[p] * (2.0 * s6 * s6 - s6) * ir2;
-                const double gc = qi * (double)hj.w * ir2 * sqrt(ir2);
-                const double gg = glj + gc;
-                fx += gg * ddx;
-                fy += gg * ddy;
-                fz += gg * ddz;
-            }
+        for (int k = 0; k < 9; ++k) {                  // independent loads
+            const int z = cz + k / 3 - 1, y = cy + k % 3 - 1;
+            const bool in = z >= 0 && z < G && y >= 0 && y < G;
+            const int row = (z * G + y) * G;
+            r0[k] = in ? A.first[row + x0] + sub : 0;
+            r1[k] = in ? A.first[row + x1 + 1] : 0;
         }
     }
-    F[i] = fx;
-    F[(size_t)n + i] = fy;
-    F[2 * (size_t)n + i] = fz;
-}
+    const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
+                 zi = (double)hi.z + (double)li.z;
+    const double qi = (double)hi.w;                    // q_hat = q sqrt(kT l_B)
+    __syncthreads();                                   // the tables
 
-// Steps (iii)-(vi) for one slot.
-__global__ __launch_bounds__(kB) void k_pm_update(float4* pos, float4* lo,
-                                                  const int* __restrict__ typ,
-                                                  const int* __restrict__ oid,
-                                                  const double* __restrict__ F, double* v, int n,
-                                                  double dt, unsigned long long seed, PmTable tb,
-                                                  ExtParams P, DevState* st) {
-    const long long step = st->step;
-    const double R = radius_at(P.R, st->t + dt);   // the new radius precedes the surface force
-    const int s = blockIdx.x * kB + threadIdx.x;
-    if (s >= n) return;
-    float4 h = pos[s], l = lo[s];
-    const int ty = typ[s];
-    const double x[3] = {(double)h.x + (double)l.x, (double)h.y + (double)l.y,
-                         (double)h.z + (double)l.z};
-    double Fe[3];
-    upd::ext_force(x, ty, R, P, Fe);
-    double u[3] = {0.0, 0.0, 0.0};
-    if (tb.kick > 0.0) {
-        double xi[3];
-        upd::gauss3((uint32_t)oid[s], (unsigned long long)step, seed, xi);
-        const double len = sqrt(xi[0] * xi[0] + xi[1] * xi[1] + xi[2] * xi[2]);
-        u[0] = xi[0] / len;
-        u[1] = xi[1] / len;
-        u[2] = xi[2] / len;
+    double fx = 0.0, fy = 0.0, fz = 0.0;
+    int cnt = 0;                                       // the lane's listed partners
+    auto evaluate = [&]() {
+        for (int k = 0; __any(k < cnt); ++k) {
+            if (k >= cnt) continue;
+            const int j = list[k][t];
+            const float4 hj = A.pos[j], lj = A.lo[j];
+            const double dx = xi - ((double)hj.x + (double)lj.x);
+            const double dy = yi - ((double)hj.y + (double)lj.y);
+            const double dz = zi - ((double)hj.z + (double)lj.z);
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const int p = ty * tb.T + A.typ[j];
+            if (!(r2 < tr[p])) continue;
+            const double ir2 = 1.0 / r2;
+            const double s2 = ts[p] * ir2, s6 = s2 * s2 * s2;
+            const double glj = te[p] * (2.0 * s6 * s6 - s6) * ir2;
+            const double gc = qi * (double)hj.w * ir2 * sqrt(ir2);
+            const double gg = glj + gc;
+            fx += gg * dx;
+            fy += gg * dy;
+            fz += gg * dz;
+        }
+        cnt = 0;
+    };
+    auto meet = [&](int j, bool valid, const float4& hj) {
+        const float dx = hj.x - hi.x, dy = hj.y - hi.y, dz = hj.z - hi.z;
+        if (valid && j != i && fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < screen2) list[cnt++][t] = j;
+    };
+    // windows of four candidates in flight; the lists have room for one
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        for (int j = r0[k]; __any(j < r1[k]); j += kPmWin * LANES) {
+            float4 hq[kPmWin];
+#pragma unroll
+            for (int u = 0; u < kPmWin; ++u) {
+                const int ju = j + u * LANES;
+                hq[u] = A.pos[ju < r1[k] ? ju : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < kPmWin; ++u) meet(j + u * LANES, j + u * LANES < r1[k], hq[u]);
+            if (__any(cnt > kList - kPmWin)) evaluate();
+        }
+    evaluate();
+#pragma unroll
+    for (int o = 1; o < LANES; o <<= 1) {
+        fx += __shfl_xor(fx, o);
+        fy += __shfl_xor(fy, o);
+        fz += __shfl_xor(fz, o);
     }
-    const double g = tb.gamma[ty], im = tb.inv_m[ty];
-    bool ok = true;
-    double xn[3];
-    for (int c = 0; c < 3; ++c) {
-        double vc = v[(size_t)c * n + s];
-        vc = vc + dt * (F[(size_t)c * n + s] + Fe[c] - g * vc) * im;
-        vc += tb.kick * u[c];
-        const double d = dt * vc;
-        if (!isfinite(d) || (P.jump_max > 0.0 && fabs(d) > P.jump_max)) ok = false;
-        v[(size_t)c * n + s] = vc;
-        xn[c] = x[c] + d;
+    int s = i;
+    if (LANES > 1) {
+        // one wavefront goes on, a slot a lane
+        if (sub == 0) {
+            sF[0][t / LANES] = fx;
+            sF[1][t / LANES] = fy;
+            sF[2][t / LANES] = fz;
+        }
+        __syncthreads();
+        if (t >= kPart) return;
+        s = blockIdx.x * kPart + t;
+        fx = sF[0][t];
+        fy = sF[1][t];
+        fz = sF[2][t];
+        if (s < A.n) {
+            hi = A.pos[s];
+            li = A.lo[s];
+            ty = A.typ[s];
+        }
     }
-    if (!ok) atomicMin(&st->bad_step, (unsigned long long)step);
-    h.x = (float)xn[0];
-    h.y = (float)xn[1];
-    h.z = (float)xn[2];
-    l = make_float4((float)(xn[0] - (double)h.x), (float)(xn[1] - (double)h.y),
-                    (float)(xn[2] - (double)h.z), 0.f);
-    pos[s] = h;
-    lo[s] = l;
+    const bool on = s < A.n;
+    const size_t n = (size_t)A.n;
+    if (!STEP) {
+        if (on) {
+            A.F[s] = fx;
+            A.F[n + s] = fy;
+            A.F[2 * n + s] = fz;
+        }
+        return;
+    }
+    double xn[3] = {0.0, 0.0, 0.0};
+    float m = 0.f;
+    if (on) {
+        const long long step = A.st->step;
+        const double R = radius_at(P.R, A.st->t + A.dt);   // the new radius precedes the surface force
+        const double x[3] = {(double)hi.x + (double)li.x, (double)hi.y + (double)li.y,
+                             (double)hi.z + (double)li.z};
+        const double f[3] = {fx, fy, fz};
+        double Fe[3];
+        upd::ext_force(x, ty, R, P, Fe);
+        double u[3] = {0.0, 0.0, 0.0};
+        if (tb.kick > 0.0) {
+            double xg[3];
+            upd::gauss3((uint32_t)A.oid[s], (unsigned long long)step, A.seed, xg);
+            const double len = sqrt(xg[0] * xg[0] + xg[1] * xg[1] + xg[2] * xg[2]);
+            u[0] = xg[0] / len;
+            u[1] = xg[1] / len;
+            u[2] = xg[2] / len;
+        }
+        const double g = tb.gamma[ty], im = tb.inv_m[ty];
+        bool ok = true;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            double vc = A.v[c * n + s];
+            vc = vc + A.dt * (f[c] + Fe[c] - g * vc) * im;
+            vc += tb.kick * u[c];
+            const double d = A.dt * vc;
+            if (!isfinite(d) || (P.jump_max > 0.0 && fabs(d) > P.jump_max)) ok = false;
+            A.v2[c * n + s] = vc;
+            xn[c] = x[c] + d;
+        }
+        if (!ok) atomicMin(&A.st->bad_step, (unsigned long long)step);
+        const float4 h = make_float4((float)xn[0], (float)xn[1], (float)xn[2], hi.w);
+        const float4 l = make_float4((float)(xn[0] - (double)h.x), (float)(xn[1] - (double)h.y),
+                                     (float)(xn[2] - (double)h.z), 0.f);
+        A.pos2[s] = h;
+        A.lo2[s] = l;
+        m = fmaxf(m, fmaxf(fabsf(h.x), fmaxf(fabsf(h.y), fabsf(h.z))));
+    }
+    if (!A.bin) return;
+    m = upd::wave_max(m);
+    if (t % 64 == 0 && m > __uint_as_float(C.mx[A.next_mx]))
+        atomicMax(&C.mx[A.next_mx], __float_as_uint(m));
+    pm_bin(pm_grid(mcur, tb.rmax), on, s, xn, C, A.ncell, A.nrank);
 }
 
 // Slot-order [3][n] -> original order [n][3].
@@ -317,28 +495,45 @@ bool pm_alloc(T** p, size_t count) {
     return hipMalloc(p, sizeof(T) * (count > 0 ? count : 1)) == hipSuccess;
 }
 
-// Steps (i)-(ii) at the current positions: re-sort by cell (slot arrays and
-// velocities swapped with their second buffers) and the pair forces into F.
-ld_status pm_forces(ld_ctx* c, hipStream_t s) {
+// Step (i): the slots re-sorted by cell (slot arrays and velocities swapped
+// with their second buffers).  binned: the step before counted the cells.
+ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     PaperMode* m = c->pm;
-    const int n = (int)c->n;
-    PM_LAUNCH(k_pm_absmax, dim3(64), dim3(kB), s, c->pos, n, c->sb.bounds_part);
-    const int nwg = radix_tiles(n);
-    PM_LAUNCH(k_pm_keys, dim3(nwg), dim3(kB), s, c->pos, c->lo, n, c->sb.bounds_part,
-              m->tab.rmax, m->grid, c->sb.keys, c->sb.hist, nwg);
-    int bits = 1;
-    while ((1 << bits) < kNC) ++bits;
-    unsigned long long* keys = nullptr;    // the buffer the sorted keys end in
-    HIP_TRY(launch_radix_by_high(c->sb.keys, reinterpret_cast<unsigned long long*>(c->sb.tmp4),
-                                 n, bits, c->sb.hist, s, true, &keys));
+    const int n = (int)c->n, blocks = (n + kB - 1) / kB;
+    const PmCells C = pm_cells(m->cells);
     if (!c->pos2) {
         if (!(pm_alloc(&c->pos2, (size_t)n) && pm_alloc(&c->lo2, (size_t)n) &&
               pm_alloc(&c->typ2, (size_t)n) && pm_alloc(&c->oid2, (size_t)n)))
             return fail(LD_ENOMEM, "cannot allocate the second slot arrays");
     }
-    HIP_TRY(permute_slots_into(keys, n, c->pos, c->lo, c->typ, c->oid, c->pos2, c->lo2,
-                               c->typ2, c->oid2, s));
-    PM_LAUNCH(k_pm_permute_v, dim3((n + kB - 1) / kB), dim3(kB), s, keys, n, m->v, m->v2);
+    int* cell = reinterpret_cast<int*>(c->sb.keys);       // cells and ranks
+    int* list = reinterpret_cast<int*>(c->sb.tmp4);       // lists and sorted cells
+    if (!binned) {
+        m->turn = 0;
+        PM_LAUNCH(k_pm_absmax, dim3(64), dim3(kB), s, c->pos, n, c->sb.bounds_part);
+        PM_LAUNCH(k_pm_bin, dim3(blocks), dim3(kB), s, c->pos, c->lo, n, c->sb.bounds_part,
+                  m->tab.rmax, C, cell, cell + n);
+    }
+    PM_LAUNCH(k_pm_scan, dim3(kNC / kCoarse), dim3(256), s, C, m->turn % 3, (m->turn + 2) % 3,
+              m->tab.rmax, n, c->st, adv_dt);
+    PM_LAUNCH(k_pm_list, dim3(blocks), dim3(kB), s, cell, cell + n, n, C, list);
+    PmPlace A{};
+    A.pos = c->pos;
+    A.lo = c->lo;
+    A.typ = c->typ;
+    A.oid = c->oid;
+    A.cell = cell;
+    A.list = list;
+    A.first = C.first;
+    A.v = m->v;
+    A.pos2 = c->pos2;
+    A.lo2 = c->lo2;
+    A.typ2 = c->typ2;
+    A.oid2 = c->oid2;
+    A.cell2 = list + n;
+    A.v2 = m->v2;
+    A.n = n;
+    PM_LAUNCH(k_pm_place, dim3(blocks), dim3(kB), s, A);
     c->charged_first = c->n_charged == c->n;   // cell order mixes the two kinds
     std::swap(c->pos, c->pos2);
     std::swap(c->lo, c->lo2);
@@ -346,11 +541,55 @@ ld_status pm_forces(ld_ctx* c, hipStream_t s) {
     std::swap(c->oid, c->oid2);
     std::swap(m->v, m->v2);
     c->graph_len = -1;                 // a captured graph holds the old addresses
-    PM_LAUNCH(k_pm_first, dim3((n + kB - 1) / kB), dim3(kB), s, keys, n, m->grid, m->cfirst);
-    PM_LAUNCH(k_pm_forces, dim3((n + kB - 1) / kB), dim3(kB), s, c->pos, c->lo, c->typ, keys,
-              m->grid, m->cfirst, n, m->tab, m->F);
     c->steps_since_sort = 0;
     return LD_OK;
+}
+
+PmStep pm_launch(ld_ctx* c) {
+    PaperMode* m = c->pm;
+    PmStep A{};
+    A.pos = c->pos;
+    A.lo = c->lo;
+    A.typ = c->typ;
+    A.oid = c->oid;
+    A.cell = reinterpret_cast<int*>(c->sb.tmp4) + c->n;
+    A.first = pm_cells(m->cells).first;
+    A.n = (int)c->n;
+    A.grid_mx = m->turn % 3;
+    A.cur_mx = (m->turn + 1) % 3;
+    A.next_mx = (m->turn + 2) % 3;
+    return A;
+}
+
+template <bool STEP, int LANES>
+void pm_run_as(const PmStep& A, ld_ctx* c, hipStream_t s) {
+    constexpr int part = kPmBlock<LANES> / LANES;
+    hipLaunchKernelGGL((k_pm_step<STEP, LANES>), dim3((A.n + part - 1) / part),
+                       dim3(kPmBlock<LANES>), 0, s, A, c->pm->tab, c->ext,
+                       pm_cells(c->pm->cells));
+}
+
+template <bool STEP>
+ld_status pm_run(const PmStep& A, ld_ctx* c, hipStream_t s) {
+    // four lanes a particle while a lane each would leave the chip's wavefronts
+    // few and their chains long: a step of 5000 26 us (one lane 31), of 50 000
+    // 35 (38), of 100 000 49 (44), of 250 000 79 (65)
+    if (A.n < kPmSplitN)
+        pm_run_as<STEP, 4>(A, c, s);
+    else
+        pm_run_as<STEP, 1>(A, c, s);
+    HIP_TRY(hipGetLastError());
+    return LD_OK;
+}
+
+// Steps (i)-(ii) at the current positions into F.
+ld_status pm_forces(ld_ctx* c, hipStream_t s) {
+    PaperMode* m = c->pm;
+    ld_status st = pm_sort(c, s, false, 0.0);
+    if (st != LD_OK) return st;
+    PmStep A = pm_launch(c);
+    A.F = m->F;
+    return pm_run<false>(A, c, s);
 }
 
 }  // namespace
@@ -358,21 +597,36 @@ ld_status pm_forces(ld_ctx* c, hipStream_t s) {
 void pm_free(ld_ctx* c) {
     if (!c->pm) return;
     PaperMode* m = c->pm;
-    void* b[] = {m->v, m->v2, m->F, m->grid, m->cfirst};
+    void* b[] = {m->v, m->v2, m->F, m->cells};
     for (void* p : b)
         if (p) (void)hipFree(p);
     delete m;
     c->pm = nullptr;
 }
 
-ld_status pm_step(ld_ctx* c, double dt, hipStream_t s) {
+ld_status pm_step(ld_ctx* c, double dt, hipStream_t s, bool first, bool last) {
     PaperMode* m = c->pm;
-    const int n = (int)c->n;
-    ld_status st = pm_forces(c, s);
+    const double adv = c->pend_dt;
+    c->pend_dt = 0.0;
+    ld_status st = pm_sort(c, s, !first, adv);
     if (st != LD_OK) return st;
-    PM_LAUNCH(k_pm_update, dim3((n + kB - 1) / kB), dim3(kB), s, c->pos, c->lo, c->typ, c->oid,
-              m->F, m->v, n, dt, (unsigned long long)c->seed, m->tab, c->ext, c->st);
-    HIP_TRY(launch_advance(c->st, dt, s));
+    PmStep A = pm_launch(c);
+    A.v = m->v;
+    A.pos2 = c->pos2;
+    A.lo2 = c->lo2;
+    A.v2 = m->v2;
+    A.st = c->st;
+    A.dt = dt;
+    A.seed = (unsigned long long)c->seed;
+    A.bin = last ? 0 : 1;
+    A.ncell = reinterpret_cast<int*>(c->sb.keys);
+    A.nrank = A.ncell + A.n;
+    if ((st = pm_run<true>(A, c, s)) != LD_OK) return st;
+    std::swap(c->pos, c->pos2);
+    std::swap(c->lo, c->lo2);
+    std::swap(m->v, m->v2);
+    ++m->turn;
+    c->pend_dt = dt;
     return LD_OK;
 }
 
@@ -412,6 +666,7 @@ ld_status ld_paper_enable(ld_ctx* c, const ld_paper_config* cfg) {
             tb.rint2[a * T + b] = rint * rint;
             tb.sig2[a * T + b] = sg * sg;
             tb.e24[a * T + b] = 24.0 * e;
+            tb.rtype[a] = b == 0 ? rint : std::max(tb.rtype[a], rint);
             tb.rmax = std::max(tb.rmax, rint);
         }
     for (int t = 0; t < T; ++t) {
@@ -421,7 +676,8 @@ ld_status ld_paper_enable(ld_ctx* c, const ld_paper_config* cfg) {
     tb.kick = cfg->kick;
     const size_t N = (size_t)c->n;
     bool ok = pm_alloc(&m->v, 3 * N) && pm_alloc(&m->v2, 3 * N) && pm_alloc(&m->F, 3 * N) &&
-              pm_alloc(&m->grid, 1) && pm_alloc(&m->cfirst, (size_t)kNC + 1);
+              pm_alloc(&m->cells, kCellInts) &&
+              hipMemset(m->cells, 0, sizeof(int) * kCellInts) == hipSuccess;
     if (ok) {
         std::vector<double> zero(3 * N, 0.0);
         ok = hipMemcpy(m->v, zero.data(), sizeof(double) * 3 * N, hipMemcpyHostToDevice) ==

@@ -1,0 +1,77 @@
+"""The truncated scheme's cell sort and step kernel at their edges: one cell,
+more partners than a list holds, both lane counts, and cells counted by the
+step before against cells counted anew."""
+import numpy as np
+import pytest
+
+from paper_2501_04456_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ld():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2501_04456_amd import ldrop
+    ldrop.lib()
+    return ldrop
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.lib()
+    return oracle
+
+
+def stored_charge(w):
+    """The charges as a context holds them: q sqrt(kT l_B) in FP32."""
+    c = np.sqrt(w.params.kT * w.params.bjerrum)
+    return (w.charge * c).astype(np.float32).astype(np.float64) / c
+
+
+@pytest.mark.parametrize("n,factor", [(2, 4.0), (65, 1e3), (1025, 1e3), (4097, 40.0),
+                                      (74999, 4.0), (75000, 9.0)])
+def test_forces(ld, orc, n, factor):
+    w = W.config_large(n=n, seed=31)
+    s = ld.System.from_workload(w)
+    s.paper_enable(range_factor=factor)
+    rows = np.unique(np.linspace(0, n - 1, 100).astype(int))
+    for _ in range(2):                       # the second sort starts from cell order
+        F = s.paper_forces()
+        Fo, So = orc.paper_forces(w.pos, w.type, stored_charge(w), w.params, factor, rows=rows)
+        # FP64 pair terms: a few ulp of each
+        assert (np.linalg.norm(F[rows] - Fo, axis=1) <= 1e-12 * So).all()
+
+
+@pytest.mark.parametrize("n", [63, 5000, 80001])
+def test_calls(ld, n):
+    """One call of several steps and several calls give the same bits; so do
+    two runs, whatever order the counting meets the slots in."""
+    w = W.config_medium(n=n, seed=5)
+    x = []
+    for calls in ((7,), (7,), (1, 4, 0, 2)):
+        s = ld.System.from_workload(w)
+        s.paper_enable(range_factor=4.0, kick=0.05)
+        for k in calls:
+            s.step(k, 5e-4)
+        assert s.state()[0] == 7
+        x.append((s.positions64(), s.velocities()))
+    assert np.array_equal(x[0][0], x[1][0]) and np.array_equal(x[0][1], x[1][1])
+    # a call's first step bins on the present largest coordinate, the others on
+    # the one before: cells, and with them the order of a sum, may differ
+    assert np.abs(x[0][0] - x[2][0]).max() <= 1e-9
+    assert np.abs(x[0][1] - x[2][1]).max() <= 1e-6
+
+
+def test_far_particle(ld, orc):
+    """One particle far outside leaves few, large cells; the forces hold."""
+    w = W.config_medium(n=3000, seed=8)
+    w.pos = w.pos.copy()
+    w.pos[17] = (1e5, -2e5, 3e4)
+    s = ld.System.from_workload(w)
+    s.paper_enable(range_factor=4.0)
+    F = s.paper_forces()
+    Fo, So = orc.paper_forces(w.pos, w.type, stored_charge(w), w.params, 4.0)
+    assert (np.linalg.norm(F - Fo, axis=1) <= 1e-12 * So).all()
