@@ -5,9 +5,10 @@
 // sphere).
 //
 // Sub-aggregates are the connected components of the contact graph, a pair
-// in contact when r < contact_factor sigma_ij.  Candidates come from a cell
-// list (cells of side >= the largest contact distance, radix-sorted keys;
-// the context's slot order is left alone) and are united lock-free: a union
+// in contact when r < contact_factor sigma_ij.  Candidates come from a counted
+// cell list (cells of side >= the largest contact distance; the context's slot
+// order is left alone, copies of the positions lie in cell order) and are
+// united lock-free: a union
 // hangs the larger root under the smaller with a compare-and-swap, so parent
 // indices only decrease, no cycle can form and every component ends with
 // its smallest (cell-sorted) index as root.  The label reported is the
@@ -19,23 +20,18 @@
 #include <limits>
 #include <vector>
 
+#include "ld_cells.h"
 #include "ld_host.h"
 
 namespace ld {
 
+using host::copy_out;
 using host::fail;
 
 namespace {
 
 constexpr int kB = 256;
-constexpr int kAMaxCells = 64;
-constexpr int kANC = kAMaxCells * kAMaxCells * kAMaxCells;
 constexpr int kAMaxIter = 1 << 16;      // bound of every retry loop
-
-struct AgGrid {
-    double L, hc;
-    int Gc, pad;
-};
 
 struct AgTable {
     int T;
@@ -43,100 +39,72 @@ struct AgTable {
     double half_sigma[kMaxTypes];
 };
 
-__global__ __launch_bounds__(kB) void k_ag_absmax(const float4* __restrict__ pos, int n,
-                                                  float* part) {
-    __shared__ float red[kB];
-    float m = 0.f;
-    for (int s = blockIdx.x * kB + threadIdx.x; s < n; s += gridDim.x * kB) {
-        const float4 h = pos[s];
-        m = fmaxf(m, fmaxf(fabsf(h.x), fmaxf(fabsf(h.y), fabsf(h.z))));
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int w = kB / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
+// Statistics of a call, cleared by its binning: [0] components, [1] aggregates
+// of size >= 2, [2] the largest (its size, or packed with its label), [3] error.
+using AgRes = unsigned long long;
 
-__device__ __forceinline__ int ag_cell1(double x, double L, double h, int G) {
-    int c = (int)floor((x + L) / h);
-    return c < 0 ? 0 : (c > G - 1 ? G - 1 : c);
-}
-
-// Grid (block 0 stores it), cell keys (cell << 32 | slot) from the FP64
-// positions and the first radix pass's digit counts per radix tile.
-__global__ __launch_bounds__(kB) void k_ag_keys(const float4* __restrict__ pos,
-                                                const float4* __restrict__ lo, int n,
-                                                const float* __restrict__ part, double rc,
-                                                AgGrid* g, unsigned long long* keys,
-                                                unsigned* hist, int nwg) {
-    __shared__ AgGrid sg;
-    __shared__ unsigned h[256];
-    const int t = threadIdx.x;
-    h[t] = 0u;
-    if (t < 64) {
-        float m = part[t];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-        if (t == 0) {
-            m = fmaxf(m, 1e-3f);
-            const double L = (double)(m * 1.0009765625f);
-            int G = (int)floor(2.0 * L / rc);
-            G = G < 1 ? 1 : (G > kAMaxCells ? kAMaxCells : G);
-            sg.L = L;
-            sg.Gc = G;
-            sg.hc = 2.0 * L / G;
-            sg.pad = 0;
-            if (blockIdx.x == 0) *g = sg;
+// Cells of all slots, with SURF of the surface NPs only (| |x| - R | < sigma_t
+// / 2; the others' labels are -1 and they are in no list).
+template <bool SURF>
+__global__ __launch_bounds__(kB) void k_ag_bin(const float4* __restrict__ pos,
+                                               const float4* __restrict__ lo,
+                                               const int* __restrict__ typ,
+                                               const int* __restrict__ oid, int n,
+                                               const float* __restrict__ part, double rc, double R,
+                                               AgTable tb, cells::Work C, int* cell, int* rank,
+                                               int* labels, AgRes* res) {
+#pragma clang fp contract(off)
+    const float m = cells::absmax_of(part);
+    if (blockIdx.x == 0 && threadIdx.x < 4) {
+        res[threadIdx.x] = 0ull;
+        if (threadIdx.x == 0) C.mx[0] = __float_as_uint(m);
+    }
+    const int s = blockIdx.x * kB + threadIdx.x;
+    bool live = s < n;
+    double x[3] = {0.0, 0.0, 0.0};
+    if (live) {
+        const float4 h = pos[s], l = lo[s];
+        x[0] = (double)h.x + (double)l.x;
+        x[1] = (double)h.y + (double)l.y;
+        x[2] = (double)h.z + (double)l.z;
+        if (SURF && !(fabs(sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]) - R) <
+                      tb.half_sigma[typ[s]])) {
+            live = false;
+            cell[s] = -1;
+            if (labels) labels[oid[s]] = -1;
         }
     }
-    __syncthreads();
-    const int G = sg.Gc;
-    for (int r = 0; r < kRadixRounds; ++r) {
-        const int s = blockIdx.x * kRadixTile + r * kB + t;
-        if (s < n) {
-            const float4 hp = pos[s], l = lo[s];
-            const int cx = ag_cell1((double)hp.x + (double)l.x, sg.L, sg.hc, G),
-                      cy = ag_cell1((double)hp.y + (double)l.y, sg.L, sg.hc, G),
-                      cz = ag_cell1((double)hp.z + (double)l.z, sg.L, sg.hc, G);
-            const unsigned c = (unsigned)((cz * G + cy) * G + cx);
-            keys[s] = ((unsigned long long)c << 32) | (unsigned)s;
-            atomicAdd(&h[c & 255u], 1u);
-        }
+    cells::bin<false>(cells::grid_of(m, rc), live, s, x, C, cell, rank);
+}
+
+// The listed slots in cell order: positions, type (in lo.w), slot and cell;
+// and, unless null, every one its own root.
+__global__ __launch_bounds__(kB) void k_ag_place(const float4* __restrict__ pos,
+                                                 const float4* __restrict__ lo,
+                                                 const int* __restrict__ typ,
+                                                 const int* __restrict__ cell,
+                                                 const int* __restrict__ list, cells::Work C,
+                                                 double rc, int n, float4* shi, float4* slo,
+                                                 int* slot, int* scell, int* parent, int* minoid,
+                                                 int* size, int* count) {
+    const int G = cells::grid_of(__uint_as_float(C.mx[0]), rc).Gc;
+    const int m = C.first[G * G * G], k = blockIdx.x * kB + threadIdx.x;
+    if (k == 0) *count = m;
+    if (k >= m) return;
+    const int s = list[k], c = cell[s];
+    const float4 h = pos[s];
+    float4 l = lo[s];
+    l.w = __int_as_float(typ[s]);
+    const int d = cells::place(C.first, list, c, s);
+    shi[d] = h;
+    slo[d] = l;
+    slot[d] = s;
+    scell[d] = c;
+    if (parent) {
+        parent[k] = k;
+        minoid[k] = INT_MAX;
+        size[k] = 0;
     }
-    __syncthreads();
-    hist[(size_t)t * nwg + blockIdx.x] = h[t];
-}
-
-__global__ __launch_bounds__(kB) void k_ag_fill(int* a, int m, int v) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k < m) a[k] = v;
-}
-
-__global__ __launch_bounds__(kB) void k_ag_iota(int* a, int m) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k < m) a[k] = k;
-}
-
-// First slot of every cell of the grid (G^3 cells, G from the device grid):
-// the slots of cells a..b of the sorted keys are [cfirst[a], cfirst[b + 1]).
-__global__ __launch_bounds__(kB) void k_ag_first(const unsigned long long* __restrict__ keys,
-                                                 int n, const AgGrid* __restrict__ g,
-                                                 int* cfirst) {
-    const int G = g->Gc;
-    fill_cell_first(keys, n, G * G * G, blockIdx.x * kB + threadIdx.x, cfirst);
-}
-
-// Squared FP32 screen for candidate pairs: the range widened by the worst
-// rounding of an FP32 difference of hi words (coordinates within the cube
-// half width L: hi rounding and the difference move each component by at
-// most L 2^-22, the squared sum by a few ulp), so every pair the FP64 test
-// keeps passes it.
-__device__ __forceinline__ float ag_screen2(double range, double L) {
-    const double w = range + L * 0x1p-20;
-    return (float)(w * w * (1.0 + 0x1p-18));
 }
 
 // Root of a: a bounded walk up the parent links with path halving (a
@@ -170,80 +138,68 @@ __device__ __forceinline__ void ag_unite(int* parent, int a, int b, int* err) {
     atomicOr(err, 1);
 }
 
-// Every contact pair (k, m), m > k in cell-sorted order, from the 27 cells
-// around k's cell; with SURF only pairs of two surface NPs (surf[slot] != 0).
-template <bool SURF>
-__global__ __launch_bounds__(kB) void k_ag_hook(const float4* __restrict__ pos,
-                                                const float4* __restrict__ lo,
-                                                const int* __restrict__ typ,
-                                                const unsigned long long* __restrict__ keys,
-                                                const AgGrid* __restrict__ g,
-                                                const int* __restrict__ cfirst, int n,
-                                                AgTable tb, const int* __restrict__ surf,
-                                                int* parent, int* err) {
+// The particles in cell order, count[0] of them.
+struct AgSorted {
+    const float4 *hi, *lo;              // lo.w: the type's bits
+    const int *slot, *cell, *first, *count;
+    const unsigned* mx;
+};
+
+// Every contact pair (k, m), m > k in cell order, LANES lanes a particle.
+// Bound by the chains of the lock-free unions: 30 011 NPs in patches of 125
+// 165 -> 25 us (a lane per particle, FP64 tests of all candidates before),
+// 250 000 dispersed ones 83 -> 21.
+template <int LANES>
+__global__ __launch_bounds__(kB) void k_ag_hook(AgSorted A, AgTable tb, double rc, int* parent,
+                                                int* err) {
     // the oracle's operand order, no fused multiply-add: a pair within an ulp
     // of the contact distance lands on the same side in both
 #pragma clang fp contract(off)
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k >= n) return;
-    const unsigned long long key = keys[k];
-    const int i = (int)(unsigned)key;
-    if (SURF && !surf[i]) return;
-    const float4 hi = pos[i], li = lo[i];
+    constexpr int kList = 8;
+    __shared__ int list[kList][kB];
+    const int k = blockIdx.x * (kB / LANES) + threadIdx.x / LANES;
+    const bool live = k < A.count[0];
+    const float m = __uint_as_float(A.mx[0]);
+    float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), li = hi;
+    int c = 0;
+    if (live) {
+        hi = A.hi[k];
+        li = A.lo[k];
+        c = A.cell[k];
+    }
     const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
                  zi = (double)hi.z + (double)li.z;
-    const int ti = typ[i];
-    const int G = g->Gc;
-    const int c = (int)(key >> 32);
-    const int cx = c % G, cy = (c / G) % G, cz = c / (G * G);
-    for (int dz = -1; dz <= 1; ++dz) {
-        const int z = cz + dz;
-        if (z < 0 || z >= G) continue;
-        for (int dy = -1; dy <= 1; ++dy) {
-            const int y = cy + dy;
-            if (y < 0 || y >= G) continue;
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int x = cx + dx;
-                if (x < 0 || x >= G) continue;
-                const int cc = (z * G + y) * G + x;
-                const int m1 = cfirst[cc + 1];
-                for (int m = max(cfirst[cc], k + 1); m < m1; ++m) {
-                    const int j = (int)(unsigned)keys[m];
-                    if (SURF && !surf[j]) continue;
-                    const float4 hj = pos[j], lj = lo[j];
-                    const double ddx = xi - ((double)hj.x + (double)lj.x);
-                    const double ddy = yi - ((double)hj.y + (double)lj.y);
-                    const double ddz = zi - ((double)hj.z + (double)lj.z);
-                    if (ddx * ddx + ddy * ddy + ddz * ddz < tb.rc2[ti * tb.T + typ[j]])
-                        ag_unite(parent, k, m, err);
-                }
-            }
-        }
-    }
+    const int ti = __float_as_int(li.w) * tb.T;
+    cells::walk<LANES, true, kB, kList>(
+        A.hi, A.first, cells::grid_of(m, rc).Gc, live, k, c, hi, cells::screen2(rc, m), list,
+        [&](int j) {
+            const float4 hj = A.hi[j], lj = A.lo[j];
+            const double ddx = xi - ((double)hj.x + (double)lj.x);
+            const double ddy = yi - ((double)hj.y + (double)lj.y);
+            const double ddz = zi - ((double)hj.z + (double)lj.z);
+            if (ddx * ddx + ddy * ddy + ddz * ddz < tb.rc2[ti + __float_as_int(lj.w)])
+                ag_unite(parent, k, j, err);
+        });
 }
 
-__global__ __launch_bounds__(kB) void k_ag_flatten(int* parent, int n, int* root, int* err) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k < n) root[k] = ag_find(parent, k, err);
-}
-
-// Per root: the smallest original index (label) and the size.  Lanes of a
-// wavefront with the same root combine first (one atomic per root per
-// wavefront, so a giant component costs one atomic per wavefront).
-// With a surface mask only surface NPs count.
-__global__ __launch_bounds__(kB) void k_ag_roots(const int* __restrict__ root,
-                                                 const unsigned long long* __restrict__ keys,
+// Roots, and per root the smallest original index (label) and the size.  The
+// first few roots of a wavefront are combined over their lanes (a giant
+// component costs one atomic per wavefront), the lanes left then go singly.
+__global__ __launch_bounds__(kB) void k_ag_roots(int* parent, const int* __restrict__ slot,
                                                  const int* __restrict__ oid,
-                                                 const int* __restrict__ surf, int n, int* minoid,
-                                                 int* size) {
+                                                 const int* __restrict__ count, int* root,
+                                                 int* minoid, int* size, int* err) {
     const int k = blockIdx.x * kB + threadIdx.x;
-    const int slot = k < n ? (int)(unsigned)keys[k] : 0;
-    const bool live = k < n && (!surf || surf[slot]);
-    const int r = live ? root[k] : -1;
-    const int o = live ? oid[slot] : INT_MAX;
+    const bool live = k < *count;
+    int r = -1, o = INT_MAX;
+    if (live) {
+        r = ag_find(parent, k, err);
+        root[k] = r;
+        o = oid[slot[k]];
+    }
     unsigned long long todo = __ballot(live);
     const int lane = threadIdx.x % 64;
-    for (int it = 0; it < 64 && todo; ++it) {
+    for (int it = 0; it < 4 && todo; ++it) {
         const int leader = __ffsll((long long)todo) - 1;
         const int rl = __shfl(r, leader);
         const unsigned long long same = __ballot(live && r == rl);
@@ -256,41 +212,59 @@ __global__ __launch_bounds__(kB) void k_ag_roots(const int* __restrict__ root,
         }
         todo &= ~same;
     }
+    if ((todo >> lane) & 1ull) {
+        atomicMin(&minoid[r], o);
+        atomicAdd(&size[r], 1);
+    }
 }
 
-// labels (original order) and per-workgroup partial statistics:
-// [components, aggregates (size >= 2), largest size].
+// Labels (original order) and the statistics; with SURF the largest is packed
+// as size << 32 | (INT_MAX - label), so the maximum is the largest size and,
+// among equal sizes, the smallest label.  Few workgroups: each ends with three
+// atomics on one line.
+template <bool SURF>
 __global__ __launch_bounds__(kB) void k_ag_label(const int* __restrict__ root,
-                                                 const unsigned long long* __restrict__ keys,
+                                                 const int* __restrict__ slot,
                                                  const int* __restrict__ oid,
                                                  const int* __restrict__ minoid,
-                                                 const int* __restrict__ size, int n,
-                                                 int* labels, long long* part) {
-    __shared__ long long red[3][kB];
-    const int k = blockIdx.x * kB + threadIdx.x;
-    long long comp = 0, agg = 0, big = 0;
-    if (k < n) {
+                                                 const int* __restrict__ size,
+                                                 const int* __restrict__ count, int* labels,
+                                                 AgRes* res) {
+    AgRes comp = 0ull, agg = 0ull, big = 0ull;
+    const int m = *count;
+    for (int k = blockIdx.x * kB + threadIdx.x; k < m; k += gridDim.x * kB) {
         const int r = root[k];
-        if (labels) labels[oid[(int)(unsigned)keys[k]]] = minoid[r];
+        if (labels) labels[oid[slot[k]]] = minoid[r];
         if (r == k) {
-            comp = 1;
-            agg = size[k] >= 2 ? 1 : 0;
-            big = size[k];
+            ++comp;
+            agg += size[k] >= 2 ? 1 : 0;
+            const AgRes b = SURF ? ((AgRes)size[k] << 32) | (AgRes)(unsigned)(INT_MAX - minoid[k])
+                                 : (AgRes)size[k];
+            if (b > big) big = b;
         }
     }
-    red[0][threadIdx.x] = comp;
-    red[1][threadIdx.x] = agg;
-    red[2][threadIdx.x] = big;
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
+        comp += __shfl_xor(comp, w);
+        agg += __shfl_xor(agg, w);
+        const AgRes o = __shfl_xor(big, w);
+        if (o > big) big = o;
+    }
+    __shared__ AgRes red[3][kB / 64];
+    if (threadIdx.x % 64 == 0) {
+        red[0][threadIdx.x / 64] = comp;
+        red[1][threadIdx.x / 64] = agg;
+        red[2][threadIdx.x / 64] = big;
+    }
     __syncthreads();
-    for (int w = kB / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + w];
-            red[1][threadIdx.x] += red[1][threadIdx.x + w];
-            red[2][threadIdx.x] = max(red[2][threadIdx.x], red[2][threadIdx.x + w]);
-        }
-        __syncthreads();
+    if (threadIdx.x < 3) {
+        AgRes v = 0ull;
+        for (int w = 0; w < kB / 64; ++w)
+            v = threadIdx.x < 2 ? v + red[threadIdx.x][w]
+                                : (red[2][w] > v ? red[2][w] : v);
+        if (v && threadIdx.x < 2) atomicAdd(&res[threadIdx.x], v);
+        if (v && threadIdx.x == 2) atomicMax(&res[2], v);
     }
-    if (threadIdx.x < 3) part[3 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
 }
 
 // N_surf partials per workgroup and type: | |x| - R | < sigma_t / 2.
@@ -314,100 +288,41 @@ __global__ __launch_bounds__(kB) void k_ag_surface(const float4* __restrict__ po
     if (threadIdx.x < kMaxTypes) part[(size_t)blockIdx.x * kMaxTypes + threadIdx.x] = cnt[threadIdx.x];
 }
 
-// Surface flag per slot: | |x| - R | < sigma_t / 2 (as k_ag_surface).
-__global__ __launch_bounds__(kB) void k_sf_flag(const float4* __restrict__ pos,
-                                                const float4* __restrict__ lo,
-                                                const int* __restrict__ typ, int n, double R,
-                                                AgTable tb, int* surf) {
-#pragma clang fp contract(off)
-    const int s = blockIdx.x * kB + threadIdx.x;
-    if (s >= n) return;
-    const float4 h = pos[s], l = lo[s];
-    const double x = (double)h.x + (double)l.x, y = (double)h.y + (double)l.y,
-                 z = (double)h.z + (double)l.z;
-    surf[s] = fabs(sqrt(x * x + y * y + z * z) - R) < tb.half_sigma[typ[s]] ? 1 : 0;
-}
-
-// Labels of surface NPs (-1 elsewhere) and per-workgroup partials:
-// [surface components, the largest packed as size << 32 | (INT_MAX - label)],
-// so the maximum is the largest size and, among equal sizes, the smallest
-// label.
-__global__ __launch_bounds__(kB) void k_sf_label(const int* __restrict__ root,
-                                                 const unsigned long long* __restrict__ keys,
-                                                 const int* __restrict__ oid,
-                                                 const int* __restrict__ surf,
-                                                 const int* __restrict__ minoid,
-                                                 const int* __restrict__ size, int n,
-                                                 int* labels, long long* part) {
-    __shared__ long long red[2][kB];
-    const int k = blockIdx.x * kB + threadIdx.x;
-    long long comp = 0, best = -1;
-    if (k < n) {
-        const int slot = (int)(unsigned)keys[k];
-        const int r = root[k];
-        const bool on = surf[slot] != 0;
-        if (labels) labels[oid[slot]] = on ? minoid[r] : -1;
-        if (on && r == k) {
-            comp = 1;
-            best = ((long long)size[k] << 32) | (long long)(unsigned)(INT_MAX - minoid[k]);
-        }
-    }
-    red[0][threadIdx.x] = comp;
-    red[1][threadIdx.x] = best;
-    __syncthreads();
-    for (int w = kB / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + w];
-            red[1][threadIdx.x] = max(red[1][threadIdx.x], red[1][threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x < 2) part[2 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Direction of a surface NP (FP64 hi + lo) and whether it belongs to the
-// component labelled `label`.
-__device__ __forceinline__ bool sf_member(const float4* __restrict__ pos,
-                                          const float4* __restrict__ lo,
-                                          const unsigned long long* __restrict__ keys,
-                                          const int* __restrict__ root,
-                                          const int* __restrict__ surf,
-                                          const int* __restrict__ minoid, int k, int label,
-                                          double u[3], int* slot) {
-    const int sl = (int)(unsigned)keys[k];
-    *slot = sl;
-    if (!surf[sl] || minoid[root[k]] != label) return false;
-    const float4 h = pos[sl], l = lo[sl];
+// Direction of the surface NP k (FP64 hi + lo) of cell order and whether it
+// belongs to the largest component, packed in res[2].
+__device__ __forceinline__ bool sf_member(const AgSorted& A, const int* __restrict__ root,
+                                          const int* __restrict__ minoid, const AgRes* res, int k,
+                                          double u[3], int* type) {
+    const int label = INT_MAX - (int)(unsigned)(res[2] & 0xffffffffull);
+    if (minoid[root[k]] != label) return false;
+    const float4 h = A.hi[k], l = A.lo[k];
     const double x = (double)h.x + (double)l.x, y = (double)h.y + (double)l.y,
                  z = (double)h.z + (double)l.z;
     const double r = sqrt(x * x + y * y + z * z);
     u[0] = x / r;
     u[1] = y / r;
     u[2] = z / r;
+    *type = __float_as_int(l.w);
     return true;
 }
 
 // Per-workgroup sums over the component's NPs of the unit direction and of
 // sigma: dpart[4 * block + {0, 1, 2, 3}].
-__global__ __launch_bounds__(kB) void k_sf_sums(const float4* __restrict__ pos,
-                                                const float4* __restrict__ lo,
-                                                const int* __restrict__ typ,
-                                                const unsigned long long* __restrict__ keys,
-                                                const int* __restrict__ root,
-                                                const int* __restrict__ surf,
-                                                const int* __restrict__ minoid, int n, int label,
-                                                AgTable tb, double* dpart) {
+__global__ __launch_bounds__(kB) void k_sf_sums(AgSorted A, const int* __restrict__ root,
+                                                const int* __restrict__ minoid,
+                                                const AgRes* __restrict__ res, AgTable tb,
+                                                double* dpart) {
     __shared__ double red[4][kB];
     const int k = blockIdx.x * kB + threadIdx.x;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (k < n) {
+    if (k < A.count[0]) {
         double u[3];
-        int sl;
-        if (sf_member(pos, lo, keys, root, surf, minoid, k, label, u, &sl)) {
+        int ty;
+        if (sf_member(A, root, minoid, res, k, u, &ty)) {
             v[0] = u[0];
             v[1] = u[1];
             v[2] = u[2];
-            v[3] = 2.0 * tb.half_sigma[typ[sl]];
+            v[3] = 2.0 * tb.half_sigma[ty];
         }
     }
 #pragma unroll
@@ -423,23 +338,36 @@ __global__ __launch_bounds__(kB) void k_sf_sums(const float4* __restrict__ pos,
     if (threadIdx.x < 4) dpart[4 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Per-workgroup sums of the squared angle between each member's direction
-// and u0 (from the sine and cosine, accurate for small angles).
-__global__ __launch_bounds__(kB) void k_sf_theta(const float4* __restrict__ pos,
-                                                 const float4* __restrict__ lo,
-                                                 const unsigned long long* __restrict__ keys,
-                                                 const int* __restrict__ root,
-                                                 const int* __restrict__ surf,
-                                                 const int* __restrict__ minoid, int n, int label,
-                                                 double u0x, double u0y, double u0z,
-                                                 double* dpart) {
-    __shared__ double red[kB];
+// Per-workgroup sums of the squared angle between each member's direction and
+// the mean direction (from the sine and cosine, accurate for small angles).
+// Every workgroup adds the k_sf_sums partials itself, in the same order, so
+// the host need not come in between.
+__global__ __launch_bounds__(kB) void k_sf_theta(AgSorted A, const int* __restrict__ root,
+                                                 const int* __restrict__ minoid,
+                                                 const AgRes* __restrict__ res,
+                                                 const double* __restrict__ dpart,
+                                                 double* tpart) {
+    __shared__ double red[3][kB];
+    double su[3] = {0.0, 0.0, 0.0};
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += kB)
+        for (int q = 0; q < 3; ++q) su[q] += dpart[4 * (size_t)b + q];
+    for (int q = 0; q < 3; ++q) red[q][threadIdx.x] = su[q];
+    __syncthreads();
+    for (int w = kB / 2; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w)
+            for (int q = 0; q < 3; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
+        __syncthreads();
+    }
+    for (int q = 0; q < 3; ++q) su[q] = red[q][0];
+    __syncthreads();
+    const double nu = sqrt(su[0] * su[0] + su[1] * su[1] + su[2] * su[2]);
+    const double u0x = su[0] / nu, u0y = su[1] / nu, u0z = su[2] / nu;
     const int k = blockIdx.x * kB + threadIdx.x;
     double v = 0.0;
-    if (k < n) {
+    if (k < A.count[0] && nu > 0.0) {
         double u[3];
-        int sl;
-        if (sf_member(pos, lo, keys, root, surf, minoid, k, label, u, &sl)) {
+        int ty;
+        if (sf_member(A, root, minoid, res, k, u, &ty)) {
             const double cx = u[1] * u0z - u[2] * u0y, cy = u[2] * u0x - u[0] * u0z,
                          cz = u[0] * u0y - u[1] * u0x;
             const double th = atan2(sqrt(cx * cx + cy * cy + cz * cz),
@@ -447,13 +375,13 @@ __global__ __launch_bounds__(kB) void k_sf_theta(const float4* __restrict__ pos,
             v = th * th;
         }
     }
-    red[threadIdx.x] = v;
+    red[0][threadIdx.x] = v;
     __syncthreads();
     for (int w = kB / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        if ((int)threadIdx.x < w) red[0][threadIdx.x] += red[0][threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) dpart[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) tpart[blockIdx.x] = red[0][0];
 }
 
 constexpr int kRdfMaxBins = 4096;
@@ -468,55 +396,42 @@ __global__ __launch_bounds__(kB) void k_ag_zero64(unsigned long long* a, int m) 
 // cells around k's.  The distance is formed exactly as in the all-pairs
 // histogram (FP64 hi + lo, the same operand order, no contraction; the
 // squares make it independent of the pair's orientation), so every pair
-// falls in the same bin.
-__global__ __launch_bounds__(kB) void k_ag_rdf(const float4* __restrict__ pos,
-                                               const float4* __restrict__ lo,
-                                               const unsigned long long* __restrict__ keys,
-                                               const AgGrid* __restrict__ g,
-                                               const int* __restrict__ cfirst, int n,
-                                               double r_max, int n_bins, double dr,
+// falls in the same bin.  250 000 NPs, r_max 10: 70 -> 41 us (60 with two
+// lanes a particle).
+template <int LANES>
+__global__ __launch_bounds__(kB) void k_ag_rdf(AgSorted A, double r_max, int n_bins, double dr,
                                                unsigned long long* counts) {
 #pragma clang fp contract(off)
+    constexpr int kList = LANES == 1 ? 16 : 8;
     __shared__ unsigned int hist[kRdfMaxBins];
+    __shared__ int list[kList][kB];
     for (int b = threadIdx.x; b < n_bins; b += kB) hist[b] = 0u;
     __syncthreads();
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k < n) {
-        const unsigned long long key = keys[k];
-        const int i = (int)(unsigned)key;
-        const float4 hi = pos[i], li = lo[i];
-        const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
-                     zi = (double)hi.z + (double)li.z;
-        const int G = g->Gc;
-        const float screen2 = ag_screen2(r_max, g->L);
-        const int c = (int)(key >> 32);
-        const int cx = c % G, cy = (c / G) % G, cz = c / (G * G);
-        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < G - 1 ? cx + 1 : G - 1;
-        for (int dz = -1; dz <= 1; ++dz) {
-            const int z = cz + dz;
-            if (z < 0 || z >= G) continue;
-            for (int dy = -1; dy <= 1; ++dy) {
-                const int y = cy + dy;
-                if (y < 0 || y >= G) continue;
-                const int row = (z * G + y) * G;
-                const int m1 = cfirst[row + x1 + 1];
-                for (int m = max(cfirst[row + x0], k + 1); m < m1; ++m) {
-                    const int j = (int)(unsigned)keys[m];
-                    const float4 hj = pos[j], lj = lo[j];
-                    const float sx = hj.x - hi.x, sy = hj.y - hi.y, sz = hj.z - hi.z;
-                    if (!(fmaf(sz, sz, fmaf(sy, sy, sx * sx)) < screen2)) continue;
-                    const double ex = xi - ((double)hj.x + (double)lj.x);
-                    const double ey = yi - ((double)hj.y + (double)lj.y);
-                    const double ez = zi - ((double)hj.z + (double)lj.z);
-                    const double r = sqrt(ex * ex + ey * ey + ez * ez);
-                    if (r < r_max) {
-                        const int b = (int)floor(r / dr);
-                        if (b >= 0 && b < n_bins) atomicAdd(&hist[b], 1u);
-                    }
-                }
-            }
-        }
+    const int k = blockIdx.x * (kB / LANES) + threadIdx.x / LANES;
+    const bool live = k < A.count[0];
+    const float m = __uint_as_float(A.mx[0]);
+    float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), li = hi;
+    int c = 0;
+    if (live) {
+        hi = A.hi[k];
+        li = A.lo[k];
+        c = A.cell[k];
     }
+    const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
+                 zi = (double)hi.z + (double)li.z;
+    cells::walk<LANES, true, kB, kList>(
+        A.hi, A.first, cells::grid_of(m, r_max).Gc, live, k, c, hi, cells::screen2(r_max, m),
+        list, [&](int j) {
+            const float4 hj = A.hi[j], lj = A.lo[j];
+            const double ex = xi - ((double)hj.x + (double)lj.x);
+            const double ey = yi - ((double)hj.y + (double)lj.y);
+            const double ez = zi - ((double)hj.z + (double)lj.z);
+            const double r = sqrt(ex * ex + ey * ey + ez * ez);
+            if (r < r_max) {
+                const int b = (int)floor(r / dr);
+                if (b >= 0 && b < n_bins) atomicAdd(&hist[b], 1u);
+            }
+        });
     __syncthreads();
     for (int b = threadIdx.x; b < n_bins; b += kB)
         if (hist[b]) atomicAdd(&counts[b], (unsigned long long)hist[b]);
@@ -530,18 +445,20 @@ __global__ __launch_bounds__(kB) void k_ag_rdf(const float4* __restrict__ pos,
 
 // Scratch of the aggregate calls (allocated on first use, kept by the context).
 struct AgBufs {
-    int* cfirst;     // [kANC + 1] first slot of every cell
+    int* work;       // the cell lists' workspace
     int* parent;     // [n]
     int* root;       // [n]
     int* minoid;     // [n]
     int* size;       // [n]
     int* labels;     // [n]
-    int* err;        // [1]
+    int* slot;       // [n] slots in cell order
+    int* count;      // [1] how many
     long long* part; // [blocks * kMaxTypes]
-    double* dpart;   // [blocks * 4]
-    int* surf;       // [n] surface flag per slot
-    AgGrid* grid;    // [1]
+    AgRes* res;      // [4] statistics, with the partial sums right behind
+    double* dpart;   // [blocks * 5]
 };
+
+constexpr size_t kResDoubles = 32;      // from res to dpart
 
 // Carve the scratch out of one allocation, every piece 256-byte aligned;
 // with base == nullptr only the total size is computed.
@@ -553,17 +470,17 @@ size_t ag_layout(char* base, size_t n, AgBufs* b) {
         off += (nbytes + 255) / 256 * 256;
         return q;
     };
-    b->grid = reinterpret_cast<AgGrid*>(take(sizeof(AgGrid)));
     b->part = reinterpret_cast<long long*>(take(blocks * kMaxTypes * sizeof(long long)));
-    b->dpart = reinterpret_cast<double*>(take(blocks * 4 * sizeof(double)));
-    b->surf = reinterpret_cast<int*>(take(n * sizeof(int)));
-    b->cfirst = reinterpret_cast<int*>(take((kANC + 1) * sizeof(int)));
+    b->res = reinterpret_cast<AgRes*>(take((kResDoubles + blocks * 5) * sizeof(double)));
+    b->dpart = base ? reinterpret_cast<double*>(b->res) + kResDoubles : nullptr;
+    b->work = reinterpret_cast<int*>(take(cells::kWorkInts * sizeof(int)));
     b->parent = reinterpret_cast<int*>(take(n * sizeof(int)));
     b->root = reinterpret_cast<int*>(take(n * sizeof(int)));
     b->minoid = reinterpret_cast<int*>(take(n * sizeof(int)));
     b->size = reinterpret_cast<int*>(take(n * sizeof(int)));
     b->labels = reinterpret_cast<int*>(take(n * sizeof(int)));
-    b->err = reinterpret_cast<int*>(take(sizeof(int)));
+    b->slot = reinterpret_cast<int*>(take(n * sizeof(int)));
+    b->count = reinterpret_cast<int*>(take(sizeof(int)));
     return off;
 }
 
@@ -603,56 +520,65 @@ double ag_table(const ld_ctx* c, double contact_factor, AgTable* tb) {
         if (e_ != hipSuccess) return e_;                                                  \
     } while (0)
 
-// Cell sort for cells of side >= rc: grid, keys (cell << 32 | slot) sorted by
-// cell, and every cell's first slot.  *keys_out: the sorted keys.
-hipError_t ag_cells(ld_ctx* c, const AgBufs& b, double rc, unsigned long long** keys_out) {
+// Cell lists for cells of side >= rc, and the particles in cell order (in the
+// context's FP64 scratch); with surf those within sigma / 2 of R only.
+hipError_t ag_cells(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bool surf, double R,
+                    int* labels, bool roots, AgSorted* A) {
     const int n = (int)c->n;
     hipStream_t s = c->stream;
-    const int blocks = (n + kB - 1) / kB;
-    AG_RUN(k_ag_absmax, dim3(64), c->pos, n, c->sb.bounds_part);
-    const int nwg = radix_tiles(n);
-    AG_RUN(k_ag_keys, dim3(nwg), c->pos, c->lo, n, c->sb.bounds_part, rc, b.grid, c->sb.keys,
-           c->sb.hist, nwg);
-    int bits = 1;
-    while ((1 << bits) < kANC) ++bits;
-    unsigned long long* keys = nullptr;
-    const hipError_t e = launch_radix_by_high(
-        c->sb.keys, reinterpret_cast<unsigned long long*>(c->sb.tmp4), n, bits, c->sb.hist, s,
-        true, &keys);
+    const dim3 gn((n + kB - 1) / kB);
+    const cells::Work C = cells::work_at(b.work);
+    int* cell = reinterpret_cast<int*>(c->sb.keys);       // cells and ranks
+    int* list = reinterpret_cast<int*>(c->sb.tmp4);       // lists and sorted cells
+    float4* hi = reinterpret_cast<float4*>(c->work);
+    float4* lo = hi + n;
+    hipError_t e = cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s);
     if (e != hipSuccess) return e;
-    AG_RUN(k_ag_first, dim3(blocks), keys, n, b.grid, b.cfirst);
-    *keys_out = keys;
+    if (surf)
+        AG_RUN(k_ag_bin<true>, gn, c->pos, c->lo, c->typ, c->oid, n, c->sb.bounds_part, rc, R, tb,
+               C, cell, cell + n, labels, b.res);
+    else
+        AG_RUN(k_ag_bin<false>, gn, c->pos, c->lo, c->typ, c->oid, n, c->sb.bounds_part, rc, R,
+               tb, C, cell, cell + n, labels, b.res);
+    if ((e = cells::launch_coarse(C, s)) != hipSuccess) return e;
+    if ((e = cells::launch_scan(C, 0, 1, rc, c->st, 0.0, s)) != hipSuccess) return e;
+    if ((e = cells::launch_list(cell, cell + n, n, C, list, s)) != hipSuccess) return e;
+    AG_RUN(k_ag_place, gn, c->pos, c->lo, c->typ, cell, list, C, rc, n, hi, lo, b.slot, list + n,
+           roots ? b.parent : nullptr, b.minoid, b.size, b.count);
+    *A = AgSorted{hi, lo, b.slot, list + n, C.first, b.count, C.mx};
     return hipSuccess;
 }
 
-// Cell sort, lock-free union of the contact pairs (with surf: only pairs of
-// two surface NPs), roots, and per root the size and smallest original index
-// (counting only surface NPs with surf).  *keys_out: the cell-sorted keys.
-hipError_t ag_union(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, const int* surf,
-                    unsigned long long** keys_out) {
+// Below this size more lanes a particle: a chip that one lane a particle
+// leaves idle waits for their chains (the truncated scheme's walk breaks even
+// between 50 000 and 100 000).
+constexpr int kAgSplitN = 75000;
+
+// Cell lists, lock-free union of the contact pairs (with surf: of surface NPs
+// only), roots, per root the size and smallest original index, labels and
+// statistics.
+hipError_t ag_union(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bool surf, double R,
+                    int* labels, AgSorted* A) {
     const int n = (int)c->n;
     hipStream_t s = c->stream;
-    const int blocks = (n + kB - 1) / kB;
-    const dim3 gn(blocks);
-    unsigned long long* keys = nullptr;
-    const hipError_t ec = ag_cells(c, b, rc, &keys);
+    const dim3 gn((n + kB - 1) / kB), gl(std::min((n + kB - 1) / kB, 128));
+    int* err = reinterpret_cast<int*>(b.res + 3);
+    const hipError_t ec = ag_cells(c, b, tb, rc, surf, R, labels, true, A);
     if (ec != hipSuccess) return ec;
-    AG_RUN(k_ag_iota, gn, b.parent, n);
-    AG_RUN(k_ag_fill, dim3(1), b.err, 1, 0);
-    if (surf)
-        AG_RUN(k_ag_hook<true>, gn, c->pos, c->lo, c->typ, keys, b.grid, b.cfirst, n, tb, surf,
-               b.parent, b.err);
+    if (n < kAgSplitN)
+        AG_RUN(k_ag_hook<16>, dim3((n + kB / 16 - 1) / (kB / 16)), *A, tb, rc, b.parent, err);
     else
-        AG_RUN(k_ag_hook<false>, gn, c->pos, c->lo, c->typ, keys, b.grid, b.cfirst, n, tb,
-               nullptr, b.parent, b.err);
-    AG_RUN(k_ag_flatten, gn, b.parent, n, b.root, b.err);
-    AG_RUN(k_ag_fill, gn, b.minoid, n, INT_MAX);
-    AG_RUN(k_ag_fill, gn, b.size, n, 0);
-    AG_RUN(k_ag_roots, gn, b.root, keys, c->oid, surf, n, b.minoid, b.size);
-#undef AG_RUN
-    *keys_out = keys;
+        AG_RUN(k_ag_hook<4>, dim3((n + kB / 4 - 1) / (kB / 4)), *A, tb, rc, b.parent, err);
+    AG_RUN(k_ag_roots, gn, b.parent, b.slot, c->oid, b.count, b.root, b.minoid, b.size, err);
+    if (surf)
+        AG_RUN(k_ag_label<true>, gl, b.root, b.slot, c->oid, b.minoid, b.size, b.count, labels,
+               b.res);
+    else
+        AG_RUN(k_ag_label<false>, gl, b.root, b.slot, c->oid, b.minoid, b.size, b.count, labels,
+               b.res);
     return hipSuccess;
 }
+#undef AG_RUN
 
 }  // namespace
 
@@ -670,25 +596,29 @@ ld_status ag_rdf_pairs(ld_ctx* c, double r_max, int n_bins, unsigned long long* 
     *used = false;
     const int n = (int)c->n;
     hipStream_t s = c->stream;
-    // the grid the key kernel will derive (same partial maxima, same rule)
-    AG_LAUNCH(k_ag_absmax, dim3(64), dim3(kB), s, c->pos, n, c->sb.bounds_part);
+    // the grid the binning will derive (same partial maxima, same rule)
+    AgBufs b{};
+    ld_status st = ag_buffers(c, &b);
+    if (st != LD_OK) return st;
+    const cells::Work C = cells::work_at(b.work);
+    HIP_TRY(cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s));
     float part[64];
-    HIP_TRY(hipMemcpyAsync(part, c->sb.bounds_part, sizeof part, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(copy_out(c->stage, part, c->sb.bounds_part, sizeof part, s));
     float m = 0.f;
     for (float v : part) m = std::max(m, v);
     m = std::max(m, 1e-3f);
     const double L = (double)(m * 1.0009765625f);
     if ((int)std::floor(2.0 * L / r_max) < 3) return LD_OK;
-    AgBufs b{};
-    ld_status st = ag_buffers(c, &b);
-    if (st != LD_OK) return st;
-    unsigned long long* keys = nullptr;
-    HIP_TRY(ag_cells(c, b, r_max, &keys));
-    const int blocks = (n + kB - 1) / kB;
+    AgTable tb{};
+    AgSorted A{};
+    HIP_TRY(ag_cells(c, b, tb, r_max, false, 0.0, nullptr, false, &A));
     AG_LAUNCH(k_ag_zero64, dim3((n_bins + kB - 1) / kB), dim3(kB), s, counts, n_bins);
-    AG_LAUNCH(k_ag_rdf, dim3(blocks), dim3(kB), s, c->pos, c->lo, keys, b.grid, b.cfirst, n,
-              r_max, n_bins, r_max / n_bins, counts);
+    if (n < kAgSplitN)
+        AG_LAUNCH(k_ag_rdf<4>, dim3((n + kB / 4 - 1) / (kB / 4)), dim3(kB), s, A, r_max, n_bins,
+                  r_max / n_bins, counts);
+    else
+        AG_LAUNCH(k_ag_rdf<1>, dim3((n + kB - 1) / kB), dim3(kB), s, A, r_max, n_bins,
+                  r_max / n_bins, counts);
     *used = true;
     return LD_OK;
 }
@@ -712,28 +642,13 @@ ld_status ld_aggregates(ld_ctx* c, double contact_factor, int64_t stats[3], int3
     if (st != LD_OK) return st;
     AgTable tb{};
     const double rc = ag_table(c, contact_factor, &tb);
-    unsigned long long* keys = nullptr;
-    HIP_TRY(ag_union(c, b, tb, rc, nullptr, &keys));
-    const int blocks = (n + kB - 1) / kB;
-    AG_LAUNCH(k_ag_label, dim3(blocks), dim3(kB), s, b.root, keys, c->oid, b.minoid, b.size, n,
-              labels ? b.labels : nullptr, b.part);
-    std::vector<long long> part(3 * (size_t)blocks);
-    int err = 0;
-    HIP_TRY(hipMemcpyAsync(part.data(), b.part, sizeof(long long) * part.size(),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&err, b.err, sizeof(int), hipMemcpyDeviceToHost, s));
+    AgSorted A{};
+    HIP_TRY(ag_union(c, b, tb, rc, false, 0.0, labels ? b.labels : nullptr, &A));
+    AgRes res[4];
+    HIP_TRY(copy_out(c->stage, res, b.res, sizeof res, s));
     if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (err) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
-    long long comp = 0, agg = 0, big = 0;
-    for (int k = 0; k < blocks; ++k) {
-        comp += part[3 * (size_t)k];
-        agg += part[3 * (size_t)k + 1];
-        big = std::max(big, part[3 * (size_t)k + 2]);
-    }
-    stats[0] = comp;
-    stats[1] = agg;
-    stats[2] = big;
+    if (res[3]) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
+    for (int k = 0; k < 3; ++k) stats[k] = (int64_t)res[k];
     return LD_OK;
 }
 
@@ -749,8 +664,7 @@ ld_status ld_surface_fractal(ld_ctx* c, double R, double contact_factor, double 
     hipStream_t s = c->stream;
     if (!(R >= 0.0)) {      // negative: the droplet's radius at the current time
         DevState ds;
-        HIP_TRY(hipMemcpyAsync(&ds, c->st, sizeof ds, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(copy_out(c->stage, &ds, c->st, sizeof ds, s));
         R = radius_at(c->R, ds.t);
     }
     AgBufs b{};
@@ -759,59 +673,42 @@ ld_status ld_surface_fractal(ld_ctx* c, double R, double contact_factor, double 
     AgTable tb{};
     const double rc = ag_table(c, contact_factor, &tb);
     const int blocks = (n + kB - 1) / kB;
-    AG_LAUNCH(k_sf_flag, dim3(blocks), dim3(kB), s, c->pos, c->lo, c->typ, n, R, tb, b.surf);
-    unsigned long long* keys = nullptr;
-    HIP_TRY(ag_union(c, b, tb, rc, b.surf, &keys));
-    AG_LAUNCH(k_sf_label, dim3(blocks), dim3(kB), s, b.root, keys, c->oid, b.surf, b.minoid,
-              b.size, n, labels ? b.labels : nullptr, b.part);
-    std::vector<long long> part(2 * (size_t)blocks);
-    int err = 0;
-    HIP_TRY(hipMemcpyAsync(part.data(), b.part, sizeof(long long) * part.size(),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&err, b.err, sizeof(int), hipMemcpyDeviceToHost, s));
+    AgSorted A{};
+    HIP_TRY(ag_union(c, b, tb, rc, true, R, labels ? b.labels : nullptr, &A));
+    // the largest component's mean direction, mean diameter and squared angles
+    // (partials summed in workgroup order: nothing depends on timing)
+    double* tpart = b.dpart + 4 * (size_t)blocks;
+    AG_LAUNCH(k_sf_sums, dim3(blocks), dim3(kB), s, A, b.root, b.minoid, b.res, tb, b.dpart);
+    AG_LAUNCH(k_sf_theta, dim3(blocks), dim3(kB), s, A, b.root, b.minoid, b.res, b.dpart, tpart);
+    std::vector<double> got(kResDoubles + 5 * (size_t)blocks);
+    HIP_TRY(copy_out(c->stage, got.data(), b.res, sizeof(double) * got.size(), s));
     if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (err) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
-    long long comp = 0, best = -1;
-    for (int k = 0; k < blocks; ++k) {
-        comp += part[2 * (size_t)k];
-        best = std::max(best, part[2 * (size_t)k + 1]);
-    }
+    AgRes res[4];
+    std::memcpy(res, got.data(), sizeof res);
+    const double* dp = got.data() + kResDoubles;
+    if (res[3]) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
     const double nan = std::numeric_limits<double>::quiet_NaN();
     out[0] = out[1] = out[2] = nan;
-    stats[0] = comp;
-    if (comp == 0) {
+    stats[0] = (int64_t)res[0];
+    if (res[0] == 0) {
         stats[1] = 0;
         stats[2] = -1;
         return LD_OK;
     }
-    const long long m = best >> 32;
-    const int label = INT_MAX - (int)(unsigned)(best & 0xffffffffLL);
+    const long long m = (long long)(res[2] >> 32);
     stats[1] = m;
-    stats[2] = label;
-    // the component's mean direction and mean diameter (partials summed in
-    // workgroup order, so the result does not depend on timing)
-    std::vector<double> dp(4 * (size_t)blocks);
-    AG_LAUNCH(k_sf_sums, dim3(blocks), dim3(kB), s, c->pos, c->lo, c->typ, keys, b.root, b.surf,
-              b.minoid, n, label, tb, b.dpart);
-    HIP_TRY(hipMemcpyAsync(dp.data(), b.dpart, sizeof(double) * dp.size(), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    double su[3] = {0.0, 0.0, 0.0}, ssig = 0.0;
+    stats[2] = INT_MAX - (int)(unsigned)(res[2] & 0xffffffffull);
+    double su[3] = {0.0, 0.0, 0.0}, ssig = 0.0, s2 = 0.0;
     for (int k = 0; k < blocks; ++k) {
         su[0] += dp[4 * (size_t)k];
         su[1] += dp[4 * (size_t)k + 1];
         su[2] += dp[4 * (size_t)k + 2];
         ssig += dp[4 * (size_t)k + 3];
+        s2 += dp[4 * (size_t)blocks + (size_t)k];
     }
     const double nu = std::sqrt(su[0] * su[0] + su[1] * su[1] + su[2] * su[2]);
     if (!(nu > 0.0)) return LD_OK;
     const double dm = d > 0.0 ? d : ssig / (double)m;
-    AG_LAUNCH(k_sf_theta, dim3(blocks), dim3(kB), s, c->pos, c->lo, keys, b.root, b.surf,
-              b.minoid, n, label, su[0] / nu, su[1] / nu, su[2] / nu, b.dpart);
-    HIP_TRY(hipMemcpyAsync(dp.data(), b.dpart, sizeof(double) * blocks, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    double s2 = 0.0;
-    for (int k = 0; k < blocks; ++k) s2 += dp[(size_t)k];
     const double Rg = R * std::sqrt(s2 / (double)m);
     out[0] = Rg;
     out[1] = dm;
@@ -826,8 +723,7 @@ ld_status ld_surface_count(ld_ctx* c, double R, int64_t* counts) {
     hipStream_t s = c->stream;
     if (!(R >= 0.0)) {      // negative: the droplet's radius at the current time
         DevState ds;
-        HIP_TRY(hipMemcpyAsync(&ds, c->st, sizeof ds, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(copy_out(c->stage, &ds, c->st, sizeof ds, s));
         R = radius_at(c->R, ds.t);
     }
     AgBufs b{};
@@ -839,9 +735,7 @@ ld_status ld_surface_count(ld_ctx* c, double R, int64_t* counts) {
     const int blocks = (n + kB - 1) / kB;
     AG_LAUNCH(k_ag_surface, dim3(blocks), dim3(kB), s, c->pos, c->lo, c->typ, n, R, tb, b.part);
     std::vector<long long> part((size_t)blocks * kMaxTypes);
-    HIP_TRY(hipMemcpyAsync(part.data(), b.part, sizeof(long long) * part.size(),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(copy_out(c->stage, part.data(), b.part, sizeof(long long) * part.size(), s));
     for (int t = 0; t < tb.T; ++t) {
         long long v = 0;
         for (int k = 0; k < blocks; ++k) v += part[(size_t)k * kMaxTypes + t];

@@ -22,20 +22,13 @@
 #include <cmath>
 #include <new>
 
+#include "ld_cells.h"
 #include "ld_host.h"
 #include "ld_update_core.h"
 
 namespace ld {
 
 using host::fail;
-
-constexpr int kPmMaxCells = 64;         // cells per axis at most
-
-struct PmGrid {
-    double L;                           // half width of the cube the cells divide
-    double hc;                          // cell side (>= the largest pair range)
-    int Gc;                             // cells per axis
-};
 
 // Pair constants: range^2, sigma^2 and 24 eps per type pair (FP64).
 struct PmTable {
@@ -63,97 +56,16 @@ struct PaperMode {
 namespace {
 
 constexpr int kB = 256;
-constexpr int kNC = kPmMaxCells * kPmMaxCells * kPmMaxCells;
-constexpr int kCoarse = 1024;           // cells of a coarse count (a scan workgroup's share)
-constexpr int kPmWin = 4;               // candidates loaded together
 constexpr int kPmSplitN = 75000;        // particles from which a lane takes one by itself
-
-// The integer workspace of the cell sort.  count and coarse are zero between
-// sorts; mx holds bits of the largest |coordinate| at three consecutive steps.
-struct PmCells {
-    int* count;                         // [kNC]
-    int* coarse;                        // [kNC / kCoarse]
-    int* first;                         // [kNC + 1] first slot of every cell
-    unsigned* mx;                       // [3]
-};
-constexpr size_t kCellInts = (size_t)kNC + kNC / kCoarse + kNC + 1 + 3;
-
-__host__ __device__ inline PmCells pm_cells(int* b) {
-    return PmCells{b, b + kNC, b + kNC + kNC / kCoarse,
-                   reinterpret_cast<unsigned*>(b + kNC + kNC / kCoarse + kNC + 1)};
-}
-
-// The grid of a largest coordinate m.  Coordinates beyond L fall into the edge
-// cells, which keeps any two particles closer than hc in adjacent cells, so
-// the m of an earlier step is as right as the present one.
-__device__ __forceinline__ PmGrid pm_grid(float m, double rmax) {
-    PmGrid g;
-    m = fmaxf(m, 1e-3f);
-    g.L = (double)(m * 1.0009765625f);
-    int G = (int)floor(2.0 * g.L / rmax);
-    G = G < 1 ? 1 : (G > kPmMaxCells ? kPmMaxCells : G);
-    g.Gc = G;
-    g.hc = 2.0 * g.L / G;
-    return g;
-}
-
-__device__ __forceinline__ int pm_cell1(double x, double L, double h, int G) {
-    int c = (int)floor((x + L) / h);
-    return c < 0 ? 0 : (c > G - 1 ? G - 1 : c);
-}
-
-// Count slot s (live lanes of one wavefront) into its cell; the coarse counts
-// take one atomic per distinct coarse cell of the wavefront (neighbours in
-// slot order share them).
-__device__ __forceinline__ void pm_bin(const PmGrid& g, bool live, int s, const double x[3],
-                                       const PmCells& C, int* cell, int* rank) {
-    const int c = live ? (pm_cell1(x[2], g.L, g.hc, g.Gc) * g.Gc +
-                          pm_cell1(x[1], g.L, g.hc, g.Gc)) * g.Gc +
-                             pm_cell1(x[0], g.L, g.hc, g.Gc)
-                       : -1;
-    if (live) {
-        cell[s] = c;
-        rank[s] = atomicAdd(&C.count[c], 1);
-    }
-    unsigned long long left = __ballot(live);
-    while (left) {
-        const int k = __shfl(c, (int)__builtin_ctzll(left)) / kCoarse;
-        const unsigned long long same = __ballot(live && c / kCoarse == k) & left;
-        if ((int)(threadIdx.x % 64) == (int)__builtin_ctzll(left))
-            atomicAdd(&C.coarse[k], __popcll(same));
-        left &= ~same;
-    }
-}
-
-// Largest |coordinate|, 64 partial maxima.
-__global__ __launch_bounds__(kB) void k_pm_absmax(const float4* __restrict__ pos, int n,
-                                                  float* part) {
-    __shared__ float red[kB];
-    float m = 0.f;
-    for (int s = blockIdx.x * kB + threadIdx.x; s < n; s += gridDim.x * kB) {
-        const float4 h = pos[s];
-        m = fmaxf(m, fmaxf(fabsf(h.x), fmaxf(fabsf(h.y), fabsf(h.z))));
-    }
-    red[threadIdx.x] = m;
-    __syncthreads();
-    for (int w = kB / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
 
 // Cells of all slots at positions no step of the same call has left (the
 // steps bin what they move themselves): mx[0] = mx[1] = the largest coordinate.
 __global__ __launch_bounds__(kB) void k_pm_bin(const float4* __restrict__ pos,
                                                const float4* __restrict__ lo, int n,
                                                const float* __restrict__ part, double rmax,
-                                               PmCells C, int* cell, int* rank) {
-    float m = part[threadIdx.x % 64];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+                                               cells::Work C, int* cell, int* rank) {
+    const float m = cells::absmax_of(part);
     if (blockIdx.x == 0 && threadIdx.x == 0) C.mx[0] = C.mx[1] = __float_as_uint(m);
-    const PmGrid g = pm_grid(m, rmax);
     const int s = blockIdx.x * kB + threadIdx.x;
     double x[3] = {0.0, 0.0, 0.0};
     if (s < n) {
@@ -162,63 +74,10 @@ __global__ __launch_bounds__(kB) void k_pm_bin(const float4* __restrict__ pos,
         x[1] = (double)h.y + (double)l.y;
         x[2] = (double)h.z + (double)l.z;
     }
-    pm_bin(g, s < n, s, x, C, cell, rank);
+    cells::bin<false>(cells::grid_of(m, rmax), s < n, s, x, C, cell, rank);
 }
 
-// First slot of every cell: a workgroup adds the coarse counts before its
-// kCoarse cells, scans those, and leaves their counts zero.  Also takes the
-// last step's clock advance along and clears the maximum of the next step.
-__global__ __launch_bounds__(256) void k_pm_scan(PmCells C, int grid_mx, int next_mx, double rmax,
-                                                 int n, DevState* st, double adv_dt) {
-    static_assert(kCoarse == 4 * 256 && kNC / kCoarse == 256, "one int4 and one count per thread");
-    __shared__ int wsum[2][4];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (adv_dt > 0.0) {
-            st->t = st->t + adv_dt;
-            st->step = st->step + 1;
-        }
-        C.mx[next_mx] = 0u;
-    }
-    const int G = pm_grid(__uint_as_float(C.mx[grid_mx]), rmax).Gc, M = G * G * G;
-    const int b = blockIdx.x, t = threadIdx.x, w = t / 64, lane = t % 64;
-    if (b * kCoarse >= M) return;
-    const int4 v = reinterpret_cast<const int4*>(C.count)[b * 256 + t];
-    int before = t < b ? C.coarse[t] : 0;
-    const int sum = v.x + v.y + v.z + v.w;
-    int x = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        before += __shfl_xor(before, o);
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) {
-        wsum[0][w] = before;
-        wsum[1][w] = x;
-    }
-    __syncthreads();
-    int at = wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3] + x - sum;
-    for (int k = 0; k < w; ++k) at += wsum[1][k];
-    const int c = b * kCoarse + 4 * t;               // kNC is a multiple of 4
-    C.first[c] = at;
-    C.first[c + 1] = at + v.x;
-    C.first[c + 2] = at + v.x + v.y;
-    C.first[c + 3] = at + v.x + v.y + v.z;
-    if (M - 1 >= c && M - 1 < c + 4) C.first[M] = n;
-    reinterpret_cast<int4*>(C.count)[b * 256 + t] = make_int4(0, 0, 0, 0);
-}
-
-// The slots of every cell, in the order the counting met them.
-__global__ __launch_bounds__(kB) void k_pm_list(const int* __restrict__ cell,
-                                                const int* __restrict__ rank, int n, PmCells C,
-                                                int* list) {
-    const int s = blockIdx.x * kB + threadIdx.x;
-    if (blockIdx.x == 0) C.coarse[threadIdx.x] = 0;
-    if (s < n) list[C.first[cell[s]] + rank[s]] = s;
-}
-
-// The sort itself: slot s goes to its cell's place by the number of smaller
-// slots listed there, so the order does not depend on the atomics'.
+// The sort itself.
 struct PmPlace {
     const float4 *pos, *lo;
     const int *typ, *oid, *cell, *list, *first;
@@ -232,13 +91,11 @@ __global__ __launch_bounds__(kB) void k_pm_place(PmPlace A) {
     const int k = blockIdx.x * kB + threadIdx.x;
     if (k >= A.n) return;
     const int s = A.list[k], c = A.cell[s];
-    const int f = A.first[c], e = A.first[c + 1];
     const size_t n = (size_t)A.n;
     const float4 h = A.pos[s], l = A.lo[s];
     const int ty = A.typ[s], id = A.oid[s];
     const double v0 = A.v[s], v1 = A.v[n + s], v2 = A.v[2 * n + s];
-    int d = f;
-    for (int q = f; q < e; ++q) d += A.list[q] < s;
+    const int d = cells::place(A.first, A.list, c, s);
     A.pos2[d] = h;
     A.lo2[d] = l;
     A.typ2[d] = ty;
@@ -251,16 +108,9 @@ __global__ __launch_bounds__(kB) void k_pm_place(PmPlace A) {
 
 // Steps (ii)-(vi) of consecutive slots in cell order.
 //
-// Pairs: LANES lanes share a particle and walk the 27 cells around its cell
-// (the three cells of an x-row are consecutive in key order, so nine slot
-// ranges cover them).  A candidate is first screened in FP32 from its hi word
-// against the type's largest range widened by the screen's worst rounding
-// (coordinates within the present largest one, L: hi rounding and the FP32
-// difference move each component by <= L 2^-22, the squared sum by a few
-// ulp), so every pair the FP64 test keeps passes the screen.  What passes is
-// listed per lane and evaluated in FP64 when the walk is over or a list full:
-// about 5 of 70 candidates pass at the headline's density, and evaluated
-// where they were met nearly every candidate cost a wavefront the FP64 body.
+// Pairs: LANES lanes share a particle and walk the cells around it; what
+// passes the screen (about 5 of 70 candidates at the headline's density) is
+// evaluated in FP64.
 //
 // A step of 250 000: 138 us (a sort of 24-bit keys in three passes, forces a
 // lane per particle and an update, 15 launches) -> 65 us in four launches; of
@@ -289,7 +139,7 @@ constexpr int kPmBlock = LANES == 1 ? 256 : 64 * LANES;   // threads; 64 slots w
 
 template <bool STEP, int LANES>
 __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable tb, ExtParams P,
-                                                             PmCells C) {
+                                                             cells::Work C) {
     constexpr int kBlock = kPmBlock<LANES>, kPart = kBlock / LANES;
     constexpr int kList = LANES == 1 ? 16 : 8;
     __shared__ double tr[kMaxTypes * kMaxTypes], ts[kMaxTypes * kMaxTypes],
@@ -304,31 +154,16 @@ __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable t
         te[t] = tb.e24[t];
     }
     const float mcur = __uint_as_float(C.mx[A.cur_mx]);
-    const PmGrid gr = pm_grid(__uint_as_float(C.mx[A.grid_mx]), tb.rmax);
-    const int G = gr.Gc;
+    const int G = cells::grid_of(__uint_as_float(C.mx[A.grid_mx]), tb.rmax).Gc;
     float4 hi = make_float4(0.f, 0.f, 0.f, 0.f), li = hi;
-    int ty = 0;
-    float screen2 = 0.f;
-    int r0[9], r1[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) r0[k] = r1[k] = 0;
+    int ty = 0, c = 0;
+    float screen = 0.f;
     if (live) {
         hi = A.pos[i];
         li = A.lo[i];
         ty = A.typ[i];
-        const int c = A.cell[i];
-        const double wide = tb.rtype[ty] + (double)(fmaxf(mcur, 1e-3f) * 1.0009765625f) * 0x1p-20;
-        screen2 = (float)(wide * wide * (1.0 + 0x1p-18));
-        const int cx = c % G, cy = (c / G) % G, cz = c / (G * G);
-        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < G - 1 ? cx + 1 : G - 1;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {                  // independent loads
-            const int z = cz + k / 3 - 1, y = cy + k % 3 - 1;
-            const bool in = z >= 0 && z < G && y >= 0 && y < G;
-            const int row = (z * G + y) * G;
-            r0[k] = in ? A.first[row + x0] + sub : 0;
-            r1[k] = in ? A.first[row + x1 + 1] : 0;
-        }
+        c = A.cell[i];
+        screen = cells::screen2(tb.rtype[ty], mcur);
     }
     const double xi = (double)hi.x + (double)li.x, yi = (double)hi.y + (double)li.y,
                  zi = (double)hi.z + (double)li.z;
@@ -336,48 +171,23 @@ __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable t
     __syncthreads();                                   // the tables
 
     double fx = 0.0, fy = 0.0, fz = 0.0;
-    int cnt = 0;                                       // the lane's listed partners
-    auto evaluate = [&]() {
-        for (int k = 0; __any(k < cnt); ++k) {
-            if (k >= cnt) continue;
-            const int j = list[k][t];
-            const float4 hj = A.pos[j], lj = A.lo[j];
-            const double dx = xi - ((double)hj.x + (double)lj.x);
-            const double dy = yi - ((double)hj.y + (double)lj.y);
-            const double dz = zi - ((double)hj.z + (double)lj.z);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            const int p = ty * tb.T + A.typ[j];
-            if (!(r2 < tr[p])) continue;
-            const double ir2 = 1.0 / r2;
-            const double s2 = ts[p] * ir2, s6 = s2 * s2 * s2;
-            const double glj = te[p] * (2.0 * s6 * s6 - s6) * ir2;
-            const double gc = qi * (double)hj.w * ir2 * sqrt(ir2);
-            const double gg = glj + gc;
-            fx += gg * dx;
-            fy += gg * dy;
-            fz += gg * dz;
-        }
-        cnt = 0;
-    };
-    auto meet = [&](int j, bool valid, const float4& hj) {
-        const float dx = hj.x - hi.x, dy = hj.y - hi.y, dz = hj.z - hi.z;
-        if (valid && j != i && fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < screen2) list[cnt++][t] = j;
-    };
-    // windows of four candidates in flight; the lists have room for one
-#pragma unroll
-    for (int k = 0; k < 9; ++k)
-        for (int j = r0[k]; __any(j < r1[k]); j += kPmWin * LANES) {
-            float4 hq[kPmWin];
-#pragma unroll
-            for (int u = 0; u < kPmWin; ++u) {
-                const int ju = j + u * LANES;
-                hq[u] = A.pos[ju < r1[k] ? ju : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < kPmWin; ++u) meet(j + u * LANES, j + u * LANES < r1[k], hq[u]);
-            if (__any(cnt > kList - kPmWin)) evaluate();
-        }
-    evaluate();
+    cells::walk<LANES, false, kBlock, kList>(A.pos, A.first, G, live, i, c, hi, screen, list, [&](int j) {
+        const float4 hj = A.pos[j], lj = A.lo[j];
+        const double dx = xi - ((double)hj.x + (double)lj.x);
+        const double dy = yi - ((double)hj.y + (double)lj.y);
+        const double dz = zi - ((double)hj.z + (double)lj.z);
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        const int p = ty * tb.T + A.typ[j];
+        if (!(r2 < tr[p])) return;
+        const double ir2 = 1.0 / r2;
+        const double s2 = ts[p] * ir2, s6 = s2 * s2 * s2;
+        const double glj = te[p] * (2.0 * s6 * s6 - s6) * ir2;
+        const double gc = qi * (double)hj.w * ir2 * sqrt(ir2);
+        const double gg = glj + gc;
+        fx += gg * dx;
+        fy += gg * dy;
+        fz += gg * dz;
+    });
 #pragma unroll
     for (int o = 1; o < LANES; o <<= 1) {
         fx += __shfl_xor(fx, o);
@@ -457,7 +267,7 @@ __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable t
     m = upd::wave_max(m);
     if (t % 64 == 0 && m > __uint_as_float(C.mx[A.next_mx]))
         atomicMax(&C.mx[A.next_mx], __float_as_uint(m));
-    pm_bin(pm_grid(mcur, tb.rmax), on, s, xn, C, A.ncell, A.nrank);
+    cells::bin<true>(cells::grid_of(mcur, tb.rmax), on, s, xn, C, A.ncell, A.nrank);
 }
 
 // Slot-order [3][n] -> original order [n][3].
@@ -500,7 +310,7 @@ bool pm_alloc(T** p, size_t count) {
 ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     PaperMode* m = c->pm;
     const int n = (int)c->n, blocks = (n + kB - 1) / kB;
-    const PmCells C = pm_cells(m->cells);
+    const cells::Work C = cells::work_at(m->cells);
     if (!c->pos2) {
         if (!(pm_alloc(&c->pos2, (size_t)n) && pm_alloc(&c->lo2, (size_t)n) &&
               pm_alloc(&c->typ2, (size_t)n) && pm_alloc(&c->oid2, (size_t)n)))
@@ -510,13 +320,13 @@ ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     int* list = reinterpret_cast<int*>(c->sb.tmp4);       // lists and sorted cells
     if (!binned) {
         m->turn = 0;
-        PM_LAUNCH(k_pm_absmax, dim3(64), dim3(kB), s, c->pos, n, c->sb.bounds_part);
+        HIP_TRY(cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s));
         PM_LAUNCH(k_pm_bin, dim3(blocks), dim3(kB), s, c->pos, c->lo, n, c->sb.bounds_part,
                   m->tab.rmax, C, cell, cell + n);
+        HIP_TRY(cells::launch_coarse(C, s));
     }
-    PM_LAUNCH(k_pm_scan, dim3(kNC / kCoarse), dim3(256), s, C, m->turn % 3, (m->turn + 2) % 3,
-              m->tab.rmax, n, c->st, adv_dt);
-    PM_LAUNCH(k_pm_list, dim3(blocks), dim3(kB), s, cell, cell + n, n, C, list);
+    HIP_TRY(cells::launch_scan(C, m->turn % 3, (m->turn + 2) % 3, m->tab.rmax, c->st, adv_dt, s));
+    HIP_TRY(cells::launch_list(cell, cell + n, n, C, list, s));
     PmPlace A{};
     A.pos = c->pos;
     A.lo = c->lo;
@@ -553,7 +363,7 @@ PmStep pm_launch(ld_ctx* c) {
     A.typ = c->typ;
     A.oid = c->oid;
     A.cell = reinterpret_cast<int*>(c->sb.tmp4) + c->n;
-    A.first = pm_cells(m->cells).first;
+    A.first = cells::work_at(m->cells).first;
     A.n = (int)c->n;
     A.grid_mx = m->turn % 3;
     A.cur_mx = (m->turn + 1) % 3;
@@ -566,7 +376,7 @@ void pm_run_as(const PmStep& A, ld_ctx* c, hipStream_t s) {
     constexpr int part = kPmBlock<LANES> / LANES;
     hipLaunchKernelGGL((k_pm_step<STEP, LANES>), dim3((A.n + part - 1) / part),
                        dim3(kPmBlock<LANES>), 0, s, A, c->pm->tab, c->ext,
-                       pm_cells(c->pm->cells));
+                       cells::work_at(c->pm->cells));
 }
 
 template <bool STEP>
@@ -676,8 +486,7 @@ ld_status ld_paper_enable(ld_ctx* c, const ld_paper_config* cfg) {
     tb.kick = cfg->kick;
     const size_t N = (size_t)c->n;
     bool ok = pm_alloc(&m->v, 3 * N) && pm_alloc(&m->v2, 3 * N) && pm_alloc(&m->F, 3 * N) &&
-              pm_alloc(&m->cells, kCellInts) &&
-              hipMemset(m->cells, 0, sizeof(int) * kCellInts) == hipSuccess;
+              pm_alloc(&m->cells, cells::kWorkInts);
     if (ok) {
         std::vector<double> zero(3 * N, 0.0);
         ok = hipMemcpy(m->v, zero.data(), sizeof(double) * 3 * N, hipMemcpyHostToDevice) ==

@@ -108,7 +108,16 @@ __global__ __launch_bounds__(1024) void k_rowreduce(const double* __restrict__ i
     __shared__ double red[1024];
     const double* row = in + (size_t)blockIdx.x * (size_t)n;
     double acc = OP == 0 ? 0.0 : (OP == 1 ? -INFINITY : INFINITY);
-    for (int k = threadIdx.x; k < n; k += 1024) acc = red_op<OP>(acc, row[k]);
+    // eight loads in flight; the terms join in the order of one
+    int k = threadIdx.x;
+    for (; k + 7 * 1024 < n; k += 8 * 1024) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = row[k + u * 1024];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = red_op<OP>(acc, v[u]);
+    }
+    for (; k < n; k += 1024) acc = red_op<OP>(acc, row[k]);
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 512; w >= 1; w >>= 1) {
