@@ -1047,9 +1047,7 @@ ld_status ld_rdf(ld_ctx* c, double r_max, int32_t n_bins, double V, int32_t cent
         HIP_TRY(ld::launch_moments(c->pos, c->lo, (int)N, c->work, mom, c->stream));
         HIP_TRY(hipMemcpyAsync(dctr, mom, sizeof(double) * 3, hipMemcpyDeviceToDevice, c->stream));
     } else {
-        const double z[4] = {0.0, 0.0, 0.0, 0.0};
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        HIP_TRY(hipMemcpy(dctr, z, sizeof z, hipMemcpyHostToDevice));
+        HIP_TRY(ld::launch_zero(reinterpret_cast<unsigned long long*>(dctr), 4, c->stream));
     }
     // pair counts through the cell sort when r_max is short against the
     // droplet, else by the all-pairs histogram (same bins either way)
@@ -1062,13 +1060,10 @@ ld_status ld_rdf(ld_ctx* c, double r_max, int32_t n_bins, double V, int32_t cent
     else
         HIP_TRY(ld::launch_rdf(c->pos, c->lo, (int)N, r_max, n_bins, dctr, dcnt, dcc, c->stream));
     std::vector<unsigned long long> hc(n_bins), hcc(n_bins);
-    HIP_TRY(hipMemcpyAsync(hc.data(), dcnt, sizeof(unsigned long long) * n_bins,
-                           hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(hcc.data(), dcc, sizeof(unsigned long long) * n_bins,
-                           hipMemcpyDeviceToHost, c->stream));
     ld::DevState ds;
-    HIP_TRY(hipMemcpyAsync(&ds, c->st, sizeof ds, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(copy_out(c->stage, hc.data(), dcnt, sizeof(unsigned long long) * n_bins, c->stream));
+    HIP_TRY(copy_out(c->stage, hcc.data(), dcc, sizeof(unsigned long long) * n_bins, c->stream));
+    HIP_TRY(copy_out(c->stage, &ds, c->st, sizeof ds, c->stream));
     if (!(V > 0.0)) {
         const double Rn = ld::radius_at(c->R, ds.t);
         V = 4.0 / 3.0 * M_PI * Rn * Rn * Rn;
@@ -1116,9 +1111,7 @@ ld_status ld_cbar_type(ld_ctx* c, int32_t type, double r_max, int32_t n_bins, do
         HIP_TRY(ld::launch_moments(c->pos, c->lo, (int)N, c->work, mom, c->stream));
         HIP_TRY(hipMemcpyAsync(dctr, mom, sizeof(double) * 3, hipMemcpyDeviceToDevice, c->stream));
     } else {
-        const double z[4] = {0.0, 0.0, 0.0, 0.0};
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        HIP_TRY(hipMemcpy(dctr, z, sizeof z, hipMemcpyHostToDevice));
+        HIP_TRY(ld::launch_zero(reinterpret_cast<unsigned long long*>(dctr), 4, c->stream));
     }
     HIP_TRY(ld::launch_centre_hist(c->pos, c->lo, c->typ, type, (int)N, r_max, n_bins, dctr, dcc,
                                    c->stream));
@@ -1157,39 +1150,43 @@ ld_status ld_fractal(ld_ctx* c, double k_f, double d, double eps0, int32_t max_s
     if (!(k_f > 0.0)) return fail(LD_EINVAL, "k_f must be positive");
     if (max_scales < 0 || max_scales > 40) return fail(LD_EINVAL, "max_scales in [0, 40]");
     const size_t N = (size_t)c->n;
-    // number-mean diameter and smallest diameter from the type histogram
-    if (!(d > 0.0) || !(eps0 > 0.0)) {
-        std::vector<int> ty(N);
-        HIP_TRY(hipMemcpyAsync(ty.data(), c->typ, sizeof(int) * N, hipMemcpyDeviceToHost,
-                               c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        double sum = 0.0, smin = INFINITY;
-        for (size_t s = 0; s < N; ++s) {
-            sum += c->p.sigma[ty[s]];
-            smin = std::fmin(smin, c->p.sigma[ty[s]]);
+    // scratch: two box tables of at least 2 N entries, representatives, counts
+    size_t entries = 4;
+    while (entries < 2 * N) entries *= 2;
+    unsigned long long* table[2] = {reinterpret_cast<unsigned long long*>(c->work),
+                                    reinterpret_cast<unsigned long long*>(c->work) + entries};
+    unsigned char* rep = reinterpret_cast<unsigned char*>(c->work + 8 * N);
+    int* cnt = reinterpret_cast<int*>(c->work + 10 * N);
+    const int parts = (int)std::min<size_t>((N + 255) / 256, 512);
+    std::vector<double> st((ld::kFracWords + 1) * ld::kFracParts);
+    HIP_TRY(ld::launch_frac_stats(c->pos, c->lo, c->typ, (int)N, c->aux, table[0], entries,
+                                  c->stream));
+    HIP_TRY(copy_out(c->stage, st.data(), c->aux, sizeof(double) * st.size(), c->stream));
+    double hlo[3] = {INFINITY, INFINITY, INFINITY}, hhi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    double s2 = 0.0, ntype[ld::kMaxTypes] = {};
+    for (int b = 0; b < ld::kFracParts; ++b) {
+        const double* w = st.data() + (size_t)b * ld::kFracWords;
+        for (int a = 0; a < 3; ++a) {
+            hlo[a] = std::fmin(hlo[a], w[3 + a]);
+            hhi[a] = std::fmax(hhi[a], w[6 + a]);
         }
-        if (!(d > 0.0)) d = sum / (double)N;
-        if (!(eps0 > 0.0)) eps0 = smin;
+        for (int t = 0; t < ld::kMaxTypes; ++t) ntype[t] += w[9 + t];
+        s2 += st[(size_t)ld::kFracParts * ld::kFracWords + b];
     }
-    double* mom = c->aux;
-    double* lo3 = mom + 8;
-    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(lo3 + 4);
-    HIP_TRY(ld::launch_moments(c->pos, c->lo, (int)N, c->work, mom, c->stream));
-    double hm[4];
-    HIP_TRY(copy_out(hm, mom, sizeof hm, c->stream));
-    const double Rg = hm[3];
+    // number-mean diameter and smallest diameter from the type counts
+    double sum = 0.0, smin = INFINITY;
+    for (int t = 0; t < c->p.n_types; ++t) {
+        sum += ntype[t] * c->p.sigma[t];
+        if (ntype[t] > 0.0) smin = std::fmin(smin, c->p.sigma[t]);
+    }
+    if (!(d > 0.0)) d = sum / (double)N;
+    if (!(eps0 > 0.0)) eps0 = smin;
+    const double Rg = std::sqrt(s2 / (double)N);
     out[0] = Rg;
     out[1] = std::log((double)N / k_f) / std::log(2.0 * Rg / d);
-    HIP_TRY(ld::launch_pos_rows(c->pos, c->lo, (int)N, c->work, c->stream));
-    HIP_TRY(ld::launch_rowmin(c->work, 3, (int)N, lo3, c->stream));
-    // the extents decide, per scale, whether the box indices fit 32 bits
-    double* hi3 = reinterpret_cast<double*>(cnt + 1);
-    HIP_TRY(ld::launch_rowmax(c->work, 3, (int)N, hi3, c->stream));
-    double hlo[3], hhi[3];
-    HIP_TRY(copy_out(hlo, lo3, sizeof hlo, c->stream));
-    HIP_TRY(copy_out(hhi, hi3, sizeof hhi, c->stream));
     std::vector<double> lx, ly;
     int K = 0;
+    bool fitted = true;
     for (int k = 0; k < max_scales; ++k) {
         const double e = eps0 * std::ldexp(1.0, k);
         if (e > Rg) break;
@@ -1199,24 +1196,25 @@ ld_status ld_fractal(ld_ctx* c, double k_f, double d, double eps0, int32_t max_s
             nb[a] = std::floor((hhi[a] - hlo[a]) / e) + 2.0;
             prod *= nb[a];
         }
-        if (prod <= 4294967296.0) {
-            int bits = 1;
-            while (bits < 32 && std::ldexp(1.0, bits) < prod) ++bits;
-            HIP_TRY(ld::launch_boxcount_radix(c->pos, c->lo, (int)N, lo3, e,
-                                              (unsigned long long)nb[1],
-                                              (unsigned long long)nb[2], bits, c->sb.keys,
-                                              reinterpret_cast<unsigned long long*>(c->sb.tmp4),
-                                              c->sb.hist, cnt, c->stream));
-        } else {
-            HIP_TRY(ld::launch_boxcount(c->pos, c->lo, (int)N, lo3, e, c->sb.keys,
-                                        c->sb.n_pow2, cnt, c->stream));
-        }
-        unsigned long long hc = 0;
-        HIP_TRY(copy_out(&hc, cnt, sizeof hc, c->stream));
-        if (box_counts) box_counts[k] = (int64_t)hc;
+        // beyond 64 bits of box index 21 bits an axis are kept, which do not nest
+        const bool fits = prod <= 0x1p63, anew = k == 0 || !fits || !fitted;
+        fitted = fits;
+        HIP_TRY(ld::launch_box_count(c->pos, c->lo, (int)N, anew, hlo, e,
+                                     fits ? (unsigned long long)nb[1] : 0ull,
+                                     fits ? (unsigned long long)nb[2] : 0ull, table[k % 2],
+                                     table[(k + 1) % 2], entries, rep, cnt + (size_t)k * parts,
+                                     parts, c->stream));
         lx.push_back(std::log(e));
-        ly.push_back(std::log((double)hc));
         K = k + 1;
+    }
+    std::vector<int> hc((size_t)K * parts);
+    if (K > 0)
+        HIP_TRY(copy_out(c->stage, hc.data(), cnt, sizeof(int) * hc.size(), c->stream));
+    for (int k = 0; k < K; ++k) {
+        int64_t boxes = 0;
+        for (int b = 0; b < parts; ++b) boxes += hc[(size_t)k * parts + b];
+        if (box_counts) box_counts[k] = boxes;
+        ly.push_back(std::log((double)boxes));
     }
     out[3] = (double)K;
     if (K >= 3) {

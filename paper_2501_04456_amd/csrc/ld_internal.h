@@ -185,12 +185,8 @@ hipError_t launch_gather(const float4* pos, const float4* lo, const int* typ, co
 
 // Deterministic FP64 sum of m rows of length n: out[r] = sum_s in[r*n + s].
 hipError_t launch_rowsum(const double* in, int rows, int n, double* out, hipStream_t s);
-hipError_t launch_rowmin(const double* in, int rows, int n, double* out, hipStream_t s);
-hipError_t launch_rowmax(const double* in, int rows, int n, double* out, hipStream_t s);
 
 // Positions hi + lo as FP64 rows work[0..2][n].
-hipError_t launch_pos_rows(const float4* pos, const float4* lo, int n, double* work,
-                           hipStream_t s);
 
 // Replace the charge word of every slot: pos[s].w = qhat[oid[s]].
 hipError_t launch_set_charge(float4* pos, const int* oid, const float* qhat, int n,
@@ -349,16 +345,23 @@ hipError_t launch_centre_hist(const float4* pos, const float4* lo, const int* ty
                               unsigned long long* ccounts, hipStream_t s);
 hipError_t launch_moments(const float4* pos, const float4* lo, int n, double* work,
                           double* out4, hipStream_t s);
-hipError_t launch_boxcount(const float4* pos, const float4* lo, int n, const double* lo3,
-                           double eps, unsigned long long* keys, int n_pow2,
-                           unsigned long long* count, hipStream_t s);
-// Box counting by compact box indices below 2^bits <= 2^32 (ny, nz boxes
-// along y and z) and the radix sort; keys and tmp hold n keys each, hist as
-// for the radix sort.
-hipError_t launch_boxcount_radix(const float4* pos, const float4* lo, int n, const double* lo3,
-                                 double eps, unsigned long long ny, unsigned long long nz,
-                                 int bits, unsigned long long* keys, unsigned long long* tmp,
-                                 unsigned* hist, unsigned long long* count, hipStream_t s);
+hipError_t launch_zero(unsigned long long* p, int m, hipStream_t s);
+// The fractal statistics: kFracParts partials of kFracWords doubles (sum[3],
+// smallest[3], largest[3], count per type), then kFracParts partial sums of the
+// squared distance from the centre of mass; empties the box table.
+constexpr int kFracParts = 256, kFracWords = 9 + kMaxTypes;
+hipError_t launch_frac_stats(const float4* pos, const float4* lo, const int* typ, int n,
+                             double* part, unsigned long long* table, size_t entries,
+                             hipStream_t s);
+// Boxes of side eps from lo3 that hold a particle, as `parts` partial counts.
+// entries: a power of two >= 2 n; first: look at every particle, else at those
+// whose rep[] is set (the scale of half the side set it).  ny, nz: boxes along
+// y and z, 0 where the box indices do not fit 64 bits (21 bits an axis then).
+hipError_t launch_box_count(const float4* pos, const float4* lo, int n, bool first,
+                            const double lo3[3], double eps, unsigned long long ny,
+                            unsigned long long nz, unsigned long long* table,
+                            unsigned long long* next, size_t entries, unsigned char* rep,
+                            int* count, int parts, hipStream_t s);
 
 struct FarField;
 struct PaperMode;

@@ -123,71 +123,140 @@ __global__ void k_moments_finish(const double* sums, const double* s2, int n, do
     out4[3] = sqrt(s2[0] / n);
 }
 
-__global__ __launch_bounds__(256) void k_box_keys(const float4* __restrict__ pos,
-                                                  const float4* __restrict__ lo, int n,
-                                                  int n_pow2, const double* __restrict__ lo3,
-                                                  double eps, unsigned long long* keys) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= n_pow2) return;
-    if (s >= n) {
-        keys[s] = ~0ull;
-        return;
+// Sums, extents and type counts of the positions, kFracParts partials of
+// kFracWords doubles: sum[3], smallest[3], largest[3], count[kMaxTypes].
+__global__ __launch_bounds__(256) void k_frac_stats(const float4* __restrict__ pos,
+                                                    const float4* __restrict__ lo,
+                                                    const int* __restrict__ typ, int n,
+                                                    double* part) {
+    __shared__ double red[kFracWords][4];
+    const int t = threadIdx.x, lane = t % 64;
+    double v[kFracWords];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        v[c] = 0.0;
+        v[3 + c] = INFINITY;
+        v[6 + c] = -INFINITY;
     }
-    double x[3];
-    full_pos(pos, lo, s, x);
-    const unsigned long long ix = (unsigned long long)floor((x[0] - lo3[0]) / eps);
-    const unsigned long long iy = (unsigned long long)floor((x[1] - lo3[1]) / eps);
-    const unsigned long long iz = (unsigned long long)floor((x[2] - lo3[2]) / eps);
-    keys[s] = (ix << 42) | (iy << 21) | iz;
+#pragma unroll
+    for (int q = 0; q < kMaxTypes; ++q) v[9 + q] = 0.0;
+    for (int s = blockIdx.x * 256 + t; s < n; s += kFracParts * 256) {
+        double x[3];
+        full_pos(pos, lo, s, x);
+        const int ty = typ[s];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            v[c] += x[c];
+            v[3 + c] = fmin(v[3 + c], x[c]);
+            v[6 + c] = fmax(v[6 + c], x[c]);
+        }
+#pragma unroll
+        for (int q = 0; q < kMaxTypes; ++q) v[9 + q] += ty == q ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kFracWords; ++k) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const double y = __shfl_xor(v[k], o);
+            v[k] = k < 3 || k >= 9 ? v[k] + y : (k < 6 ? fmin(v[k], y) : fmax(v[k], y));
+        }
+        if (lane == 0) red[k][t / 64] = v[k];
+    }
+    __syncthreads();
+    if (t < kFracWords) {
+        double y = red[t][0];
+        for (int w = 1; w < 4; ++w)
+            y = t < 3 || t >= 9 ? y + red[t][w]
+                                : (t < 6 ? fmin(y, red[t][w]) : fmax(y, red[t][w]));
+        part[blockIdx.x * kFracWords + t] = y;
+    }
 }
 
-// Compact box keys: (box index << 32) | slot, box index = (ix ny + iy) nz + iz
-// with ix, iy, iz formed exactly as in k_box_keys; the caller guarantees
-// nx ny nz <= 2^32.
-__global__ __launch_bounds__(256) void k_box_keys32(const float4* __restrict__ pos,
-                                                    const float4* __restrict__ lo, int n,
-                                                    const double* __restrict__ lo3, double eps,
-                                                    unsigned long long ny, unsigned long long nz,
-                                                    unsigned long long* keys) {
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= n) return;
-    double x[3];
-    full_pos(pos, lo, s, x);
-    const unsigned long long ix = (unsigned long long)floor((x[0] - lo3[0]) / eps);
-    const unsigned long long iy = (unsigned long long)floor((x[1] - lo3[1]) / eps);
-    const unsigned long long iz = (unsigned long long)floor((x[2] - lo3[2]) / eps);
-    keys[s] = (((ix * ny + iy) * nz + iz) << 32) | (unsigned long long)(unsigned)s;
-}
-
-// Distinct high words of keys sorted by them.
-__global__ __launch_bounds__(256) void k_count_distinct_high(const unsigned long long* keys, int n,
-                                                             unsigned long long* count) {
-    __shared__ unsigned int red[256];
-    unsigned int c = 0;
-    for (int s = blockIdx.x * 256 + threadIdx.x; s < n; s += gridDim.x * 256)
-        c += (s == 0 || (keys[s] >> 32) != (keys[s - 1] >> 32)) ? 1u : 0u;
-    red[threadIdx.x] = c;
+// Squared distances from the centre of mass (every workgroup adds the partial
+// sums itself, in one order), kFracParts partials; empties the first table.
+__global__ __launch_bounds__(256) void k_frac_dev2(const float4* __restrict__ pos,
+                                                   const float4* __restrict__ lo, int n,
+                                                   const double* __restrict__ part, double* dev2,
+                                                   unsigned long long* table, size_t entries) {
+#pragma clang fp contract(off)
+    static_assert(kFracParts == 256, "one partial per thread");
+    __shared__ double red[3][256];
+    const int t = threadIdx.x;
+    for (int c = 0; c < 3; ++c) red[c][t] = part[t * kFracWords + c];
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        if (t < w)
+            for (int c = 0; c < 3; ++c) red[c][t] += red[c][t + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicAdd(count, (unsigned long long)red[0]);
-}
-
-__global__ __launch_bounds__(256) void k_count_distinct(const unsigned long long* keys, int n,
-                                                        unsigned long long* count) {
-    __shared__ unsigned int red[256];
-    unsigned int c = 0;
-    for (int s = blockIdx.x * 256 + threadIdx.x; s < n; s += gridDim.x * 256)
-        c += (s == 0 || keys[s] != keys[s - 1]) ? 1u : 0u;
-    red[threadIdx.x] = c;
+    const double c0 = red[0][0] / n, c1 = red[1][0] / n, c2 = red[2][0] / n;
+    __syncthreads();
+    double v = 0.0;
+    for (int s = blockIdx.x * 256 + t; s < n; s += kFracParts * 256) {
+        double x[3];
+        full_pos(pos, lo, s, x);
+        const double dx = c0 - x[0], dy = c1 - x[1], dz = c2 - x[2];
+        v += dx * dx + dy * dy + dz * dz;
+    }
+    for (size_t k = (size_t)blockIdx.x * 256 + t; k < entries; k += kFracParts * 256)
+        table[k] = ~0ull;
+    red[0][t] = v;
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        if (t < w) red[0][t] += red[0][t + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) atomicAdd(count, (unsigned long long)red[0]);
+    if (t == 0) dev2[blockIdx.x] = red[0][0];
+}
+
+// Boxes of side eps that hold a particle: each particle looks its box up in a
+// hash table of at least twice n entries (linear probing), and whoever enters
+// it is the box's only representative.  Boxes of twice the side hold whole
+// boxes of this one (the same FP64 quotient, halved exactly), so only the
+// representatives, one flag a slot, look on at the next scale.  Empties the
+// table of the next scale.  Bound by one random table access a particle at
+// the finest scales: the eight scales of 250 000 NPs 640 us with a sort of box
+// keys for each, 160 so.
+__global__ __launch_bounds__(256) void k_box_count(const float4* __restrict__ pos,
+                                                   const float4* __restrict__ lo, int n, int first,
+                                                   double lo0, double lo1, double lo2, double eps,
+                                                   unsigned long long ny, unsigned long long nz,
+                                                   unsigned long long* table,
+                                                   unsigned long long* next, size_t entries,
+                                                   unsigned char* rep, int* count) {
+    __shared__ int red[4];
+    int c = 0;
+    const size_t mask = entries - 1;
+    for (int s = blockIdx.x * 256 + threadIdx.x; s < n; s += gridDim.x * 256) {
+        if (!first && !rep[s]) continue;
+        double x[3];
+        full_pos(pos, lo, s, x);
+        const unsigned long long ix = (unsigned long long)floor((x[0] - lo0) / eps);
+        const unsigned long long iy = (unsigned long long)floor((x[1] - lo1) / eps);
+        const unsigned long long iz = (unsigned long long)floor((x[2] - lo2) / eps);
+        const unsigned long long key = ny ? (ix * ny + iy) * nz + iz : (ix << 42) | (iy << 21) | iz;
+        unsigned long long h = key * 0x9E3779B97F4A7C15ull;
+        h ^= h >> 32;
+        bool mine = false;
+        for (size_t probe = 0; probe < entries; ++probe) {
+            unsigned long long* e = table + ((h + probe) & mask);
+            unsigned long long old = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (old == ~0ull) old = atomicCAS(e, ~0ull, key);
+            if (old == ~0ull || old == key) {
+                mine = old == ~0ull;
+                break;
+            }
+        }
+        rep[s] = mine ? 1 : 0;
+        c += mine ? 1 : 0;
+    }
+    for (size_t k = (size_t)blockIdx.x * 256 + threadIdx.x; k < entries; k += gridDim.x * 256)
+        next[k] = ~0ull;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) count[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
 __global__ __launch_bounds__(256) void k_set_charge(float4* pos, const int* __restrict__ oid,
@@ -223,12 +292,6 @@ hipError_t launch_centre_hist(const float4* pos, const float4* lo, const int* ty
     return hipGetLastError();
 }
 
-hipError_t launch_pos_rows(const float4* pos, const float4* lo, int n, double* work,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(k_pos_rows, dim3((n + 255) / 256), dim3(256), 0, s, pos, lo, n, work);
-    return hipGetLastError();
-}
-
 hipError_t launch_set_charge(float4* pos, const int* oid, const float* qhat, int n,
                              hipStream_t s) {
     hipLaunchKernelGGL(k_set_charge, dim3((n + 255) / 256), dim3(256), 0, s, pos, oid, qhat, n);
@@ -250,29 +313,27 @@ hipError_t launch_moments(const float4* pos, const float4* lo, int n, double* wo
     return hipGetLastError();
 }
 
-hipError_t launch_boxcount_radix(const float4* pos, const float4* lo, int n, const double* lo3,
-                                 double eps, unsigned long long ny, unsigned long long nz,
-                                 int bits, unsigned long long* keys, unsigned long long* tmp,
-                                 unsigned* hist, unsigned long long* count, hipStream_t s) {
-    hipLaunchKernelGGL(k_box_keys32, dim3((n + 255) / 256), dim3(256), 0, s, pos, lo, n, lo3, eps,
-                       ny, nz, keys);
-    unsigned long long* sorted = nullptr;
-    hipError_t e = launch_radix_by_high(keys, tmp, n, bits, hist, s, false, &sorted);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, count, 1);
-    hipLaunchKernelGGL(k_count_distinct_high, dim3(64), dim3(256), 0, s, sorted, n, count);
+hipError_t launch_zero(unsigned long long* p, int m, hipStream_t s) {
+    hipLaunchKernelGGL(k_zero_u64, dim3((m + 255) / 256), dim3(256), 0, s, p, m);
     return hipGetLastError();
 }
 
-hipError_t launch_boxcount(const float4* pos, const float4* lo, int n, const double* lo3,
-                           double eps, unsigned long long* keys, int n_pow2,
-                           unsigned long long* count, hipStream_t s) {
-    hipLaunchKernelGGL(k_box_keys, dim3((n_pow2 + 255) / 256), dim3(256), 0, s, pos, lo, n,
-                       n_pow2, lo3, eps, keys);
-    hipError_t e = launch_bitonic(keys, n_pow2, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, count, 1);
-    hipLaunchKernelGGL(k_count_distinct, dim3(64), dim3(256), 0, s, keys, n, count);
+hipError_t launch_frac_stats(const float4* pos, const float4* lo, const int* typ, int n,
+                             double* part, unsigned long long* table, size_t entries,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_frac_stats, dim3(kFracParts), dim3(256), 0, s, pos, lo, typ, n, part);
+    hipLaunchKernelGGL(k_frac_dev2, dim3(kFracParts), dim3(256), 0, s, pos, lo, n, part,
+                       part + kFracParts * kFracWords, table, entries);
+    return hipGetLastError();
+}
+
+hipError_t launch_box_count(const float4* pos, const float4* lo, int n, bool first,
+                            const double lo3[3], double eps, unsigned long long ny,
+                            unsigned long long nz, unsigned long long* table,
+                            unsigned long long* next, size_t entries, unsigned char* rep,
+                            int* count, int parts, hipStream_t s) {
+    hipLaunchKernelGGL(k_box_count, dim3(parts), dim3(256), 0, s, pos, lo, n, first ? 1 : 0,
+                       lo3[0], lo3[1], lo3[2], eps, ny, nz, table, next, entries, rep, count);
     return hipGetLastError();
 }
 

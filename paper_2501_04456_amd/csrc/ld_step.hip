@@ -94,12 +94,11 @@ __global__ __launch_bounds__(kBlock) void k_gather(
 }
 
 // One workgroup per row; each lane reduces a fixed strided subset in order,
-// then a fixed tree: the result depends only on n.  OP: 0 sum, 1 max, 2 min.
+// then a fixed tree: the result depends only on n.  OP: 0 sum, 1 max.
 template <int OP>
 __device__ __forceinline__ double red_op(double a, double b) {
     if constexpr (OP == 0) return a + b;
-    else if constexpr (OP == 1) return fmax(a, b);
-    else return fmin(a, b);
+    else return fmax(a, b);
 }
 
 template <int OP>
@@ -107,7 +106,7 @@ __global__ __launch_bounds__(1024) void k_rowreduce(const double* __restrict__ i
                                                     double* out) {
     __shared__ double red[1024];
     const double* row = in + (size_t)blockIdx.x * (size_t)n;
-    double acc = OP == 0 ? 0.0 : (OP == 1 ? -INFINITY : INFINITY);
+    double acc = OP == 0 ? 0.0 : -INFINITY;
     // eight loads in flight; the terms join in the order of one
     int k = threadIdx.x;
     for (; k + 7 * 1024 < n; k += 8 * 1024) {
@@ -282,16 +281,6 @@ hipError_t launch_gather(const float4* pos, const float4* lo, const int* typ, co
 
 hipError_t launch_rowsum(const double* in, int rows, int n, double* out, hipStream_t s) {
     hipLaunchKernelGGL(k_rowreduce<0>, dim3(rows), dim3(1024), 0, s, in, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_rowmin(const double* in, int rows, int n, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_rowreduce<2>, dim3(rows), dim3(1024), 0, s, in, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_rowmax(const double* in, int rows, int n, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_rowreduce<1>, dim3(rows), dim3(1024), 0, s, in, n, out);
     return hipGetLastError();
 }
 
