@@ -27,13 +27,13 @@ ld_status fail(ld_status s, const char* fmt, ...);
 bool is_device_ptr(const void* p);
 hipError_t copy_in(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s);
-constexpr size_t kReadSlot = 512 << 10, kBatchSlot = 2 << 20;
+constexpr size_t kReadSlot = 512 << 10, kBatchSlot = 1 << 20;
 
 // A stage whose slots together hold about `bytes`, each at most max_slot (read
 // back best in pieces of 512 KiB, which the host still finds in its cache: 250
 // 000 positions 205 us, with 1 or 2 MiB 245; batches uploaded best in pieces of
-// 2 MiB: 16 MB with 0.5, 1, 2 MiB 690, 595, 570 us a training pass, 690 with a
-// pageable copy into a buffer allocated for it).  Without
+// 1 MiB: training passes of 16 MB with 0.5, 1, 2 MiB 760, 640, 780 us, 800 with
+// a pageable copy into a buffer allocated for it).  Without
 // pinned memory it stays empty and copies are not staged.
 void stage_init(HostStage& h, size_t bytes, size_t max_slot);
 void stage_free(HostStage& h);
