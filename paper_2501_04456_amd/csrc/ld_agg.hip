@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kB) void k_ag_hook(AgSorted A, AgTable tb, double r
     // the oracle's operand order, no fused multiply-add: a pair within an ulp
     // of the contact distance lands on the same side in both
 #pragma clang fp contract(off)
-    constexpr int kList = 8;
+    constexpr int kList = 16;
     __shared__ int list[kList][kB];
     const int k = blockIdx.x * (kB / LANES) + threadIdx.x / LANES;
     const bool live = k < A.count[0];
@@ -402,7 +402,7 @@ template <int LANES>
 __global__ __launch_bounds__(kB) void k_ag_rdf(AgSorted A, double r_max, int n_bins, double dr,
                                                unsigned long long* counts) {
 #pragma clang fp contract(off)
-    constexpr int kList = LANES == 1 ? 16 : 8;
+    constexpr int kList = 16;
     __shared__ unsigned int hist[kRdfMaxBins];
     __shared__ int list[kList][kB];
     for (int b = threadIdx.x; b < n_bins; b += kB) hist[b] = 0u;

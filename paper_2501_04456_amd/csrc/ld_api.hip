@@ -1158,7 +1158,7 @@ ld_status ld_fractal(ld_ctx* c, double k_f, double d, double eps0, int32_t max_s
                                     reinterpret_cast<unsigned long long*>(c->work) + entries};
     unsigned char* rep = reinterpret_cast<unsigned char*>(c->work + 8 * N);
     int* cnt = reinterpret_cast<int*>(c->work + 10 * N);
-    const int parts = (int)std::min<size_t>((N + 255) / 256, 512);
+    const int parts = (int)std::min<size_t>((N + 255) / 256, 1024);
     std::vector<double> st((ld::kFracWords + 1) * ld::kFracParts);
     HIP_TRY(ld::launch_frac_stats(c->pos, c->lo, c->typ, (int)N, c->aux, table[0], entries,
                                   c->stream));

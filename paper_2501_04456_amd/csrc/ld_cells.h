@@ -141,20 +141,34 @@ __device__ __forceinline__ void walk(const float4* __restrict__ pos,
             if (k < cnt) eval(list[k][t]);
         cnt = 0;
     };
+    auto meet = [&](int j, bool valid, const float4& hj) {
+        const float dx = hj.x - hi.x, dy = hj.y - hi.y, dz = hj.z - hi.z;
+        if (valid && j != i && fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < screen) list[cnt++][t] = j;
+    };
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r0[k] = (HALF ? max(r0[k], i + 1) : r0[k]) + sub;
+    if constexpr (LANES > 1) {
+        // every row's first LANES candidates in flight together, which few
+        // rows outlast; a list has room for nine
+        static_assert(LIST >= 9 + kWin, "room for the first candidates");
+        float4 hq[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) hq[k] = pos[r0[k] < r1[k] ? r0[k] : 0];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            meet(r0[k], r0[k] < r1[k], hq[k]);
+            r0[k] += LANES;
+        }
+        if (__any(cnt > LIST - kWin)) flush();
+    }
 #pragma unroll
     for (int k = 0; k < 9; ++k)
-        for (int j = (HALF ? max(r0[k], i + 1) : r0[k]) + sub; __any(j < r1[k]);
-             j += kWin * LANES) {
+        for (int j = r0[k]; __any(j < r1[k]); j += kWin * LANES) {
             float4 hq[kWin];                           // in flight together
 #pragma unroll
             for (int u = 0; u < kWin; ++u) hq[u] = pos[j + u * LANES < r1[k] ? j + u * LANES : 0];
 #pragma unroll
-            for (int u = 0; u < kWin; ++u) {
-                const int ju = j + u * LANES;
-                const float dx = hq[u].x - hi.x, dy = hq[u].y - hi.y, dz = hq[u].z - hi.z;
-                if (ju < r1[k] && ju != i && fmaf(dz, dz, fmaf(dy, dy, dx * dx)) < screen)
-                    list[cnt++][t] = ju;
-            }
+            for (int u = 0; u < kWin; ++u) meet(j + u * LANES, j + u * LANES < r1[k], hq[u]);
             if (__any(cnt > LIST - kWin)) flush();
         }
     flush();

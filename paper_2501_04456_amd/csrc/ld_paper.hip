@@ -56,7 +56,7 @@ struct PaperMode {
 namespace {
 
 constexpr int kB = 256;
-constexpr int kPmSplitN = 75000;        // particles from which a lane takes one by itself
+constexpr int kPmSplitN = 60000;        // particles from which a lane takes one by itself
 
 // Cells of all slots at positions no step of the same call has left (the
 // steps bin what they move themselves): mx[0] = mx[1] = the largest coordinate.
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kB) void k_pm_place(PmPlace A) {
 //
 // A step of 250 000: 138 us (a sort of 24-bit keys in three passes, forces a
 // lane per particle and an update, 15 launches) -> 65 us in four launches; of
-// 5000: 110 -> 26 us.
+// 5000: 110 -> 23 us.
 //
 // With STEP the slots are then moved into the second buffers (other
 // workgroups still read the first), and with bin counted into the next
@@ -141,7 +141,7 @@ template <bool STEP, int LANES>
 __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable tb, ExtParams P,
                                                              cells::Work C) {
     constexpr int kBlock = kPmBlock<LANES>, kPart = kBlock / LANES;
-    constexpr int kList = LANES == 1 ? 16 : 8;
+    constexpr int kList = 16;
     __shared__ double tr[kMaxTypes * kMaxTypes], ts[kMaxTypes * kMaxTypes],
         te[kMaxTypes * kMaxTypes], sF[3][LANES == 1 ? 1 : kPart];
     __shared__ int list[kList][kBlock];
@@ -381,11 +381,12 @@ void pm_run_as(const PmStep& A, ld_ctx* c, hipStream_t s) {
 
 template <bool STEP>
 ld_status pm_run(const PmStep& A, ld_ctx* c, hipStream_t s) {
-    // four lanes a particle while a lane each would leave the chip's wavefronts
-    // few and their chains long: a step of 5000 26 us (one lane 31), of 50 000
-    // 35 (38), of 100 000 49 (44), of 250 000 79 (65)
+    // eight lanes a particle while a lane each would leave the chip's wavefronts
+    // few and their chains long: a step of 5000 23 us (four lanes 25, one 32),
+    // of 25 000 28 (28, 36), of 50 000 35 (34, 38), of 100 000 50 (47, 45), of
+    // 250 000 97 (77, 65)
     if (A.n < kPmSplitN)
-        pm_run_as<STEP, 4>(A, c, s);
+        pm_run_as<STEP, 8>(A, c, s);
     else
         pm_run_as<STEP, 1>(A, c, s);
     HIP_TRY(hipGetLastError());

@@ -32,7 +32,7 @@ def stored_charge(w):
 
 
 @pytest.mark.parametrize("n,factor", [(2, 4.0), (65, 1e3), (1025, 1e3), (4097, 40.0),
-                                      (74999, 4.0), (75000, 9.0)])
+                                      (59999, 4.0), (60000, 4.0), (74999, 4.0), (75000, 9.0)])
 def test_forces(ld, orc, n, factor):
     w = W.config_large(n=n, seed=31)
     s = ld.System.from_workload(w)
