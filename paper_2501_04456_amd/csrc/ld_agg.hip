@@ -580,6 +580,17 @@ hipError_t ag_union(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bo
 }
 #undef AG_RUN
 
+// The statistics and, unless null, the labels: together where host labels fit.
+hipError_t ag_read(ld_ctx* c, void* res, const void* dres, size_t bytes, int32_t* labels,
+                   const int* dlabels) {
+    const size_t lbytes = labels ? sizeof(int32_t) * (size_t)c->n : 0;
+    if (labels && !host::is_device_ptr(labels))
+        return copy_out(c->stage, {{res, dres, bytes}, {labels, dlabels, lbytes}}, c->stream);
+    const hipError_t e = copy_out(c->stage, res, dres, bytes, c->stream);
+    return e != hipSuccess || !labels ? e
+                                      : copy_out(c->stage, labels, dlabels, lbytes, c->stream);
+}
+
 }  // namespace
 
 void ag_free(ld_ctx* c) {
@@ -645,8 +656,7 @@ ld_status ld_aggregates(ld_ctx* c, double contact_factor, int64_t stats[3], int3
     AgSorted A{};
     HIP_TRY(ag_union(c, b, tb, rc, false, 0.0, labels ? b.labels : nullptr, &A));
     AgRes res[4];
-    HIP_TRY(copy_out(c->stage, res, b.res, sizeof res, s));
-    if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
+    HIP_TRY(ag_read(c, res, b.res, sizeof res, labels, b.labels));
     if (res[3]) return fail(LD_EHIP, "contact-graph union did not settle within its bound");
     for (int k = 0; k < 3; ++k) stats[k] = (int64_t)res[k];
     return LD_OK;
@@ -681,8 +691,7 @@ ld_status ld_surface_fractal(ld_ctx* c, double R, double contact_factor, double 
     AG_LAUNCH(k_sf_sums, dim3(blocks), dim3(kB), s, A, b.root, b.minoid, b.res, tb, b.dpart);
     AG_LAUNCH(k_sf_theta, dim3(blocks), dim3(kB), s, A, b.root, b.minoid, b.res, b.dpart, tpart);
     std::vector<double> got(kResDoubles + 5 * (size_t)blocks);
-    HIP_TRY(copy_out(c->stage, got.data(), b.res, sizeof(double) * got.size(), s));
-    if (labels) HIP_TRY(copy_out(c->stage, labels, b.labels, sizeof(int32_t) * (size_t)n, s));
+    HIP_TRY(ag_read(c, got.data(), b.res, sizeof(double) * got.size(), labels, b.labels));
     AgRes res[4];
     std::memcpy(res, got.data(), sizeof res);
     const double* dp = got.data() + kResDoubles;

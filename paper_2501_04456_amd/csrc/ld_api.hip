@@ -105,7 +105,7 @@ hipError_t to_slot(void* dst, const void* src, size_t bytes, hipStream_t s) {
 
 hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
     if (!h.buf || is_device_ptr(dst)) return copy_out(dst, src, bytes, s);
-    struct Piece {
+    struct Part {
         char* slot;
         int k;
         size_t at, len;
@@ -114,7 +114,7 @@ hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipS
     hipError_t e = hipSuccess;
     while (e == hipSuccess && (at < bytes || done < issued)) {
         if (at < bytes && issued - done < HostStage::kSlots) {
-            Piece& p = q[issued % HostStage::kSlots];
+            Part& p = q[issued % HostStage::kSlots];
             p.at = at;
             p.len = std::min(h.slot, bytes - at);
             e = stage_take(h, &p.slot, &p.k);
@@ -124,13 +124,41 @@ hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipS
             at += p.len;
             ++issued;
         } else {
-            const Piece& p = q[done % HostStage::kSlots];
+            const Part& p = q[done % HostStage::kSlots];
             e = hipEventSynchronize(h.ev[p.k]);
             if (e == hipSuccess) std::memcpy((char*)dst + p.at, p.slot, p.len);
             ++done;
         }
     }
     return e;
+}
+
+hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream_t s) {
+    size_t total = 0;
+    for (const Piece& p : pieces) total += (p.bytes + 15) / 16 * 16;
+    hipError_t e = hipSuccess;
+    if (!h.buf || total > h.slot) {
+        for (const Piece& p : pieces)
+            if (e == hipSuccess) e = copy_out(h, p.dst, p.src, p.bytes, s);
+        return e;
+    }
+    char* slot;
+    int k;
+    e = stage_take(h, &slot, &k);
+    size_t at = 0;
+    for (const Piece& p : pieces) {
+        if (e == hipSuccess && p.bytes) e = to_slot(slot + at, p.src, p.bytes, s);
+        at += (p.bytes + 15) / 16 * 16;
+    }
+    if (e == hipSuccess) e = stage_mark(h, k, s);
+    if (e == hipSuccess) e = hipEventSynchronize(h.ev[k]);
+    if (e != hipSuccess) return e;
+    at = 0;
+    for (const Piece& p : pieces) {
+        std::memcpy(p.dst, slot + at, p.bytes);
+        at += (p.bytes + 15) / 16 * 16;
+    }
+    return hipSuccess;
 }
 
 hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
@@ -1062,9 +1090,9 @@ ld_status ld_rdf(ld_ctx* c, double r_max, int32_t n_bins, double V, int32_t cent
         HIP_TRY(ld::launch_rdf(c->pos, c->lo, (int)N, r_max, n_bins, dctr, dcnt, dcc, c->stream));
     std::vector<unsigned long long> hc(n_bins), hcc(n_bins);
     ld::DevState ds;
-    HIP_TRY(copy_out(c->stage, hc.data(), dcnt, sizeof(unsigned long long) * n_bins, c->stream));
-    HIP_TRY(copy_out(c->stage, hcc.data(), dcc, sizeof(unsigned long long) * n_bins, c->stream));
-    HIP_TRY(copy_out(c->stage, &ds, c->st, sizeof ds, c->stream));
+    const size_t bytes = sizeof(unsigned long long) * n_bins;
+    HIP_TRY(copy_out(c->stage, {{hc.data(), dcnt, bytes}, {hcc.data(), dcc, bytes},
+                                {&ds, c->st, sizeof ds}}, c->stream));
     if (!(V > 0.0)) {
         const double Rn = ld::radius_at(c->R, ds.t);
         V = 4.0 / 3.0 * M_PI * Rn * Rn * Rn;

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cstring>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -41,6 +42,13 @@ void stage_free(HostStage& h);
 // enqueued on s last uses it.
 hipError_t stage_take(HostStage& h, char** slot, int* k);
 hipError_t stage_mark(HostStage& h, int k, hipStream_t s);
+// Several small pieces (together at most a slot) read back with one wait.
+struct Piece {
+    void* dst;                           // host
+    const void* src;
+    size_t bytes;
+};
+hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream_t s);
 // copy_out and copy_in through the stage; the first waits.
 hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s);
