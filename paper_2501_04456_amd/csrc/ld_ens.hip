@@ -370,7 +370,7 @@ ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
     e->pend_dt = 0.0;
     auto launch = [&](int lj, int coulomb) {
         A.lj_blocks = lj;
-        A.lj_every = lj > 0 ? (lj + coulomb) / lj : 1;
+        A.lj_every = sym::lj_stride(lj, coulomb);
         hipLaunchKernelGGL(k_ens_pair, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
         A.adv_dt = 0.0;
     };

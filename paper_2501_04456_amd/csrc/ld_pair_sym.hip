@@ -122,7 +122,7 @@ hipError_t launch_pair_sym(const PairLaunch& L, const PairTable& tab, hipStream_
     auto launch = [&](int lj, int coulomb) {
         A.lj_blocks = lj;
         if (lj + coulomb == 0) return;
-        A.lj_every = lj > 0 ? (lj + coulomb) / lj : 1;
+        A.lj_every = sym::lj_stride(lj, coulomb);
         if (A.p.jb == 4)
             hipLaunchKernelGGL(k_pair_sym<4>, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
         else

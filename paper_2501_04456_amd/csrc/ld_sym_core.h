@@ -25,8 +25,8 @@
 // Blocks.  jb consecutive groups (4 or 8) make a block; a workgroup of
 // kSymWaves wavefronts takes the rows of mA blocks against a run of column
 // blocks.  In a column block its wavefronts start at different groups and
-// go round, a barrier per group, so the FP64 column sums in LDS have one
-// writer at a time and a fixed order.  Block pairs are shared out
+// go round, a barrier every jb / kSymWaves groups, so the FP64 column sums in
+// LDS have one writer at a time and a fixed order.  Block pairs are shared out
 // cyclically (a takes b = a + 1 .. a + nbc/2 mod nbc), so every row block
 // has the same work and each unordered pair of blocks one owner.
 //
@@ -55,6 +55,16 @@ using namespace pair;
 
 constexpr int kW = kSymWaves;
 constexpr int kRows = 16;                  // rows per lane
+
+// Every how many workgroups of a launch one takes a Lennard-Jones group while
+// there are any.  An odd number: workgroups go to the 8 XCDs in turn and there
+// to 4 shader engines in turn, so that groups every second or fourth workgroup
+// leave half or a quarter of the engines without Coulomb tasks (65 536 charged
+// slots stepped 1.02 ms so and step 0.97, 200 000 stepped 11.3 and step 8.3).
+inline int lj_stride(int lj, int tasks) {
+    const int k = lj > 0 ? (lj + tasks) / lj : 1;
+    return k % 2 ? k : k - 1;
+}
 
 // What a workgroup works on: one droplet's slots and boxes, and its force
 // partials F[slot][3][stride], already at the droplet's first slot.
