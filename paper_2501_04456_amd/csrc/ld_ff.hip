@@ -2032,8 +2032,9 @@ ld_status ensure_batch(FarField* f, int B_) {
 }
 
 // Forward (saving activations) + loss + backward into f->grad for the batch
-// in bX / bT (B_ rows, targets already scaled).  Returns the loss.
-ld_status fwd_bwd(FarField* f, int B_, hipStream_t s, double* loss) {
+// in bX / bT (B_ rows, targets already scaled).  Returns the loss and, unless
+// grads is null, the gradients.
+ld_status fwd_bwd(FarField* f, int B_, hipStream_t s, double* loss, float* grads = nullptr) {
     const int H = f->H, Op = f->Op, Kp = f->Kp;
     float* W = f->W;
     float* gW = f->grad;
@@ -2064,9 +2065,15 @@ ld_status fwd_bwd(FarField* f, int B_, hipStream_t s, double* loss) {
 #undef TRY
     if (loss) {
         std::vector<double> parts(nparts);
-        HIP_TRY(hipMemcpyAsync(parts.data(), f->loss_part, sizeof(double) * nparts,
-                               hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        const Piece loss_parts{parts.data(), f->loss_part, sizeof(double) * nparts};
+        if (grads && !is_device_ptr(grads)) {
+            HIP_TRY(copy_out(f->stage, {loss_parts, {grads, f->grad, sizeof(float) * f->nW}}, s));
+        } else {
+            if (grads)
+                HIP_TRY(hipMemcpyAsync(grads, f->grad, sizeof(float) * f->nW,
+                                       hipMemcpyDeviceToDevice, s));
+            HIP_TRY(copy_out(f->stage, {loss_parts}, s));
+        }
         double l = 0.0;
         for (double v : parts) l += v;
         *loss = l;
@@ -2453,13 +2460,15 @@ ld_status ld_ff_grads(ld_ctx* c, const float* X, const float* T, int64_t m, floa
     hipStream_t s = c->stream;
     ld_status st = ensure_batch(f, (int)m);
     if (st != LD_OK) return st;
-    hipError_t e = pad_in(c, X, (int)m, s);
-    if (e == hipSuccess) e = copy_in(f->stage, f->bT, T, sizeof(float) * (size_t)m * 3, s);
+    // the targets first, so that nothing is left to fetch behind the features
+    if (!f->stage.buf) stage_init(f->stage, HostStage::kSlots * kBatchSlot, kBatchSlot);
+    hipError_t e = copy_in(f->stage, f->bT, T, sizeof(float) * (size_t)m * 3, s);
+    if (e == hipSuccess) e = pad_in(c, X, (int)m, s);
     if (e != hipSuccess) return fail(LD_EHIP, "staging batch: %s", hipGetErrorString(e));
-    st = fwd_bwd(f, (int)m, s, loss);
-    if (st != LD_OK) return st;
-    HIP_TRY(copy_out(f->stage, grads, f->grad, sizeof(float) * f->nW, s));
-    return LD_OK;
+    double l = 0.0;
+    st = fwd_bwd(f, (int)m, s, &l, grads);
+    if (st == LD_OK && loss) *loss = l;
+    return st;
 }
 
 ld_status ld_ff_collect(ld_ctx* c, int32_t reset, int32_t max_snapshots) {
