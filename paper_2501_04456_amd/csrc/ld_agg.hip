@@ -521,7 +521,8 @@ double ag_table(const ld_ctx* c, double contact_factor, AgTable* tb) {
     } while (0)
 
 // Cell lists for cells of side >= rc, and the particles in cell order (in the
-// context's FP64 scratch); with surf those within sigma / 2 of R only.
+// context's FP64 scratch); with surf those within sigma / 2 of R only.  Follows
+// launch_absmax.
 hipError_t ag_cells(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bool surf, double R,
                     int* labels, bool roots, AgSorted* A) {
     const int n = (int)c->n;
@@ -532,8 +533,7 @@ hipError_t ag_cells(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bo
     int* list = reinterpret_cast<int*>(c->sb.tmp4);       // lists and sorted cells
     float4* hi = reinterpret_cast<float4*>(c->work);
     float4* lo = hi + n;
-    hipError_t e = cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s);
-    if (e != hipSuccess) return e;
+    hipError_t e;
     if (surf)
         AG_RUN(k_ag_bin<true>, gn, c->pos, c->lo, c->typ, c->oid, n, c->sb.bounds_part, rc, R, tb,
                C, cell, cell + n, labels, b.res);
@@ -563,8 +563,9 @@ hipError_t ag_union(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bo
     hipStream_t s = c->stream;
     const dim3 gn((n + kB - 1) / kB), gl(std::min((n + kB - 1) / kB, 128));
     int* err = reinterpret_cast<int*>(b.res + 3);
-    const hipError_t ec = ag_cells(c, b, tb, rc, surf, R, labels, true, A);
-    if (ec != hipSuccess) return ec;
+    hipError_t e = cells::launch_absmax(c->pos, n, c->sb.bounds_part, cells::work_at(b.work), s);
+    if (e == hipSuccess) e = ag_cells(c, b, tb, rc, surf, R, labels, true, A);
+    if (e != hipSuccess) return e;
     if (n < kAgSplitN)
         AG_RUN(k_ag_hook<16>, dim3((n + kB / 16 - 1) / (kB / 16)), *A, tb, rc, b.parent, err);
     else

@@ -240,7 +240,10 @@ __global__ __launch_bounds__(256) void k_box_count(const float4* __restrict__ po
         bool mine = false;
         for (size_t probe = 0; probe < entries; ++probe) {
             unsigned long long* e = table + ((h + probe) & mask);
-            unsigned long long old = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // (a look first where many may share a box; representatives of half
+            // the side are at most eight to a box)
+            unsigned long long old = ~0ull;
+            if (first) old = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (old == ~0ull) old = atomicCAS(e, ~0ull, key);
             if (old == ~0ull || old == key) {
                 mine = old == ~0ull;
