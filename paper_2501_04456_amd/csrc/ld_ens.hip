@@ -5,7 +5,7 @@
 // pair sum of all droplets is one list of tasks of the symmetric kernel
 // (ld_sym_core.h: the rows of a block of 256 slots of a droplet against a run
 // of its column blocks), longest first, with the Lennard-Jones groups of all
-// droplets spread between them.  The update runs over all 64-slot tiles of
+// droplets before or between them.  The update runs over all 64-slot tiles of
 // all droplets in one launch and leaves the tiles' new boxes.  A droplet's
 // noise is keyed by its seed and the particle's index inside the droplet, so
 // each droplet follows exactly the stream it would follow alone.
@@ -18,7 +18,7 @@
 // Measured on 256 droplets of 500 to 8000 charged NPs (sum of N^2 3.04e9),
 // against one-sided tiles drawn by persistent wavefronts from an atomic queue
 // (longest first), a Lennard-Jones launch, a box launch and two one-thread
-// launches: a step 1189 -> 971 us.  12 droplets of 500 to 2000: 141 -> 27 us
+// launches: a step 1189 -> 895 us.  12 droplets of 500 to 2000: 141 -> 27 us
 // (there a wavefront had walked a whole droplet by itself).
 #include <algorithm>
 #include <cstdio>
@@ -107,6 +107,30 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
     V.nA = pl.nA;
     V.nds = pl.nds;
     sym::task<kEnsJB>(V, tk.y, tk.z, tk.w & 0xffff, tk.w >> 16, sh.c);
+}
+
+// The Lennard-Jones groups in a launch of their own, five wavefronts per SIMD
+// instead of the tasks' three: from kEnsLjApart tiles on, where they are many
+// rounds over the chip and hide their latency themselves.  256 droplets, 10 974
+// tiles: a step 949 -> 895 us (915 with four wavefronts, 931 with six, which
+// spill); 128 droplets, 5651 tiles: 435 and 431; 40 droplets, 1378 tiles: 108
+// and 117.
+constexpr int kEnsLjApart = 8192;
+
+__global__ __launch_bounds__(64 * sym::kW, 5) void k_ens_lj(EnsPairArgs A) {
+    __shared__ pair::LjShared<sym::kW, 3> sh;
+    const int2 tl = A.tiles[blockIdx.x];
+    const int d = tl.x;
+    const int o = A.off[d], nd = A.off[d + 1] - o;
+    const PairTable* tb = A.tabs + d;         // sig2d, e24d, e4d, rc2d follow each other
+    double* F = A.F + A.plan[d].base;
+    double sums[3];
+    if (!pair::lj_group<false, true, sym::kW>(A.pos + o, A.lo + o, A.typ + o, A.box + A.tbase[d],
+                                              nd, (tl.y - o) / kGroup, tb->T, tb->rc2max,
+                                              tb->sig2d, sh, sums))
+        return;
+    const size_t i = (size_t)(tl.y - o) + threadIdx.x;
+    for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
 }
 
 // Force of a droplet's slot i: its partials in order, four in flight.
@@ -374,12 +398,15 @@ ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
         hipLaunchKernelGGL(k_ens_pair, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
         A.adv_dt = 0.0;
     };
+    const bool apart = e->ntiles >= kEnsLjApart;
+    if (apart)
+        hipLaunchKernelGGL(k_ens_lj, dim3(e->ntiles), dim3(64 * sym::kW), 0, s, A);
     if (!t0) {
-        launch(e->ntiles, e->ntasks);
+        launch(apart ? 0 : e->ntiles, e->ntasks);
         HIP_TRY(hipGetLastError());
         return LD_OK;
     }
-    launch(e->ntiles, 0);
+    if (!apart) launch(e->ntiles, 0);
     HIP_TRY(hipEventRecord(t0, s));
     launch(0, e->ntasks);
     HIP_TRY(hipEventRecord(t1, s));

@@ -76,3 +76,21 @@ def test_many_droplets(ld, orc):
     F = ens.forces().cpu().numpy().reshape(8193, 2, 3)
     Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params)
     assert (np.linalg.norm(F - Fo, axis=2) <= 1e-5 * So).all()
+
+
+@pytest.mark.parametrize("drops", [127, 128])
+def test_groups_apart(ld, orc, drops):
+    """The largest ensemble with the groups between the tasks and the smallest
+    with a launch of their own (64 tiles each)."""
+    w = _droplets((4096,), 5)[0]
+    ens = ld.Ensemble([w.replace(seed=k) for k in range(drops)])
+    F = ens.forces().cpu().numpy().reshape(drops, w.n, 3)
+    rows = np.unique(np.linspace(0, w.n - 1, 100).astype(int))
+    Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params, rows=rows)
+    assert (np.linalg.norm(F[:, rows] - Fo, axis=2) <= 1e-5 * So).all()
+    ens.kernel_timing(True)                 # the timed launches give the same steps
+    ens.step(2, 1e-6)
+    x = ens.positions64()
+    other = ld.Ensemble([w.replace(seed=k) for k in range(drops)])
+    other.step(2, 1e-6)
+    assert np.array_equal(x, other.positions64())
