@@ -294,6 +294,13 @@ bool timing_events(ld_ctx* c, unsigned char kind, hipEvent_t* e0, hipEvent_t* e1
     c->ev_kind.push_back(kind);
     return true;
 }
+
+hipError_t refresh_boxes(ld_ctx* c, hipStream_t s) {
+    if (!c->boxes_stale) return hipSuccess;
+    const hipError_t e = launch_boxes(c->pos, (int)c->n, c->box, s);
+    if (e == hipSuccess) c->boxes_stale = false;
+    return e;
+}
 }  // namespace ld
 
 namespace {
@@ -383,6 +390,7 @@ int pair_parts(const ld_ctx* c) {
 int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; }
 
 ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
+    HIP_TRY(ld::refresh_boxes(c, s));
     ld::PairLaunch L{};
     L.pos = c->pos;
     L.lo = c->lo;
@@ -420,6 +428,7 @@ ld_status run_sort(ld_ctx* c, hipStream_t s) {
     const float clip = std::isfinite(rmax) && rmax > 0.0 ? (float)(2.0 * rmax) : INFINITY;
     HIP_TRY(ld::launch_sort(c->pos, c->lo, c->typ, c->oid, (int)c->n, c->sb, s, clip));
     HIP_TRY(ld::launch_boxes(c->pos, (int)c->n, c->box, s));
+    c->boxes_stale = false;
     c->steps_since_sort = 0;
     c->charged_first = c->spatial = true;
     return LD_OK;
@@ -468,6 +477,7 @@ ld_status enqueue_step(ld_ctx* c, double dt, hipStream_t s, bool timed) {
         L.j_split = js;
         L.n_full = (int)c->n;
         HIP_TRY(ld::launch_update(L, c->ext, s));
+        c->boxes_stale = false;
         HIP_TRY(ld::launch_advance(c->st, dt, s));
         ++c->steps_since_sort;
         return LD_OK;
@@ -953,6 +963,7 @@ ld_status ld_set_positions(ld_ctx* c, const float* pos, const float* pos_lo) {
     HIP_TRY(hipMemcpyAsync(c->pos, h.data(), sizeof(float4) * N, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemcpyAsync(c->lo, l.data(), sizeof(float4) * N, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(ld::launch_boxes(c->pos, (int)N, c->box, c->stream));
+    c->boxes_stale = false;
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->tune.sort_every > 0) c->steps_since_sort = c->tune.sort_every;
     c->spatial = false;

@@ -1829,6 +1829,7 @@ ld_status ff_near(ld_ctx* c, hipStream_t s) {
         std::swap(c->lo, c->lo2);
         std::swap(c->typ, c->typ2);
         std::swap(c->oid, c->oid2);
+        c->boxes_stale = true;
         c->graph_len = -1;
     }
     // timed: the near-field pair kernels alone
@@ -1897,9 +1898,7 @@ ld_status gemm(hipStream_t s, const float* A, int lda, int tA, const float* B, i
 }
 
 // The learned pair forces of every slot into Fpart[0] (and optional parts).
-// boxes: refresh the 64-slot group boxes for the new slot order (not needed
-// when the update, which rewrites them, follows).
-ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm, bool boxes) {
+ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm) {
     FarField* f = FF(c);
     const int n = (int)c->n;
     const int G = f->cfg.grid, M = G * G * G, H = f->H;
@@ -1938,7 +1937,6 @@ ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm, bo
                 c->lo, n, G, f->grid, f->Ac, f->W + f->offW1 + (size_t)(f->K - 3) * H,
                 f->W + f->offb1, f->W + f->offW2, f->W + f->offb2, f->W + f->offW3,
                 f->W + f->offb3, f->out_scale, f->Fnear, f->Ep, c->Fpart, Fc, Fm);
-        if (boxes) HIP_TRY(ld::launch_boxes(c->pos, n, c->box, s));
         return LD_OK;
     }
     KLAUNCH(k_layer1, dim3((unsigned)(((size_t)n * H + kB - 1) / kB)), dim3(kB), s, c->pos, c->lo,
@@ -1952,17 +1950,24 @@ ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm, bo
     if (st != LD_OK) return st;
     KLAUNCH(k_combine, dim3((n + kB - 1) / kB), dim3(kB), s, c->pos, n, f->Fnear, f->Ep, f->y,
             f->Op, f->out_scale, c->Fpart, Fc, Fm);
-    if (boxes) HIP_TRY(ld::launch_boxes(c->pos, n, c->box, s));
     return LD_OK;
 }
 
-// Direct pair forces summed into one slot-order array dst [3][n].
-ld_status ff_direct_total(ld_ctx* c, hipStream_t s, double* dst) {
+// Direct pair forces by the one-sided kernel, c->tune.j_split partials.
+ld_status ff_direct(ld_ctx* c, hipStream_t s) {
+    HIP_TRY(ld::refresh_boxes(c, s));
     ld::PairLaunch L{};
     L.pos = c->pos; L.lo = c->lo; L.typ = c->typ; L.box = c->box; L.n = (int)c->n;
     L.block = c->tune.block; L.j_split = c->tune.j_split; L.comp = c->tune.comp;
     L.cull = c->tune.cull; L.Fpart = c->Fpart;
     HIP_TRY(ld::launch_pair(L, c->tab, s));
+    return LD_OK;
+}
+
+// The same summed into one slot-order array dst [3][n].
+ld_status ff_direct_total(ld_ctx* c, hipStream_t s, double* dst) {
+    const ld_status st = ff_direct(c, s);
+    if (st != LD_OK) return st;
     KLAUNCH(k_sum_parts, dim3((3 * (int)c->n + kB - 1) / kB), dim3(kB), s, c->Fpart,
             c->tune.j_split, (int)c->n, dst);
     return LD_OK;
@@ -1973,7 +1978,7 @@ ld_status ff_judge_now(ld_ctx* c, double* med) {
     FarField* f = FF(c);
     const int n = (int)c->n;
     hipStream_t s = c->stream;
-    ld_status st = ff_learned_forces(c, s, nullptr, nullptr, true);   // re-sorts, Fpart[0]
+    ld_status st = ff_learned_forces(c, s, nullptr, nullptr);   // re-sorts, Fpart[0]
     if (st != LD_OK) return st;
     double* Fl = c->work;                  // [3][n]
     double* Fd = c->work + 3 * (size_t)n;  // [3][n]
@@ -2119,17 +2124,13 @@ ld_status ff_step_forces(ld_ctx* c, hipStream_t s, int* j_split_used) {
     }
     ++f->window_steps;
     if (f->mode == 1 || f->active) {
-        // the update that follows rewrites the group boxes
-        ld_status st = ff_learned_forces(c, s, nullptr, nullptr, false);
+        ld_status st = ff_learned_forces(c, s, nullptr, nullptr);
         if (st != LD_OK) return st;
         *j_split_used = 1;
         ++f->learned_steps;
     } else {
-        ld::PairLaunch L{};
-        L.pos = c->pos; L.lo = c->lo; L.typ = c->typ; L.box = c->box; L.n = (int)c->n;
-        L.block = c->tune.block; L.j_split = c->tune.j_split; L.comp = c->tune.comp;
-        L.cull = c->tune.cull; L.Fpart = c->Fpart;
-        HIP_TRY(ld::launch_pair(L, c->tab, s));
+        const ld_status st = ff_direct(c, s);
+        if (st != LD_OK) return st;
         *j_split_used = c->tune.j_split;
         ++f->direct_steps;
     }
@@ -2370,7 +2371,7 @@ ld_status ld_ff_forces(ld_ctx* c, int32_t part, double* out) {
         KLAUNCH(k_q_times, dim3((n + kB - 1) / kB), dim3(kB), s, c->pos, n, f->Efar, Fc);
         src = Fc;
     } else {
-        ld_status st = ff_learned_forces(c, s, Fc, Fm, true);
+        ld_status st = ff_learned_forces(c, s, Fc, Fm);
         if (st != LD_OK) return st;
         src = part == 0 ? f->Fnear : part == 1 ? Fc : part == 2 ? Fm : c->Fpart;
     }

@@ -422,6 +422,9 @@ struct ld_ctx {
     int64_t n_charged = 0;
     bool charged_first = false;
     bool spatial = false;
+    // the group boxes are of other positions or another slot order (after a
+    // step of the truncated scheme or a cell sort): refresh_boxes before use
+    bool boxes_stale = false;
     double* S_slot = nullptr;            // [n]
     double* U_slot = nullptr;            // [2][n]
     double* work = nullptr;              // [16][n] FP64 scratch (outputs, reductions)
@@ -463,6 +466,9 @@ constexpr unsigned char kTimedNear = 1;      // the learned path's near-field ke
 // A (start, end) pair of timing events from the context's pool, recorded as
 // bracketing `kind`; false when no event could be created.
 bool timing_events(ld_ctx* c, unsigned char kind, hipEvent_t* e0, hipEvent_t* e1);
+// The boxes of the slots as they are (launched only if they are stale): what
+// selects near groups and skips uncharged ones in every direct force kernel.
+hipError_t refresh_boxes(ld_ctx* c, hipStream_t s);
 // Learned far field hooks used by the step loop (defined in ld_ff.hip).
 void ff_free(ld_ctx* c);
 bool ff_active(const ld_ctx* c);

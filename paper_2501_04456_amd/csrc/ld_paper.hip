@@ -350,6 +350,7 @@ ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     std::swap(c->typ, c->typ2);
     std::swap(c->oid, c->oid2);
     std::swap(m->v, m->v2);
+    c->boxes_stale = true;             // cell order now; a step moves the slots as well
     c->graph_len = -1;                 // a captured graph holds the old addresses
     c->steps_since_sort = 0;
     return LD_OK;
@@ -504,7 +505,6 @@ ld_status ld_paper_enable(ld_ctx* c, const ld_paper_config* cfg) {
 ld_status ld_paper_disable(ld_ctx* c) {
     g_err.clear();
     if (!c) return fail(LD_EINVAL, "ctx is NULL");
-    if (c->pm) HIP_TRY(launch_boxes(c->pos, (int)c->n, c->box, c->stream));   // cell order
     HIP_TRY(hipStreamSynchronize(c->stream));
     pm_free(c);
     return LD_OK;
@@ -518,7 +518,6 @@ ld_status ld_paper_forces(ld_ctx* c, double* F) {
     hipStream_t s = c->stream;
     ld_status st = pm_forces(c, s);
     if (st != LD_OK) return st;
-    HIP_TRY(launch_boxes(c->pos, n, c->box, s));   // the slot order changed
     double* dF = c->work;
     PM_LAUNCH(k_pm_to_orig, dim3((n + kB - 1) / kB), dim3(kB), s, c->pm->F, c->oid, n, dF);
     HIP_TRY(copy_out(c->stage, F, dF, sizeof(double) * 3 * (size_t)n, s));

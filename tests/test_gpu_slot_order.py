@@ -1,0 +1,93 @@
+"""Forces and diagnostics after calls that leave the slots in another order or
+at other places without an update's boxes: steps of the truncated scheme,
+training snapshots and the exact far field, on droplets with uncharged
+particles, against the oracle at the positions read back."""
+import numpy as np
+import pytest
+
+from paper_2501_04456_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ld():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2501_04456_amd import ldrop
+    ldrop.lib()
+    return ldrop
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.build()
+    return oracle
+
+
+def droplet(n):
+    # dense enough for thousands of Lennard-Jones pairs
+    w = W.config_large(n=n, seed=n)
+    w.pos = W.sample_positions(w.type, w.params.sigma, 0.45 * w.radius.R0, n)
+    return w
+
+
+def check_energies(orc, w, x, U, net, fmax):
+    do = orc.State(w, pos=x).diagnostics()
+    _, S, _ = orc.pair_forces(x, w.type, w.charge, w.params)
+    assert abs(do[0]) > 1.0
+    # the bounds of the diagnostics' own test: FP32 pair terms, FP64 sums
+    assert U[0] == pytest.approx(do[0], rel=1e-5)
+    assert U[1] == pytest.approx(do[1], rel=1e-5)
+    assert np.all(np.abs(net) <= 1e-5 * S.sum())
+    assert fmax == pytest.approx(do[8], rel=1e-4)
+
+
+def check_forces(orc, s, w, x):
+    F = s.forces(ext=False)["pair"].cpu().numpy()
+    Fo, So, _ = orc.pair_forces(x, w.type, w.charge, w.params)
+    assert (np.linalg.norm(F - Fo, axis=1) <= 1e-5 * So).all()
+
+
+def check(orc, s, w):
+    x = s.positions64()
+    d = s.diagnostics()
+    check_energies(orc, w, x, d[:2], d[5:8], d[8])
+    check_forces(orc, s, w, x)
+
+
+# the one-launch kernel, the one-sided kernel in its place without culling, and
+# a size that the symmetric kernel serves where the slots' order allows it
+@pytest.mark.parametrize("n,tune", [(3000, {}), (3000, dict(cull=0)), (12500, {})])
+@pytest.mark.parametrize("first", ["forces", "diagnostics", "step"])
+def test_truncated_scheme(ld, orc, n, tune, first):
+    w = droplet(n)
+    s = ld.System.from_workload(w)
+    if tune:
+        s.set_tuning(**tune)
+    s.paper_enable(range_factor=4.0, kick=0.02, inertial_mass=[2.0] * len(w.params.mass))
+    if first == "step":
+        d = s.step(3, 1e-5, diag=True)
+        check_energies(orc, w, s.positions64(), d["U"][:2], d["net_force"], d["max_force"])
+    else:
+        s.step(3, 1e-5)
+        if first == "forces":
+            check_forces(orc, s, w, s.positions64())
+    check(orc, s, w)
+    s.step(2, 1e-5)                          # stale again
+    check(orc, s, w)
+    s.paper_disable()
+    check(orc, s, w)
+
+
+@pytest.mark.parametrize("call", ["collect", "far", "learned"])
+def test_learned_calls(ld, orc, call):
+    w = droplet(3000)
+    s = ld.System.from_workload(w)
+    s.ff_enable(grid=8, block=3, hidden=16, near_mode=ld.NEAR_BLOCK)
+    if call == "collect":
+        s.ff_collect(reset=True, max_snapshots=1)
+    else:
+        s.ff_forces(4 if call == "far" else 0)
+    check(orc, s, w)
