@@ -324,7 +324,8 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
         const unsigned long long jclose = __ballot(j < n && point_box_dist2(hj, bi) < cull2);
         if (jclose == 0ull) return;
         // the close slots, packed; lo.w carries the slot; padded to a
-        // multiple of four with filler out of everyone's range
+        // multiple of four with filler (slot -1; its distance alone would not
+        // keep it out of a range of 1e18 sigma or of none)
         const int at = __popcll(jclose & ((1ull << lane) - 1ull));
         const int m4 = (__popcll(jclose) + 3) & ~3;
         lj.w = __int_as_float(j);
@@ -336,7 +337,7 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
         }
         if (lane >= __popcll(jclose) && lane < m4) {
             sh.hi[w][lane] = make_float4(kFarAway, kFarAway, kFarAway, 0.f);
-            sh.lo[w][lane] = make_float4(0.f, 0.f, 0.f, __int_as_float(i));
+            sh.lo[w][lane] = make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -358,7 +359,7 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
             bool in[4], any = false;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                in[k] = live && !(r2[k] >= cull2) && jj[k] != i;
+                in[k] = live && !(r2[k] >= cull2) && jj[k] != i && jj[k] >= 0;
                 any = any || in[k];
             }
             if (!__any(any)) continue;

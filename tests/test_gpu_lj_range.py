@@ -1,0 +1,59 @@
+"""Lennard-Jones ranges beyond every distance, up to infinite: the padding of a
+near group's slots is no partner, in any of the kernels that take the groups."""
+import numpy as np
+import pytest
+
+from paper_2501_04456_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ld():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2501_04456_amd import ldrop
+    ldrop.lib()
+    return ldrop
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    oracle.build()
+    return oracle
+
+
+def lj_droplet(n, cut):
+    """Lennard-Jones alone, at contact density (FP64 on both sides)."""
+    w = W.config_large(n=n, seed=n)
+    w.pos = W.sample_positions(w.type, w.params.sigma, 0.35 * w.radius.R0, n)
+    w.charge = np.zeros(n)
+    w.params.lj_cut = cut
+    return w
+
+
+# sizes that leave a last group of 1, 2, 3 and 63 slots, and none
+@pytest.mark.parametrize("cut", [2.5, 1e15, 1e19, 1e30, np.inf])
+@pytest.mark.parametrize("n,tune", [(65, {}), (130, {}), (1027, {}), (1024, {}), (1087, dict(cull=0)),
+                                    (12353, {})])
+def test_forces(ld, orc, n, tune, cut):
+    w = lj_droplet(n, cut)
+    s = ld.System.from_workload(w)
+    if tune:
+        s.set_tuning(**tune)
+    F = s.forces(ext=False)["pair"].cpu().numpy()
+    rows = np.unique(np.linspace(0, n - 1, 300).astype(int))
+    Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params, rows=rows)
+    # the same FP64 terms in another order: a few hundred ulp of their sum
+    assert (np.linalg.norm(F[rows] - Fo, axis=1) <= 1e-12 * So).all()
+
+
+@pytest.mark.parametrize("cut", [2.5, 1e30])
+@pytest.mark.parametrize("drops", [2, 8193])
+def test_ensemble(ld, orc, drops, cut):
+    w = lj_droplet(131, cut)
+    ens = ld.Ensemble([w.replace(seed=k) for k in range(drops)])
+    F = ens.forces().cpu().numpy().reshape(drops, w.n, 3)
+    Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params)
+    assert (np.linalg.norm(F - Fo, axis=2) <= 1e-12 * So).all()
