@@ -63,9 +63,15 @@ struct EnsPairArgs {
     int lj_blocks, lj_every;
 };
 
-__global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
+// kExact: slots without spatial order (more droplets than the sort key holds),
+// two wavefronts per SIMD, the low words in LDS.  8200 droplets of 1000 (20):
+// tasks 2.7 -> 3.8 ms against positions relative to the boxes, 3.9 the one-sided
+// tiles that took exact differences before; a step 6.3 (0.16), 6.6 (0.25) with
+// those tiles.
+template <bool kExact>
+__global__ __launch_bounds__(64 * sym::kW, kExact ? 2 : 3) void k_ens_pair(EnsPairArgs A) {
     __shared__ union U {
-        sym::Shared<kEnsJB> c;
+        sym::Shared<kEnsJB, kExact> c;
         pair::LjShared<sym::kW, 3> lj;
         __device__ U() {}
     } sh;
@@ -85,9 +91,10 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
     double* F = A.F + pl.base;
     if (lj) {
         double sums[3];
-        if (!pair::lj_group<false, true, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
-                                                  A.box + A.tbase[d], nd, (tl.y - o) / kGroup,
-                                                  tb->T, tb->rc2max, tb->sig2d, sh.lj, sums))
+        if (!pair::lj_group<false, !kExact, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
+                                                     A.box + A.tbase[d], nd,
+                                                     (tl.y - o) / kGroup, tb->T, tb->rc2max,
+                                                     tb->sig2d, sh.lj, sums))
             return;
         const size_t i = (size_t)(tl.y - o) + threadIdx.x;
         for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
@@ -106,7 +113,7 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
     V.mA = pl.mA;
     V.nA = pl.nA;
     V.nds = pl.nds;
-    sym::task<kEnsJB>(V, tk.y, tk.z, tk.w & 0xffff, tk.w >> 16, sh.c);
+    sym::task<kEnsJB, kExact>(V, tk.y, tk.z, tk.w & 0xffff, tk.w >> 16, sh.c);
 }
 
 // The Lennard-Jones groups in a launch of their own, five wavefronts per SIMD
@@ -117,6 +124,7 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_ens_pair(EnsPairArgs A) {
 // and 117.
 constexpr int kEnsLjApart = 8192;
 
+template <bool kExact>
 __global__ __launch_bounds__(64 * sym::kW, 5) void k_ens_lj(EnsPairArgs A) {
     __shared__ pair::LjShared<sym::kW, 3> sh;
     const int2 tl = A.tiles[blockIdx.x];
@@ -125,9 +133,9 @@ __global__ __launch_bounds__(64 * sym::kW, 5) void k_ens_lj(EnsPairArgs A) {
     const PairTable* tb = A.tabs + d;         // sig2d, e24d, e4d, rc2d follow each other
     double* F = A.F + A.plan[d].base;
     double sums[3];
-    if (!pair::lj_group<false, true, sym::kW>(A.pos + o, A.lo + o, A.typ + o, A.box + A.tbase[d],
-                                              nd, (tl.y - o) / kGroup, tb->T, tb->rc2max,
-                                              tb->sig2d, sh, sums))
+    if (!pair::lj_group<false, !kExact, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
+                                                 A.box + A.tbase[d], nd, (tl.y - o) / kGroup,
+                                                 tb->T, tb->rc2max, tb->sig2d, sh, sums))
         return;
     const size_t i = (size_t)(tl.y - o) + threadIdx.x;
     for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
@@ -395,12 +403,14 @@ ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
     auto launch = [&](int lj, int coulomb) {
         A.lj_blocks = lj;
         A.lj_every = sym::lj_stride(lj, coulomb);
-        hipLaunchKernelGGL(k_ens_pair, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
+        hipLaunchKernelGGL(e->cull ? k_ens_pair<false> : k_ens_pair<true>, dim3(lj + coulomb),
+                           dim3(64 * sym::kW), 0, s, A);
         A.adv_dt = 0.0;
     };
     const bool apart = e->ntiles >= kEnsLjApart;
     if (apart)
-        hipLaunchKernelGGL(k_ens_lj, dim3(e->ntiles), dim3(64 * sym::kW), 0, s, A);
+        hipLaunchKernelGGL(e->cull ? k_ens_lj<false> : k_ens_lj<true>, dim3(e->ntiles),
+                           dim3(64 * sym::kW), 0, s, A);
     if (!t0) {
         launch(apart ? 0 : e->ntiles, e->ntasks);
         HIP_TRY(hipGetLastError());

@@ -44,6 +44,13 @@
 // groups near each other of which one is stretched are left to k_lj, which
 // takes their Coulomb terms from the exact (hi, lo) differences in FP64.
 // Groups without charge have no Coulomb terms and are not visited.
+//
+// Slots in no spatial order (kExact: ensembles of more droplets than the sort
+// key holds) have boxes as wide as the droplet, where positions relative to a
+// centre would lose up to 2^-17 sigma a component: every pair then takes the
+// exact differences of the high and low words, the rows' low words from LDS
+// (a lane's 64 row words and 48 sums leave no registers for them), and no
+// pair is left to k_lj.
 #pragma once
 
 #include "ld_pair_core.h"
@@ -79,11 +86,15 @@ struct View {
     int nbc, mA, nA, nds;                  // as in SymPlan
 };
 
-template <int kJB>
+constexpr int kLoPitch = kRows + 1;         // the four lane groups' rows in different banks
+
+template <int kJB, bool kExact = false>
 struct Shared {
     float4 sx[kW][kGroup];
     float sj[kW][4 * kGroup];
     double acc[kJB][3][kGroup];            // column sums of the current block
+    float4 cl[kExact ? kW : 1][kExact ? kGroup : 1];          // columns' low words
+    float4 rl[kExact ? kW : 1][kExact ? 4 * kLoPitch : 1];    // rows' low words
 };
 
 __device__ __forceinline__ void sync_wave() {
@@ -102,6 +113,10 @@ __device__ __forceinline__ float4 rel_slot(const View& A, int s, bool words, flo
     if (words) return h;
     const float4 lw = A.lo[s];
     return make_float4((h.x - o.x) + lw.x, (h.y - o.y) + lw.y, (h.z - o.z) + lw.z, h.w);
+}
+
+__device__ __forceinline__ float4 low_words(const View& A, int s) {
+    return s < A.n ? A.lo[s] : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // a.lo + a.hi in lanes 0..31, b.lo + b.hi in lanes 32..63.
@@ -145,17 +160,28 @@ __device__ __forceinline__ float fold_rows(const float (&v)[kRows], int c) {
 // Row sums go on in S; the column sums, 64 x {x, y, z}, into sj.  kTiny keeps
 // the self pair's weight finite (its differences are 0) and is far below the
 // r^2 of any two particles; one loop serves near and far tiles alike, as two
-// would each want their own registers for the 48 row sums.
-__device__ __forceinline__ void tile(const float4* __restrict__ sx, float* __restrict__ sj,
+// would each want their own registers for the 48 row sums.  kExact: cl, rl
+// hold the low words (rl in steps of kLoPitch a lane group).
+template <bool kExact>
+__device__ __forceinline__ void tile(const float4* __restrict__ sx, const float4* __restrict__ cl,
+                                     const float4* __restrict__ rl, float* __restrict__ sj,
                                      const float4 (&P)[kRows], float (&Sx)[kRows],
                                      float (&Sy)[kRows], float (&Sz)[kRows], int g, int c) {
 #pragma unroll 1
     for (int ct = 0; ct < 4; ++ct) {
         const float4 v = sx[16 * ct + c];
+        float4 vl = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (kExact) vl = cl[16 * ct + c];
         float jx = 0.f, jy = 0.f, jz = 0.f;
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
-            const float dx = v.x - P[r].x, dy = v.y - P[r].y, dz = v.z - P[r].z;
+            float dx = v.x - P[r].x, dy = v.y - P[r].y, dz = v.z - P[r].z;
+            if constexpr (kExact) {
+                const float4 l = rl[g * kLoPitch + r];
+                dx += vl.x - l.x;
+                dy += vl.y - l.y;
+                dz += vl.z - l.z;
+            }
             const float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, kTiny)));
             const float ri = __builtin_amdgcn_rsqf(r2);
             const float w = ri * (ri * ri);
@@ -182,9 +208,9 @@ __device__ __forceinline__ bool owns(int a, int b, int nbc) {
 // One task: the rows of super-block sa against the column super-blocks at
 // distances s0 .. s1 - 1; row partials go to slot 1 + nds + chunk, column
 // partials to slot 1 + distance.
-template <int kJB>
+template <int kJB, bool kExact = false>
 __device__ __forceinline__ void task(const View& A, int sa, int chunk, int s0, int s1,
-                                     Shared<kJB>& sh) {
+                                     Shared<kJB, kExact>& sh) {
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
     const int l = threadIdx.x % kGroup, g = l >> 4, c = l & 15;
     const size_t n = A.stride;
@@ -214,7 +240,7 @@ __device__ __forceinline__ void task(const View& A, int sa, int chunk, int s0, i
                     float3 o = make_float3(0.f, 0.f, 0.f);
                     if (ilive) {
                         bi = A.box[gi];
-                        ist = stretched(bi);
+                        ist = kExact || stretched(bi);
                         if (!ist)
                             o = make_float3(0.5f * (bi.lo.x + bi.hi.x), 0.5f * (bi.lo.y + bi.hi.y),
                                             0.5f * (bi.lo.z + bi.hi.z));
@@ -222,6 +248,7 @@ __device__ __forceinline__ void task(const View& A, int sa, int chunk, int s0, i
                     // rows through LDS: a lane's 16 rows are 16-lane broadcasts
                     sync_wave();
                     sh.sx[w][l] = rel_slot(A, gi * kGroup + l, ist, o);
+                    if constexpr (kExact) sh.rl[w][g * kLoPitch + c] = low_words(A, gi * kGroup + l);
                     sync_wave();
                     float Sx[kRows], Sy[kRows], Sz[kRows];
 #pragma unroll
@@ -246,11 +273,13 @@ __device__ __forceinline__ void task(const View& A, int sa, int chunk, int s0, i
                         if (__builtin_amdgcn_readfirstlane((int)take)) {
                             const int j = gj * kGroup + l;
                             const float4 q = rel_slot(A, j, ist, o);
+                            float4 ql = make_float4(0.f, 0.f, 0.f, 0.f);
+                            if constexpr (kExact) ql = low_words(A, j);
                             // near pairs with a stretched box are left to k_lj, which
                             // decides by the same tests (such a box is near almost
                             // everything, so the particles are tested one by one)
                             bool exact = false;
-                            if (sym_leaves_out(bi, bj) && box_dist2(bi, bj) < cull2) {
+                            if (!kExact && sym_leaves_out(bi, bj) && box_dist2(bi, bj) < cull2) {
                                 const int i = gi * kGroup + l;
                                 exact = __any(i < A.n && point_box_dist2(A.pos[min(i, A.n - 1)],
                                                                          bj) < cull2) &&
@@ -260,8 +289,10 @@ __device__ __forceinline__ void task(const View& A, int sa, int chunk, int s0, i
                             if (!exact) {
                                 sync_wave();
                                 sh.sx[w][l] = q;
+                                if constexpr (kExact) sh.cl[w][l] = ql;
                                 sync_wave();
-                                tile(sh.sx[w], sh.sj[w], P, Sx, Sy, Sz, g, c);
+                                tile<kExact>(sh.sx[w], sh.cl[kExact ? w : 0],
+                                             sh.rl[kExact ? w : 0], sh.sj[w], P, Sx, Sy, Sz, g, c);
                                 sync_wave();
                                 if (gi != gj) {
                                     for (int d = 0; d < 3; ++d)
