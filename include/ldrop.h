@@ -106,8 +106,14 @@ typedef struct {
     double tab_R[LD_R_TABLE_MAX];  /* table: radii at the knots (>= 0) */
 } ld_radius;
 
-/* Launch configuration of the pair kernel (filled in by ld_autotune or set
- * by hand).  Zero fields mean "library default". */
+/* Launch configuration of the one-sided pair kernels (filled in by
+ * ld_autotune or set by hand).  Zero fields mean "library default".
+ * block, j_split and comp shape the one-sided kernel that serves cull = 0,
+ * the learned path's direct sums and slots that are out of order, and the
+ * one-launch kernel that takes the steps of culled droplets below 12288 NPs
+ * (which has a shape of its own while they are at their defaults).  The
+ * symmetric kernel that takes the steps of larger ones has one shape and adds
+ * its FP32 sums in FP64 whatever they say. */
 typedef struct {
     int32_t block;          /* work-items per workgroup: 64, 128, 256 or 512 */
     int32_t j_split;        /* number of j ranges per i tile (1 .. 64) */

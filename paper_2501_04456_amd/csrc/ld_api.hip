@@ -1,6 +1,7 @@
 // The C ABI of libldrop (declared in include/ldrop.h): argument checking,
 // device buffers, host/device pointer handling and the per-step launch
 // sequence.  No C++ exception crosses this boundary.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -314,34 +315,44 @@ void build_tables(ld_ctx* c) { make_tables(c->p, c->R, c->tab, c->ext); }
 // the one-launch kernel, of 12 288 65 against 67, of 20 000 131 against 151).
 constexpr int64_t kSymMinN = 12288;
 
+// k_pair's launch shape for n slots: enough workgroups to fill 256 CUs (7
+// resident per CU) many times over (a short tail), but at least 256 j per split
+// so each workgroup streams whole LDS tiles.  Blocks of 128 while the splits are
+// few, 256 beyond (9000 slots 71 us a step with either, 16 000 118 and 114, the
+// unsplit diagnostics 1069 and 981, 1828 and 1669).  (Block 64 with culling
+// keeps a whole j tile in registers: one wavefront per SIMD.)
+void pair_shape(int64_t n, int* block, int* split) {
+    *block = n > 8192 ? 256 : 128;
+    const int64_t tiles = (n + *block - 1) / *block;
+    const int64_t cap = std::max<int64_t>(n / 256, 1);
+    *split = (int)std::min<int64_t>({(32768 + tiles - 1) / tiles, cap, 32});
+}
+
 void default_tuning(ld_ctx* c) {
     ld_tuning& t = c->tune;
     std::memset(&t, 0, sizeof t);
-    const int64_t n = c->n;
-    t.block = 256;
-    if (n < kSymMinN) {
-        // One-launch kernel.  Up to 8192 slots eight wavefronts to a workgroup
-        // and two groups each (the Lennard-Jones workgroups are the longest
-        // chains: 5000 slots 28 us a step against 30 with four wavefronts);
-        // above, four, and as many as make eight per SIMD (8192).
-        const int64_t groups = (n + ld::kGroup - 1) / ld::kGroup;
-        if (n <= 8192) t.block = 512;
-        int64_t split = n <= 8192 ? (groups + 15) / 16 : (2048 + groups - 1) / groups;
-        t.j_split = (int)split;
-    } else {
-        // k_pair, where it still runs: enough workgroups to fill 256 CUs (7
-        // resident per CU) many times over (a short tail), but at least 256 j
-        // per split so each workgroup streams whole LDS tiles
-        const int64_t tiles = (n + t.block - 1) / t.block;
-        int64_t split = (32768 + tiles - 1) / tiles;
-        const int64_t cap = n / 256;
-        if (split > cap) split = cap;
-        if (split > 32) split = 32;
-        t.j_split = (int)split;
-    }
+    pair_shape(c->n, &t.block, &t.j_split);
     t.comp = 1;            // blocked Kahan over the FP32 blocks (costs ~1 %)
     t.sort_every = 50;
     t.cull = 1;
+}
+
+// The one-launch kernel's shape: the tuning's, or where that is k_pair's default
+// its own.  Up to 8192 slots eight wavefronts to a workgroup and two groups each
+// (the Lennard-Jones workgroups are the longest chains: 5000 slots 28 us a step
+// against 30 with four wavefronts); above, four, and as many as make eight per
+// SIMD (8192).  k_pair wants other shapes: with this kernel's the learned path's
+// direct fallback took 83 us a step of 1000 slots and 88 of 5000, with its own
+// 43 and 53.
+void direct_shape(int64_t n, const ld_tuning& t, int* block, int* split) {
+    *block = t.block;
+    *split = t.j_split;
+    int pb, ps;
+    pair_shape(n, &pb, &ps);
+    if (t.block != pb || t.j_split != ps) return;
+    const int64_t groups = (n + ld::kGroup - 1) / ld::kGroup;
+    *block = n <= 8192 ? 512 : 256;
+    *split = (int)(n <= 8192 ? (groups + 15) / 16 : (2048 + groups - 1) / groups);
 }
 
 // A captured graph bakes in buffer pointers and parameter tables: drop it
@@ -376,16 +387,28 @@ bool use_sym(const ld_ctx* c) {
            c->tune.sort_every > 0 && c->sym.slots <= c->j_split_cap;
 }
 
+// Force partials that the one-sided kernels of this context may want.
+int one_sided_parts(const ld_ctx* c, const ld_tuning& t) {
+    int block, split = 0;
+    if (c->n < kSymMinN) direct_shape(c->n, t, &block, &split);
+    return std::max(t.j_split, 1 + split);
+}
+
 // Whether they come from the one-launch kernel of small droplets (with
-// culling; block and j_split shape it).
+// culling).
 bool use_direct(const ld_ctx* c) {
-    return !use_sym(c) && c->n < kSymMinN && c->tune.cull == 1 && c->tune.j_split < c->j_split_cap;
+    return !use_sym(c) && c->n < kSymMinN && c->tune.cull == 1 &&
+           one_sided_parts(c, c->tune) <= c->j_split_cap;
 }
 
 // Force partials the update and the gather add up, and the slots that have
 // more than the first.
 int pair_parts(const ld_ctx* c) {
-    return use_sym(c) ? c->sym.slots : use_direct(c) ? 1 + c->tune.j_split : c->tune.j_split;
+    if (use_sym(c)) return c->sym.slots;
+    if (!use_direct(c)) return c->tune.j_split;
+    int block, split;
+    direct_shape(c->n, c->tune, &block, &split);
+    return 1 + split;
 }
 int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; }
 
@@ -406,6 +429,7 @@ ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
     L.U = diag ? c->U_slot : nullptr;
     L.sym = !diag && use_sym(c) ? &c->sym : nullptr;
     L.direct = !diag && use_direct(c) ? 1 : 0;
+    if (L.direct) direct_shape(c->n, c->tune, &L.block, &L.j_split);
     L.st = c->st;
     if (L.sym || L.direct) {
         L.adv_dt = c->pend_dt;             // the last step's clock advance
@@ -741,7 +765,7 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
             (void)hipGetLastError();
         }
     }
-    if (!ok || ensure_split_capacity(c, c->tune.j_split + 1) != LD_OK) {
+    if (!ok || ensure_split_capacity(c, one_sided_parts(c, c->tune)) != LD_OK) {
         free_all(c);
         delete c;
         return fail(LD_ENOMEM, "device allocation failed for n=%lld", (long long)n);
@@ -1295,7 +1319,7 @@ ld_status ld_set_tuning(ld_ctx* c, const ld_tuning* t) {
         return fail(LD_EINVAL, "graph_steps must be in [0, 4096]");
     if (u.sort_every > 4096) return fail(LD_EINVAL, "sort_every must be <= 4096");
     HIP_TRY(hipStreamSynchronize(c->stream));
-    ld_status st = ensure_split_capacity(c, u.j_split + 1);
+    ld_status st = ensure_split_capacity(c, one_sided_parts(c, u));
     if (st != LD_OK) return st;
     c->tune = u;
     invalidate_graph(c);
@@ -1479,9 +1503,11 @@ ld_status ld_autotune(ld_ctx* c, const char* cache_path, int32_t force, ld_tunin
     for (int b : blocks) {
         for (int js : splits) {
             if (js > cap || (c->n + b - 1) / b * (int64_t)js > 65535 * 8) continue;
-            if (ensure_split_capacity(c, js + 1) != LD_OK) continue;
-            c->tune.block = b;
-            c->tune.j_split = js;
+            ld_tuning u = c->tune;
+            u.block = b;
+            u.j_split = js;
+            if (ensure_split_capacity(c, one_sided_parts(c, u)) != LD_OK) continue;
+            c->tune = u;
             double ms_min = INFINITY;
             for (int rep = 0; rep < 4 && st == LD_OK; ++rep) {
                 if (hipEventRecord(e0, c->stream) != hipSuccess) st = LD_EHIP;
