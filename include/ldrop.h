@@ -328,13 +328,15 @@ ld_status ld_fractal(ld_ctx* ctx, double k_f, double d, double eps0, int32_t max
 ld_status ld_get_tuning(ld_ctx* ctx, ld_tuning* t);
 ld_status ld_set_tuning(ld_ctx* ctx, const ld_tuning* t);
 
-/* Search the one-sided pair kernels' launch shape (workgroup size 128/256/512
- * x j split 1..32; the symmetric kernel of larger droplets has one shape) by timing launches on the current state with HIP events, keep
- * the fastest, and return the resulting tuning in *out (may be NULL).
+/* Search the launch shape (workgroup size 128/256/512 x j split 1..32, and the
+ * shape in use) of the one-sided kernel that the tuning shapes in this context
+ * -- the one-launch kernel where the steps take that, else the tiled one -- by
+ * timing its launches on the current state with HIP events, keep the fastest,
+ * and return the resulting tuning in *out (may be NULL).
  * compensation, culling, sorting and graph settings are kept.  cache_path
  * (may be NULL) is a text file of "key block j_split ms" lines, keyed by GPU
- * architecture, size bucket (quarter octaves of n), type count and mode; a
- * hit is applied without timing unless force != 0.  Leaves positions and
+ * architecture, size bucket (quarter octaves of n), type count, mode and kernel;
+ * a hit is applied without timing unless force != 0.  Leaves positions and
  * the step state unchanged.  Errors: LD_EINVAL, LD_EHIP. */
 ld_status ld_autotune(ld_ctx* ctx, const char* cache_path, int32_t force, ld_tuning* out);
 

@@ -412,7 +412,8 @@ int pair_parts(const ld_ctx* c) {
 }
 int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; }
 
-ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
+// one_sided: by k_pair, whatever kernel the context's steps take.
+ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed, bool one_sided = false) {
     HIP_TRY(ld::refresh_boxes(c, s));
     ld::PairLaunch L{};
     L.pos = c->pos;
@@ -427,8 +428,9 @@ ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed) {
     L.Fpart = c->Fpart;
     L.S = diag ? c->S_slot : nullptr;
     L.U = diag ? c->U_slot : nullptr;
-    L.sym = !diag && use_sym(c) ? &c->sym : nullptr;
-    L.direct = !diag && use_direct(c) ? 1 : 0;
+    one_sided = one_sided || diag;
+    L.sym = !one_sided && use_sym(c) ? &c->sym : nullptr;
+    L.direct = !one_sided && use_direct(c) ? 1 : 0;
     if (L.direct) direct_shape(c->n, c->tune, &L.block, &L.j_split);
     L.st = c->st;
     if (L.sym || L.direct) {
@@ -1455,7 +1457,11 @@ ld_status ld_autotune(ld_ctx* c, const char* cache_path, int32_t force, ld_tunin
     g_err.clear();
     if (!c) return fail(LD_EINVAL, "ctx is NULL");
     HIP_TRY(hipStreamSynchronize(c->stream));
-    // cache key: architecture, size bucket (quarter octaves), types, mode
+    // the kernel whose shape this context's tuning is: the one-launch kernel
+    // where its steps take that, else k_pair (also where they take the symmetric
+    // kernel, which has one shape: k_pair then serves what that cannot)
+    const bool direct = use_direct(c) && !ld::ff_active(c);
+    // cache key: architecture, size bucket (quarter octaves), types, mode, kernel
     hipDeviceProp_t prop;
     HIP_TRY(hipGetDeviceProperties(&prop, c->device));
     char arch[64];
@@ -1464,8 +1470,8 @@ ld_status ld_autotune(ld_ctx* c, const char* cache_path, int32_t force, ld_tunin
         if (*q == ':' || *q == ' ') *q = '_';
     const int bucket = (int)std::floor(std::log2((double)c->n) * 4.0);
     char key[160];
-    std::snprintf(key, sizeof key, "%s/nb%d/T%d/cull%d/comp%d", arch, bucket, c->p.n_types,
-                  c->tune.cull, c->tune.comp);
+    std::snprintf(key, sizeof key, "%s/nb%d/T%d/cull%d/comp%d/%s2", arch, bucket, c->p.n_types,
+                  c->tune.cull, c->tune.comp, direct ? "direct" : "pair");
     std::vector<std::string> lines;
     if (cache_path && !force) {
         if (FILE* f = std::fopen(cache_path, "r")) {
@@ -1493,38 +1499,39 @@ ld_status ld_autotune(ld_ctx* c, const char* cache_path, int32_t force, ld_tunin
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    const int blocks[] = {128, 256, 512};
+    // the shape in use first, which may be none of the search's
     const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-    int64_t cap = c->n / 256;
-    if (cap < 1) cap = 1;
+    const int64_t cap = std::max<int64_t>(c->n / 256, 1);
+    std::vector<ld_tuning> shapes(1, saved);
+    for (int b : {128, 256, 512})
+        for (int js : splits) {
+            if (js > cap || (c->n + b - 1) / b * (int64_t)js > 65535 * 8) continue;
+            ld_tuning u = saved;
+            u.block = b;
+            u.j_split = js;
+            shapes.push_back(u);
+        }
     double best_ms = INFINITY;
     ld_tuning best = saved;
     ld_status st = LD_OK;
-    for (int b : blocks) {
-        for (int js : splits) {
-            if (js > cap || (c->n + b - 1) / b * (int64_t)js > 65535 * 8) continue;
-            ld_tuning u = c->tune;
-            u.block = b;
-            u.j_split = js;
-            if (ensure_split_capacity(c, one_sided_parts(c, u)) != LD_OK) continue;
-            c->tune = u;
-            double ms_min = INFINITY;
-            for (int rep = 0; rep < 4 && st == LD_OK; ++rep) {
-                if (hipEventRecord(e0, c->stream) != hipSuccess) st = LD_EHIP;
-                if (st == LD_OK) st = run_pair(c, false, c->stream, false);
-                if (st == LD_OK && hipEventRecord(e1, c->stream) != hipSuccess) st = LD_EHIP;
-                if (st == LD_OK && hipEventSynchronize(e1) != hipSuccess) st = LD_EHIP;
-                float ms = 0.f;
-                if (st == LD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) st = LD_EHIP;
-                if (rep > 0 && ms < ms_min) ms_min = ms;   // first launch is a warm-up
-            }
-            if (st != LD_OK) break;
-            if (ms_min < best_ms) {
-                best_ms = ms_min;
-                best = c->tune;
-            }
+    for (const ld_tuning& u : shapes) {
+        if (ensure_split_capacity(c, one_sided_parts(c, u)) != LD_OK) continue;
+        c->tune = u;
+        double ms_min = INFINITY;
+        for (int rep = 0; rep < 4 && st == LD_OK; ++rep) {
+            if (hipEventRecord(e0, c->stream) != hipSuccess) st = LD_EHIP;
+            if (st == LD_OK) st = run_pair(c, false, c->stream, false, !direct);
+            if (st == LD_OK && hipEventRecord(e1, c->stream) != hipSuccess) st = LD_EHIP;
+            if (st == LD_OK && hipEventSynchronize(e1) != hipSuccess) st = LD_EHIP;
+            float ms = 0.f;
+            if (st == LD_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess) st = LD_EHIP;
+            if (rep > 0 && ms < ms_min) ms_min = ms;   // first launch is a warm-up
         }
         if (st != LD_OK) break;
+        if (ms_min < best_ms) {
+            best_ms = ms_min;
+            best = u;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
