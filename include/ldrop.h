@@ -624,7 +624,12 @@ ld_status ld_surface_fractal(ld_ctx* ctx, double R, double contact_factor, doubl
  *                      noise stream (uniform on the unit sphere),
  *   x <- x + dt v.
  * ld_params.noise is not used (kT still scales Coulomb through l_B).
- * Velocities are FP64, kept in slot order on the device. */
+ * Velocities are FP64, kept in slot order on the device.
+ * A step's cells are those of the largest coordinate one step earlier (of the
+ * present one after ld_paper_enable and ld_set_positions), so trajectories are
+ * the same, bit for bit, however their steps are split into ld_step calls and
+ * whatever is read or evaluated between those; positions written back by
+ * ld_set_positions may go on with another order of the FP64 sums. */
 typedef struct {
     double range_factor;                 /* > 0 (the paper: 4) */
     double kick;                         /* >= 0: magnitude of the random velocity */

@@ -993,6 +993,7 @@ ld_status ld_set_positions(ld_ctx* c, const float* pos, const float* pos_lo) {
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (c->tune.sort_every > 0) c->steps_since_sort = c->tune.sort_every;
     c->spatial = false;
+    ld::pm_moved(c);
     return LD_OK;
 }
 

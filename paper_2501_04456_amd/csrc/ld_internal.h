@@ -477,6 +477,7 @@ bool ff_active(const ld_ctx* c);
 ld_status ff_step_forces(ld_ctx* c, hipStream_t s, int* j_split_used);
 // The paper's own scheme (defined in ld_paper.hip): one step, and release.
 ld_status pm_step(ld_ctx* c, double dt, hipStream_t s, bool first, bool last);
+void pm_moved(ld_ctx* c);                // the positions were replaced
 void pm_free(ld_ctx* c);
 // Aggregate statistics scratch (ld_agg.hip).
 void ag_free(ld_ctx* c);

@@ -49,7 +49,12 @@ struct PaperMode {
     double* v = nullptr;                // [3][n] velocities, slot order
     double* v2 = nullptr;               // [3][n] second buffer (re-sort)
     double* F = nullptr;                // [3][n] pair forces, slot order
-    unsigned turn = 0;                  // steps since the cells were counted on their own
+    // Steps since the largest coordinate was taken on its own.  The cells of a
+    // step are those of the largest coordinate before the step before it, also
+    // across calls (known: the workspace holds it and the present one), so a
+    // trajectory does not depend on how its steps are split into calls.
+    unsigned turn = 0;
+    bool known = false;
     int* cells = nullptr;               // counts, coarse counts, first slots, largest coordinates
 };
 
@@ -59,13 +64,15 @@ constexpr int kB = 256;
 constexpr int kPmSplitN = 60000;        // particles from which a lane takes one by itself
 
 // Cells of all slots at positions no step of the same call has left (the
-// steps bin what they move themselves): mx[0] = mx[1] = the largest coordinate.
+// steps bin what they move themselves), on the grid of mx[grid_mx]; with
+// grid_mx < 0 of the largest coordinate, which becomes mx[0] = mx[1].
 __global__ __launch_bounds__(kB) void k_pm_bin(const float4* __restrict__ pos,
                                                const float4* __restrict__ lo, int n,
-                                               const float* __restrict__ part, double rmax,
-                                               cells::Work C, int* cell, int* rank) {
-    const float m = cells::absmax_of(part);
-    if (blockIdx.x == 0 && threadIdx.x == 0) C.mx[0] = C.mx[1] = __float_as_uint(m);
+                                               const float* __restrict__ part, int grid_mx,
+                                               double rmax, cells::Work C, int* cell, int* rank) {
+    const float m = grid_mx < 0 ? cells::absmax_of(part) : __uint_as_float(C.mx[grid_mx]);
+    if (grid_mx < 0 && blockIdx.x == 0 && threadIdx.x == 0)
+        C.mx[0] = C.mx[1] = __float_as_uint(m);
     const int s = blockIdx.x * kB + threadIdx.x;
     double x[3] = {0.0, 0.0, 0.0};
     if (s < n) {
@@ -262,11 +269,14 @@ __global__ __launch_bounds__(kPmBlock<LANES>) void k_pm_step(PmStep A, PmTable t
         A.pos2[s] = h;
         A.lo2[s] = l;
         m = fmaxf(m, fmaxf(fabsf(h.x), fmaxf(fabsf(h.y), fabsf(h.z))));
+        xn[0] = (double)h.x + (double)l.x;             // as k_pm_bin would read them
+        xn[1] = (double)h.y + (double)l.y;
+        xn[2] = (double)h.z + (double)l.z;
     }
-    if (!A.bin) return;
     m = upd::wave_max(m);
     if (t % 64 == 0 && m > __uint_as_float(C.mx[A.next_mx]))
         atomicMax(&C.mx[A.next_mx], __float_as_uint(m));
+    if (!A.bin) return;
     cells::bin<true>(cells::grid_of(mcur, tb.rmax), on, s, xn, C, A.ncell, A.nrank);
 }
 
@@ -318,11 +328,13 @@ ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     }
     int* cell = reinterpret_cast<int*>(c->sb.keys);       // cells and ranks
     int* list = reinterpret_cast<int*>(c->sb.tmp4);       // lists and sorted cells
+    const bool known = m->known;
+    m->known = false;                  // until the step or the forces are enqueued
     if (!binned) {
-        m->turn = 0;
-        HIP_TRY(cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s));
+        if (!known) m->turn = 0;
+        HIP_TRY(cells::launch_absmax(c->pos, n, c->sb.bounds_part, C, s));   // and no counts
         PM_LAUNCH(k_pm_bin, dim3(blocks), dim3(kB), s, c->pos, c->lo, n, c->sb.bounds_part,
-                  m->tab.rmax, C, cell, cell + n);
+                  known ? (int)(m->turn % 3) : -1, m->tab.rmax, C, cell, cell + n);
         HIP_TRY(cells::launch_coarse(C, s));
     }
     HIP_TRY(cells::launch_scan(C, m->turn % 3, (m->turn + 2) % 3, m->tab.rmax, c->st, adv_dt, s));
@@ -401,10 +413,15 @@ ld_status pm_forces(ld_ctx* c, hipStream_t s) {
     if (st != LD_OK) return st;
     PmStep A = pm_launch(c);
     A.F = m->F;
-    return pm_run<false>(A, c, s);
+    if ((st = pm_run<false>(A, c, s)) == LD_OK) m->known = true;
+    return st;
 }
 
 }  // namespace
+
+void pm_moved(ld_ctx* c) {
+    if (c->pm) c->pm->known = false;
+}
 
 void pm_free(ld_ctx* c) {
     if (!c->pm) return;
@@ -438,6 +455,7 @@ ld_status pm_step(ld_ctx* c, double dt, hipStream_t s, bool first, bool last) {
     std::swap(c->lo, c->lo2);
     std::swap(m->v, m->v2);
     ++m->turn;
+    m->known = true;
     c->pend_dt = dt;
     return LD_OK;
 }
