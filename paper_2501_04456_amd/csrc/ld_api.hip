@@ -50,17 +50,22 @@ hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s) {
     return hipStreamSynchronize(s);
 }
 
-void stage_init(HostStage& h, size_t bytes, size_t max_slot) {
-    size_t slot = (bytes / HostStage::kSlots + 4095) / 4096 * 4096;
-    slot = std::min(std::max(slot, HostStage::kMinSlot), max_slot);
-    bool ok = hipHostMalloc((void**)&h.buf, slot * HostStage::kSlots) == hipSuccess;
+void stage_plan(HostStage& h, size_t bytes, size_t max_slot) {
+    const size_t slot = (bytes / HostStage::kSlots + 4095) / 4096 * 4096;
+    h.slot = std::min(std::max(slot, HostStage::kMinSlot), max_slot);
+}
+
+bool stage_open(HostStage& h) {
+    if (h.buf || h.tried) return h.buf != nullptr;
+    bool ok = hipHostMalloc((void**)&h.buf, h.slot * HostStage::kSlots) == hipSuccess;
     for (hipEvent_t& e : h.ev)
         ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-    h.slot = slot;
     if (!ok) {
         stage_free(h);
         (void)hipGetLastError();
     }
+    h.tried = true;
+    return ok;
 }
 
 void stage_free(HostStage& h) {
@@ -105,7 +110,7 @@ hipError_t to_slot(void* dst, const void* src, size_t bytes, hipStream_t s) {
 }  // namespace
 
 hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
-    if (!h.buf || is_device_ptr(dst)) return copy_out(dst, src, bytes, s);
+    if (is_device_ptr(dst) || !stage_open(h)) return copy_out(dst, src, bytes, s);
     struct Part {
         char* slot;
         int k;
@@ -138,7 +143,7 @@ hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream
     size_t total = 0;
     for (const Piece& p : pieces) total += (p.bytes + 15) / 16 * 16;
     hipError_t e = hipSuccess;
-    if (!h.buf || total > h.slot) {
+    if (total > h.slot || !stage_open(h)) {
         for (const Piece& p : pieces)
             if (e == hipSuccess) e = copy_out(h, p.dst, p.src, p.bytes, s);
         return e;
@@ -163,7 +168,7 @@ hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream
 }
 
 hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
-    if (!h.buf || is_device_ptr(src)) return copy_in(dst, src, bytes, s);
+    if (is_device_ptr(src) || !stage_open(h)) return copy_in(dst, src, bytes, s);
     hipError_t e = hipSuccess;
     for (size_t at = 0; at < bytes && e == hipSuccess; at += h.slot) {
         const size_t len = std::min(h.slot, bytes - at);
@@ -773,7 +778,7 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
         return fail(LD_ENOMEM, "device allocation failed for n=%lld", (long long)n);
     }
 
-    stage_init(c->stage, 3 * sizeof(double) * N, kReadSlot);
+    stage_plan(c->stage, 3 * sizeof(double) * N, kReadSlot);
     const double qs = std::sqrt(p->kT * p->bjerrum);
     std::vector<float4> h4(N), l4(N);
     std::vector<int> ids(N);
@@ -1015,7 +1020,7 @@ ld_status ld_get_positions64(ld_ctx* c, double* x) {
     if (!c || !x) return fail(LD_EINVAL, "ctx and x are required");
     const size_t N = (size_t)c->n, bytes = sizeof(double) * 3 * N;
     // a small frame is written to the pinned slot by the kernel itself
-    if (c->stage.buf && bytes <= ld::kDirectOut && !is_device_ptr(x)) {
+    if (bytes <= ld::kDirectOut && !is_device_ptr(x) && stage_open(c->stage)) {
         char* p;
         int k;
         HIP_TRY(stage_take(c->stage, &p, &k));

@@ -2173,6 +2173,7 @@ ld_status ld_ff_enable(ld_ctx* c, const ld_ff_config* cfg) {
     f->cfg = *cfg;
     f->rlj = maxlj;
     init_layout(f);
+    stage_plan(f->stage, HostStage::kSlots * kBatchSlot, kBatchSlot);
     // source splits of the local expansion: up to 16, partials within 128 MB
     {
         const size_t Mc = (size_t)cfg->grid * cfg->grid * cfg->grid;
@@ -2389,8 +2390,7 @@ static hipError_t pad_in(ld_ctx* c, const float* X, int m, hipStream_t s) {
     float* tmp = nullptr;
     hipError_t e = hipSuccess;
     if (!is_device_ptr(X)) {
-        if (!f->stage.buf) stage_init(f->stage, HostStage::kSlots * kBatchSlot, kBatchSlot);
-        const int per = f->stage.buf ? (int)(f->stage.slot / row) : 0;
+        const int per = stage_open(f->stage) ? (int)(f->stage.slot / row) : 0;
         if (per > 0) {
             for (int r = 0; r < m && e == hipSuccess; r += per) {
                 const int k = std::min(per, m - r);
@@ -2462,7 +2462,6 @@ ld_status ld_ff_grads(ld_ctx* c, const float* X, const float* T, int64_t m, floa
     ld_status st = ensure_batch(f, (int)m);
     if (st != LD_OK) return st;
     // the targets first, so that nothing is left to fetch behind the features
-    if (!f->stage.buf) stage_init(f->stage, HostStage::kSlots * kBatchSlot, kBatchSlot);
     hipError_t e = copy_in(f->stage, f->bT, T, sizeof(float) * (size_t)m * 3, s);
     if (e == hipSuccess) e = pad_in(c, X, (int)m, s);
     if (e != hipSuccess) return fail(LD_EHIP, "staging batch: %s", hipGetErrorString(e));

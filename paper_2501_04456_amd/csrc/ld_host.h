@@ -30,13 +30,17 @@ hipError_t copy_in(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t copy_out(void* dst, const void* src, size_t bytes, hipStream_t s);
 constexpr size_t kReadSlot = 512 << 10, kBatchSlot = 1 << 20;
 
-// A stage whose slots together hold about `bytes`, each at most max_slot (read
+// Plans a stage whose slots together hold about `bytes`, each at most max_slot (read
 // back best in pieces of 512 KiB, which the host still finds in its cache: 250
 // 000 positions 205 us, with 1 or 2 MiB 245; batches uploaded best in pieces of
 // 1 MiB: training passes of 16 MB with 0.5, 1, 2 MiB 760, 640, 780 us, 800 with
-// a pageable copy into a buffer allocated for it).  Without
-// pinned memory it stays empty and copies are not staged.
-void stage_init(HostStage& h, size_t bytes, size_t max_slot);
+// a pageable copy into a buffer allocated for it).  The memory is taken by the
+// first copy: a context that is never read back needs none (30 us to pin and 60
+// to give back, of 250 for a small droplet's context).
+void stage_plan(HostStage& h, size_t bytes, size_t max_slot);
+// Whether there are slots; without pinned memory there are none and copies are
+// not staged.
+bool stage_open(HostStage& h);
 void stage_free(HostStage& h);
 // The next slot, free for the host to write; stage_mark records that the work
 // enqueued on s last uses it.

@@ -380,8 +380,9 @@ namespace ld {
 struct HostStage {
     static constexpr int kSlots = 4;
     static constexpr size_t kMinSlot = 128 << 10;
-    char* buf = nullptr;                 // kSlots * slot bytes; null: copies are not staged
+    char* buf = nullptr;                 // kSlots * slot bytes, from the first copy on
     size_t slot = 0;
+    bool tried = false;                  // without buf: no pinned memory, copies are not staged
     hipEvent_t ev[kSlots] = {};
     unsigned turn = 0;
 };
