@@ -529,6 +529,7 @@ ld_status capture_chunk(ld_ctx* c, double dt, int len) {
     }
     if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     const int64_t saved = c->steps_since_sort;
+    const bool first = c->charged_first, spatial = c->spatial, stale = c->boxes_stale;
     HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
     ld_status st = LD_OK;
     if (c->tune.sort_every > 0) c->steps_since_sort = c->tune.sort_every;
@@ -537,7 +538,11 @@ ld_status capture_chunk(ld_ctx* c, double dt, int len) {
     c->pend_dt = 0.0;
     hipGraph_t g = nullptr;
     hipError_t err = hipStreamEndCapture(c->cap_stream, &g);
+    // nothing has run: the slots and boxes are what they were until a replay
     c->steps_since_sort = saved;
+    c->charged_first = first;
+    c->spatial = spatial;
+    c->boxes_stale = stale;
     if (st != LD_OK) {
         if (g) (void)hipGraphDestroy(g);
         return st;
@@ -919,6 +924,7 @@ ld_status step_loop(ld_ctx* c, double dt, int64_t n_steps) {
             }
             HIP_TRY(hipGraphLaunch(c->graph, c->stream));
             if (c->tune.sort_every > 0) c->charged_first = c->spatial = true;
+            c->boxes_stale = false;
             c->steps_since_sort = c->tune.sort_every > 0 ? len : 0;
             left -= len;
             continue;

@@ -91,3 +91,22 @@ def test_learned_calls(ld, orc, call):
     else:
         s.ff_forces(4 if call == "far" else 0)
     check(orc, s, w)
+
+
+@pytest.mark.parametrize("n,sort_every", [(3000, -1), (3000, 4), (12500, -1), (12500, 4)])
+def test_graph_after_cell_order(ld, n, sort_every):
+    """Captured steps that start from cell order and stale boxes, replayed, and
+    the same steps one by one."""
+    x = []
+    for graph in (0, 4):
+        s = ld.System.from_workload(droplet(n))
+        s.paper_enable(range_factor=4.0, kick=0.02)
+        s.step(2, 1e-5)
+        s.paper_disable()
+        s.set_tuning(sort_every=sort_every, graph_steps=graph)
+        s.step(4, 1e-5)                      # up to the first re-sort
+        for _ in range(3):
+            s.step(4, 1e-5)
+            s.forces()
+        x.append(s.positions64())
+    assert np.array_equal(x[0], x[1])
