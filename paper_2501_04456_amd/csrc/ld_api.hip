@@ -373,15 +373,23 @@ void invalidate_graph(ld_ctx* c) {
 ld_status ensure_split_capacity(ld_ctx* c, int split) {
     if (split <= c->j_split_cap) return LD_OK;
     invalidate_graph(c);
+    const int old = c->j_split_cap;
     if (c->Fpart) (void)hipFree(c->Fpart);
     c->Fpart = nullptr;
     c->j_split_cap = 0;
-    if (hipMalloc(&c->Fpart, sizeof(double) * 3 * (size_t)c->n * split) != hipSuccess)
-        return fail(LD_ENOMEM, "cannot allocate %d force partials", split);
-    c->j_split_cap = split;
-    return LD_OK;
+    auto take = [&](int k) {
+        if (hipMalloc(&c->Fpart, sizeof(double) * 3 * (size_t)c->n * k) != hipSuccess) {
+            c->Fpart = nullptr;
+            (void)hipGetLastError();
+            return false;
+        }
+        c->j_split_cap = k;
+        return true;
+    };
+    if (take(split)) return LD_OK;
+    if (old > 0) (void)take(old);        // the tuning in use still wants them
+    return fail(LD_ENOMEM, "cannot allocate %d force partials", split);
 }
-
 
 // Whether the direct forces come from the symmetric pair kernel: the
 // context has a plan, the slots are in the order it wants and kept so by
@@ -419,6 +427,7 @@ int pair_full(const ld_ctx* c) { return use_sym(c) ? c->sym.n_full : (int)c->n; 
 
 // one_sided: by k_pair, whatever kernel the context's steps take.
 ld_status run_pair(ld_ctx* c, bool diag, hipStream_t s, bool timed, bool one_sided = false) {
+    if (!c->Fpart) return fail(LD_ENOMEM, "the force partials could not be allocated");
     HIP_TRY(ld::refresh_boxes(c, s));
     ld::PairLaunch L{};
     L.pos = c->pos;
@@ -774,7 +783,6 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
         } else if (ensure_split_capacity(c, c->sym.slots) != LD_OK) {
             c->sym.slots = 0;
             g_err.clear();
-            (void)hipGetLastError();
         }
     }
     if (!ok || ensure_split_capacity(c, one_sided_parts(c, c->tune)) != LD_OK) {

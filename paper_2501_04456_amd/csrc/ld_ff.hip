@@ -1902,6 +1902,7 @@ ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm) {
     FarField* f = FF(c);
     const int n = (int)c->n;
     const int G = f->cfg.grid, M = G * G * G, H = f->H;
+    if (!c->Fpart) return fail(LD_ENOMEM, "the force partials could not be allocated");
     ld_status st = ff_near(c, s);
     if (st != LD_OK) return st;
     st = ff_grid_and_coarse(c, s);
@@ -1955,6 +1956,7 @@ ld_status ff_learned_forces(ld_ctx* c, hipStream_t s, double* Fc, double* Fm) {
 
 // Direct pair forces by the one-sided kernel, c->tune.j_split partials.
 ld_status ff_direct(ld_ctx* c, hipStream_t s) {
+    if (!c->Fpart) return fail(LD_ENOMEM, "the force partials could not be allocated");
     HIP_TRY(ld::refresh_boxes(c, s));
     ld::PairLaunch L{};
     L.pos = c->pos; L.lo = c->lo; L.typ = c->typ; L.box = c->box; L.n = (int)c->n;
