@@ -118,7 +118,8 @@ typedef struct {
     int32_t block;          /* work-items per workgroup: 64, 128, 256 or 512 */
     int32_t j_split;        /* number of j ranges per i tile (1 .. 64) */
     int32_t comp;           /* 0: FP32 blocks flushed to FP64; 1: blocked Kahan */
-    int32_t sort_every;     /* steps between spatial re-sorts (<0: never) */
+    int32_t sort_every;     /* steps between spatial re-sorts (<0: never, but for
+                               one when ld_set_positions replaces them) */
     int32_t cull;           /* 1: skip the LJ test for tile pairs beyond range */
     int32_t graph_steps;    /* > 0: replay steps from a captured HIP graph; a
                                chunk is sort_every steps starting with the

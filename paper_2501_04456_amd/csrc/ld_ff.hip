@@ -1830,6 +1830,7 @@ ld_status ff_near(ld_ctx* c, hipStream_t s) {
         std::swap(c->typ, c->typ2);
         std::swap(c->oid, c->oid2);
         c->boxes_stale = true;
+        c->spatial = true;
         c->graph_len = -1;
     }
     // timed: the near-field pair kernels alone

@@ -363,6 +363,7 @@ ld_status pm_sort(ld_ctx* c, hipStream_t s, bool binned, double adv_dt) {
     std::swap(c->oid, c->oid2);
     std::swap(m->v, m->v2);
     c->boxes_stale = true;             // cell order now; a step moves the slots as well
+    c->spatial = true;
     c->graph_len = -1;                 // a captured graph holds the old addresses
     c->steps_since_sort = 0;
     return LD_OK;
