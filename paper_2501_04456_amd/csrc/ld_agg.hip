@@ -581,15 +581,12 @@ hipError_t ag_union(ld_ctx* c, const AgBufs& b, const AgTable& tb, double rc, bo
 }
 #undef AG_RUN
 
-// The statistics and, unless null, the labels: together where host labels fit.
+// The statistics and, unless null, the labels.
 hipError_t ag_read(ld_ctx* c, void* res, const void* dres, size_t bytes, int32_t* labels,
                    const int* dlabels) {
-    const size_t lbytes = labels ? sizeof(int32_t) * (size_t)c->n : 0;
-    if (labels && !host::is_device_ptr(labels))
-        return copy_out(c->stage, {{res, dres, bytes}, {labels, dlabels, lbytes}}, c->stream);
-    const hipError_t e = copy_out(c->stage, res, dres, bytes, c->stream);
-    return e != hipSuccess || !labels ? e
-                                      : copy_out(c->stage, labels, dlabels, lbytes, c->stream);
+    return copy_out(c->stage,
+                    {{res, dres, bytes}, {labels, dlabels, sizeof(int32_t) * (size_t)c->n}},
+                    c->stream);
 }
 
 }  // namespace

@@ -109,62 +109,89 @@ hipError_t to_slot(void* dst, const void* src, size_t bytes, hipStream_t s) {
 
 }  // namespace
 
-hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
-    if (is_device_ptr(dst) || !stage_open(h)) return copy_out(dst, src, bytes, s);
-    struct Part {
-        char* slot;
-        int k;
-        size_t at, len;
-    } q[HostStage::kSlots];
-    size_t issued = 0, done = 0, at = 0;
+namespace {
+
+// The pieces in the order the slots take them: a slot holds as much of them as
+// fits, every part at a multiple of 16 bytes.
+struct SlotWalk {
+    int piece = 0;
+    size_t at = 0, fill = 0;
+};
+struct SlotPart {
+    char* dst;
+    const char* src;
+    size_t off, len;
+    bool last;                           // of its slot
+};
+SlotPart slot_part(SlotWalk& w, const Piece* q, int n, size_t slot) {
+    SlotPart p;
+    p.dst = (char*)q[w.piece].dst + w.at;
+    p.src = (const char*)q[w.piece].src + w.at;
+    p.off = w.fill;
+    p.len = std::min(slot - w.fill, q[w.piece].bytes - w.at);
+    w.at += p.len;
+    w.fill += (p.len + 15) / 16 * 16;
+    if (w.at == q[w.piece].bytes) {
+        ++w.piece;
+        w.at = 0;
+    }
+    p.last = w.fill >= slot || w.piece == n;
+    if (p.last) w.fill = 0;
+    return p;
+}
+
+}  // namespace
+
+hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream_t s) {
+    Piece q[kMaxPieces];
+    int n = 0;
+    for (const Piece& p : pieces) {
+        if (!p.dst || !p.bytes) continue;
+        if (!is_device_ptr(p.dst)) {
+            q[n++] = p;
+            continue;
+        }
+        const hipError_t e = hipMemcpyAsync(p.dst, p.src, p.bytes, hipMemcpyDeviceToDevice, s);
+        if (e != hipSuccess) return e;
+    }
+    if (n == 0 || !stage_open(h)) {
+        for (int k = 0; k < n; ++k) {
+            const hipError_t e =
+                hipMemcpyAsync(q[k].dst, q[k].src, q[k].bytes, hipMemcpyDeviceToHost, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipStreamSynchronize(s);
+    }
+    SlotWalk in, out;
+    char* slot[HostStage::kSlots];
+    int k[HostStage::kSlots];
+    unsigned issued = 0, done = 0;
     hipError_t e = hipSuccess;
-    while (e == hipSuccess && (at < bytes || done < issued)) {
-        if (at < bytes && issued - done < HostStage::kSlots) {
-            Part& p = q[issued % HostStage::kSlots];
-            p.at = at;
-            p.len = std::min(h.slot, bytes - at);
-            e = stage_take(h, &p.slot, &p.k);
-            if (e == hipSuccess)
-                e = to_slot(p.slot, (const char*)src + at, p.len, s);
-            if (e == hipSuccess) e = stage_mark(h, p.k, s);
-            at += p.len;
-            ++issued;
+    while (e == hipSuccess && (in.piece < n || done < issued)) {
+        if (in.piece < n && issued - done < (unsigned)HostStage::kSlots) {
+            const int m = (int)(issued++ % HostStage::kSlots);
+            e = stage_take(h, &slot[m], &k[m]);
+            for (bool last = false; e == hipSuccess && !last;) {
+                const SlotPart p = slot_part(in, q, n, h.slot);
+                e = to_slot(slot[m] + p.off, p.src, p.len, s);
+                last = p.last;
+            }
+            if (e == hipSuccess) e = stage_mark(h, k[m], s);
         } else {
-            const Part& p = q[done % HostStage::kSlots];
-            e = hipEventSynchronize(h.ev[p.k]);
-            if (e == hipSuccess) std::memcpy((char*)dst + p.at, p.slot, p.len);
-            ++done;
+            const int m = (int)(done++ % HostStage::kSlots);
+            e = hipEventSynchronize(h.ev[k[m]]);
+            for (bool last = false; e == hipSuccess && !last;) {
+                const SlotPart p = slot_part(out, q, n, h.slot);
+                std::memcpy(p.dst, slot[m] + p.off, p.len);
+                last = p.last;
+            }
         }
     }
     return e;
 }
 
-hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream_t s) {
-    size_t total = 0;
-    for (const Piece& p : pieces) total += (p.bytes + 15) / 16 * 16;
-    hipError_t e = hipSuccess;
-    if (total > h.slot || !stage_open(h)) {
-        for (const Piece& p : pieces)
-            if (e == hipSuccess) e = copy_out(h, p.dst, p.src, p.bytes, s);
-        return e;
-    }
-    char* slot;
-    int k;
-    e = stage_take(h, &slot, &k);
-    size_t at = 0;
-    for (const Piece& p : pieces) {
-        if (e == hipSuccess && p.bytes) e = to_slot(slot + at, p.src, p.bytes, s);
-        at += (p.bytes + 15) / 16 * 16;
-    }
-    if (e == hipSuccess) e = stage_mark(h, k, s);
-    if (e == hipSuccess) e = hipEventSynchronize(h.ev[k]);
-    if (e != hipSuccess) return e;
-    at = 0;
-    for (const Piece& p : pieces) {
-        std::memcpy(p.dst, slot + at, p.bytes);
-        at += (p.bytes + 15) / 16 * 16;
-    }
-    return hipSuccess;
+hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
+    return copy_out(h, {{dst, src, bytes}}, s);
 }
 
 hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s) {
@@ -879,11 +906,11 @@ ld_status ld_forces(ld_ctx* c, double* F_pair, double* F_ext, double* S, double*
                               F_pair ? dF : nullptr, F_ext ? dE : nullptr, S ? dS : nullptr,
                               c->stream));
     if (U) HIP_TRY(ld::launch_rowsum(c->U_slot, 2, (int)N, dU, c->stream));
-    if (F_pair) HIP_TRY(copy_out(c->stage, F_pair, dF, sizeof(double) * 3 * N, c->stream));
-    if (F_ext) HIP_TRY(copy_out(c->stage, F_ext, dE, sizeof(double) * 3 * N, c->stream));
-    if (S) HIP_TRY(copy_out(c->stage, S, dS, sizeof(double) * N, c->stream));
-    if (U) HIP_TRY(copy_out(U, dU, sizeof(double) * 2, c->stream));
-    return wait_stream(c);
+    HIP_TRY(copy_out(c->stage, {{F_pair, dF, sizeof(double) * 3 * N},
+                                {F_ext, dE, sizeof(double) * 3 * N},
+                                {S, dS, sizeof(double) * N},
+                                {U, dU, sizeof(double) * 2}}, c->stream));
+    return LD_OK;
 }
 
 ld_status ld_step(ld_ctx* c, double dt, int64_t n_steps, const ld_radius* R,
@@ -1042,9 +1069,9 @@ ld_status ld_get_positions(ld_ctx* c, float* pos, float* pos_lo) {
     float* lo = hi + 3 * N;
     HIP_TRY(ld::launch_positions(c->pos, c->lo, c->oid, (int)N, nullptr, pos ? hi : nullptr,
                                  pos_lo ? lo : nullptr, c->stream));
-    if (pos) HIP_TRY(copy_out(c->stage, pos, hi, sizeof(float) * 3 * N, c->stream));
-    if (pos_lo) HIP_TRY(copy_out(c->stage, pos_lo, lo, sizeof(float) * 3 * N, c->stream));
-    return wait_stream(c);
+    const size_t bytes = sizeof(float) * 3 * N;
+    HIP_TRY(copy_out(c->stage, {{pos, hi, bytes}, {pos_lo, lo, bytes}}, c->stream));
+    return LD_OK;
 }
 
 ld_status ld_get_positions64(ld_ctx* c, double* x) {
@@ -1378,12 +1405,11 @@ ld_status ld_checkpoint_save(ld_ctx* c, const char* path) {
     std::vector<float4> h(N), l(N);
     std::vector<int> ty(N), ids(N);
     ld::DevState ds;
-    HIP_TRY(hipMemcpyAsync(h.data(), c->pos, sizeof(float4) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(l.data(), c->lo, sizeof(float4) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(ty.data(), c->typ, sizeof(int) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(ids.data(), c->oid, sizeof(int) * N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(&ds, c->st, sizeof ds, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    HIP_TRY(copy_out(c->stage, {{h.data(), c->pos, sizeof(float4) * N},
+                                {l.data(), c->lo, sizeof(float4) * N},
+                                {ty.data(), c->typ, sizeof(int) * N},
+                                {ids.data(), c->oid, sizeof(int) * N},
+                                {&ds, c->st, sizeof ds}}, c->stream));
     FILE* f = std::fopen(path, "wb");
     if (!f) return fail(LD_ESTATE, "cannot open %s for writing", path);
     const int64_t n64 = c->n, sss = c->steps_since_sort;

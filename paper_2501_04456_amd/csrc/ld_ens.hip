@@ -892,9 +892,8 @@ ld_status ld_ens_get_positions(ld_ens* e, float* pos, float* pos_lo) {
                        e->pos, e->lo, e->did, e->lid, e->off, e->total,
                        (double*)nullptr, hi, lo);
     HIP_TRY(hipGetLastError());
-    if (pos) HIP_TRY(copy_out(e->stage, pos, hi, sizeof(float) * 3 * N, e->stream));
-    if (pos_lo) HIP_TRY(copy_out(e->stage, pos_lo, lo, sizeof(float) * 3 * N, e->stream));
-    HIP_TRY(hipStreamSynchronize(e->stream));
+    const size_t bytes = sizeof(float) * 3 * N;
+    HIP_TRY(copy_out(e->stage, {{pos, hi, bytes}, {pos_lo, lo, bytes}}, e->stream));
     return LD_OK;
 }
 

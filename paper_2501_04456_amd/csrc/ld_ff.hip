@@ -2074,14 +2074,7 @@ ld_status fwd_bwd(FarField* f, int B_, hipStream_t s, double* loss, float* grads
     if (loss) {
         std::vector<double> parts(nparts);
         const Piece loss_parts{parts.data(), f->loss_part, sizeof(double) * nparts};
-        if (grads && !is_device_ptr(grads)) {
-            HIP_TRY(copy_out(f->stage, {loss_parts, {grads, f->grad, sizeof(float) * f->nW}}, s));
-        } else {
-            if (grads)
-                HIP_TRY(hipMemcpyAsync(grads, f->grad, sizeof(float) * f->nW,
-                                       hipMemcpyDeviceToDevice, s));
-            HIP_TRY(copy_out(f->stage, {loss_parts}, s));
-        }
+        HIP_TRY(copy_out(f->stage, {loss_parts, {grads, f->grad, sizeof(float) * f->nW}}, s));
         double l = 0.0;
         for (double v : parts) l += v;
         *loss = l;

@@ -46,14 +46,16 @@ void stage_free(HostStage& h);
 // enqueued on s last uses it.
 hipError_t stage_take(HostStage& h, char** slot, int* k);
 hipError_t stage_mark(HostStage& h, int k, hipStream_t s);
-// Several small pieces (together at most a slot) read back with one wait.
+// copy_out and copy_in through the stage; the first waits for all that the
+// stream holds, several pieces (null destinations are left out) share the slots
+// and the wait.
 struct Piece {
-    void* dst;                           // host
+    void* dst;                           // host or device
     const void* src;
     size_t bytes;
 };
+constexpr int kMaxPieces = 8;
 hipError_t copy_out(HostStage& h, std::initializer_list<Piece> pieces, hipStream_t s);
-// copy_out and copy_in through the stage; the first waits.
 hipError_t copy_out(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t copy_in(HostStage& h, void* dst, const void* src, size_t bytes, hipStream_t s);
 ld_status check_params(const ld_params* p);

@@ -540,7 +540,6 @@ ld_status ld_paper_forces(ld_ctx* c, double* F) {
     double* dF = c->work;
     PM_LAUNCH(k_pm_to_orig, dim3((n + kB - 1) / kB), dim3(kB), s, c->pm->F, c->oid, n, dF);
     HIP_TRY(copy_out(c->stage, F, dF, sizeof(double) * 3 * (size_t)n, s));
-    HIP_TRY(hipStreamSynchronize(s));
     return LD_OK;
 }
 
@@ -552,7 +551,6 @@ ld_status ld_paper_get_velocities(ld_ctx* c, double* v) {
     double* d = c->work;
     PM_LAUNCH(k_pm_to_orig, dim3((n + kB - 1) / kB), dim3(kB), c->stream, c->pm->v, c->oid, n, d);
     HIP_TRY(copy_out(c->stage, v, d, sizeof(double) * 3 * (size_t)n, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
     return LD_OK;
 }
 
