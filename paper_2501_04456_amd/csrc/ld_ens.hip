@@ -608,13 +608,6 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
         for (int64_t i0 = 0; i0 < offs[d + 1] - offs[d]; i0 += kGroup)
             tiles.push_back(make_int2(d, (int)(offs[d] + i0)));
     }
-    // fewer, larger super-blocks once the partials would take kEnsMaxBytes
-    size_t f_doubles = 0;
-    for (int max_super = 128; max_super >= 8; max_super /= 2) {
-        f_doubles = plan_tasks(offs, max_super, plans, tasks);
-        if (f_doubles * sizeof(double) <= kEnsMaxBytes) break;
-    }
-    e->ntasks = (int)tasks.size();
     std::vector<int> off32(offs.begin(), offs.end());
     const size_t N = (size_t)total;
     bool ok = hipMalloc(&e->pos, sizeof(float4) * N) == hipSuccess &&
@@ -623,12 +616,10 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
               hipMalloc(&e->did, sizeof(int) * N) == hipSuccess &&
               hipMalloc(&e->lid, sizeof(int) * N) == hipSuccess &&
               hipMalloc(&e->off, sizeof(int) * (n_drop + 1)) == hipSuccess &&
-              hipMalloc(&e->tasks, sizeof(int4) * tasks.size()) == hipSuccess &&
               hipMalloc(&e->plan, sizeof(DropPlan) * n_drop) == hipSuccess &&
               hipMalloc(&e->tabs, sizeof(PairTable) * n_drop) == hipSuccess &&
               hipMalloc(&e->ext, sizeof(ExtParams) * n_drop) == hipSuccess &&
               hipMalloc(&e->seeds, sizeof(unsigned long long) * n_drop) == hipSuccess &&
-              hipMalloc(&e->F, sizeof(double) * f_doubles) == hipSuccess &&
               hipMalloc(&e->work, sizeof(double) * 3 * N) == hipSuccess &&
               hipMalloc(&e->st, sizeof(DevState)) == hipSuccess &&
               hipMalloc(&e->tbase, sizeof(int) * n_drop) == hipSuccess &&
@@ -645,6 +636,20 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
              hipMalloc(&e->sb.keys, sizeof(unsigned long long) * n_pow2) == hipSuccess &&
              hipMalloc(&e->sb.tmp4, sizeof(float4) * N) == hipSuccess &&
              hipMalloc(&e->sb.tmp_i, sizeof(int) * N) == hipSuccess;
+    // fewer, larger super-blocks where the partials would take kEnsMaxBytes or
+    // more than there is
+    bool have = false;
+    for (int max_super = 128; ok && max_super >= 8 && !have; max_super /= 2) {
+        const size_t bytes = sizeof(double) * plan_tasks(offs, max_super, plans, tasks);
+        if (bytes > kEnsMaxBytes && max_super > 8) continue;
+        have = hipMalloc(&e->F, bytes) == hipSuccess;
+        if (!have) {
+            e->F = nullptr;
+            (void)hipGetLastError();
+        }
+    }
+    e->ntasks = (int)tasks.size();
+    ok = ok && have && hipMalloc(&e->tasks, sizeof(int4) * tasks.size()) == hipSuccess;
     if (!ok) {
         ens_free(e);
         delete e;
