@@ -53,8 +53,9 @@ struct ExtParams {
     ld_radius R;
 };
 
-// Device-resident step state.  Kernels of a step read it; a one-thread
-// kernel after the update advances it, so captured graphs replay correctly.
+// Device-resident step state.  Kernels of a step read it; the next step's force
+// launch advances it, or a one-thread kernel after a run's last update, so
+// captured graphs replay correctly.
 struct DevState {
     long long step;                      // global step counter n
     double t;                            // time t_n
@@ -64,7 +65,7 @@ struct DevState {
 };
 
 struct Box {
-    float4 lo, hi;                       // .w unused
+    float4 lo, hi;                       // lo.w: 1 if the slots hold a charge, else 0
 };
 
 // Radius schedule, FP64.
@@ -120,7 +121,7 @@ struct PairLaunch {
     int n;
     int block;
     int j_split;
-    int comp;
+    int comp;                            // of the one-sided kernels
     int cull;
     double* Fpart;                       // [j_split][3][n]
     double* S;                           // [n] or nullptr (diagnostic mode)
@@ -144,12 +145,12 @@ hipError_t launch_direct(const PairLaunch& L, const PairTable& tab, hipStream_t 
 // the Coulomb part, which then has a launch of its own.
 hipError_t launch_pair(const PairLaunch& L, const PairTable& tab, hipStream_t s,
                        hipEvent_t before_coulomb = nullptr, hipEvent_t after_coulomb = nullptr);
-// Mean square displacement against FP64 reference positions [3][n] in
-// original order: store the reference, or reduce the mean into out[0].
 // Positions in original order: FP64 x [n][3], FP32 hi and lo [n][3] (each may
 // be null).
 hipError_t launch_positions(const float4* pos, const float4* lo, const int* oid, int n, double* x,
                             float* hi_out, float* lo_out, hipStream_t s);
+// Mean square displacement against FP64 reference positions [3][n] in
+// original order: store the reference, or reduce the mean into out[0].
 hipError_t launch_msd_ref(const float4* pos, const float4* lo, const int* oid, int n,
                           double* ref, hipStream_t s);
 hipError_t launch_msd(const float4* pos, const float4* lo, const int* oid, int n,
@@ -185,8 +186,6 @@ hipError_t launch_gather(const float4* pos, const float4* lo, const int* typ, co
 
 // Deterministic FP64 sum of m rows of length n: out[r] = sum_s in[r*n + s].
 hipError_t launch_rowsum(const double* in, int rows, int n, double* out, hipStream_t s);
-
-// Positions hi + lo as FP64 rows work[0..2][n].
 
 // Replace the charge word of every slot: pos[s].w = qhat[oid[s]].
 hipError_t launch_set_charge(float4* pos, const int* oid, const float* qhat, int n,

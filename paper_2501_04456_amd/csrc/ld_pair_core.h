@@ -1,7 +1,7 @@
-// Inner loops of the all-pairs force sum, shared by the single-droplet
-// kernel (ld_pair.hip) and the ensemble kernel (ld_ens.hip).
+// Inner loops of the one-sided all-pairs Coulomb sum (k_pair in ld_pair.hip,
+// k_direct in ld_direct.hip), and the Lennard-Jones groups of all force kernels.
 //
-// Per pair the Coulomb-only path is 12 FP32 VALU operations plus one
+// Per pair the Coulomb path is 12 FP32 VALU operations plus one
 // v_rsq_f32: three subtractions, r^2 as mul+fma+fma, q_j r^-3 as three
 // multiplications and three fma into FP32 block accumulators.  Each lane sums
 // KB = 32 pair terms in FP32 and then moves the block into FP64 totals
@@ -47,15 +47,13 @@ __device__ __forceinline__ void flush(Acc& a, float bx, float by, float bz) {
 }
 
 // 64 j particles with no LJ partner in range and no self pair: Coulomb only.
-// UNROLL: pairs in flight per lane; full unrolling (32) suits the
-// single-droplet kernel's register budget, the ensemble kernel takes fewer.
-template <int COMP, int UNROLL = 32>
+template <int COMP>
 __device__ __forceinline__ void group_far(const float4* __restrict__ sp, const float4 pi,
                                           Acc& a) {
 #pragma unroll
     for (int kb = 0; kb < kGroup; kb += KB) {
         float bx = 0.f, by = 0.f, bz = 0.f;
-#pragma unroll UNROLL
+#pragma unroll
         for (int k = 0; k < KB; ++k) {
             const float4 pj = sp[kb + k];
             const float dx = pj.x - pi.x;
@@ -143,7 +141,7 @@ __device__ __forceinline__ void group_near(const float4* __restrict__ sp,
 // 64 j particles near i's group (within the largest LJ range of its box) or
 // holding i itself: the Coulomb terms, the self pair left out, from
 // positions taken relative to an origin c near both groups (the centre of
-// the box of the workgroup's slots, or of the ensemble tile's box).  Each
+// the box of the workgroup's slots).  Each
 // staged j and the lane's own i hold (hi - c) + lo rounded to FP32, so a
 // difference carries the rounding of |x - c| (tens of sigma for the groups
 // this loop sees) instead of |x|: near |x| = 300 sigma one ulp of a

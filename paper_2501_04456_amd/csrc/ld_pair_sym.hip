@@ -64,13 +64,17 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_pair_sym(SymArgs A) {
 // Blocks, super-blocks and chunks for n slots of which the first `charged`
 // are charged.  Larger super-blocks take fewer partials (each is an FP64
 // triple per slot, written once and read once by the update): the smallest
-// that stays within kSymAimBytes, else the largest if it does within
-// kSymMaxBytes.
+// (from one block of 4 groups, or two of 8) that stays within kSymAimBytes,
+// else the largest if it does within kSymMaxBytes.
 //   nds: column super-blocks a row super-block can own pairs with (itself
 //        first); one column partial each.
-//   chunks: runs of those, one row partial each: enough workgroups for about
-//        twelve rounds over the chip's 768 (three per compute unit), the
-//        last runs short so that the launch ends evenly.
+//   chunks: runs of those, one row partial each, as long as leaves about twelve
+//        rounds of workgroups over the chip's 768 (three per compute unit), the
+//        last runs short so that the launch ends evenly.  A run is one
+//        super-block at least, so there are fewer workgroups where the
+//        super-blocks are few: all charged, 1200 at 12 288 slots, 3280 at
+//        81 920, 2046 at 500 000 (super-blocks of 16), 8320 to 11 200 at 32 768,
+//        81 919, 250 000 and 1 200 000.
 // Blocks of 4 groups below kSymSmallN slots, where blocks of 8 are too few
 // workgroups to share out evenly.
 bool sym_plan(int64_t n, int64_t charged, SymPlan* p) {
