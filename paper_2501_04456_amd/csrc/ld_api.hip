@@ -55,6 +55,11 @@ void stage_plan(HostStage& h, size_t bytes, size_t max_slot) {
     h.slot = std::min(std::max(slot, HostStage::kMinSlot), max_slot);
 }
 
+void stage_plan_frame(HostStage& h, size_t bytes) {
+    stage_plan(h, bytes, kReadSlot);
+    if (bytes > kDirectOut) (void)stage_open(h);
+}
+
 bool stage_open(HostStage& h) {
     if (h.buf || h.tried) return h.buf != nullptr;
     bool ok = hipHostMalloc((void**)&h.buf, h.slot * HostStage::kSlots) == hipSuccess;
@@ -834,7 +839,7 @@ ld_status ld_init(ld_ctx** out, int64_t n, const int32_t* type, const double* ch
         return fail(LD_ENOMEM, "device allocation failed for n=%lld", (long long)n);
     }
 
-    stage_plan(c->stage, 3 * sizeof(double) * N, kReadSlot);
+    stage_plan_frame(c->stage, 3 * sizeof(double) * N);
     const double qs = std::sqrt(p->kT * p->bjerrum);
     std::vector<float4> h4(N), l4(N);
     std::vector<int> ids(N);

@@ -655,7 +655,7 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
         delete e;
         return fail(LD_ENOMEM, "device allocation failed for %lld particles", (long long)total);
     }
-    stage_plan(e->stage, 3 * sizeof(double) * N, kReadSlot);
+    stage_plan_frame(e->stage, 3 * sizeof(double) * N);
     DevState ds{};
     ds.bad_step = ~0ull;
     hipError_t err = hipSuccess;

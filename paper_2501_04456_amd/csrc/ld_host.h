@@ -35,9 +35,12 @@ constexpr size_t kReadSlot = 512 << 10, kBatchSlot = 1 << 20;
 // 000 positions 205 us, with 1 or 2 MiB 245; batches uploaded best in pieces of
 // 1 MiB: training passes of 16 MB with 0.5, 1, 2 MiB 760, 640, 780 us, 800 with
 // a pageable copy into a buffer allocated for it).  The memory is taken by the
-// first copy: a context that is never read back needs none (30 us to pin and 60
-// to give back, of 250 for a small droplet's context).
+// first copy where a frame is at most kDirectOut, else at once: pinning takes 30
+// us of the 250 that a small droplet's context takes to make, and 60 to give
+// back; behind work in flight it takes longer for larger contexts (the first
+// analysis of 250 000 NPs 1160 us, 1270 with it in there).
 void stage_plan(HostStage& h, size_t bytes, size_t max_slot);
+void stage_plan_frame(HostStage& h, size_t bytes);
 // Whether there are slots; without pinned memory there are none and copies are
 // not staged.
 bool stage_open(HostStage& h);
