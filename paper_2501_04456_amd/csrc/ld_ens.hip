@@ -18,7 +18,7 @@
 // Measured on 256 droplets of 500 to 8000 charged NPs (sum of N^2 3.04e9),
 // against one-sided tiles drawn by persistent wavefronts from an atomic queue
 // (longest first), a Lennard-Jones launch, a box launch and two one-thread
-// launches: a step 1189 -> 895 us.  12 droplets of 500 to 2000: 141 -> 27 us
+// launches: a step 1189 -> 884 us.  12 droplets of 500 to 2000: 104 -> 26 us
 // (there a wavefront had walked a whole droplet by itself).
 #include <algorithm>
 #include <cstdio>
@@ -118,10 +118,10 @@ __global__ __launch_bounds__(64 * sym::kW, kExact ? 2 : 3) void k_ens_pair(EnsPa
 
 // The Lennard-Jones groups in a launch of their own, five wavefronts per SIMD
 // instead of the tasks' three: from kEnsLjApart tiles on, where they are many
-// rounds over the chip and hide their latency themselves.  256 droplets, 10 974
-// tiles: a step 949 -> 895 us (915 with four wavefronts, 931 with six, which
-// spill); 128 droplets, 5651 tiles: 435 and 431; 40 droplets, 1378 tiles: 108
-// and 117.
+// rounds over the chip and hide their latency themselves.  Between the tasks and
+// apart: 256 droplets, 10 974 tiles, 936 and 884 us a step; 128 droplets, 5651
+// tiles, 447 and 440; 40 droplets 154 and 160; 12 26 and 37.  (Four wavefronts
+// per SIMD, and six, which spill: 2 and 4 % slower than five.)
 constexpr int kEnsLjApart = 8192;
 
 template <bool kExact>

@@ -251,10 +251,11 @@ __device__ __forceinline__ float point_box_dist2(const float4& p, const Box& b) 
 //     lists at once, so the FP64 code runs as often as the longest list is
 //     long, not for every slot that some lane has in range.
 // Measured against a loop over every slot of the near groups with the FP64
-// terms inline: 5000 slots 27.5 -> 14.3 us a launch, 32768 slots 30.8 -> 27.9
-// us; at 250 000 slots 126 -> 140 us, where the pair loops no longer flag the
-// group pairs that hold a pair in range (one operation in fourteen of their
-// near loops).
+// terms inline: 5000 slots 27.5 -> 14.3 us a launch, 32768 slots 31.3 -> 26.8,
+// 250 000 slots 127 -> 118, and the pair loops no longer flag the group pairs
+// that hold a pair in range (one operation in fourteen of their near loops).
+// Slots without spatial order have all groups near each other, which costs more
+// than those flags did: the callers see to the order (order_slots).
 // Partners come in the same order whatever the timing, and the wavefronts'
 // sums are added in order.
 //
@@ -302,15 +303,14 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
     const Box bi = box[gi];
     // Box tests, and the FP32 screen of the high words: the range widened by
     // what their rounding and that of the difference move a component at the
-    // coordinates a near pair can have; the cutoff itself is decided in FP64.
+    // coordinates a partner of the lane's particle can have (not its box, which
+    // one NP thrown far out may stretch); the cutoff itself is decided in FP64.
     // (With the low words in the screen too, a second LDS read for each
     // candidate, the groups of 8200 unsorted droplets of 1000 took 4.05 ms, 2.8
     // before the lists; so a step of them takes 6.3 ms, 6.9 then.)
     const float cull2 = rc2max * 1.0001f;
     const float reach = sqrtf(cull2);
-    const float far = fmaxf(fmaxf(fmaxf(fabsf(bi.lo.x), fabsf(bi.hi.x)),
-                                  fmaxf(fabsf(bi.lo.y), fabsf(bi.hi.y))),
-                            fmaxf(fabsf(bi.lo.z), fabsf(bi.hi.z)));
+    const float far = fmaxf(fabsf(pi.x), fmaxf(fabsf(pi.y), fabsf(pi.z)));
     const float wide = reach + (far + reach) * 0x1p-20f;
     const float screen = wide * wide;
     double L[3] = {0.0, 0.0, 0.0};

@@ -57,3 +57,37 @@ def test_ensemble(ld, orc, drops, cut):
     F = ens.forces().cpu().numpy().reshape(drops, w.n, 3)
     Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params)
     assert (np.linalg.norm(F - Fo, axis=2) <= 1e-12 * So).all()
+
+
+
+# partners on either side of the range, which only the low words tell apart
+@pytest.mark.parametrize("far", [0.0, 300.0, 3e4, 1e6])
+@pytest.mark.parametrize("n,tune", [(130, {}), (1087, dict(cull=0)), (12353, {})])
+def test_far_from_the_origin(ld, orc, n, tune, far):
+    w = lj_droplet(n, 2.5)
+    rng = np.random.default_rng(n)
+    w.type = rng.permutation(w.type)
+    m = (n + 1) // 2
+    side = int(np.ceil(m ** (1 / 3)))
+    # pairs on a lattice wide enough that nobody else is in range
+    site = np.stack(np.unravel_index(np.arange(m), (side,) * 3), 1) * 16.0 - 8.0 * side
+    site += far * np.array([1.0, -0.7, 0.4])
+    u = rng.normal(size=(m, 3))
+    u /= np.linalg.norm(u, axis=1)[:, None]
+    s = np.asarray(w.params.sigma)
+    rc = 2.5 * 0.5 * (s[w.type[:m]] + s[np.resize(w.type[m:], m)])
+    r = rc * (1.0 + rng.choice([-1.0, 1.0], m) * 10.0 ** rng.uniform(-7, -3, m))
+    x = np.concatenate([site, site + u * r[:, None]])[:n]
+    hi = x.astype(np.float32)
+    lo = (x - hi).astype(np.float32)
+    x = hi.astype(np.float64) + lo
+    order = rng.permutation(n)
+    w.type, hi, lo, x = w.type[order], hi[order], lo[order], x[order]
+    d = ld.System.from_workload(w)
+    if tune:
+        d.set_tuning(**tune)
+    d.set_positions(hi, lo)
+    F = d.forces(ext=False)["pair"].cpu().numpy()
+    Fo, So, _ = orc.pair_forces(x, w.type, w.charge, w.params)
+    assert 0.2 < (So > 0).mean() < 0.8               # both sides occur
+    assert (np.linalg.norm(F - Fo, axis=1) <= 1e-12 * So).all()
