@@ -44,11 +44,11 @@ struct CoulombShared {
     double red[WAVES][3][kGroup];
 };
 
-template <int WAVES, int COMP>
+template <int WAVES, int COMP, bool LONG>
 __global__ __launch_bounds__(WAVES * kGroup) void k_direct(DirectArgs A) {
     __shared__ union U {
         CoulombShared<WAVES> c;
-        LjBlock<WAVES, 3> lj;
+        LjBlock<WAVES, 3, LONG> lj;
         __device__ U() {}
     } sh;
     if (A.adv_dt > 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(WAVES * kGroup) void k_direct(DirectArgs A) {
     const size_t n = (size_t)A.n;
     if ((int)blockIdx.x < A.lj_blocks) {
         double sums[3];
-        if (!lj_block<false, false, WAVES>(A.pos, A.lo, A.typ, A.box, A.n, blockIdx.x, A.tab,
-                                           sh.lj, sums))
+        if (!lj_block<false, false, WAVES, LONG>(A.pos, A.lo, A.typ, A.box, A.n, blockIdx.x, A.tab,
+                                                 sh.lj, sums))
             return;
         const size_t i = (size_t)blockIdx.x * kGroup + threadIdx.x;
         for (int c = 0; c < 3; ++c) A.F[c * n + i] = -sums[c];
@@ -141,12 +141,10 @@ hipError_t launch_waves(const PairLaunch& L, const PairTable& tab, hipStream_t s
     A.tab = tab;
     auto launch = [&](int lj, int coulomb) {
         A.lj_blocks = lj;
-        if (L.comp == 0)
-            hipLaunchKernelGGL((k_direct<WAVES, 0>), dim3(lj + coulomb), dim3(WAVES * kGroup), 0, s,
-                               A);
-        else
-            hipLaunchKernelGGL((k_direct<WAVES, 1>), dim3(lj + coulomb), dim3(WAVES * kGroup), 0, s,
-                               A);
+        const bool far = lj_long(tab);
+        hipLaunchKernelGGL(L.comp == 0 ? (far ? k_direct<WAVES, 0, true> : k_direct<WAVES, 0, false>)
+                                       : (far ? k_direct<WAVES, 1, true> : k_direct<WAVES, 1, false>),
+                           dim3(lj + coulomb), dim3(WAVES * kGroup), 0, s, A);
         A.adv_dt = 0.0;
     };
     const int tiles = A.ngroups * A.j_split;

@@ -68,11 +68,11 @@ struct EnsPairArgs {
 // tasks 2.7 -> 3.8 ms against positions relative to the boxes, 3.9 the one-sided
 // tiles that took exact differences before; a step 6.3 (0.16), 6.6 (0.25) with
 // those tiles.
-template <bool kExact>
+template <bool kExact, bool LONG>
 __global__ __launch_bounds__(64 * sym::kW, kExact ? 2 : 3) void k_ens_pair(EnsPairArgs A) {
     __shared__ union U {
         sym::Shared<kEnsJB, kExact> c;
-        pair::LjShared<sym::kW, 3> lj;
+        pair::LjShared<sym::kW, 3, LONG> lj;
         __device__ U() {}
     } sh;
     if (A.adv_dt > 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -91,10 +91,10 @@ __global__ __launch_bounds__(64 * sym::kW, kExact ? 2 : 3) void k_ens_pair(EnsPa
     double* F = A.F + pl.base;
     if (lj) {
         double sums[3];
-        if (!pair::lj_group<false, !kExact, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
-                                                     A.box + A.tbase[d], nd,
-                                                     (tl.y - o) / kGroup, tb->T, tb->rc2max,
-                                                     tb->sig2d, sh.lj, sums))
+        if (!pair::lj_group<false, !kExact, sym::kW, LONG>(A.pos + o, A.lo + o, A.typ + o,
+                                                           A.box + A.tbase[d], nd,
+                                                           (tl.y - o) / kGroup, tb->T,
+                                                           tb->rc2max, tb->sig2d, sh.lj, sums))
             return;
         const size_t i = (size_t)(tl.y - o) + threadIdx.x;
         for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
@@ -124,18 +124,19 @@ __global__ __launch_bounds__(64 * sym::kW, kExact ? 2 : 3) void k_ens_pair(EnsPa
 // per SIMD, and six, which spill: 2 and 4 % slower than five.)
 constexpr int kEnsLjApart = 8192;
 
-template <bool kExact>
-__global__ __launch_bounds__(64 * sym::kW, 5) void k_ens_lj(EnsPairArgs A) {
-    __shared__ pair::LjShared<sym::kW, 3> sh;
+template <bool kExact, bool LONG>
+__global__ __launch_bounds__(64 * sym::kW, LONG ? 4 : 5) void k_ens_lj(EnsPairArgs A) {
+    __shared__ pair::LjShared<sym::kW, 3, LONG> sh;
     const int2 tl = A.tiles[blockIdx.x];
     const int d = tl.x;
     const int o = A.off[d], nd = A.off[d + 1] - o;
     const PairTable* tb = A.tabs + d;         // sig2d, e24d, e4d, rc2d follow each other
     double* F = A.F + A.plan[d].base;
     double sums[3];
-    if (!pair::lj_group<false, !kExact, sym::kW>(A.pos + o, A.lo + o, A.typ + o,
-                                                 A.box + A.tbase[d], nd, (tl.y - o) / kGroup,
-                                                 tb->T, tb->rc2max, tb->sig2d, sh, sums))
+    if (!pair::lj_group<false, !kExact, sym::kW, LONG>(A.pos + o, A.lo + o, A.typ + o,
+                                                       A.box + A.tbase[d], nd,
+                                                       (tl.y - o) / kGroup, tb->T, tb->rc2max,
+                                                       tb->sig2d, sh, sums))
         return;
     const size_t i = (size_t)(tl.y - o) + threadIdx.x;
     for (int c = 0; c < 3; ++c) F[c * (size_t)nd + i] = -sums[c];
@@ -332,6 +333,7 @@ struct ld_ens {
     std::vector<hipEvent_t> ev;
     size_t ev_used = 0;
     // spatial ordering and tile culling
+    bool lj_long = false;                // a droplet's Lennard-Jones range is long
     bool cull = false;                   // off when droplets or slots exceed the key fields
     Box* box = nullptr;                  // [ntiles]
     int* tbase = nullptr;                // [n_drop] first tile of each droplet
@@ -403,14 +405,16 @@ ld_status enqueue_pair(ld_ens* e, hipStream_t s, hipEvent_t t0 = nullptr,
     auto launch = [&](int lj, int coulomb) {
         A.lj_blocks = lj;
         A.lj_every = sym::lj_stride(lj, coulomb);
-        hipLaunchKernelGGL(e->cull ? k_ens_pair<false> : k_ens_pair<true>, dim3(lj + coulomb),
-                           dim3(64 * sym::kW), 0, s, A);
+        hipLaunchKernelGGL(e->cull ? (e->lj_long ? k_ens_pair<false, true> : k_ens_pair<false, false>)
+                                   : (e->lj_long ? k_ens_pair<true, true> : k_ens_pair<true, false>),
+                           dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
         A.adv_dt = 0.0;
     };
     const bool apart = e->ntiles >= kEnsLjApart;
     if (apart)
-        hipLaunchKernelGGL(e->cull ? k_ens_lj<false> : k_ens_lj<true>, dim3(e->ntiles),
-                           dim3(64 * sym::kW), 0, s, A);
+        hipLaunchKernelGGL(e->cull ? (e->lj_long ? k_ens_lj<false, true> : k_ens_lj<false, false>)
+                                   : (e->lj_long ? k_ens_lj<true, true> : k_ens_lj<true, false>),
+                           dim3(e->ntiles), dim3(64 * sym::kW), 0, s, A);
     if (!t0) {
         launch(apart ? 0 : e->ntiles, e->ntasks);
         HIP_TRY(hipGetLastError());
@@ -585,6 +589,7 @@ ld_status ld_ens_init(ld_ens** out, int32_t n_drop, const int64_t* offsets, cons
     std::vector<int> tbase(n_drop);
     for (int d = 0; d < n_drop; ++d) {
         make_tables(p[d], R[d], tabs[d], exts[d]);
+        e->lj_long = e->lj_long || pair::lj_long(tabs[d]);
         sd[d] = seeds[d];
         const double qs = std::sqrt(p[d].kT * p[d].bjerrum);
         for (int64_t i = offs[d]; i < offs[d + 1]; ++i) {

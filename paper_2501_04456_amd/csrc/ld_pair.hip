@@ -220,7 +220,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 64 ? 1 : LD_PAIR_MIN_WAVES) void k_
 // Lennard-Jones forces of every slot (and, with DIAG, S and the LJ energy row
 // of U), added into partial 0 after k_pair.  One workgroup per 64-slot i
 // group (lj_group).
-template <bool DIAG, int WAVES>
+template <bool DIAG, int WAVES, bool LONG>
 __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict__ pos,
                                                         const float4* __restrict__ lo,
                                                         const int* __restrict__ typ,
@@ -229,10 +229,11 @@ __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict_
                                                         double* __restrict__ S_out,
                                                         double* __restrict__ U_out,
                                                         PairTable tab) {
-    __shared__ LjBlock<WAVES, DIAG ? 5 : 3> sh;
+    __shared__ LjBlock<WAVES, DIAG ? 5 : 3, LONG> sh;
     double sums[DIAG ? 5 : 3];
     const int i = blockIdx.x * kGroup + threadIdx.x;
-    if (!lj_block<DIAG, false, WAVES>(pos, lo, typ, box, n, blockIdx.x, tab, sh, sums)) return;
+    if (!lj_block<DIAG, false, WAVES, LONG>(pos, lo, typ, box, n, blockIdx.x, tab, sh, sums))
+        return;
     for (int c = 0; c < 3; ++c) F[(size_t)c * (size_t)n + i] -= sums[c];
     if constexpr (DIAG) {
         S_out[i] += sums[3];
@@ -242,15 +243,22 @@ __global__ __launch_bounds__(WAVES * kGroup) void k_lj(const float4* __restrict_
 
 // Wavefronts per i group: 16 while the groups are too few to fill the chip
 // with four each.
-template <bool DIAG>
+template <bool DIAG, bool LONG>
 void launch_lj(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
     const dim3 grid((L.n + kGroup - 1) / kGroup);
     if (grid.x < 1024)
-        hipLaunchKernelGGL((k_lj<DIAG, 16>), grid, dim3(16 * kGroup), 0, s, L.pos, L.lo, L.typ,
-                           L.box, L.n, L.Fpart, L.S, L.U, tab);
+        hipLaunchKernelGGL((k_lj<DIAG, 16, LONG>), grid, dim3(16 * kGroup), 0, s, L.pos, L.lo,
+                           L.typ, L.box, L.n, L.Fpart, L.S, L.U, tab);
     else
-        hipLaunchKernelGGL((k_lj<DIAG, 4>), grid, dim3(4 * kGroup), 0, s, L.pos, L.lo, L.typ,
-                           L.box, L.n, L.Fpart, L.S, L.U, tab);
+        hipLaunchKernelGGL((k_lj<DIAG, 4, LONG>), grid, dim3(4 * kGroup), 0, s, L.pos, L.lo,
+                           L.typ, L.box, L.n, L.Fpart, L.S, L.U, tab);
+}
+template <bool DIAG>
+void launch_lj(const PairLaunch& L, const PairTable& tab, hipStream_t s) {
+    if (lj_long(tab))
+        launch_lj<DIAG, true>(L, tab, s);
+    else
+        launch_lj<DIAG, false>(L, tab, s);
 }
 
 template <int BLOCK, int COMP, bool DIAG, bool CULL>

@@ -271,11 +271,24 @@ constexpr int kLjList = 8;               // partners a lane holds between evalua
 
 constexpr int kLjScan = 4;               // boxes / 64 a wavefront tests per round
 
-template <int WAVES, int SUMS>
+// LONG: where a type pair's range is beyond kLjLong lengths, most slots in sight
+// are in range of many lanes.  Four slots that at least kLjInline of their 256
+// lanes have in range are then evaluated where they are met, from LDS, instead of
+// from the lists (the partners of a lane keep their order).  A step at 30
+// sigma_ij of 11 000 slots 625 -> 501 us, 32 768 1076 -> 912, 64 droplets of 500 to
+// 4000 473 -> 359; at 11 sigma_ij (the longest 22) 174 -> 164, 368 -> 350, 192 ->
+// 188; at 8 (the longest 16) 110 and 113, 284 and 287, 160 and 170, for the 30
+// registers more that it takes: so shorter ranges go without.
+constexpr float kLjLong = 20.f;
+constexpr int kLjInline = 16;
+inline bool lj_long(const PairTable& tab) { return tab.rc2max > kLjLong * kLjLong; }
+
+template <int WAVES, int SUMS, bool LONG>
 struct LjShared {
     union {
         struct {
             float4 hi[WAVES][kGroup];            // .w: the slot
+            float4 lo[LONG ? WAVES : 1][LONG ? kGroup : 1];   // .w: the type
             int list[WAVES][kLjList][kGroup];
         };
         double red[WAVES][SUMS][kGroup];         // after the last round
@@ -284,13 +297,13 @@ struct LjShared {
     int found[WAVES];
 };
 
-template <bool DIAG, bool SYM, int WAVES>
+template <bool DIAG, bool SYM, int WAVES, bool LONG>
 __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
                                          const float4* __restrict__ lo,
                                          const int* __restrict__ typ, const Box* __restrict__ box,
                                          int n, int gi, int T, float rc2max,
                                          const double* __restrict__ t64,
-                                         LjShared<WAVES, DIAG ? 5 : 3>& sh,
+                                         LjShared<WAVES, DIAG ? 5 : 3, LONG>& sh,
                                          double (&sums)[DIAG ? 5 : 3]) {
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kGroup);
     const int lane = threadIdx.x % kGroup;
@@ -345,6 +358,7 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bool staged = false;                     // the low words and types too
         for (int k0 = 0; k0 < m4; k0 += 4) {
             // four slots in flight: the loop is bound by LDS latency
             float r2[4];
@@ -363,6 +377,37 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
                 any = any || in[k];
             }
             if (!__any(any)) continue;
+            if constexpr (LONG) {
+                int pass = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) pass += __popcll(__ballot(in[k]));
+                if (pass >= kLjInline) {
+                    evaluate();                  // the partners met before
+                    if (!staged) {
+                        if ((jclose >> lane) & 1ull) {
+                            float4 l = lo[j];
+                            l.w = __int_as_float(typ[j]);
+                            sh.lo[w][at] = l;
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                        staged = true;
+                    }
+                    float4 pj[4], qj[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        pj[k] = sh.hi[w][k0 + k];
+                        qj[k] = sh.lo[w][k0 + k];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        if (in[k])
+                            lj_pair64<DIAG>(pj[k], qj[k], pi, li, t64,
+                                            ti * T + __float_as_int(qj[k].w), L, S, U);
+                    continue;
+                }
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (in[k]) sh.list[w][cnt++][lane] = jj[k];
@@ -443,18 +488,18 @@ __device__ __forceinline__ bool lj_group(const float4* __restrict__ pos,
 }
 
 // lj_group with the type constants staged in LDS first (a whole workgroup).
-template <int WAVES, int SUMS>
+template <int WAVES, int SUMS, bool LONG>
 struct LjBlock {
     double t64[4 * kMaxTypes * kMaxTypes];
-    LjShared<WAVES, SUMS> g;
+    LjShared<WAVES, SUMS, LONG> g;
 };
 
-template <bool DIAG, bool SYM, int WAVES>
+template <bool DIAG, bool SYM, int WAVES, bool LONG>
 __device__ __forceinline__ bool lj_block(const float4* __restrict__ pos,
                                          const float4* __restrict__ lo,
                                          const int* __restrict__ typ, const Box* __restrict__ box,
                                          int n, int gi, const PairTable& tab,
-                                         LjBlock<WAVES, DIAG ? 5 : 3>& sh,
+                                         LjBlock<WAVES, DIAG ? 5 : 3, LONG>& sh,
                                          double (&sums)[DIAG ? 5 : 3]) {
     for (int k = threadIdx.x; k < kMaxTypes * kMaxTypes; k += WAVES * kGroup) {
         sh.t64[k] = tab.sig2d[k];
@@ -463,8 +508,8 @@ __device__ __forceinline__ bool lj_block(const float4* __restrict__ pos,
         sh.t64[3 * kMaxTypes * kMaxTypes + k] = tab.rc2d[k];
     }
     __syncthreads();
-    return lj_group<DIAG, SYM, WAVES>(pos, lo, typ, box, n, gi, tab.T, tab.rc2max, sh.t64, sh.g,
-                                      sums);
+    return lj_group<DIAG, SYM, WAVES, LONG>(pos, lo, typ, box, n, gi, tab.T, tab.rc2max, sh.t64,
+                                            sh.g, sums);
 }
 
 }  // namespace pair

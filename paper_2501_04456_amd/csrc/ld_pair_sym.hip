@@ -19,11 +19,11 @@ struct SymArgs {
     SymPlan p;
 };
 
-template <int kJB>
+template <int kJB, bool LONG>
 __global__ __launch_bounds__(64 * sym::kW, 3) void k_pair_sym(SymArgs A) {
     __shared__ union U {
         sym::Shared<kJB> c;
-        pair::LjBlock<sym::kW, 3> lj;
+        pair::LjBlock<sym::kW, 3, LONG> lj;
         __device__ U() {}
     } sh;
     if (A.adv_dt > 0.0 && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -34,8 +34,8 @@ __global__ __launch_bounds__(64 * sym::kW, 3) void k_pair_sym(SymArgs A) {
     const int turn = (int)blockIdx.x / A.lj_every;
     if ((int)blockIdx.x % A.lj_every == 0 && turn < A.lj_blocks) {
         double sums[3];
-        if (!pair::lj_block<false, true, sym::kW>(A.pos, A.lo, A.typ, A.box, A.n, turn, A.tab,
-                                                  sh.lj, sums))
+        if (!pair::lj_block<false, true, sym::kW, LONG>(A.pos, A.lo, A.typ, A.box, A.n, turn,
+                                                        A.tab, sh.lj, sums))
             return;
         const size_t i = (size_t)turn * kGroup + threadIdx.x;
         for (int c = 0; c < 3; ++c) A.F[c * (size_t)A.n + i] = -sums[c];
@@ -127,10 +127,10 @@ hipError_t launch_pair_sym(const PairLaunch& L, const PairTable& tab, hipStream_
         A.lj_blocks = lj;
         if (lj + coulomb == 0) return;
         A.lj_every = sym::lj_stride(lj, coulomb);
-        if (A.p.jb == 4)
-            hipLaunchKernelGGL(k_pair_sym<4>, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
-        else
-            hipLaunchKernelGGL(k_pair_sym<8>, dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
+        const bool far = pair::lj_long(tab);
+        hipLaunchKernelGGL(A.p.jb == 4 ? (far ? k_pair_sym<4, true> : k_pair_sym<4, false>)
+                                       : (far ? k_pair_sym<8, true> : k_pair_sym<8, false>),
+                           dim3(lj + coulomb), dim3(64 * sym::kW), 0, s, A);
         A.adv_dt = 0.0;
     };
     if (!after_coulomb) {

@@ -1,5 +1,7 @@
 """Lennard-Jones ranges beyond every distance, up to infinite: the padding of a
 near group's slots is no partner, in any of the kernels that take the groups."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -91,3 +93,46 @@ def test_far_from_the_origin(ld, orc, n, tune, far):
     Fo, So, _ = orc.pair_forces(x, w.type, w.charge, w.params)
     assert 0.2 < (So > 0).mean() < 0.8               # both sides occur
     assert (np.linalg.norm(F - Fo, axis=1) <= 1e-12 * So).all()
+
+
+# ranges either side of the one from which dense windows are taken at once (a
+# longest range of 20), and windows with few, some and all slots in range
+@pytest.mark.parametrize("cut", [8.0, 11.0, 30.0])
+@pytest.mark.parametrize("n,tune", [(65, {}), (1027, {}), (1087, dict(cull=0)), (9001, {}),
+                                    (12353, {})])
+def test_long_ranges(ld, orc, n, tune, cut):
+    w = W.config_large(n=n, seed=n)
+    hi = w.pos.astype(np.float32)
+    w.pos = hi.astype(np.float64) + (w.pos - hi).astype(np.float32)     # as it is held
+    w.charge = np.zeros(n)
+    w.params.lj_cut = cut
+    s = ld.System.from_workload(w)
+    if tune:
+        s.set_tuning(**tune)
+    rows = np.unique(np.linspace(0, n - 1, 300).astype(int))
+    Fo, So, _ = orc.pair_forces(w.pos, w.type, w.charge, w.params, rows=rows)
+    F = s.forces(ext=False)["pair"].cpu().numpy()
+    assert (np.linalg.norm(F[rows] - Fo, axis=1) <= 1e-12 * So).all()
+    d = s.forces(ext=False, S=True)                  # the diagnostic instances
+    assert (np.linalg.norm(d["pair"].cpu().numpy()[rows] - Fo, axis=1) <= 1e-12 * So).all()
+    assert (np.abs(d["S"].cpu().numpy()[rows] - So) <= 1e-12 * So).all()
+
+
+@pytest.mark.parametrize("cut", [11.0, 30.0])
+@pytest.mark.parametrize("drops", [3, 150, 8193])
+def test_long_ranges_of_ensembles(ld, orc, drops, cut):
+    """150: the groups in a launch of their own; 8193: exact differences.  One
+    droplet's range alone decides for all of them."""
+    w = W.config_large(n=131 if drops > 150 else 4000, seed=5)
+    hi = w.pos.astype(np.float32)
+    w.pos = hi.astype(np.float64) + (w.pos - hi).astype(np.float32)
+    w.charge = np.zeros(w.n)
+    e = [w.replace(seed=k) for k in range(drops)]
+    far = w.replace(seed=1)
+    far.params = dataclasses.replace(w.params, lj_cut=cut)
+    e[1] = far
+    F = ld.Ensemble(e).forces().cpu().numpy().reshape(drops, w.n, 3)
+    rows = np.unique(np.linspace(0, w.n - 1, 300).astype(int))
+    for d in (0, 1, drops - 1):
+        Fo, So, _ = orc.pair_forces(e[d].pos, e[d].type, e[d].charge, e[d].params, rows=rows)
+        assert (np.linalg.norm(F[d, rows] - Fo, axis=1) <= 1e-12 * So).all()
