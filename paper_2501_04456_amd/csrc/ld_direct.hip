@@ -147,13 +147,30 @@ hipError_t launch_waves(const PairLaunch& L, const PairTable& tab, hipStream_t s
                            dim3(lj + coulomb), dim3(WAVES * kGroup), 0, s, A);
         A.adv_dt = 0.0;
     };
+    // A single wavefront is longer at a Lennard-Jones group than at a short run of
+    // tiles, so blocks of 64 give the groups a launch of four wavefronts each.
+    // Steps in 8 parts 59 -> 34 us (1000 slots), 121 -> 107 (11 000); in one part,
+    // where the runs are the longer ones, 94 -> 118 (2500), and two groups or less
+    // 20 -> 23 (100): those stay in one launch.
+    const bool apart = WAVES == 1 && A.ngroups > 2 && A.ngroups <= 24 * A.j_split;
+    auto groups = [&] {
+        if (!apart) {
+            launch(A.ngroups, 0);
+        } else {
+            A.lj_blocks = A.ngroups;
+            hipLaunchKernelGGL((lj_long(tab) ? k_direct<4, 0, true> : k_direct<4, 0, false>),
+                               dim3(A.ngroups), dim3(4 * kGroup), 0, s, A);
+            A.adv_dt = 0.0;
+        }
+    };
     const int tiles = A.ngroups * A.j_split;
     if (!after_coulomb) {
-        launch(A.ngroups, tiles);
+        if (apart) groups();
+        launch(apart ? 0 : A.ngroups, tiles);
         return hipGetLastError();
     }
     // timed: the Coulomb tiles by themselves
-    launch(A.ngroups, 0);
+    groups();
     hipError_t e = hipEventRecord(before_coulomb, s);
     if (e != hipSuccess) return e;
     launch(0, tiles);

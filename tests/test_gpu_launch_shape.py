@@ -65,3 +65,26 @@ def test_shapes_used(ld, n):
     nrm = np.linalg.norm(own, axis=1)
     assert np.median(np.linalg.norm(other - own, axis=1) / nrm) <= 1e-6
     assert np.median(np.linalg.norm(plain - own, axis=1) / nrm) <= 1e-6
+
+
+# the Lennard-Jones groups in the tiles' launch (1 and 2 groups; more than 24
+# to a part) and in one of their own
+@pytest.mark.parametrize("n,parts", [(64, 1), (128, 4), (129, 1), (1536, 1), (1537, 1), (4999, 3),
+                                     (4999, 8)])
+@pytest.mark.parametrize("cut", [2.5, 30.0])
+def test_blocks_of_one_wavefront(ld, n, parts, cut):
+    w = W.config_large(n=n, seed=n)
+    w.params.lj_cut = cut
+    a, b = ld.System.from_workload(w), ld.System.from_workload(w)
+    a.set_tuning(block=64, j_split=parts, sort_every=3)
+    b.set_tuning(block=256, j_split=parts, sort_every=3)
+    Fa, Fb = (s.forces(ext=False)["pair"].cpu().numpy() for s in (a, b))
+    S = b.forces(ext=False, S=True)["S"].cpu().numpy()
+    # FP32 terms of the same pairs, two roundings of 2^-24 each at most apart
+    assert (np.linalg.norm(Fa - Fb, axis=1) <= 1e-6 * S).all()
+    # the clock goes on once a step, eager and captured
+    c = ld.System.from_workload(w)
+    c.set_tuning(block=64, j_split=parts, sort_every=3, graph_steps=3)
+    d = [s.step(6, 1e-6, diag=True) for s in (a, c)]
+    assert np.array_equal(a.positions64(), c.positions64())
+    assert all(x["step"] == 6 and x["t"] == pytest.approx(6e-6, rel=1e-12) for x in d)
